@@ -419,56 +419,173 @@ __device__ __forceinline__ void neumann(const ASrc& A, v4f (&Xt)[NB * (NB + 1) /
 // Newton-Schulz iteration (paper Alg. 3, Eq. 8) for the matrix I + A:
 //   X <- X0 = I / C;   n_iter times:  Y <- (I + A) X;   X <- 2 X - X Y.
 // Every iterate is a polynomial in A, hence lower triangular: the same tile structure as above.
-// State: X in both orientations (X Y needs X as a left factor, (I + A) X as a right factor).
-// Result: Xt, every tile in T orientation.
+// X lives in N orientation (fp32).  Column j of tiles of Y = X + A X needs column j of X only, and column j of X Y the
+// columns j and up of X as a left factor, so the iteration runs over the columns from the last to the first and turns each
+// into its left form (T orientation) just before changing it.  That form comes from the packed tiles by one product
+// with the identity each, exact for 16-bit values: two products per iteration instead of the three that
+// updating X in both orientations takes, and half of the state.
+// The first iteration from X0 = I / C is a scaling, X1 = 2/C I - (I + A) / C^2, and is written down directly.
+// Result: Xn, every tile in N orientation.
+//
+// What bounds it is the matrix cores (16 cycles a 16-bit instruction, whether it contracts 16 or 32 deep) and the vector
+// instructions between them, which at two wavefronts per SIMD hardly overlap:
+//   16-bit operands: one 32-deep instruction contracts two adjacent tiles: 28 instructions + 10 transposes per iteration at
+//     C = 64 instead of 60.  8 192 fused matrices of C = 64, bf16: 73 -> 58 us; standalone 60 -> 48 us.
+//   fp32 operands: three 32-deep bf16 instructions per tile product on values split into three bf16 parts (Split3)
+//     instead of four 16x16x4 fp32 instructions of 32 cycles: 150 instructions of 16 cycles per iteration instead of 240 of
+//     32.  The same matrices: 346 -> 188 us (matrix cores 0.90 -> 0.49 busy), standalone 352 -> 185 us; error against 64
+//     bits 1.01e-7 -> 0.97e-7 and 4.1e-8 -> 3.4e-8 (below the diagonal).
 // ---------------------------------------------------------------------------------------------
+
+// 16-bit operands: tile rows / columns 2 p and 2 p + 1 side by side; the tile of a pair that lies above the diagonal is zero.
+template <int OP, int NB> struct NsOperands {
+    static constexpr int NP = (NB + 1) / 2;
+    typedef PairOp<OP> Left[NB][NP];   // [tile row][pair of tile columns]
+    typedef PairOp<OP> Right[NP];      // one tile column: [pair of tile rows]
+    static __device__ __forceinline__ void set_left(Left& l, int i, int k, Opnd<OP> x) { l[i][k / 2].set(k & 1, x); }
+    static __device__ __forceinline__ void clear(Left& l)
+    {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (i % 2 == 0) l[i][i / 2].set(1, Opnd<OP>{});
+    }
+    // operands of tile column j from its tiles v[i], i >= j
+    static __device__ __forceinline__ void set_right(Right& r, int j, const v4f (&v)[NB])
+    {
+#pragma unroll
+        for (int i = 0; i < 2 * NP; ++i)
+            if (i / 2 >= j / 2) r[i / 2].set(i & 1, i >= j && i < NB ? pack<OP>(v[i]) : Opnd<OP>{});
+    }
+    // acc[i] += sum over k of left(i, k) right(k, j), i >= j; the tile rows take turns, so that consecutive instructions
+    // belong to different sums
+    static __device__ __forceinline__ void product(const Left& l, const Right& r, int j, v4f (&acc)[NB])
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                if (i >= j && p >= j / 2 && p <= i / 2) acc[i] = tn_pair<OP>(l[i][p], r[p], acc[i]);
+    }
+    // Columns 2 p and 2 p + 1 of X are turned together, before the later one is used: its products read the whole pair
+    // (against a zero, so the other half has to be there and finite).
+    static constexpr bool TURN_PAIRS = NB > 1;
+    // left(i, j) <- the transpose of tile i of the right column j
+    static __device__ __forceinline__ void transpose(Left& l, const Right& r, int i, int j, const PairOp<OP>& id)
+    {
+        set_left(l, i, j, pack<OP>(tn<OP>(r[i / 2].get(i & 1), id.get(0), zero4())));
+    }
+    static __device__ __forceinline__ PairOp<OP> identity(Lane ln)
+    {
+        PairOp<OP> id;
+        id.set(0, pack<OP>(identity_tile(ln)));
+        id.set(1, Opnd<OP>{});
+        return id;
+    }
+    static __device__ __forceinline__ void put_left(Left& l, int i, int j, v4f at) { set_left(l, i, j, pack<OP>(at)); }
+    // the (rounded) value of left(i, j) in N orientation
+    static __device__ __forceinline__ v4f value_n(const Left& l, int i, int j, const PairOp<OP>& id)
+    {
+        return tn<OP>(l[i][j / 2].get(j & 1), id.get(0), zero4());
+    }
+};
+
+// fp32 operands: each tile split into three bf16 parts.
+template <int NB> struct NsOperands<OP_F32, NB> {
+    typedef Split3 Left[NB * (NB + 1) / 2];
+    typedef Split3 Right[NB];
+    static __device__ __forceinline__ void clear(Left&) {}
+    static __device__ __forceinline__ void set_right(Right& r, int j, const v4f (&v)[NB])
+    {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (i >= j) r[i] = split3(v[i]);
+    }
+    static constexpr bool TURN_PAIRS = false;
+    static __device__ __forceinline__ void product(const Left& l, const Right& r, int j, v4f (&acc)[NB])
+    {
+        v4f cross[NB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) cross[i] = zero4();
+#pragma unroll
+        for (int part = 0; part < 3; ++part)
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    if (k < j || k > i) continue;
+                    if (part < 2)
+                        cross[i] = tn_split(part, l[tix(i, k)], r[k], cross[i]);
+                    else
+                        acc[i] = tn_split(part, l[tix(i, k)], r[k], acc[i]);
+                }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (i >= j) acc[i] += cross[i];
+    }
+    static __device__ __forceinline__ void transpose(Left& l, const Right& r, int i, int j, const Opnd<OP_BF16>& id)
+    {
+        l[tix(i, j)] = join3(pack<OP_BF16>(tn<OP_BF16>(r[i].m(), id, zero4())), pack<OP_BF16>(tn<OP_BF16>(r[i].h(), id, zero4())),
+                             pack<OP_BF16>(tn<OP_BF16>(r[i].l(), id, zero4())));
+    }
+    static __device__ __forceinline__ Opnd<OP_BF16> identity(Lane ln) { return pack<OP_BF16>(identity_tile(ln)); }
+    static __device__ __forceinline__ void put_left(Left& l, int i, int j, v4f at) { l[tix(i, j)] = split3(at); }
+    static __device__ __forceinline__ v4f value_n(const Left& l, int i, int j, const Opnd<OP_BF16>& id)
+    {
+        const Split3& s = l[tix(i, j)];
+        return tn<OP_BF16>(s.l(), id, tn<OP_BF16>(s.m(), id, tn<OP_BF16>(s.h(), id, zero4())));  // h + m + l, exact in this order
+    }
+};
+
 template <int OP, int NB, class ASrc>
-__device__ __forceinline__ void newton_schulz(const ASrc& A, v4f (&Xt)[NB * (NB + 1) / 2], int n_iter, Lane ln)
+__device__ __forceinline__ void newton_schulz(const ASrc& A, v4f (&Xn)[NB * (NB + 1) / 2], int n_iter, Lane ln)
 {
-    constexpr int NT = NB * (NB + 1) / 2;
-    Opnd<OP> Lt[NT];
-    v4f Xn[NT];
+    typedef NsOperands<OP, NB> Ops;
+    constexpr float X0 = 1.f / (16 * NB);
+    typename Ops::Left Al;
+    const auto id = Ops::identity(ln);
+    Ops::clear(Al);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int j = 0; j <= i; ++j) {
-            Lt[tix(i, j)] = pack<OP>(A.template get<true>(i, j));
-            v4f x;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) x[r] = (i == j && 4 * ln.q + r == ln.n) ? 1.f / (16 * NB) : 0.f;
-            Xn[tix(i, j)] = x;
-            Xt[tix(i, j)] = x;
+            const v4f unit = i == j ? identity_tile(ln) : zero4();
+            Ops::put_left(Al, i, j, A.template get<true>(i, j));
+            Xn[tix(i, j)] = 2.f * X0 * unit - X0 * X0 * (unit + Ops::value_n(Al, i, j, id));
         }
 #pragma unroll 1
-    for (int it = 0; it < n_iter; ++it) {
-        Opnd<OP> xn[NT], xt[NT], yn[NT];
+    for (int it = 1; it < n_iter; ++it) {
+        typename Ops::Left Xl;
+        Ops::clear(Xl);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            xn[t] = pack<OP>(Xn[t]);
-            xt[t] = pack<OP>(Xt[t]);
-        }
+        for (int j = NB - 1; j >= 0; --j) {
+            v4f col[NB];
+            typename Ops::Right x, y;
+            if (!Ops::TURN_PAIRS || (j & 1)) {
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
+                for (int c = Ops::TURN_PAIRS ? j - 1 : j; c <= j; ++c) {
 #pragma unroll
-            for (int j = 0; j <= i; ++j) {  // Y = X + A X
-                v4f acc = Xn[tix(i, j)];
+                    for (int i = 0; i < NB; ++i)
+                        if (i >= c) col[i] = Xn[tix(i, c)];
+                    Ops::set_right(x, c, col);
 #pragma unroll
-                for (int k = j; k <= i; ++k) acc = tn<OP>(Lt[tix(i, k)], xn[tix(k, j)], acc);
-                yn[tix(i, j)] = pack<OP>(acc);
-            }
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j <= i; ++j) {  // X <- 2 X - X Y, in both orientations
-                v4f pn = zero4(), pt = zero4();
-#pragma unroll
-                for (int k = j; k <= i; ++k) {
-                    pn = tn<OP>(xt[tix(i, k)], yn[tix(k, j)], pn);
-                    pt = tn<OP>(yn[tix(k, j)], xt[tix(i, k)], pt);
+                    for (int i = 0; i < NB; ++i)
+                        if (i >= c) Ops::transpose(Xl, x, i, c, id);
                 }
-                Xn[tix(i, j)] = 2.f * Xn[tix(i, j)] - pn;
-                Xt[tix(i, j)] = 2.f * Xt[tix(i, j)] - pt;
+            } else {
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    if (i >= j) col[i] = Xn[tix(i, j)];
+                Ops::set_right(x, j, col);
             }
+            Ops::product(Al, x, j, col);  // Y = X + A X
+            Ops::set_right(y, j, col);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) col[i] = zero4();
+            Ops::product(Xl, y, j, col);
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                if (i >= j) Xn[tix(i, j)] = 2.f * Xn[tix(i, j)] - col[i];
+        }
     }
 }
 

@@ -929,8 +929,8 @@ __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float*
     } else if (METHOD == M_NEWTON_SCHULZ) {
         v4f Xt[NT];
         newton_schulz<OP, NB>(src, Xt, aux, ln);  // aux = number of iterations
-        if constexpr (REFINE) refine_once<OP, NB>(src, Xt, [](int, int) { return true; }, lds, ln);
-        store_result<NB>(Tm, Xt, [](int, int) { return true; }, lds, ln);
+        if constexpr (REFINE) refine_once<OP, NB>(src, Xt, [](int, int) { return false; }, lds, ln);  // (turns every tile)
+        store_result<NB>(Tm, Xt, [](int, int) { return REFINE; }, lds, ln);
     } else if (METHOD == M_NEUMANN) {
         v4f Xt[NT];
         neumann<OP, NB>(src, Xt, ln);
@@ -966,8 +966,15 @@ template <> struct TriInvPointers<M_FWD> {
     typedef float* __restrict__ out;
 };
 
+// Wavefronts per SIMD the register allocator has to leave room for.  Newton-Schulz with fp32 operands at C = 64 needs two:
+// its matrix-core and its vector instructions take about the same time and overlap only between wavefronts.
+template <int OP, int NB, int METHOD, bool REFINE> constexpr int min_waves_per_simd()
+{
+    return (METHOD == M_NEWTON_SCHULZ && OP == OP_F32 && NB == 4 && !REFINE) ? 2 : 1;
+}
+
 template <int OP, int NB, int METHOD, bool REFINE = false>
-__global__ __launch_bounds__(64) void k_tri_inv(typename TriInvPointers<METHOD>::in A, typename TriInvPointers<METHOD>::out T, int64_t n_mat,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_tri_inv(typename TriInvPointers<METHOD>::in A, typename TriInvPointers<METHOD>::out T, int64_t n_mat,
                                                 int in_dt, int aux, int out_dt)
 {
     constexpr int C = 16 * NB;
@@ -1031,7 +1038,7 @@ __device__ __forceinline__ int64_t fused_matrix_index(int64_t n_chunk, int H, in
 }
 
 template <int KD, int OP, int NB, int METHOD, int DKS, bool REFINE = false, int WPB = 1>
-__global__ __launch_bounds__(64 * WPB) void k_gdn_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_gdn_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt, int spread)
 {
@@ -1059,7 +1066,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gdn_tri_inv(const void* __restrict
 
 // Fused kernel of the scalar / no-gate kinds for head dimensions without a specialised build.
 template <int KD, int OP, int NB, int METHOD>
-__global__ __launch_bounds__(64) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
                                                            int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt)
 {
@@ -1083,7 +1090,7 @@ __global__ __launch_bounds__(64) void k_gdn_any_dk_tri_inv(const void* __restric
 
 // Fused kernel for the per-channel gate: g is [B, Tlen, H, d_k]; the gated keys are rounded to OP.
 template <int OP, int NB, int METHOD, int WPB = 1, bool REFINE = false>
-__global__ __launch_bounds__(64 * WPB) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int k_dt, int aux, int out_dt, int spread)
 {

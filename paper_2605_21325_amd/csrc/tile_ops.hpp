@@ -161,6 +161,87 @@ template <int OP, class FX, class FY> __device__ __forceinline__ v4f tn_sum(int 
 
 __device__ __forceinline__ v4f zero4() { return v4f{0.f, 0.f, 0.f, 0.f}; }
 
+// The 16 x 16 identity in tile layout (either orientation).
+__device__ __forceinline__ v4f identity_tile(Lane ln)
+{
+    v4f v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = 4 * ln.q + r == ln.n ? 1.f : 0.f;
+    return v;
+}
+
+// Two packed 16-bit tiles as one operand of the 32-deep instructions (gfx950): contraction slot 8 q + e stands for row
+// 4 q + e of the first tile (e < 4) or row 4 q + e - 4 of the second, the same on both operands, so the halves are just
+// the two packed tiles.  A chain of these instructions holds no 16-deep ones: the two kinds feeding one accumulator were
+// seen to give wrong tiles.
+template <int OP> struct PairOp {
+    v4u u;
+    __device__ __forceinline__ void set(int half, Opnd<OP> x)
+    {
+        const v2u w = __builtin_bit_cast(v2u, x.x);
+        u[2 * half] = w[0];
+        u[2 * half + 1] = w[1];
+    }
+    __device__ __forceinline__ Opnd<OP> get(int half) const
+    {
+        Opnd<OP> o;
+        o.x = __builtin_bit_cast(decltype(o.x), v2u{u[2 * half], u[2 * half + 1]});
+        return o;
+    }
+};
+template <int OP> __device__ __forceinline__ v4f tn_pair(PairOp<OP> x, PairOp<OP> y, v4f acc)
+{
+    if constexpr (OP == OP_F16)
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, x.u), __builtin_bit_cast(v8h, y.u), acc, 0, 0, 0);
+    else
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, x.u), __builtin_bit_cast(v8bf, y.u), acc, 0, 0, 0);
+}
+
+// An fp32 tile as the sum of three bf16 tiles, x = h + m + l: h = bf16(x), m = bf16(x - h), l = x - h - m, which is exact
+// (24 = 3 x 8 bits; both differences are exact, and what remains after m has at most 8 bits).  The product of two such
+// tiles is hh + hm + mh + hl + lh + mm up to terms below 2^-26 |x| |y| (an fp32 product rounds at 2^-24), all of
+// it accumulated in fp32: three 32-deep bf16 instructions of 16 cycles against four 16x16x4 fp32 instructions of 32.
+// Splitting costs 22 vector instructions a tile, so it pays where an operand is used several times.  Values above
+// 3.39e38 (the largest bf16) do not split.
+// The parts sit side by side in the order m h l, so that two overlapping windows of either operand feed the instructions:
+//   (m h) . (m h) = mm + hh,   (m h) . (h l) = mh + hl,   (h l) . (m h) = hm + lh.
+typedef uint32_t v6u __attribute__((ext_vector_type(6)));
+struct Split3 {
+    v6u u;
+    __device__ __forceinline__ Opnd<OP_BF16> m() const { return {__builtin_bit_cast(v4s, v2u{u[0], u[1]})}; }
+    __device__ __forceinline__ Opnd<OP_BF16> h() const { return {__builtin_bit_cast(v4s, v2u{u[2], u[3]})}; }
+    __device__ __forceinline__ Opnd<OP_BF16> l() const { return {__builtin_bit_cast(v4s, v2u{u[4], u[5]})}; }
+    __device__ __forceinline__ v8bf mh() const { return __builtin_bit_cast(v8bf, __builtin_shufflevector(u, u, 0, 1, 2, 3)); }
+    __device__ __forceinline__ v8bf hl() const { return __builtin_bit_cast(v8bf, __builtin_shufflevector(u, u, 2, 3, 4, 5)); }
+};
+__device__ __forceinline__ Split3 join3(Opnd<OP_BF16> m, Opnd<OP_BF16> h, Opnd<OP_BF16> l)
+{
+    const v2u a = __builtin_bit_cast(v2u, m.x), b = __builtin_bit_cast(v2u, h.x), c = __builtin_bit_cast(v2u, l.x);
+    return {v6u{a[0], a[1], b[0], b[1], c[0], c[1]}};
+}
+__device__ __forceinline__ v4f minus_bf16(v4f x, Opnd<OP_BF16> y)
+{
+#pragma clang fp contract(off)  // (x may be a product in the caller: fused into the subtraction it would lose its rounding)
+    const v2u w = __builtin_bit_cast(v2u, y.x);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] -= __builtin_bit_cast(float, (r & 1) ? (w[r / 2] & 0xffff0000u) : (w[r / 2] << 16));
+    return x;
+}
+__device__ __forceinline__ Split3 split3(v4f x)
+{
+    const Opnd<OP_BF16> h = pack<OP_BF16>(x);
+    x = minus_bf16(x, h);
+    const Opnd<OP_BF16> m = pack<OP_BF16>(x);
+    return join3(m, h, pack<OP_BF16>(minus_bf16(x, m)));
+}
+// acc + one part of X^T Y: the cross terms (0 and 1) or the leading term (2).  A sum of products keeps its cross terms in an
+// accumulator of their own until the end: in one accumulator every term would be rounded at the size of the whole sum,
+// three times per product (measured 1.5 times the error of fp32 products; with two accumulators 0.85 times).
+__device__ __forceinline__ v4f tn_split(int part, Split3 x, Split3 y, v4f acc)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(part == 0 ? x.hl() : x.mh(), part == 1 ? y.hl() : y.mh(), acc, 0, 0, 0);
+}
+
 // Index of lower tile (i, j), i >= j, in a packed array of NB*(NB+1)/2 tiles.
 __host__ __device__ constexpr int tix(int i, int j) { return i * (i + 1) / 2 + j; }
 

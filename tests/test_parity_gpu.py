@@ -862,6 +862,27 @@ def test_sixteen_bit_result_argument_errors():
     assert e.value.status == -3
 
 
+# ------------------------------------------------------------------ every Newton-Schulz iterate at C <= 64
+@pytest.mark.parametrize("op", _OPS, ids=lambda o: tri.DTYPE_NAMES[o])
+@pytest.mark.parametrize("C", [16, 32, 64])
+def test_newton_schulz_iterates(C, op):
+    """The m-th iterate, converged or not, against its closed form X_m = T (I - R0^(2^m)) in 64 bits (strictly lower part: the
+    stored diagonal is exactly 1): m = 1 is the start that is written down directly, m = 2 the first full iteration.  The
+    entries of A span eight orders of magnitude, so that every part of a split operand counts."""
+    from oracle import methods
+    A = si.random_strict_lower(5, C, 0.15, seed=23)
+    A[1] *= 1e-4
+    A[2, C // 2:] *= 1e-6
+    for m in (1, 2, 3, 9):
+        T = tri.tri_inv_ex(A.to(DEV), method=tri.NEWTON_SCHULZ, op_dtype=op, flags=tri.flag_iters(m))
+        got = np.tril(T.cpu().numpy().astype(np.float64), -1)
+        for k in range(A.shape[0]):
+            want = np.tril(methods.newton_schulz_closed_form(np.tril(A[k].numpy().astype(np.float64), -1), m), -1)
+            err = np.linalg.norm(got[k] - want) / np.linalg.norm(want)
+            # fp16: the start (I + A) / C^2 times entries of 1e-5 lies among the subnormal operands
+            assert err <= (TOL[op] if op != tri.F16 or k != 1 else 1e-1), (C, m, k, err)
+
+
 # ------------------------------------------------------------------ forward substitution by wavefront shuffles
 @pytest.mark.parametrize("dt", [torch.float32, torch.float16, torch.bfloat16])
 def test_forward_substitution_shuffle_variant(cases, dt):
