@@ -36,8 +36,10 @@ typedef enum { TRIINV_F32 = 0, TRIINV_F16 = 1, TRIINV_BF16 = 2 } triinv_dtype;
 
 /* Inversion methods. */
 typedef enum {
-    /* Row-wise forward substitution in fp32 vector arithmetic; the direct, matmul-free, stable
-     * baseline (the role of the vectorised column sweep, paper Sec. 3.1).  Ignores op_dtype. */
+    /* Forward substitution in fp32, 16 rows at a time: the 16 x 16 diagonal blocks row by row in vector arithmetic,
+     * the products of a tile row with the rows above it in fp32 matrix-core products; the direct, stable baseline
+     * (the role of the vectorised column sweep, paper Sec. 3.1).  Ignores op_dtype.  (TRIINV_FLAG_FWD_SHUFFLE: the
+     * row-by-row form without matrix products.) */
     TRIINV_FWD_SUBST = 0,
     /* Blocked 2x2 recursion (paper Alg. 4, Sec. 3.3, Eq. 7 in its lower-triangular reading):
      * X <- D_e + D_o - D_o A D_e for block sizes 1, 2, ..., C/2.  Log-stable. */

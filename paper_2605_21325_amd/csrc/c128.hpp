@@ -287,7 +287,7 @@ __device__ __forceinline__ void c128_store_result(v4f* mail, float* strip, Out T
             for (int a = 0; a < 4; ++a) mail[(4 * k + a) * 64 + lane] = Wc[k][a];
     }
     __syncthreads();  // wave 0's tiles of W are in LDS, and nobody reads the keys any more
-    zero_strip_patch(strip, ln);
+    zero_strip_patch<8>(strip, ln);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         v4f row[8];

@@ -107,13 +107,13 @@ int CAT(launch_tri_inv_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const Tr
 
 #endif
 
-// Unused dynamic LDS that keeps a compute unit (160 KB of LDS) at two workgroups = two wavefronts per
-// SIMD for the 16-bit-operand recursions at C = 64.  Those kernels are bound by the memory system,
-// not by latency: with more wavefronts resident they measured 2-4 % slower (more requests queued at
-// the memory controllers, none served sooner).
+// Unused dynamic LDS that keeps a compute unit (160 KB of LDS) at two workgroups = two wavefronts per SIMD for the
+// 16-bit-operand recursions at C = 64, and at four at C = 32.  Those kernels are bound by the memory system, not by latency:
+// with more wavefronts resident they measured 2-4 % slower (more requests queued at the memory controllers, none served
+// sooner).
 template <int METHOD> constexpr unsigned occupancy_pad_bytes()
 {
-    return (NB == 4 && WPB == 4 && OP != OP_F32 && (METHOD == M_BLOCK || METHOD == M_MIXED || METHOD == M_MIXED32 || METHOD == M_BLOCK_DIRECT)) ? 24576u : 0u;
+    return ((NB == 4 || NB == 2) && WPB == 4 && OP != OP_F32 && (METHOD == M_BLOCK || METHOD == M_MIXED || METHOD == M_MIXED32 || METHOD == M_BLOCK_DIRECT)) ? 24576u : 0u;
 }
 
 template <int KD, int METHOD, int DKS, bool REFINE = false> static int go_gdn(const GdnArgs& a)

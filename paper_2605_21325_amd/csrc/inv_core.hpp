@@ -95,7 +95,7 @@ __device__ __forceinline__ void leaf_neumann(v4f LN, v4f LT, v4f& XN, v4f& XT, L
 // Leaves by forward substitution in fp32 vector arithmetic (the direct method of paper Sec. 3.1
 // as the start X0 of Alg. 4 at b0 = 16).  Four leaves at a time: lane group q solves leaf q, lane
 // n its column n; the leaf's rows are read back from LDS with one address per lane group (LDS
-// broadcast).  lds: LEAF_FWD_FLOATS floats, wave-private.
+// broadcast).  lds: min(NB, 4) * LEAF_STRIDE floats, wave-private.
 // ---------------------------------------------------------------------------------------------
 constexpr int LEAF_LD = 20;                       // row stride inside a staged leaf
 constexpr int LEAF_STRIDE = 16 * LEAF_LD + 8;     // leaf stride: the four groups' rows fall into different banks
@@ -106,6 +106,30 @@ __device__ __forceinline__ void leaf_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Column c of the inverse of one staged leaf.  row_done(i): called when t[i] is final.
+struct NoRowHook {
+    __device__ __forceinline__ void operator()(int) const {}
+};
+template <class RowDone = NoRowHook>
+__device__ __forceinline__ void solve_leaf_column(const float* Al, int c, float (&t)[16], RowDone row_done = RowDone())
+{
+    t[0] = (c == 0) ? 1.f : 0.f;
+    row_done(0);
+#pragma unroll
+    for (int i = 1; i < 16; ++i) {
+        float acc = 0.f;
+#pragma unroll
+        for (int j4 = 0; j4 < i; j4 += 4) {
+            const v4f a = *reinterpret_cast<const v4f*>(&Al[i * LEAF_LD + j4]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (j4 + r < i) acc += a[r] * t[j4 + r];
+        }
+        t[i] = (c < i) ? -acc : ((c == i) ? 1.f : 0.f);
+        row_done(i);
+    }
 }
 
 template <int NB, class ASrc>
@@ -120,25 +144,14 @@ __device__ __forceinline__ void leaves_forward_substitution(const ASrc& A, v4f (
             *reinterpret_cast<v4f*>(&lds[d * LEAF_STRIDE + ln.n * LEAF_LD + 4 * ln.q]) = v;
         }
         leaf_lds_sync();
-        const float* Al = lds + ln.q * LEAF_STRIDE;  // this lane group's leaf
+        // this lane group's leaf (fewer leaves than lane groups: the surplus groups solve the last one along with its own)
+        float* Al = lds + (ln.q < PER ? ln.q : PER - 1) * LEAF_STRIDE;
         const int c = ln.n;
         float t[16];
-        t[0] = (c == 0) ? 1.f : 0.f;
-#pragma unroll
-        for (int i = 1; i < 16; ++i) {
-            float acc = 0.f;
-#pragma unroll
-            for (int j4 = 0; j4 < i; j4 += 4) {
-                const v4f a = *reinterpret_cast<const v4f*>(&Al[i * LEAF_LD + j4]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (j4 + r < i) acc += a[r] * t[j4 + r];
-            }
-            t[i] = (c < i) ? -acc : ((c == i) ? 1.f : 0.f);
-        }
+        solve_leaf_column(Al, c, t);
         leaf_lds_sync();
 #pragma unroll
-        for (int i = 0; i < 16; ++i) lds[ln.q * LEAF_STRIDE + i * LEAF_LD + c] = t[i];
+        for (int i = 0; i < 16; ++i) Al[i * LEAF_LD + c] = t[i];
         leaf_lds_sync();
 #pragma unroll
         for (int d = 0; d < PER; ++d) {
@@ -182,7 +195,7 @@ __device__ __forceinline__ v4f transpose_tile(v4f t, float* patch, Lane ln)
 template <int NB, bool ROOT_T>
 __host__ __device__ constexpr bool result_is_T(int i, int j)
 {
-    return (NB == 1) ? false : ((j >= NB / 2) ? true : ((i < NB / 2) ? false : ROOT_T));
+    return (NB == 1) ? ROOT_T : ((j >= NB / 2) ? true : ((i < NB / 2) ? false : ROOT_T));
 }
 
 enum : int { LEAF_BLOCK_RECURSIVE = 0, LEAF_NEUMANN = 1, LEAF_FORWARD = 2, LEAF_NEUMANN32 = 3 };

@@ -4,10 +4,10 @@
 //                         four wavefronts = four adjacent heads per workgroup at C <= 64)
 //   k_kda_tri_inv         per-channel gate: gated keys contracted 32 channels at a time
 //   k_gdn_any_dk_tri_inv  head dimensions without a specialised build (channel loop)
-//   k_tri_inv_fwd_shuffle64  forward substitution with wavefront shuffles (baseline variant)
+//   k_tri_inv_fwd_shuffle64  row-by-row forward substitution with wavefront shuffles (baseline variant)
 // and, at C = 128, four wavefronts per matrix with tiles in LDS for the methods whose state does not fit
 // one wavefront: k_*_neumann128 (Neumann product), k_*_ns128 (Newton-Schulz).
-// Methods: forward substitution (fp32 vector arithmetic, A broadcast through LDS), blocked recursion, mixed
+// Methods: forward substitution (fp32, 16 rows at a time), blocked recursion, mixed
 // recursion, blocked recursion from directly solved blocks, Neumann product, Newton-Schulz, refinement
 // (inv_core.hpp).  csrc/chunk_map.hpp says where a chunk's tokens are.
 #pragma once
@@ -33,6 +33,7 @@ __device__ __forceinline__ void wave_lds_sync()
 template <int NB> struct GlobalA {
     static constexpr int C = 16 * NB;
     static constexpr bool kFromMemory = true;   // a tile is a plain load: fetch it when it is needed
+    static constexpr bool kHoldsKeys = false;
     const void* base;  // first element of this matrix
     int dt;            // OP_F32 / OP_F16 / OP_BF16 storage
     Lane ln;
@@ -192,6 +193,7 @@ template <int NB, bool NOGATE = false> struct GateVec {
 
 template <int KD, int NB, int DKS> struct GramA {
     static constexpr bool kFromMemory = false;  // a tile costs matrix-core work and pins the key registers
+    static constexpr bool kHoldsKeys = true;
     typedef typename KeyVec<KD>::type kvec;
     static constexpr int C = 16 * NB;
     static constexpr int KSTEP = (KD == OP_F32) ? 16 : 32;  // channels per k-step
@@ -272,6 +274,7 @@ template <int NB, int METHOD> __host__ __device__ constexpr bool need_tile(int i
 // Tile source 3: all tiles precomputed in registers.
 template <int NB> struct PreA {
     static constexpr bool kFromMemory = false;
+    static constexpr bool kHoldsKeys = false;
     v4f n[NB * (NB + 1) / 2], t[NB * (NB + 1) / 2];
     template <bool TR> __device__ __forceinline__ v4f get(int i, int j) const { return TR ? t[tix(i, j)] : n[tix(i, j)]; }
 };
@@ -586,7 +589,7 @@ __device__ __forceinline__ void build_A_scalar_any_dk(PreA<NB>& out, const void*
 // cache lines written by one instruction stream to HBM markedly faster than the 64-byte pieces
 // a tile-shaped store produces.  Diagonal tiles get an exact unit diagonal and exact zeros above
 // it; columns right of the diagonal tile are zero-filled.
-// lds: STORE_LDS_FLOATS floats.
+// lds: store_lds_floats<NB>() floats.
 // ---------------------------------------------------------------------------------------------
 // Streaming stores of the result.  Whole 16-byte pieces of full rows go out non-temporal and at
 // system scope (written through the caches: T is consumed by a later kernel, never re-read here);
@@ -628,38 +631,24 @@ __device__ __forceinline__ void stream_store(v4f v, __amdgpu_buffer_rsrc_t out, 
     stream_store(__builtin_bit_cast(v4u, v), out, lane_offset, uniform_offset);
 }
 __device__ __forceinline__ void stream_store(float v, float* p) { __builtin_nontemporal_store(v, p); }
-// Element idx of a result matrix whose element size ESZ is known at compile time (so that the row part of the address
-// folds into the store's immediate offset): fp32, or rounded to nearest even into the 16-bit type the caller asked for.
-// ESZ = 0: the element size is read at run time, one address for both widths.
-template <int ESZ> __device__ __forceinline__ void stream_store(float v, Out Tm, int64_t idx)
-{
-    if constexpr (ESZ == 4) {
-        __builtin_nontemporal_store(v, static_cast<float*>(Tm.base) + idx);
-    } else if constexpr (ESZ == 2) {
-        __builtin_nontemporal_store((uint16_t)(Tm.dt == OP_F16 ? pack2_f16(v, 0.f) : pack2_bf16(v, 0.f)),
-                                    static_cast<uint16_t*>(Tm.base) + idx);
-    } else {
-        const int sh = Tm.dt == OP_F32 ? 2 : 1;
-        char* const p = static_cast<char*>(Tm.base) + (idx << sh);
-        if (sh == 2)
-            __builtin_nontemporal_store(v, reinterpret_cast<float*>(p));
-        else
-            __builtin_nontemporal_store((uint16_t)(Tm.dt == OP_F16 ? pack2_f16(v, 0.f) : pack2_bf16(v, 0.f)), reinterpret_cast<uint16_t*>(p));
-    }
-}
-
-constexpr int STORE_LD = 16 * 8 + 4;                  // row stride of the patch (fits C = 128), floats
-constexpr int STORE_LDS_FLOATS = 16 * STORE_LD;
+// Row stride of the patch in floats.  C <= 32 has a patch of its own size: with one that fits C = 128 its wavefronts would clear
+// 8 KB of LDS for a 1 or 4 KB result, and 18 of them would fill a compute unit (65536 matrices of C = 16, forward
+// substitution: 41.9 us).  C = 64 keeps the larger one: it holds four wavefronts' workgroups to four per
+// compute unit, and those kernels run slower with more (see occupancy_pad_bytes).
+template <int NB> __host__ __device__ constexpr int store_ld() { return NB <= 2 ? 16 * NB + 4 : 16 * 8 + 4; }
+template <int NB> __host__ __device__ constexpr int store_lds_floats() { return 16 * store_ld<NB>(); }
+constexpr int STORE_LDS_FLOATS = store_lds_floats<8>();
 
 // Zero the strip patch.  Strips stored afterwards in ascending order then find zeros right of their diagonal tile (strip
 // i only writes tiles 0..i), which spares them a select per stored element.
-__device__ __forceinline__ void zero_strip_patch(float* lds, Lane ln)
+template <int NB> __device__ __forceinline__ void zero_strip_patch(float* lds, Lane ln)
 {
+    constexpr int VECS = store_lds_floats<NB>() / 4;
     const int lane = 16 * ln.q + ln.n;
 #pragma unroll
-    for (int k = 0; k < (STORE_LDS_FLOATS / 4 + 63) / 64; ++k) {
+    for (int k = 0; k < (VECS + 63) / 64; ++k) {
         const int p = 64 * k + lane;
-        if (p < STORE_LDS_FLOATS / 4) *reinterpret_cast<v4f*>(&lds[4 * p]) = zero4();
+        if (p < VECS) *reinterpret_cast<v4f*>(&lds[4 * p]) = zero4();
     }
     wave_lds_sync();
 }
@@ -671,6 +660,7 @@ __device__ __forceinline__ void store_strip(Out Tm, int i, const v4f (&row)[NB],
                                             float diag = 1.f)
 {
     constexpr int C = 16 * NB;
+    constexpr int LD = store_ld<NB>();
     const int lane = 16 * ln.q + ln.n;
     const __amdgpu_buffer_rsrc_t out = matrix_buffer(Tm, C);
 #pragma unroll
@@ -685,14 +675,14 @@ __device__ __forceinline__ void store_strip(Out Tm, int i, const v4f (&row)[NB],
                     v[r] = (rr == cc) ? diag : ((rr > cc) ? v[r] : 0.f);
                 }
             }
-            *reinterpret_cast<v4f*>(&lds[ln.n * STORE_LD + 16 * j + 4 * ln.q]) = v;
+            *reinterpret_cast<v4f*>(&lds[ln.n * LD + 16 * j + 4 * ln.q]) = v;
         } else {            // v[r] = T[16i + 4q + r][16j + n]
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int rr = 4 * ln.q + r, cc = ln.n;
                 float x = v[r];
                 if (i == j) x = (rr == cc) ? diag : ((rr > cc) ? x : 0.f);
-                lds[rr * STORE_LD + 16 * j + cc] = x;
+                lds[rr * LD + 16 * j + cc] = x;
             }
         }
     }
@@ -704,7 +694,7 @@ __device__ __forceinline__ void store_strip(Out Tm, int i, const v4f (&row)[NB],
         for (int k = 0; k < 16 / RPI; ++k) {
             const int rr = RPI * k + lane / LPR, cc = 4 * (lane % LPR);
             // unconditional read (columns right of the diagonal tile hold stale patch contents), then a select
-            v4f v = *reinterpret_cast<const v4f*>(&lds[rr * STORE_LD + cc]);
+            v4f v = *reinterpret_cast<const v4f*>(&lds[rr * LD + cc]);
             if (!ZEROED && cc >= 16 * (i + 1)) v = zero4();
             stream_store(v, out, ((lane / LPR) * C + cc) * 4, (16 * i + RPI * k) * C * 4);
         }
@@ -715,8 +705,8 @@ __device__ __forceinline__ void store_strip(Out Tm, int i, const v4f (&row)[NB],
         for (int k = 0; k < ITER; ++k) {
             const int rr = RPI * k + lane / LPR, cc = 8 * (lane % LPR);
             if (RPI > 16 && rr >= 16) continue;  // C = 16: more lanes than the strip has 16-byte pieces
-            v4f a = *reinterpret_cast<const v4f*>(&lds[rr * STORE_LD + cc]);
-            v4f b = *reinterpret_cast<const v4f*>(&lds[rr * STORE_LD + cc + 4]);
+            v4f a = *reinterpret_cast<const v4f*>(&lds[rr * LD + cc]);
+            v4f b = *reinterpret_cast<const v4f*>(&lds[rr * LD + cc + 4]);
             if (!ZEROED && cc >= 16 * (i + 1)) a = zero4();
             if (!ZEROED && cc + 4 >= 16 * (i + 1)) b = zero4();
             const v4u p = Tm.dt == OP_F16 ? v4u{pack2_f16(a[0], a[1]), pack2_f16(a[2], a[3]), pack2_f16(b[0], b[1]), pack2_f16(b[2], b[3])}
@@ -731,7 +721,28 @@ template <int NB, class IsT>
 __device__ __forceinline__ void store_result(Out Tm, const v4f (&Tt)[NB * (NB + 1) / 2], IsT is_t, float* lds, Lane ln,
                                              float diag = 1.f)
 {
-    zero_strip_patch(lds, ln);
+    if constexpr (NB == 1) {
+        // a single tile in T orientation is already 16 rows of four 16-byte pieces: no turn through LDS (C = 16, 65536 matrices,
+        // fp32 operands, standalone blocked recursion 29 -> 21 us together with the smaller patch)
+        if (is_t(0, 0)) {
+            const __amdgpu_buffer_rsrc_t out = matrix_buffer(Tm, 16);
+            v4f v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int cc = 4 * ln.q + r;
+                v[r] = (ln.n == cc) ? diag : ((ln.n > cc) ? Tt[0][r] : 0.f);
+            }
+            const int e = ln.n * 16 + 4 * ln.q;
+            if (Tm.dt == OP_F32)
+                stream_store(v, out, e * 4);
+            else
+                __builtin_amdgcn_raw_buffer_store_b64(Tm.dt == OP_F16 ? v2u{pack2_f16(v[0], v[1]), pack2_f16(v[2], v[3])}
+                                                                      : v2u{pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])},
+                                                      out, e * 2, 0, CACHE_SC0_SC1_NT);
+            return;
+        }
+    }
+    zero_strip_patch<NB>(lds, ln);
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
         v4f row[NB];
@@ -742,70 +753,78 @@ __device__ __forceinline__ void store_result(Out Tm, const v4f (&Tt)[NB * (NB + 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Forward substitution, row by row, in fp32 vector arithmetic.  Lane = one column c of T:
-//   T[i][c] = [i == c] - sum_{j < i} A[i][j] T[j][c]
-// so every lane needs the same A[i][j]: the rows of A are staged through LDS, 16 rows at a
-// time (double-buffered), and read back with wave-uniform addresses (LDS broadcast).
-// C = 128 runs two passes of 64 columns; pass p only involves rows and columns >= 64 p.
-// Cost per matrix: C(C-1)/2 FMAs per lane plus one 16-byte LDS broadcast read per four of them; a
-// single running sum per row measured faster than four interleaved partial sums.
-// lds: wave-private, 2 * 16 * (C + 4) floats.
+// Forward substitution in fp32, 16 rows at a time.  The 16 x 16 diagonal blocks are solved row by row in vector arithmetic
+// (leaves_forward_substitution: D_i = (I + A_ii)^-1), and a tile row of T follows from the rows above it by
+//   T_ik = -D_i (A_ik T_kk + ... + A_i,i-1 T_i-1,k),   k < i,
+// in fp32 matrix-core products.  A row of A is needed only for its own row of T, so T takes A's place in registers.
+// Row by row throughout, a matrix of C = 128 took 10144 dependent multiply-adds and 2536 LDS broadcasts per lane, with A in
+// 36 KB of LDS and therefore one wavefront per SIMD; this way 112 tile products, two wavefronts, and it is bound by memory.
+// 2048 fused matrices of C = 128 140 -> 42 us, one call of 64: 63 -> 15 us; standalone fp32 135 -> 83 us (4096 matrices);
+// C = 64 fused 69 -> 53 us, standalone 53 -> 44 us (8192).  Error against 64 bits 1.5e-7 -> 1.4e-7 and 8.4e-8 -> 6.2e-8
+// below the diagonal, 5.4e-7 -> 5.8e-7 on correlated keys without decay.
 // ---------------------------------------------------------------------------------------------
-template <int NB> constexpr int fwd_lds_floats() { return 2 * 16 * (16 * NB + 4); }
+// All tiles of A are formed first, from the last tile row up: a source that holds keys needs them ever less then, and A and
+// the remaining keys fit two wavefronts per SIMD at C = 128.
+template <int NB> struct TilesT {
+    static constexpr bool kFromMemory = false;
+    const v4f (&t)[NB * (NB + 1) / 2];
+    template <bool TR> __device__ __forceinline__ v4f get(int i, int j) const { return t[tix(i, j)]; }
+};
 
-template <int NB, int ESZ, class ASrc>
+template <int NB, class ASrc>
 __device__ __forceinline__ void forward_substitution(const ASrc& A, Out Tm, float* lds, Lane ln)
 {
-    constexpr int C = 16 * NB;
-    constexpr int LD = C + 4;
-    constexpr int PASSES = C >= 64 ? C / 64 : 1;  // C < 64: one pass, lanes >= C idle along (they store nothing)
-    const int lane = 16 * ln.q + ln.n;
-#pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-        const int c = 64 * p + lane;  // this lane's column
-        const bool mine = C >= 64 || c < C;
-        float Tc[C];                  // Tc[k] = T[64p + k][c]
-        if (p > 0) {
-            // rows above this pass's diagonal block: columns >= 64p are zero there
-#pragma unroll 8
-            for (int i = 0; i < 64 * p; ++i) stream_store<ESZ>(0.f, Tm, (int64_t)i * C + c);
+    if constexpr (NB == 1) {
+        // one leaf: its rows are stored as they are finished, without another turn through LDS (a copy per element size: a
+        // choice inside the loop splits it into blocks, and all reads of the leaf end up before the first)
+        const v4f a = A.template get<true>(0, 0);
+        *reinterpret_cast<v4f*>(&lds[ln.n * LEAF_LD + 4 * ln.q]) = a;
+        leaf_lds_sync();
+        float t[16];
+        if (Tm.dt == OP_F32) {
+            float* const out = static_cast<float*>(Tm.base) + ln.n;
+            solve_leaf_column(lds, ln.n, t, [&](int i) { if (ln.q == 0) __builtin_nontemporal_store(t[i], out + 16 * i); });
+        } else {
+            uint16_t* const out = static_cast<uint16_t*>(Tm.base) + ln.n;
+            solve_leaf_column(lds, ln.n, t, [&](int i) {
+                if (ln.q == 0) __builtin_nontemporal_store((uint16_t)(Tm.dt == OP_F16 ? pack2_f16(t[i], 0.f) : pack2_bf16(t[i], 0.f)), out + 16 * i);
+            });
         }
-        v4f stage[NB];  // tiles (s, 4p..s) of the strip being staged, T orientation = row-major pieces
-        stage[4 * p] = A.template get<true>(4 * p, 4 * p);
+        return;
+    }
+    v4f T[NB * (NB + 1) / 2];  // A in T orientation, then row by row T in N orientation
 #pragma unroll
-        for (int s = 4 * p; s < NB; ++s) {
-            float* buf = lds + (s & 1) * 16 * LD;
+    for (int i = NB - 1; i >= 0; --i) {
 #pragma unroll
-            for (int j = 4 * p; j <= s; ++j) *reinterpret_cast<v4f*>(&buf[ln.n * LD + 16 * j + 4 * ln.q]) = stage[j];
-            wave_lds_sync();
-            if (s + 1 < NB) {
+        for (int j = 0; j <= i; ++j) T[tix(i, j)] = A.template get<true>(i, j);
+        if (ASrc::kHoldsKeys && NB == 8) __builtin_amdgcn_sched_barrier(0);
+    }
+    v4f leafN[NB], leafT[NB];
+    leaves_forward_substitution<NB>(TilesT<NB>{T}, leafN, leafT, lds, ln);
 #pragma unroll
-                for (int j = 4 * p; j <= s + 1; ++j) stage[j] = A.template get<true>(s + 1, j);
-            }
+    for (int i = 0; i < NB; ++i) {
+        T[tix(i, i)] = leafN[i];
+        Opnd<OP_F32> a[NB];
 #pragma unroll
-            for (int ii = 0; ii < 16; ++ii) {
-                const int i = 16 * s + ii;
-                float acc = 0.f;
+        for (int j = 0; j < NB; ++j)
+            if (j < i) a[j] = pack<OP_F32>(T[tix(i, j)]);
 #pragma unroll
-                for (int j4 = 64 * p; j4 < i; j4 += 4) {
-                    const v4f a = *reinterpret_cast<const v4f*>(&buf[ii * LD + j4]);
+        for (int k = 0; k < NB; ++k) {
+            if (k >= i) continue;
+            v4f s = zero4();
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (j4 + r < i) acc += a[r] * Tc[j4 + r - 64 * p];
-                }
-                const float t = (c < i) ? -acc : ((c == i) ? 1.f : 0.f);
-                Tc[i - 64 * p] = t;
-                if (mine) stream_store<ESZ>(t, Tm, (int64_t)i * C + c);
-            }
+            for (int j = NB - 1; j >= 0; --j)
+                if (j >= k && j < i) s = tn<OP_F32>(a[j], pack<OP_F32>(T[tix(j, k)]), s);
+            T[tix(i, k)] = tn<OP_F32>(pack<OP_F32>(leafT[i]), pack<OP_F32>(-s), zero4());
         }
     }
+    store_result<NB>(Tm, T, [](int, int) { return false; }, lds, ln);
 }
 
-// Forward substitution at C = 64 with the row of A broadcast by wavefront shuffles instead of LDS: lane l
+// Forward substitution at C = 64 row by row, the row of A broadcast by wavefront shuffles: lane l
 // holds A[i][l] of every row i (one coalesced 256-byte load per row, all 63 issued up front) and
-// T[:, l]; A[i][j] reaches every lane through a v_readlane of lane j.  One shuffle per multiply-add
-// makes this variant issue about twice the vector instructions of the LDS-broadcast form above
-// (measured: see the benchmark table); it is kept as the plain shuffle baseline.
+// T[:, l]; A[i][j] reaches every lane through a v_readlane of lane j, one shuffle per multiply-add.  Kept as the plain
+// shuffle baseline (210 us for 16384 matrices).
 __device__ __forceinline__ void forward_substitution_shuffle64(const void* Am, int in_dt, float* Tm, Lane ln)
 {
     constexpr int C = 64;
@@ -847,51 +866,6 @@ __global__ __launch_bounds__(64) void k_tri_inv_fwd_shuffle64(const void* __rest
                                    lane_id());
 }
 
-// The same substitution with all of A resident in LDS (tile-packed, 1 KB per lower tile): used at
-// C >= 64 when the tiles come out of registers (Gram products), so that the key registers and the
-// tile registers are free before the running values of T take theirs (C = 64: 10 KB per wavefront,
-// four wavefronts per SIMD; 140 -> 122 us on the 16 384-matrix workload against the strip-staged form).
-template <int NB> constexpr int fwd_resident_lds_floats() { return NB * (NB + 1) / 2 * 256; }
-
-template <int NB, int ESZ, class ASrc>
-__device__ __forceinline__ void forward_substitution_resident(const ASrc& A, Out Tm, float* lds, Lane ln)
-{
-    constexpr int C = 16 * NB;
-    const int lane = 16 * ln.q + ln.n;
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j <= i; ++j)
-            *reinterpret_cast<v4f*>(&lds[tix(i, j) * 256 + ln.n * 16 + 4 * ln.q]) = A.template get<true>(i, j);
-    wave_lds_sync();
-#pragma unroll
-    for (int p = 0; p < C / 64; ++p) {
-        const int c = 64 * p + lane;
-        float Tc[C];
-        if (p > 0) {
-#pragma unroll 8
-            for (int i = 0; i < 64 * p; ++i) stream_store<ESZ>(0.f, Tm, (int64_t)i * C + c);
-        }
-#pragma unroll
-        for (int i = 64 * p; i < C; ++i) {
-            float acc = 0.f;
-#pragma unroll
-            for (int j4 = 64 * p; j4 < i; j4 += 4) {
-                const v4f a = *reinterpret_cast<const v4f*>(&lds[tix(i / 16, j4 / 16) * 256 + (i % 16) * 16 + (j4 % 16)]);
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (j4 + r < i) acc += a[r] * Tc[j4 + r - 64 * p];
-            }
-            const float t = (c < i) ? -acc : ((c == i) ? 1.f : 0.f);
-            Tc[i - 64 * p] = t;
-            stream_store<ESZ>(t, Tm, (int64_t)i * C + c);
-            // keep the scheduler from hoisting later rows' LDS reads over this row (they do not depend on
-            // it, and hoisted by the hundred they would spill the running values of T)
-            if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Kernels
 // ---------------------------------------------------------------------------------------------
@@ -914,18 +888,7 @@ __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float*
         return;
     }
     if (METHOD == M_FWD) {
-        // The strip-staged form (standalone entry point, small C) gets one copy per element size of the result: the
-        // wave-uniform branch costs nothing, a run-time element size costs every store its immediate offset (107 against
-        // 116 us on 16 384 matrices of C = 64).  The fused, LDS-resident form keeps one copy with a run-time size: two
-        // copies behind the Gram prologue nearly double its registers (100 -> 193 at C = 64: 122 -> 136 us).
-        if constexpr (NB >= 4 && !ASrc::kFromMemory) {
-            forward_substitution_resident<NB, 0>(src, Tm, lds, ln);
-        } else {
-            if (Tm.dt == OP_F32)
-                forward_substitution<NB, 4>(src, Tm, lds, ln);
-            else
-                forward_substitution<NB, 2>(src, Tm, lds, ln);
-        }
+        forward_substitution<NB>(src, Tm, lds, ln);
     } else if (METHOD == M_NEWTON_SCHULZ) {
         v4f Xt[NT];
         newton_schulz<OP, NB>(src, Xt, aux, ln);  // aux = number of iterations
@@ -949,10 +912,13 @@ __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float*
     }
 }
 
-template <int NB, int METHOD, bool FUSED = false> constexpr int core_lds_floats()
+// LDS of one wavefront's inversion: the store patch, which also serves as transpose patch and holds the staged leaves of the
+// direct methods (a leaf per tile row, at most four at a time).
+template <int NB> constexpr int core_lds_floats()
 {
-    static_assert(STORE_LDS_FLOATS >= XPOSE_FLOATS && STORE_LDS_FLOATS >= LEAF_FWD_FLOATS, "the store patch is the largest user");
-    return METHOD != M_FWD ? STORE_LDS_FLOATS : (FUSED && NB >= 4) ? fwd_resident_lds_floats<NB>() : fwd_lds_floats<NB>();
+    constexpr int leaves = (NB < 4 ? NB : 4) * LEAF_STRIDE;
+    constexpr int small = leaves > XPOSE_FLOATS ? leaves : XPOSE_FLOATS;
+    return store_lds_floats<NB>() > small ? store_lds_floats<NB>() : small;
 }
 
 // The matrix-product kernels may be run in place (A and T the same memory: the composed path of the fused entry points),
@@ -967,10 +933,12 @@ template <> struct TriInvPointers<M_FWD> {
 };
 
 // Wavefronts per SIMD the register allocator has to leave room for.  Newton-Schulz with fp32 operands at C = 64 needs two:
-// its matrix-core and its vector instructions take about the same time and overlap only between wavefronts.
-template <int OP, int NB, int METHOD, bool REFINE> constexpr int min_waves_per_simd()
+// its matrix-core and its vector instructions take about the same time and overlap only between wavefronts.  So does forward
+// substitution from keys of d_k = 128 at C = 128 (229 registers this way, 291 and one wavefront otherwise).  The channel-loop
+// kernels at C = 128 hold A beside the running keys and would spill.
+template <int OP, int NB, int METHOD, bool REFINE, bool CHANNEL_LOOP = false> constexpr int min_waves_per_simd()
 {
-    return (METHOD == M_NEWTON_SCHULZ && OP == OP_F32 && NB == 4 && !REFINE) ? 2 : 1;
+    return ((METHOD == M_NEWTON_SCHULZ && OP == OP_F32 && NB == 4 && !REFINE) || (METHOD == M_FWD && NB == 8 && !CHANNEL_LOOP)) ? 2 : 1;
 }
 
 template <int OP, int NB, int METHOD, bool REFINE = false>
@@ -978,7 +946,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_pe
                                                 int in_dt, int aux, int out_dt)
 {
     constexpr int C = 16 * NB;
-    __shared__ __attribute__((aligned(16))) float lds[core_lds_floats<NB, METHOD>()];
+    __shared__ __attribute__((aligned(16))) float lds[core_lds_floats<NB>()];
     const int64_t m = blockIdx.x;
     if (m >= n_mat) return;
     const Lane ln = lane_id();
@@ -1043,7 +1011,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt, int spread)
 {
     constexpr int C = 16 * NB;
-    constexpr int CORE = core_lds_floats<NB, METHOD, true>();
+    constexpr int CORE = core_lds_floats<NB>();
     constexpr int GATE = gate_lds_floats<NB>();
     constexpr int PER_WAVE = CORE > GATE ? CORE : GATE;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
@@ -1066,12 +1034,12 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
 
 // Fused kernel of the scalar / no-gate kinds for head dimensions without a specialised build.
 template <int KD, int OP, int NB, int METHOD>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false, true>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
                                                            int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt)
 {
     constexpr int C = 16 * NB;
-    constexpr int CORE = core_lds_floats<NB, METHOD, true>();
+    constexpr int CORE = core_lds_floats<NB>();
     constexpr int GATE = gate_lds_floats<NB>();
     __shared__ __attribute__((aligned(16))) float lds[CORE > GATE ? CORE : GATE];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
@@ -1090,12 +1058,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_pe
 
 // Fused kernel for the per-channel gate: g is [B, Tlen, H, d_k]; the gated keys are rounded to OP.
 template <int OP, int NB, int METHOD, int WPB = 1, bool REFINE = false>
-__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE, true>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int k_dt, int aux, int out_dt, int spread)
 {
     constexpr int C = 16 * NB;
-    constexpr int CORE = core_lds_floats<NB, METHOD, true>();
+    constexpr int CORE = core_lds_floats<NB>();
     constexpr int PER_WAVE = CORE > C ? CORE : C;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
     float* lds = lds_all + ((WPB == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * PER_WAVE;

@@ -273,6 +273,11 @@ __device__ __forceinline__ void invert_and_apply(const ASrc& src, RhsX<OP, NB>& 
     }
 }
 
+// LDS of one wavefront.  It only holds the gate's values and transposes tiles; the size is what keeps C <= 32 at four wavefronts
+// per SIMD, where these kernels, bound by the memory system, are fastest (C = 16, one right-hand side, 65536 matrices: 131
+// against 139 us with eight).
+constexpr int SOLVE_LDS_FLOATS = STORE_LDS_FLOATS;
+
 // XPOS: where the loads of X's first column group are issued -- 1: between the Gram products and the recursion (every
 // tile of A is formed first, so the keys' registers are free); 2: after the recursion; 3: as many tile rows as fit beside
 // the keys before the recursion, the rest inside its last merge or after it (see invert_and_apply).
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(1, NB 
                                                             int H, int d_k, int aux, int spread)
 {
     constexpr int C = 16 * NB;
-    constexpr int CORE = core_lds_floats<NB, METHOD, true>();
+    constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int GATE = gate_lds_floats<NB>();
     constexpr int PER_WAVE = CORE > GATE ? CORE : GATE;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
@@ -334,7 +339,7 @@ __global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restri
                                                             int H, int d_k, int k_dt, int aux, int spread)
 {
     constexpr int C = 16 * NB;
-    constexpr int CORE = core_lds_floats<NB, METHOD, true>();
+    constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int PER_WAVE = CORE > C ? CORE : C;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
     float* lds = lds_all + ((WPB == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * PER_WAVE;
@@ -368,7 +373,7 @@ __global__ __launch_bounds__(64) void k_gdn_any_dk_tri_solve(const void* __restr
                                                              int H, int d_k, int aux)
 {
     constexpr int C = 16 * NB;
-    constexpr int CORE = core_lds_floats<NB, METHOD, true>();
+    constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int GATE = gate_lds_floats<NB>();
     __shared__ __attribute__((aligned(16))) float lds[CORE > GATE ? CORE : GATE];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);

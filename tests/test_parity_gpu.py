@@ -883,6 +883,25 @@ def test_newton_schulz_iterates(C, op):
             assert err <= (TOL[op] if op != tri.F16 or k != 1 else 1e-1), (C, m, k, err)
 
 
+# ------------------------------------------------------------------ forward substitution, 16 rows at a time
+@pytest.mark.parametrize("in_dt", [torch.float32, torch.bfloat16], ids=["A_f32", "A_bf16"])
+@pytest.mark.parametrize("C", [16, 32, 64, 128])
+def test_forward_substitution_by_tile_rows(C, in_dt):
+    """Every element against the oracle within the elementwise bound, garbage on and above the diagonal, for one matrix and for an
+    odd number of them; a matrix without off-diagonal tiles (block diagonal) and one with the diagonal tiles empty, where
+    a tile row's two halves (the leaf, the products) each stand alone; the 16-bit result is the fp32 one rounded once."""
+    A = si.random_strict_lower(7, C, 0.2, seed=31).to(in_dt)
+    tile = torch.arange(C) // 16
+    same = tile[:, None] == tile[None, :]
+    A[1][~same] = 0
+    A[2][same] = 0
+    for n in (1, 7):
+        T = tri.tri_inv_ex(A[:n].to(DEV), method=tri.FWD_SUBST, op_dtype=tri.F32)
+        check(T, oracle.tri_inv(A[:n]), 1e-5, f"forward C={C} n={n}")
+    for out in (torch.float16, torch.bfloat16):
+        assert torch.equal(tri.tri_inv_ex(A.to(DEV), method=tri.FWD_SUBST, op_dtype=tri.F32, out_dtype=out), T.to(out))
+
+
 # ------------------------------------------------------------------ forward substitution by wavefront shuffles
 @pytest.mark.parametrize("dt", [torch.float32, torch.float16, torch.bfloat16])
 def test_forward_substitution_shuffle_variant(cases, dt):
