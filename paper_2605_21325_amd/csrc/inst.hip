@@ -30,10 +30,18 @@ namespace triinv {
 constexpr int NB = TRIINV_INST_NB;
 constexpr int OP = TRIINV_INST_OP;
 
+// CALL with IN = the element type of A as a compile-time constant.
+#define TRIINV_FOR_INPUT(dt, CALL) \
+    switch (dt) {                  \
+    case OP_F32: { constexpr int IN = OP_F32; CALL; } \
+    case OP_F16: { constexpr int IN = OP_F16; CALL; } \
+    default: { constexpr int IN = OP_BF16; CALL; }    \
+    }
+
 template <int METHOD, bool REFINE = false> static int go_tri(const TriInvArgs& a)
 {
-    return launch_kernel(a.dry, k_tri_inv<OP, NB, METHOD, REFINE>, dim3((unsigned)a.n_mat), dim3(64), 0, a.stream, a.A, a.T, a.n_mat,
-                       a.in_dt, a.iters, a.out_dt);
+    TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv<IN, OP, NB, METHOD, REFINE>), dim3((unsigned)a.n_mat), dim3(64), 0,
+                                                   a.stream, a.A, a.T, a.n_mat, a.iters, a.out_dt))
 }
 
 // Fused matrix-core kernels at C <= 64 run four matrices (adjacent heads) per workgroup.
@@ -65,7 +73,8 @@ int CAT(launch_tri_inv_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const Tr
             TriInvArgs first = a;
             first.refine = false;
             if (const int rc = CAT(launch_tri_inv_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(first)) return rc;
-            return launch_kernel(a.dry, k_tri_inv_refine128<OP>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.A, a.T, a.n_mat, a.in_dt);
+            TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv_refine128<IN, OP>), dim3((unsigned)a.n_mat), dim3(256), 0, a.stream,
+                                                           a.A, a.T, a.n_mat))
         }
 #endif
         return 1;
@@ -92,13 +101,15 @@ int CAT(launch_tri_inv_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const Tr
 #if TRIINV_INST_NB <= 4
         return go_tri<M_NEWTON_SCHULZ>(a);
 #else   // X in both orientations does not fit one wave's registers at C = 128: four waves, X and Y in LDS
-        return launch_kernel(a.dry, k_tri_inv_ns128<OP>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.A, a.T, a.n_mat, a.in_dt, a.iters, a.out_dt);
+        TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv_ns128<IN, OP>), dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.A, a.T,
+                                                       a.n_mat, a.iters, a.out_dt))
 #endif
     case M_NEUMANN:
 #if TRIINV_INST_NB <= 4
         return go_tri<M_NEUMANN>(a);
 #else   // C = 128: the one-wave register version would spill; a workgroup of four waves shares Y in LDS
-        return launch_kernel(a.dry, k_tri_inv_neumann128<OP>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.A, a.T, a.n_mat, a.in_dt, a.out_dt);
+        TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv_neumann128<IN, OP>), dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.A,
+                                                       a.T, a.n_mat, a.out_dt))
 #endif
 #endif
     default: return 1;

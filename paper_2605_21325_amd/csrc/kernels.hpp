@@ -28,46 +28,41 @@ __device__ __forceinline__ void wave_lds_sync()
 }
 
 // ---------------------------------------------------------------------------------------------
-// Tile source 1: A in global memory (row-major C x C, element type chosen at run time).
+// Tile source 1: A in global memory (row-major C x C, element type IN), a load per tile.
 // ---------------------------------------------------------------------------------------------
-template <int NB> struct GlobalA {
+template <int IN> __device__ __forceinline__ float widen16(uint16_t u) { return IN == OP_F16 ? f16_to_f32(u) : bf16_to_f32(u); }
+
+template <int NB, int IN> struct GlobalA {
     static constexpr int C = 16 * NB;
     static constexpr bool kFromMemory = true;   // a tile is a plain load: fetch it when it is needed
     static constexpr bool kHoldsKeys = false;
     const void* base;  // first element of this matrix
-    int dt;            // OP_F32 / OP_F16 / OP_BF16 storage
     Lane ln;
-
-    __device__ __forceinline__ float elem16(uint16_t u) const { return dt == OP_F16 ? f16_to_f32(u) : bf16_to_f32(u); }
 
     template <bool TR> __device__ __forceinline__ v4f get(int i, int j) const
     {
         v4f v;
         if (!TR) {  // v[r] = A[16i + 4q + r][16j + n]
-            const int64_t off = (int64_t)(16 * i + 4 * ln.q) * C + 16 * j + ln.n;
-            if (dt == OP_F32) {
-                const float* p = static_cast<const float*>(base) + off;
+            const int off = (16 * i + 4 * ln.q) * C + 16 * j + ln.n;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = p[r * C];
-            } else {
-                const uint16_t* p = static_cast<const uint16_t*>(base) + off;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = elem16(p[r * C]);
+            for (int r = 0; r < 4; ++r) {
+                if constexpr (IN == OP_F32)
+                    v[r] = static_cast<const float*>(base)[off + r * C];
+                else
+                    v[r] = widen16<IN>(static_cast<const uint16_t*>(base)[off + r * C]);
             }
             if (i == j) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) v[r] = (4 * ln.q + r > ln.n) ? v[r] : 0.f;
             }
         } else {  // v[r] = A[16i + n][16j + 4q + r]
-            const int64_t off = (int64_t)(16 * i + ln.n) * C + 16 * j + 4 * ln.q;
-            if (dt == OP_F32) {
+            const int off = (16 * i + ln.n) * C + 16 * j + 4 * ln.q;
+            if constexpr (IN == OP_F32) {
                 v = *reinterpret_cast<const v4f*>(static_cast<const float*>(base) + off);
             } else {
-                const uint2 u = *reinterpret_cast<const uint2*>(static_cast<const uint16_t*>(base) + off);
-                v[0] = elem16((uint16_t)(u.x & 0xffff));
-                v[1] = elem16((uint16_t)(u.x >> 16));
-                v[2] = elem16((uint16_t)(u.y & 0xffff));
-                v[3] = elem16((uint16_t)(u.y >> 16));
+                const v2u u = *reinterpret_cast<const v2u*>(static_cast<const uint16_t*>(base) + off);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = widen16<IN>((uint16_t)(r & 1 ? u[r / 2] >> 16 : u[r / 2] & 0xffff));
             }
             if (i == j) {
 #pragma unroll
@@ -277,6 +272,98 @@ template <int NB> struct PreA {
     static constexpr bool kHoldsKeys = false;
     v4f n[NB * (NB + 1) / 2], t[NB * (NB + 1) / 2];
     template <bool TR> __device__ __forceinline__ v4f get(int i, int j) const { return TR ? t[tix(i, j)] : n[tix(i, j)]; }
+};
+
+// ---------------------------------------------------------------------------------------------
+// Tile source 4: every tile of a given A requested before the first is used, so that a wavefront waits for memory once and not
+// at every level of the recursion (fp32, where the tile-wise loads already are whole 64-byte pieces: 1-4 % at C >= 64, 8 % at
+// C <= 32).
+// ---------------------------------------------------------------------------------------------
+template <int NB, int METHOD> struct LoadedA {  // fp32 elements
+    static constexpr bool kFromMemory = true;
+    static constexpr bool kHoldsKeys = false;
+    PreA<NB> tiles;
+    __device__ __forceinline__ void load(const void* base, Lane ln)
+    {
+        const GlobalA<NB, OP_F32> mem{base, ln};
+#pragma unroll
+        for (int d = 0; d < NB; ++d)  // in the order of use: near the diagonal first
+#pragma unroll
+            for (int i = d; i < NB; ++i) {
+                const int j = i - d;
+                if (need_tile<NB, METHOD>(i, j, true)) tiles.t[tix(i, j)] = mem.template get<true>(i, j);
+                if (need_tile<NB, METHOD>(i, j, false)) tiles.n[tix(i, j)] = mem.template get<false>(i, j);
+            }
+    }
+    template <bool TR> __device__ __forceinline__ v4f get(int i, int j) const { return tiles.template get<TR>(i, j); }
+};
+
+// 16-bit elements.  A lane loads 16 bytes of a row, two lane groups' share of a tile: two swaps between the lane groups per
+// register pair (v_permlane16_swap, v_permlane32_swap) make T-orientation tiles of two neighbours out of them, which are
+// matrix-core operands as they stand.  The N orientation is a product with the identity, exact for 16-bit values.  Loaded
+// tile by tile (8 bytes a lane, 2 bytes in N orientation, 32-byte row pieces, each level of the recursion
+// waiting for its own) the same kernels took: bf16 A, blocked recursion, 8192 matrices of C = 128, bf16 result 137 against
+// 87 us, fp32 result 178 against 137; 16384 of C = 64, bf16 result 56 against 47, fp32 77 against 71; C = 16 18.2 against 11.3.
+template <int IN, int OP, int NB> struct LoadedA16 {
+    static constexpr int C = 16 * NB;
+    static constexpr bool kFromMemory = true;
+    static constexpr bool kHoldsKeys = false;
+    v2u raw[NB * (NB + 1) / 2];  // T orientation
+    Opnd<IN> id;
+
+    __device__ __forceinline__ void load(const void* base, Lane ln)
+    {
+        const uint16_t* const p = static_cast<const uint16_t*>(base) + ln.n * C;
+        if constexpr (NB == 1) {
+            raw[0] = *reinterpret_cast<const v2u*>(p + 4 * ln.q);
+        } else {
+            v4u u[NB][(NB + 1) / 2];
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int k = 0; k <= i / 2; ++k) u[i][k] = *reinterpret_cast<const v4u*>(p + 16 * i * C + 32 * k + 8 * ln.q);
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int k = 0; k <= i / 2; ++k)
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        // (x: columns 8q + 2w, +1;  y: columns 8q + 4 + 2w, +1) -> columns 4q + 2w, +1 of either tile
+                        const auto odd = __builtin_amdgcn_permlane16_swap(u[i][k][w], u[i][k][2 + w], false, false);
+                        const auto half = __builtin_amdgcn_permlane32_swap(odd[0], odd[1], false, false);
+                        raw[tix(i, 2 * k)][w] = half[0];
+                        if (2 * k + 1 <= i) raw[tix(i, 2 * k + 1)][w] = half[1];
+                    }
+        }
+        const Mask<IN> low = make_mask<IN>(ln.n > 4 * ln.q, ln.n > 4 * ln.q + 1, ln.n > 4 * ln.q + 2, ln.n > 4 * ln.q + 3);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) raw[tix(i, i)] &= low.m;
+        id = pack<IN>(identity_tile(ln));
+    }
+    __device__ __forceinline__ Opnd<IN> stored(int i, int j) const
+    {
+        Opnd<IN> o;
+        o.x = __builtin_bit_cast(decltype(o.x), raw[tix(i, j)]);
+        return o;
+    }
+    template <bool TR> __device__ __forceinline__ v4f get(int i, int j) const
+    {
+        if constexpr (!TR) return tn<IN>(stored(i, j), id, zero4());
+        v4f v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = widen16<IN>((uint16_t)(r & 1 ? raw[tix(i, j)][r / 2] >> 16 : raw[tix(i, j)][r / 2] & 0xffff));
+        return v;
+    }
+    template <bool TR> __device__ __forceinline__ Opnd<OP> operand(int i, int j) const
+    {
+        if constexpr (TR && IN == OP)
+            return stored(i, j);
+        else
+            return pack<OP>(get<TR>(i, j));
+    }
+};
+template <int IN, int OP, int NB> struct PackedSource<LoadedA16<IN, OP, NB>> {
+    static constexpr bool value = true;
 };
 
 // One k-step (32 channels; lane (q, n) holds channels 8q..8q+7 of row n) as a matrix-core operand.
@@ -941,20 +1028,30 @@ template <int OP, int NB, int METHOD, bool REFINE, bool CHANNEL_LOOP = false> co
     return ((METHOD == M_NEWTON_SCHULZ && OP == OP_F32 && NB == 4 && !REFINE) || (METHOD == M_FWD && NB == 8 && !CHANNEL_LOOP)) ? 2 : 1;
 }
 
-template <int OP, int NB, int METHOD, bool REFINE = false>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_tri_inv(typename TriInvPointers<METHOD>::in A, typename TriInvPointers<METHOD>::out T, int64_t n_mat,
-                                                int in_dt, int aux, int out_dt)
+template <int IN, int OP, int NB, int METHOD, bool REFINE = false>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_tri_inv(
+    typename TriInvPointers<METHOD>::in A, typename TriInvPointers<METHOD>::out T, int64_t n_mat, int aux, int out_dt)
 {
     constexpr int C = 16 * NB;
     __shared__ __attribute__((aligned(16))) float lds[core_lds_floats<NB>()];
     const int64_t m = blockIdx.x;
     if (m >= n_mat) return;
     const Lane ln = lane_id();
-    GlobalA<NB> src;
-    src.base = static_cast<const char*>(A) + m * C * C * (in_dt == OP_F32 ? 4 : 2);
-    src.dt = in_dt;
-    src.ln = ln;
-    invert_and_store<OP, NB, METHOD, GlobalA<NB>, REFINE>(src, out_matrix(T, m, C, out_dt), lds, ln, aux);
+    const void* const base = static_cast<const char*>(A) + m * C * C * (IN == OP_F32 ? 4 : 2);
+    const Out Tm = out_matrix(T, m, C, out_dt);
+    if constexpr (IN != OP_F32) {
+        LoadedA16<IN, OP, NB> src;
+        src.load(base, ln);
+        invert_and_store<OP, NB, METHOD, LoadedA16<IN, OP, NB>, REFINE>(src, Tm, lds, ln, aux);
+    } else if constexpr (REFINE || (METHOD == M_BLOCK_DIRECT && NB == 8)) {
+        // tile by tile: the refinement step wants every tile once more, in both orientations; the direct leaves at C = 128 do
+        // little enough before the merges to gain nothing from the early loads (84 us against 85, 4096 matrices)
+        invert_and_store<OP, NB, METHOD, GlobalA<NB, IN>, REFINE>(GlobalA<NB, IN>{base, ln}, Tm, lds, ln, aux);
+    } else {
+        LoadedA<NB, METHOD> src;
+        src.load(base, ln);
+        invert_and_store<OP, NB, METHOD, LoadedA<NB, METHOD>, REFINE>(src, Tm, lds, ln, aux);
+    }
 }
 
 // Workgroup -> matrix map of the fused kernels.  Workgroups are handed to the 8 XCDs round-robin
@@ -1434,17 +1531,14 @@ __device__ __forceinline__ void refine128_run(const ASrc& A, float* Tm, float* Y
     n128_store<W>(Out{Tm, OP_F32}, Xt, Y + w * STORE_LDS_FLOATS, ln);
 }
 
-template <int OP>
-__global__ __launch_bounds__(256) void k_tri_inv_refine128(const void* __restrict__ A, float* T, int64_t n_mat, int in_dt)
+template <int IN, int OP>
+__global__ __launch_bounds__(256) void k_tri_inv_refine128(const void* __restrict__ A, float* T, int64_t n_mat)
 {
     __shared__ __attribute__((aligned(16))) float Y[N128_LDS_FLOATS];
     const int64_t m = blockIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Lane ln = lane_id();
-    GlobalA<N128_NB> src;
-    src.base = static_cast<const char*>(A) + m * 128 * 128 * (in_dt == OP_F32 ? 4 : 2);
-    src.dt = in_dt;
-    src.ln = ln;
+    const GlobalA<N128_NB, IN> src{static_cast<const char*>(A) + m * 128 * 128 * (IN == OP_F32 ? 4 : 2), ln};
     (void)n_mat;
     TRIINV_PER_WAVE(w, (refine128_run<OP, W>(src, T + m * 128 * 128, Y, ln, w)))
 }
@@ -1473,17 +1567,14 @@ __global__ __launch_bounds__(256) void k_gdn_tri_inv_refine128(const void* __res
     TRIINV_PER_WAVE(w, (refine128_run<OP, W>(src, T + m * C * C, Y, ln, w)))
 }
 
-template <int OP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_tri_inv_ns128(const void* A, float* T, int64_t n_mat, int in_dt, int n_iter, int out_dt)  // may run in place
+template <int IN, int OP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_tri_inv_ns128(const void* A, float* T, int64_t n_mat, int n_iter, int out_dt)  // may run in place
 {
     __shared__ __attribute__((aligned(16))) char lds[ns128_lds_bytes<OP>()];
     const int64_t m = blockIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Lane ln = lane_id();
-    GlobalA<N128_NB> src;
-    src.base = static_cast<const char*>(A) + m * 128 * 128 * (in_dt == OP_F32 ? 4 : 2);
-    src.dt = in_dt;
-    src.ln = ln;
+    const GlobalA<N128_NB, IN> src{static_cast<const char*>(A) + m * 128 * 128 * (IN == OP_F32 ? 4 : 2), ln};
     (void)n_mat;
     Opnd<OP> At[9];
     TRIINV_PER_WAVE(w, (ns128_tiles_of<OP, W>(src, At)))
@@ -1522,17 +1613,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F3
     TRIINV_PER_WAVE(w, (ns128_run<OP, W>(At, out_matrix(T, m, C, out_dt), lds, ln, n_iter, w)))
 }
 
-template <int OP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_tri_inv_neumann128(const void* A, float* T, int64_t n_mat, int in_dt, int out_dt)  // may run in place
+template <int IN, int OP>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_tri_inv_neumann128(const void* A, float* T, int64_t n_mat, int out_dt)  // may run in place
 {
     __shared__ __attribute__((aligned(16))) char lds[ns128_lds_bytes<OP>()];
     const int64_t m = blockIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Lane ln = lane_id();
-    GlobalA<N128_NB> src;
-    src.base = static_cast<const char*>(A) + m * 128 * 128 * (in_dt == OP_F32 ? 4 : 2);
-    src.dt = in_dt;
-    src.ln = ln;
+    const GlobalA<N128_NB, IN> src{static_cast<const char*>(A) + m * 128 * 128 * (IN == OP_F32 ? 4 : 2), ln};
     (void)n_mat;
     v4f Xt[9];
     Opnd<OP> yt[9];
