@@ -81,6 +81,8 @@ def lib() -> ctypes.CDLL:
         L.gdn_chunk_tri_solve_multi.restype = i32
         L.gdn_chunk_tri_solve_varlen.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i32, i64, i64, i32, i32, i32, i32, i32, i32, i32, i32, vp, u32]
         L.gdn_chunk_tri_solve_varlen.restype = i32
+        L.triinv_detail_chunk_offsets.argtypes = [vp, i32, i32, i64, vp, vp, vp]
+        L.triinv_detail_chunk_offsets.restype = i32
         L.triinv_status_string.argtypes = [i32]
         L.triinv_status_string.restype = ctypes.c_char_p
         L.triinv_version.argtypes = []
@@ -97,15 +99,25 @@ def version() -> int:
     return int(lib().triinv_version())
 
 
+_DTYPE_CODE = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
+
+
 def dtype_code(dt: torch.dtype) -> int:
     try:
-        return {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}[dt]
+        return _DTYPE_CODE[dt]
     except KeyError:
         raise TypeError(f"unsupported element type {dt}") from None
 
 
+# The current stream's handle without a Stream object around it (a microsecond of every call), where this torch has that call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device_index = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None and _device_index is not None:
+            return _raw_stream(_device_index()) or None
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) or None
 
@@ -202,6 +214,39 @@ def varlen_chunk_offsets(seqlens, C: int):
     return cu_s, cu_c
 
 
+def _chunk_offsets(K: torch.Tensor, seqlens, C: int, stream):
+    """(device addresses of cu_seqlens and cu_chunks, number of sequences, total chunks, tensors to keep alive) for packed
+    sequences of the given lengths.  The offsets of up to 900 sequences travel as kernel arguments on the launch stream, behind
+    which the caller's kernel follows: copying two host lists to the device waited for the device twice a call (76 against
+    41 us for 48 sequences).  Where that does not apply (another device, a stream that is no torch stream, lengths that are no plain
+    non-negative integers) they are copied."""
+    total = K.shape[0]
+    if not isinstance(seqlens, (list, tuple)):
+        seqlens = list(seqlens)
+    n = len(seqlens)
+    if n <= 900 and K.is_cuda and K.device.index == torch.cuda.current_device() and (
+            stream is None or (isinstance(stream, torch.cuda.Stream) and stream.device == K.device)):
+        try:
+            lens = (ctypes.c_int64 * n)(*seqlens)
+        except TypeError:
+            lens = (ctypes.c_int64 * n)(*[int(x) for x in seqlens])
+        if stream is None:
+            cu = torch.empty(2 * (n + 1), dtype=torch.int64, device=K.device)
+        else:
+            with torch.cuda.stream(stream):  # the memory belongs to the stream that writes and reads it
+                cu = torch.empty(2 * (n + 1), dtype=torch.int64, device=K.device)
+        chunks = ctypes.c_int64()
+        st = lib().triinv_detail_chunk_offsets(lens, n, C, total, cu.data_ptr(), ctypes.byref(chunks), _stream_ptr(stream))
+        if st == OK:
+            return cu.data_ptr(), cu.data_ptr() + 8 * (n + 1), n, chunks.value, (cu,)
+    cu_s, cu_c = varlen_chunk_offsets(seqlens, C)
+    if cu_s[-1] != total:
+        raise ValueError(f"sequence lengths sum to {cu_s[-1]}, K holds {total} tokens")
+    cu_seqlens = torch.tensor(cu_s, dtype=torch.int64, device=K.device)
+    cu_chunks = torch.tensor(cu_c, dtype=torch.int64, device=K.device)
+    return cu_seqlens.data_ptr(), cu_chunks.data_ptr(), len(cu_s) - 1, cu_c[-1], (cu_seqlens, cu_chunks)
+
+
 def gdn_chunk_tri_inv_varlen(K: torch.Tensor, beta: torch.Tensor, g: Optional[torch.Tensor], seqlens, C: int,
                              T: Optional[torch.Tensor] = None, gate_kind: int = GATE_SCALAR,
                              method: int = BLOCK_RECURSIVE, op_dtype: int = BF16, stream=None, flags: int = 0,
@@ -209,19 +254,15 @@ def gdn_chunk_tri_inv_varlen(K: torch.Tensor, beta: torch.Tensor, g: Optional[to
     """Fused build + invert on packed variable-length sequences: K [total_tokens, H, d_k], beta
     [total_tokens, H], g [total_tokens, H] (or [total_tokens, H, d_k]); seqlens = host sequence of lengths."""
     total, H, d_k = K.shape
-    cu_s, cu_c = varlen_chunk_offsets(seqlens, C)
-    if cu_s[-1] != total:
-        raise ValueError(f"sequence lengths sum to {cu_s[-1]}, K holds {total} tokens")
-    cu_seqlens = torch.tensor(cu_s, dtype=torch.int64, device=K.device)
-    cu_chunks = torch.tensor(cu_c, dtype=torch.int64, device=K.device)
-    T, flags = _out(T, out_dtype, (cu_c[-1] * H, C, C), K.device, flags)
+    cu_s, cu_c, n_seq, n_chunk, keep = _chunk_offsets(K, seqlens, C, stream)
+    T, flags = _out(T, out_dtype, (n_chunk * H, C, C), K.device, flags)
     gp = None if g is None else _dev(g, "g")
     st = lib().gdn_chunk_tri_inv_varlen(_dev(K, "K"), _dev(beta, "beta"), gp, _dev(T, "T") if T.numel() else None,
-                                        cu_seqlens.data_ptr(), cu_chunks.data_ptr(), len(cu_s) - 1, total, cu_c[-1], H, d_k, C,
+                                        cu_s, cu_c, n_seq, total, n_chunk, H, d_k, C,
                                         dtype_code(K.dtype), gate_kind, method, op_dtype, _stream_ptr(stream), flags)
     if st != OK:
         raise TriInvError(st, "gdn_chunk_tri_inv_varlen")
-    T._triinv_keepalive = (cu_seqlens, cu_chunks)  # the launch is asynchronous: the offsets live as long as the result
+    T._triinv_keepalive = keep  # the launch is asynchronous: the offsets live as long as the result
     return T
 
 
@@ -246,7 +287,7 @@ def gdn_chunk_tri_solve(K: torch.Tensor, beta: torch.Tensor, g: Optional[torch.T
     of X is the operand type of every product."""
     B, Tlen, H, d_k = K.shape
     d_x = X.shape[-1]
-    if tuple(X.shape[:3]) != (B, Tlen, H):
+    if X.shape[:3] != K.shape[:3]:
         raise ValueError("X must be [B, Tlen, H, d_x]")
     if W is None:
         W = torch.empty_like(X)
@@ -270,11 +311,7 @@ def gdn_chunk_tri_solve_varlen(K: torch.Tensor, beta: torch.Tensor, g: Optional[
     d_x = X.shape[-1]
     if tuple(X.shape[:2]) != (total, H):
         raise ValueError("X must be [total_tokens, H, d_x]")
-    cu_s, cu_c = varlen_chunk_offsets(seqlens, C)
-    if cu_s[-1] != total:
-        raise ValueError(f"sequence lengths sum to {cu_s[-1]}, K holds {total} tokens")
-    cu_seqlens = torch.tensor(cu_s, dtype=torch.int64, device=K.device)
-    cu_chunks = torch.tensor(cu_c, dtype=torch.int64, device=K.device)
+    cu_s, cu_c, n_seq, n_chunk, keep = _chunk_offsets(K, seqlens, C, stream)
     if W is None:
         W = torch.empty_like(X)
     elif W.shape != X.shape or W.dtype != X.dtype:
@@ -282,12 +319,12 @@ def gdn_chunk_tri_solve_varlen(K: torch.Tensor, beta: torch.Tensor, g: Optional[
     gp = None if g is None else _dev(g, "g")
     sp = None if row_scale is None else _dev(row_scale, "row_scale")
     st = lib().gdn_chunk_tri_solve_varlen(_dev(K, "K"), _dev(beta, "beta"), gp, _dev(X, "X") if X.numel() else None, sp,
-                                          _dev(W, "W") if W.numel() else None, cu_seqlens.data_ptr(), cu_chunks.data_ptr(),
-                                          len(cu_s) - 1, total, cu_c[-1], H, d_k, d_x, C, dtype_code(K.dtype), gate_kind, method,
+                                          _dev(W, "W") if W.numel() else None, cu_s, cu_c,
+                                          n_seq, total, n_chunk, H, d_k, d_x, C, dtype_code(K.dtype), gate_kind, method,
                                           dtype_code(X.dtype), _stream_ptr(stream), flags)
     if st != OK:
         raise TriInvError(st, "gdn_chunk_tri_solve_varlen")
-    W._triinv_keepalive = (cu_seqlens, cu_chunks)  # the launch is asynchronous: the offsets live as long as the result
+    W._triinv_keepalive = keep  # the launch is asynchronous: the offsets live as long as the result
     return W
 
 
@@ -304,7 +341,7 @@ def gdn_chunk_tri_solve_multi(K: torch.Tensor, beta: torch.Tensor, g: Optional[t
     if len(row_scales) != n or len(Ws) != n:
         raise ValueError("Xs, row_scales and Ws must have the same length")
     for x, w in zip(Xs, Ws):
-        if tuple(x.shape[:3]) != (B, Tlen, H) or x.dtype != Xs[0].dtype or w.shape != x.shape or w.dtype != x.dtype:
+        if x.shape[:3] != K.shape[:3] or x.dtype != Xs[0].dtype or w.shape != x.shape or w.dtype != x.dtype:
             raise ValueError("every X must be [B, Tlen, H, d_x] of one element type, every W like its X")
     vp_arr = ctypes.c_void_p * n
     xp = vp_arr(*[_dev(x, "X") if x.numel() else None for x in Xs])
@@ -312,9 +349,7 @@ def gdn_chunk_tri_solve_multi(K: torch.Tensor, beta: torch.Tensor, g: Optional[t
     wp = vp_arr(*[_dev(w, "W") if w.numel() else None for w in Ws])
     dx = (ctypes.c_int32 * n)(*[int(x.shape[-1]) for x in Xs])
     gp = None if g is None else _dev(g, "g")
-    st = lib().gdn_chunk_tri_solve_multi(_dev(K, "K"), _dev(beta, "beta"), gp, n, ctypes.cast(xp, ctypes.c_void_p),
-                                         ctypes.cast(sp, ctypes.c_void_p), ctypes.cast(wp, ctypes.c_void_p),
-                                         ctypes.cast(dx, ctypes.c_void_p), B, Tlen, H, d_k, C, dtype_code(K.dtype), gate_kind, method,
+    st = lib().gdn_chunk_tri_solve_multi(_dev(K, "K"), _dev(beta, "beta"), gp, n, xp, sp, wp, dx, B, Tlen, H, d_k, C, dtype_code(K.dtype), gate_kind, method,
                                          dtype_code(Xs[0].dtype), _stream_ptr(stream), flags)
     if st != OK:
         raise TriInvError(st, "gdn_chunk_tri_solve_multi")

@@ -178,9 +178,48 @@ int solve_common(const void* K, const float* beta, const float* g, int n_rhs, co
     return finish(nb);
 }
 
+// Offsets by value: written to device memory by a kernel whose arguments they are, without a copy engine or a host wait.
+struct OffsetBlock {
+    static constexpr int MAX = 460;  // 8-byte values; with the other arguments below the 4 KB of a launch's argument buffer
+    int64_t v[MAX];
+};
+__global__ __launch_bounds__(64) void k_put_offsets(int64_t* dst, int n, OffsetBlock block)
+{
+    for (int i = threadIdx.x; i < n; i += 64) dst[i] = block.v[i];
+}
+
 }  // namespace
 
 extern "C" {
+
+// Used by the Python binding, no part of the interface in triinv.h.  lens: HOST array of n_seq sequence lengths.  Writes
+// cu_seqlens (n_seq + 1 values) and behind it cu_chunks (n_seq + 1 values) to device memory dst, on the stream, and the number of
+// chunks to *n_chunk.  Refused before any launch: negative lengths, a sum other than total_tokens, more than 900 sequences.
+int triinv_detail_chunk_offsets(const int64_t* lens, int n_seq, int C, int64_t total_tokens, int64_t* dst, int64_t* n_chunk,
+                                void* hip_stream)
+{
+    if (n_seq < 0 || n_seq > 900 || !dst || !n_chunk || (n_seq > 0 && !lens)) return TRIINV_ERR_BAD_SHAPE;
+    if (!chunk_size_ok(C)) return TRIINV_ERR_BAD_C;
+    int64_t cu[2 * 901];
+    const int n = 2 * (n_seq + 1);
+    cu[0] = cu[n_seq + 1] = 0;
+    for (int s = 0; s < n_seq; ++s) {
+        if (lens[s] < 0 || lens[s] > total_tokens) return TRIINV_ERR_BAD_SHAPE;
+        cu[s + 1] = cu[s] + lens[s];
+        cu[n_seq + 2 + s] = cu[n_seq + 1 + s] + (lens[s] + C - 1) / C;
+    }
+    if (cu[n_seq] != total_tokens) return TRIINV_ERR_BAD_SHAPE;
+    *n_chunk = cu[n - 1];
+    for (int i = 0; i < n; i += OffsetBlock::MAX) {
+        OffsetBlock block;
+        const int m = n - i < OffsetBlock::MAX ? n - i : OffsetBlock::MAX;
+        for (int k = 0; k < m; ++k) block.v[k] = cu[i + k];
+        for (int k = m; k < OffsetBlock::MAX; ++k) block.v[k] = 0;
+        if (const int rc = finish(launch_kernel(false, k_put_offsets, dim3(1), dim3(64), 0, static_cast<hipStream_t>(hip_stream), dst + i, m, block)))
+            return rc;
+    }
+    return TRIINV_OK;
+}
 
 int tri_inv_ex(const void* A, float* T, int64_t n_mat, int C, int in_dtype, int method, int op_dtype, void* hip_stream,
                uint32_t flags)

@@ -226,3 +226,15 @@ def test_no_kernel_uses_scratch_memory_or_spills():
     assert len(res) > 50
     bad = {k: v for k, v in res.items() if v.get("scratch", 0) > 0 or v.get("vgpr_spill", 0) > 0}
     assert not bad, bad
+
+
+def test_chunk_offsets_helper_refuses_before_any_launch(L):
+    f = L.triinv_detail_chunk_offsets
+    out = ctypes.c_int64(-1)
+    lens = (ctypes.c_int64 * 2)(3, 4)
+    assert f(lens, 2, 48, 7, P, ctypes.byref(out), None) == -2
+    assert f(lens, 2, 64, 8, P, ctypes.byref(out), None) == -5       # the lengths do not sum to the tokens there are
+    assert f((ctypes.c_int64 * 2)(-1, 8), 2, 64, 7, P, ctypes.byref(out), None) == -5
+    assert f((ctypes.c_int64 * 901)(), 901, 64, 0, P, ctypes.byref(out), None) == -5
+    assert f(lens, 2, 64, 7, None, ctypes.byref(out), None) == -5
+    assert out.value == -1

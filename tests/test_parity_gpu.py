@@ -883,6 +883,48 @@ def test_newton_schulz_iterates(C, op):
             assert err <= (TOL[op] if op != tri.F16 or k != 1 else 1e-1), (C, m, k, err)
 
 
+# ------------------------------------------------------------------ packed sequences: the offsets' way to the device
+@pytest.mark.parametrize("n_seq", [0, 1, 228, 229, 230, 459, 900])
+def test_chunk_offsets_by_kernel_arguments(n_seq):
+    """The offsets of n_seq sequences (empty ones among them) against the host lists, at the sizes where one launch's argument block
+    (460 values) ends inside, at and behind an array."""
+    import ctypes
+    r = np.random.default_rng(n_seq)
+    lens = [int(x) for x in r.integers(0, 300, n_seq)]
+    dst = torch.full((2 * (n_seq + 1) + 2,), -7, dtype=torch.int64, device=DEV)
+    chunks = ctypes.c_int64(-1)
+    st = tri.lib().triinv_detail_chunk_offsets((ctypes.c_int64 * n_seq)(*lens), n_seq, 64, sum(lens), dst.data_ptr(), ctypes.byref(chunks), None)
+    torch.cuda.synchronize()
+    cu_s, cu_c = tri.varlen_chunk_offsets(lens, 64)
+    assert st == 0 and chunks.value == cu_c[-1]
+    assert dst.tolist() == cu_s + cu_c + [-7, -7]
+
+
+def test_packed_sequences_by_either_route():
+    """Lists, numpy integers, tensors and generators of lengths, a side stream, and more sequences than the kernel-argument route takes
+    give the same result; a wrong sum is refused as before."""
+    lens = [3] * 905 + [70, 130, 1]
+    total, H, C = sum(lens), 2, 64
+    g = torch.Generator().manual_seed(3)
+    K = torch.nn.functional.normalize(torch.randn(total, H, 64, generator=g), dim=-1).bfloat16().to(DEV)
+    beta = torch.rand(total, H, generator=g).to(DEV)
+    every = tri.gdn_chunk_tri_inv_varlen(K, beta, None, lens, C, gate_kind=tri.GATE_NONE)      # copied
+    few = [2715, 70, 130, 1]
+    for way in (few, tuple(few), np.array(few), torch.tensor(few), iter(few)):
+        T = tri.gdn_chunk_tri_inv_varlen(K, beta, None, way, C, gate_kind=tri.GATE_NONE)
+        assert torch.equal(T[-5 * H:], every[-5 * H:]), type(way)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    S = tri.gdn_chunk_tri_inv_varlen(K, beta, None, few, C, gate_kind=tri.GATE_NONE, stream=side)
+    torch.cuda.synchronize()
+    assert torch.equal(S, T)
+    for wrong in (few + [1], [2716] + few[1:], [2715, 70, -1, 132]):
+        if sum(wrong) == total:
+            continue
+        with pytest.raises(ValueError):
+            tri.gdn_chunk_tri_inv_varlen(K, beta, None, wrong, C, gate_kind=tri.GATE_NONE)
+
+
 # ------------------------------------------------------------------ every element of a given 16-bit A in its place
 @pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
 @pytest.mark.parametrize("C", [16, 32, 64, 128])
