@@ -14,6 +14,13 @@ namespace triinv {
 // 16 x 16 leaves.  Both return the leaf inverse in both orientations (XN = X, XT = X^T).
 // ---------------------------------------------------------------------------------------------
 
+__device__ __forceinline__ void leaf_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Blocked recursion inside the leaf (paper Alg. 4 with b0 = 1, Lemma C.1): block sizes 1, 2, 4, 8.
 // The level b = 1 starts from X = I, so D_o A D_e only picks the entries A[i][i-1], i odd.
 // Each later level applies X <- X - D_o A_b D_e with A_b = A restricted to its 2b x 2b diagonal
@@ -51,6 +58,66 @@ __device__ __forceinline__ void leaf_block_recursive(v4f LN, v4f LT, v4f& XN, v4
         const v4f P2 = tn<OP>(masked<OP>(LNo, Ms), oTo, zero4());   // -A^T D_o^T = -(D_o A)^T
         XN = tn<OP>(oTo, pack<OP>(P1), XN);                         // X - D_o A D_e
         XT = tn<OP>(eNo, pack<OP>(P2), XT);                         // (X - D_o A D_e)^T
+    }
+}
+
+// The same recursion with fp32 operands on COUNT leaves at a time, level by level.  An fp32 tile product is four instructions of 32
+// cycles, so the leaves, not the merges, are most of a matrix's matrix-core time: here a level forms X - D_o (A D_e) in
+// N orientation only and turns it through LDS (a patch per leaf, so that the leaves' turns overlap), and the level b = 2
+// contracts only the two of four instructions whose slots (rows 4q + r) hold non-zeros: r = 0, 1 are the even blocks of
+// size 2, r = 2, 3 the odd ones.  20 instructions per leaf instead of 48.  Standalone blocked recursion, 4099 matrices of
+// C = 64: 27 -> 20 us (bf16 A, 8192: 49 -> 31 us), 4096 of C = 128 107 -> 85 us, C = 16 (32768) 31 -> 18 us; from keys, 128 of C = 64
+// 10.8 -> 8.1 us, 8192 54 -> 53 us (bound by memory; four leaves side by side instead of two, waiting for all keys: 55 us).
+// patch: COUNT * XPOSE_FLOATS floats.
+constexpr int XPOSE_LD = 20;
+constexpr int XPOSE_FLOATS = 16 * XPOSE_LD;
+
+template <int COUNT>
+__device__ __forceinline__ void leaves_block_recursive_f32(const v4f (&LN)[COUNT], const v4f (&LT)[COUNT], v4f (&XN)[COUNT], v4f (&XT)[COUNT],
+                                                           float* patch, Lane ln)
+{
+#pragma unroll
+    for (int d = 0; d < COUNT; ++d)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int a = 4 * ln.q + r, b = ln.n;
+            XN[d][r] = (a == b) ? 1.f : (((a & 1) && b == a - 1) ? -LN[d][r] : 0.f);
+            XT[d][r] = (a == b) ? 1.f : (((b & 1) && a == b - 1) ? -LT[d][r] : 0.f);
+        }
+#pragma unroll
+    for (int lb = 1; lb < 4; ++lb) {
+        bool ke[4], ko[4], ks[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int a = 4 * ln.q + r, b = ln.n;
+            const bool same_b = (a >> lb) == (b >> lb), even = ((a >> lb) & 1) == 0;
+            ke[r] = same_b && even;
+            ko[r] = same_b && !even;
+            ks[r] = (a >> (lb + 1)) == (b >> (lb + 1));
+        }
+        v4f P[COUNT];
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) P[d] = zero4();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int d = 0; d < COUNT; ++d)
+                if (lb > 1 || r < 2)  // -A D_e
+                    P[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(ks[r] ? -LT[d][r] : 0.f, ke[r] ? XN[d][r] : 0.f, P[d], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int d = 0; d < COUNT; ++d)
+                if (lb > 1 || r >= 2)  // X - D_o A D_e
+                    XN[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(ko[r] ? XT[d][r] : 0.f, P[d][r], XN[d], 0, 0, 0);
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) patch[d * XPOSE_FLOATS + (4 * ln.q + r) * XPOSE_LD + ln.n] = XN[d][r];
+        leaf_lds_sync();
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) XT[d] = *reinterpret_cast<const v4f*>(&patch[d * XPOSE_FLOATS + ln.n * XPOSE_LD + 4 * ln.q]);
+        leaf_lds_sync();
     }
 }
 
@@ -100,13 +167,6 @@ __device__ __forceinline__ void leaf_neumann(v4f LN, v4f LT, v4f& XN, v4f& XT, L
 constexpr int LEAF_LD = 20;                       // row stride inside a staged leaf
 constexpr int LEAF_STRIDE = 16 * LEAF_LD + 8;     // leaf stride: the four groups' rows fall into different banks
 constexpr int LEAF_FWD_FLOATS = 4 * LEAF_STRIDE;
-
-__device__ __forceinline__ void leaf_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // Column c of the inverse of one staged leaf.  row_done(i): called when t[i] is final.
 struct NoRowHook {
@@ -166,9 +226,6 @@ __device__ __forceinline__ void leaves_forward_substitution(const ASrc& A, v4f (
 // ---------------------------------------------------------------------------------------------
 // Tile transpose through a wave-private LDS patch of 16 x 20 floats.
 // ---------------------------------------------------------------------------------------------
-constexpr int XPOSE_LD = 20;
-constexpr int XPOSE_FLOATS = 16 * XPOSE_LD;
-
 __device__ __forceinline__ v4f transpose_tile(v4f t, float* patch, Lane ln)
 {
 #pragma unroll
@@ -231,7 +288,8 @@ struct NoHook {
 // after_last_fetch: called in the last merge once its tiles of A have been fetched, i.e. when A is no longer needed
 // (a source that builds its tiles from keys held in registers has those registers free from here on).
 // leaves_out: if not null, receives the 16 x 16 diagonal blocks of the result in both orientations ([2 d] = N, [2 d + 1] = T).
-template <int OP, int NB, bool ROOT_T, int LEAF, class ASrc, class Hook = NoHook>
+// PATCHES: transpose patches (XPOSE_FLOATS floats each) there are at `patch`.
+template <int OP, int NB, bool ROOT_T, int LEAF, int PATCHES = 1, class ASrc, class Hook = NoHook>
 __device__ __forceinline__ void block_recursive(const ASrc& A, v4f (&Tt)[NB * (NB + 1) / 2], float* patch, Lane ln, int leaf_r = 0,
                                                 Hook after_last_fetch = Hook(), v4f* leaves_out = nullptr)
 {
@@ -256,6 +314,24 @@ __device__ __forceinline__ void block_recursive(const ASrc& A, v4f (&Tt)[NB * (N
             leafN[2 * p] = transpose_tile(X[tix(0, 0)], patch, ln);
             leafN[2 * p + 1] = transpose_tile(X[tix(1, 1)], patch, ln);
             Tt[tix(2 * p + 1, 2 * p)] = blockT ? X[tix(1, 0)] : transpose_tile(X[tix(1, 0)], patch, ln);
+        }
+    } else if constexpr (OP == OP_F32 && LEAF == LEAF_BLOCK_RECURSIVE && PATCHES > 1) {
+        constexpr int PER = PATCHES < NB ? PATCHES : NB;
+        static_assert(NB % PER == 0, "the leaves go in equal groups");
+#pragma unroll
+        for (int pass = 0; pass < NB / PER; ++pass) {
+            v4f LN[PER], LT[PER], XN[PER], XT[PER];
+#pragma unroll
+            for (int d = 0; d < PER; ++d) {
+                LN[d] = A.template get<false>(PER * pass + d, PER * pass + d);
+                LT[d] = A.template get<true>(PER * pass + d, PER * pass + d);
+            }
+            leaves_block_recursive_f32<PER>(LN, LT, XN, XT, patch, ln);
+#pragma unroll
+            for (int d = 0; d < PER; ++d) {
+                leafN[PER * pass + d] = XN[d];
+                leafT[PER * pass + d] = XT[d];
+            }
         }
     } else {
 #pragma unroll

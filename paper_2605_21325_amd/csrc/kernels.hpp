@@ -958,6 +958,15 @@ __global__ __launch_bounds__(64) void k_tri_inv_fwd_shuffle64(const void* __rest
 // ---------------------------------------------------------------------------------------------
 template <int NB> constexpr int gate_lds_floats() { return 2 * 16 * NB; }
 
+// LDS of one wavefront's inversion: the store patch, which also serves as transpose patch and holds the staged leaves of the
+// direct methods (a leaf per tile row, at most four at a time).
+template <int NB> constexpr int core_lds_floats()
+{
+    constexpr int leaves = (NB < 4 ? NB : 4) * LEAF_STRIDE;
+    constexpr int small = leaves > XPOSE_FLOATS ? leaves : XPOSE_FLOATS;
+    return store_lds_floats<NB>() > small ? store_lds_floats<NB>() : small;
+}
+
 // REFINE: one iterative-refinement step after a matrix-product method (C = 64 only).
 template <int OP, int NB, int METHOD, class ASrc, bool REFINE = false>
 __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float* lds, Lane ln, int aux = 0)
@@ -989,7 +998,11 @@ __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float*
     } else {
         v4f Tt[NT];
         constexpr int LEAF = METHOD == M_MIXED ? LEAF_NEUMANN : METHOD == M_MIXED32 ? LEAF_NEUMANN32 : METHOD == M_BLOCK_DIRECT ? LEAF_FORWARD : LEAF_BLOCK_RECURSIVE;
-        block_recursive<OP, NB, ROOT_T, LEAF>(src, Tt, lds, ln, aux);  // aux = refinement steps on the leaves (mixed recursion)
+        // fp32 leaves side by side: four where A is given; two where it comes from keys, so that the first start before the
+        // last keys are there; one after the other in the channel-loop kernels at C = 128, which hold all of A beside them
+        constexpr int PATCHES = ASrc::kFromMemory ? 4 : ASrc::kHoldsKeys ? 2 : NB == 8 ? 1 : 4;
+        static_assert((PATCHES < NB ? PATCHES : NB) * XPOSE_FLOATS <= core_lds_floats<NB>(), "a patch per leaf");
+        block_recursive<OP, NB, ROOT_T, LEAF, PATCHES>(src, Tt, lds, ln, aux);  // aux = refinement steps on the leaves (mixed recursion)
         if constexpr (REFINE) {
             refine_once<OP, NB>(src, Tt, [](int i, int j) { return result_is_T<NB, ROOT_T>(i, j); }, lds, ln);
             store_result<NB>(Tm, Tt, [](int, int) { return true; }, lds, ln);
@@ -997,15 +1010,6 @@ __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float*
             store_result<NB>(Tm, Tt, [](int i, int j) { return result_is_T<NB, ROOT_T>(i, j); }, lds, ln);
         }
     }
-}
-
-// LDS of one wavefront's inversion: the store patch, which also serves as transpose patch and holds the staged leaves of the
-// direct methods (a leaf per tile row, at most four at a time).
-template <int NB> constexpr int core_lds_floats()
-{
-    constexpr int leaves = (NB < 4 ? NB : 4) * LEAF_STRIDE;
-    constexpr int small = leaves > XPOSE_FLOATS ? leaves : XPOSE_FLOATS;
-    return store_lds_floats<NB>() > small ? store_lds_floats<NB>() : small;
 }
 
 // The matrix-product kernels may be run in place (A and T the same memory: the composed path of the fused entry points),

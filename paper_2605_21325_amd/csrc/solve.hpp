@@ -202,6 +202,11 @@ template <int OP, int NB> struct RhsX {
     }
 };
 
+// LDS of one wavefront.  It only holds the gate's values and transposes tiles; the size is what keeps C <= 32 at four wavefronts
+// per SIMD, where these kernels, bound by the memory system, are fastest (C = 16, one right-hand side, 65536 matrices: 131
+// against 139 us with eight).
+constexpr int SOLVE_LDS_FLOATS = STORE_LDS_FLOATS;
+
 // Recursion (blocked, or mixed with aux refinement steps on the leaves), then W_k = T diag(s_k) X_k for the NRHS
 // right-hand sides in turn; x holds the first one, next_rhs(k) re-initialises x for right-hand side k and starts the
 // loads of its first column group.  Two right-hand sides are built at C <= 64 only, where the 10 fp32 tiles of T stay
@@ -219,7 +224,8 @@ __device__ __forceinline__ void invert_and_apply(const ASrc& src, RhsX<OP, NB>& 
     v4f Tm[NT];  // T orientation: Tm[tix(i, j)][r] = T[16 i + n][16 j + 4 q + r], exact unit diagonal, zeros above it
     {
         constexpr int LEAF = METHOD == M_MIXED ? LEAF_NEUMANN : LEAF_BLOCK_RECURSIVE;
-        block_recursive<OP, NB, ROOT_T, LEAF>(src, Tm, lds, ln, aux, [&]() {
+        // (fp32 leaves side by side at C = 64; at C <= 32 these kernels are bound by memory and were 5 % slower with them)
+        block_recursive<OP, NB, ROOT_T, LEAF, NB >= 4 ? 4 : 1>(src, Tm, lds, ln, aux, [&]() {
             if constexpr (ISSUE_FROM < NB && IN_MERGE) x.issue(0, ISSUE_FROM, NB);
         });
         if constexpr (ISSUE_FROM < NB && !IN_MERGE) x.issue(0, ISSUE_FROM, NB);
@@ -272,11 +278,6 @@ __device__ __forceinline__ void invert_and_apply(const ASrc& src, RhsX<OP, NB>& 
         }
     }
 }
-
-// LDS of one wavefront.  It only holds the gate's values and transposes tiles; the size is what keeps C <= 32 at four wavefronts
-// per SIMD, where these kernels, bound by the memory system, are fastest (C = 16, one right-hand side, 65536 matrices: 131
-// against 139 us with eight).
-constexpr int SOLVE_LDS_FLOATS = STORE_LDS_FLOATS;
 
 // XPOS: where the loads of X's first column group are issued -- 1: between the Gram products and the recursion (every
 // tile of A is formed first, so the keys' registers are free); 2: after the recursion; 3: as many tile rows as fit beside

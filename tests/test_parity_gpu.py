@@ -925,22 +925,23 @@ def test_packed_sequences_by_either_route():
             tri.gdn_chunk_tri_inv_varlen(K, beta, None, wrong, C, gate_kind=tri.GATE_NONE)
 
 
-# ------------------------------------------------------------------ every element of a given 16-bit A in its place
-@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+# ------------------------------------------------------------------ every element of a given A in its place
+@pytest.mark.parametrize("dt", [torch.float32, torch.float16, torch.bfloat16], ids=["f32", "f16", "bf16"])
 @pytest.mark.parametrize("C", [16, 32, 64, 128])
-def test_sixteen_bit_input_elements_in_place(C, dt):
+def test_input_elements_in_place(C, dt):
     """Matrices with a single entry below the diagonal, where (I + A)^-1 = I - A exactly, the entry walking over every position
-    of the tiles at the edges and over the element pairs whose lanes exchange data; NaN on and above the diagonal."""
+    of the tiles at the edges, of every level inside a leaf and over the element pairs whose lanes exchange data; NaN on and above
+    the diagonal."""
     pos = [(i, j) for i in range(C) for j in range(i) if (i % 16 in (0, 1, 7, 15) or j // 16 == i // 16) and j % 4 in (0, 1, 3)]
     A = torch.full((len(pos), C, C), float("nan"))
     low = torch.tril(torch.ones(C, C, dtype=torch.bool), -1)
     A[:, low] = 0
     want = torch.eye(C).repeat(len(pos), 1, 1)
     for m, (i, j) in enumerate(pos):
-        A[m, i, j] = 1 + j / 128 if dt == torch.bfloat16 else 1 + (i * C + j) / 16384 // (1 / 1024) / 1024
+        A[m, i, j] = 1 + j / 128 if dt != torch.float16 else 1 + (i * C + j) / 16384 // (1 / 1024) / 1024
         want[m, i, j] = -A[m, i, j]
     for method in (tri.BLOCK_RECURSIVE, tri.FWD_SUBST):
-        T = tri.tri_inv_ex(A.to(dt).to(DEV), method=method, op_dtype={torch.float16: tri.F16, torch.bfloat16: tri.BF16}[dt])
+        T = tri.tri_inv_ex(A.to(dt).to(DEV), method=method, op_dtype={torch.float32: tri.F32, torch.float16: tri.F16, torch.bfloat16: tri.BF16}[dt])
         assert torch.equal(T.cpu(), want), (C, dt, tri.METHOD_NAMES[method])
 
 
