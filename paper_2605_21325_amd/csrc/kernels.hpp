@@ -1204,7 +1204,7 @@ __device__ __forceinline__ v4f lds_tile_read_n(const float* t, Lane ln)
 template <int W> __host__ __device__ constexpr int n128_row(int s) { return s <= W ? W : 7 - W; }
 template <int W> __host__ __device__ constexpr int n128_col(int s) { return s <= W ? s : s - (W + 1); }
 
-template <int W>
+template <int W, bool IS_T = true>
 __device__ __forceinline__ void n128_store(Out Tm, const v4f (&Xt)[9], float* patch, Lane ln)
 {
 #pragma unroll
@@ -1214,7 +1214,7 @@ __device__ __forceinline__ void n128_store(Out Tm, const v4f (&Xt)[9], float* pa
 #pragma unroll
         for (int j = 0; j < N128_NB; ++j)
             if (j <= i) row[j] = Xt[s0 + j];
-        store_strip<N128_NB>(Tm, i, row, [](int) { return true; }, patch, ln);
+        store_strip<N128_NB>(Tm, i, row, [](int) { return IS_T; }, patch, ln);
     }
 }
 
@@ -1229,8 +1229,8 @@ __device__ __forceinline__ void n128_store(Out Tm, const v4f (&Xt)[9], float* pa
 // ---------------------------------------------------------------------------------------------
 // Newton-Schulz at C = 128 (paper Alg. 3, Eq. 8, for I + A): the same four-wavefront workgroup.
 //   X <- I / C;  n_iter times:  Y <- X + A X;  X <- 2 X - X Y.
-// Wave w owns tile rows w and 7 - w: it keeps its rows of A (T orientation, packed operands) and of X (both
-// orientations, fp32) in registers and reads the right factor of every product (a tile of X, then of Y, in N
+// Wave w owns tile rows w and 7 - w: it keeps its rows of A (T orientation, packed operands) and of X (N
+// orientation, fp32) in registers and reads the right factor of every product (a tile of X, then of Y, in N
 // orientation) from LDS.  A right factor in N orientation is exactly the register image its producer holds,
 // so a tile crosses between waves as a mailbox: 64 consecutive slots of one packed operand each, lane l of the
 // reader taking what lane l of the writer left.  No transposition, no bank conflicts, and the rounding to the
@@ -1256,63 +1256,131 @@ template <int OP> constexpr int ns128_lds_bytes()
 
 template <int W> __host__ __device__ constexpr int n128_slot(int i, int k) { return i == W ? k : (W + 1) + k; }
 
+// The wave's two tile rows as left operands, and one tile column as right operand.  16-bit operands: pairs of tiles for the
+// 32-deep instructions (a tile above the diagonal is zero); fp32: tile by tile.
+template <int OP, int W> struct Ns128Operands {
+    static constexpr bool PAIRED = OP != OP_F32;
+    static constexpr int NP = PAIRED ? 4 : 8;                                   // slots along a tile row
+    struct Slot {
+        Opnd<OP> lo, hi;                                                        // (hi: PAIRED only)
+    };
+    typedef Slot Left[2][NP];                                                   // rows W and 7 - W
+    typedef Slot Right[NP];
+    static __device__ __forceinline__ void put(Slot* row, int k, Opnd<OP> x)
+    {
+        if (!PAIRED) row[k].lo = x;
+        else if (k & 1) row[k / 2].hi = x;
+        else row[k / 2].lo = x;
+    }
+    static __device__ __forceinline__ v4f product(const Slot* l, const Slot* r, int i, int j, v4f acc)
+    {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            if constexpr (PAIRED) {
+                if (p < j / 2 || p > i / 2) continue;
+                PairOp<OP> x, y;
+                x.set(0, l[p].lo);
+                x.set(1, l[p].hi);
+                y.set(0, r[p].lo);
+                y.set(1, r[p].hi);
+                acc = tn_pair<OP>(x, y, acc);
+            } else {
+                if (p >= j && p <= i) acc = tn<OP>(l[p].lo, r[p].lo, acc);
+            }
+        }
+        return acc;
+    }
+};
+
+// The transpose of a tile, exact: by products with the identity.
+template <int OP> __device__ __forceinline__ v4f turned(v4f x, Opnd<OP_BF16> id_bf16, Opnd<OP> id)
+{
+    if constexpr (OP == OP_F32) {
+        const Split3 s = split3(x);
+        return tn<OP_BF16>(s.l(), id_bf16, tn<OP_BF16>(s.m(), id_bf16, tn<OP_BF16>(s.h(), id_bf16, zero4())));
+    } else {
+        return tn<OP>(pack<OP>(x), id, zero4());  // (of the rounded tile)
+    }
+}
+
 // At: this wave's nine tiles of A in T orientation (slot order of n128_row / n128_col).  lds: ns128_lds_bytes<OP>() bytes
 // that no wave uses for anything else any more.
+// X is kept in N orientation only and turned once per iteration (exactly, by products with the identity); a tile column of the
+// right factor is read from LDS once for both of the wave's rows; 16-bit operands contract two tiles per instruction; the
+// first iteration from I / C is a scaling.  The critical wave issues 51 matrix instructions per iteration instead of
+// 111 (16-bit operands); what is left is LDS reads, packing and two barriers.  4096 fused matrices, bf16 operands 235 -> 205 us,
+// standalone 222 -> 187 us; 2048 with fp32 operands 341 -> 248 us (still matrix-core bound), standalone 668 -> 473 us.
 template <int OP, int W>
 __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char* lds, Lane ln, int n_iter, int w)
 {
     typedef MailTiles<OP> Mail;
+    typedef Ns128Operands<OP, W> Ops;
+    constexpr int ROW[2] = {W, 7 - W};
+    constexpr float X0 = 1.f / 128.f;
     char* const X = lds;
     char* const Y = lds + Mail::BYTES;
-    v4f Xn[9], Xt[9];
+    const v4f unit = identity_tile(ln);
+    const Opnd<OP> id = pack<OP>(unit);
+    const Opnd<OP_BF16> id_bf16 = pack<OP_BF16>(unit);
+    typename Ops::Left Al = {};
+    v4f Xn[9];
 #pragma unroll
     for (int s = 0; s < 9; ++s) {
         const int i = n128_row<W>(s), j = n128_col<W>(s);
-        v4f x;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[r] = (i == j && 4 * ln.q + r == ln.n) ? 1.f / 128.f : 0.f;
-        Xn[s] = x;
-        Xt[s] = x;
-        Mail::put(X, tix(i, j), pack<OP>(x), ln);
+        Ops::put(Al[s <= W ? 0 : 1], j, At[s]);
+        v4f a;
+        if constexpr (OP == OP_F32)
+            a = turned<OP>(At[s].x, id_bf16, id);
+        else
+            a = tn<OP>(At[s], id, zero4());
+        if (i == j) a += unit;
+        Xn[s] = (i == j ? 2.f * X0 : 0.f) * unit - X0 * X0 * a;
+        Mail::put(X, tix(i, j), pack<OP>(Xn[s]), ln);
     }
     __syncthreads();
 #pragma unroll 1
-    for (int it = 0; it < n_iter; ++it) {
+    for (int it = 1; it < n_iter; ++it) {
+        // a tile column j of a matrix in LDS, rows j .. 7 - W
+        const auto column = [&](const char* base, int j, typename Ops::Right& r) {
+#pragma unroll
+            for (int k = 0; k < N128_NB; ++k) {
+                if (k > (Ops::PAIRED ? (7 - W) | 1 : 7 - W) || k < (Ops::PAIRED ? j & ~1 : j)) continue;
+                Ops::put(r, k, k >= j && k <= 7 - W ? Mail::get(base, tix(k, j), ln) : Opnd<OP>{});
+            }
+        };
         // Y(i,j) = X(i,j) + sum_k A(i,k) X(k,j) on this wave's rows
 #pragma unroll
-        for (int s = 0; s < 9; ++s) {
-            const int i = n128_row<W>(s), j = n128_col<W>(s);
-            const v4f acc = tn_sum<OP>(
-                j, i, [&](int k) { return At[n128_slot<W>(i, k)]; }, [&](int k) { return Mail::get(X, tix(k, j), ln); }, Xn[s]);
-            Mail::put(Y, tix(i, j), pack<OP>(acc), ln);
+        for (int j = 0; j <= 7 - W; ++j) {
+            typename Ops::Right x;
+            column(X, j, x);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (j > ROW[h]) continue;
+                const int s = n128_slot<W>(ROW[h], j);
+                Mail::put(Y, tix(ROW[h], j), pack<OP>(Ops::product(Al[h], x, ROW[h], j, Xn[s])), ln);
+            }
         }
+        typename Ops::Left Xl = {};
+#pragma unroll
+        for (int s = 0; s < 9; ++s) Ops::put(Xl[s <= W ? 0 : 1], n128_col<W>(s), pack<OP>(turned<OP>(Xn[s], id_bf16, id)));
         __syncthreads();  // Y complete; nobody reads X from LDS any more in this iteration
-        // X(i,j) <- 2 X(i,j) - sum_k X(i,k) Y(k,j), both orientations; the packed old row first
+        // X(i,j) <- 2 X(i,j) - sum_k X(i,k) Y(k,j)
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const int i = half == 0 ? W : 7 - W, s0 = half == 0 ? 0 : W + 1;
-            Opnd<OP> xo[N128_NB];
+        for (int j = 0; j <= 7 - W; ++j) {
+            typename Ops::Right y;
+            column(Y, j, y);
 #pragma unroll
-            for (int k = 0; k < N128_NB; ++k)
-                if (k <= i) xo[k] = pack<OP>(Xt[s0 + k]);
-#pragma unroll
-            for (int j = 0; j < N128_NB; ++j) {
-                if (j > i) continue;
-                Opnd<OP> y[N128_NB];
-#pragma unroll
-                for (int k = 0; k < N128_NB; ++k)
-                    if (k >= j && k <= i) y[k] = Mail::get(Y, tix(k, j), ln);
-                const v4f pn = tn_sum<OP>(j, i, [&](int k) { return xo[k]; }, [&](int k) { return y[k]; }, zero4());
-                const v4f pt = tn_sum<OP>(j, i, [&](int k) { return y[k]; }, [&](int k) { return xo[k]; }, zero4());
-                Xn[s0 + j] = 2.f * Xn[s0 + j] - pn;
-                Xt[s0 + j] = 2.f * Xt[s0 + j] - pt;
-                Mail::put(X, tix(i, j), pack<OP>(Xn[s0 + j]), ln);
+            for (int h = 0; h < 2; ++h) {
+                if (j > ROW[h]) continue;
+                const int s = n128_slot<W>(ROW[h], j);
+                Xn[s] = 2.f * Xn[s] - Ops::product(Xl[h], y, ROW[h], j, zero4());
+                Mail::put(X, tix(ROW[h], j), pack<OP>(Xn[s]), ln);
             }
         }
         __syncthreads();  // X complete; nobody reads Y any more
     }
     // X and Y in LDS are dead: their memory becomes the four store patches
-    n128_store<W>(Tm, Xt, reinterpret_cast<float*>(lds) + w * STORE_LDS_FLOATS, ln);
+    n128_store<W, false>(Tm, Xn, reinterpret_cast<float*>(lds) + w * STORE_LDS_FLOATS, ln);
 }
 
 // The fused kernel's tiles of A: the four waves load the chunk's keys once between them (wave w its tile rows w and
