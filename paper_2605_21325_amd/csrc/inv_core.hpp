@@ -158,6 +158,78 @@ __device__ __forceinline__ void leaf_neumann(v4f LN, v4f LT, v4f& XN, v4f& XT, L
     }
 }
 
+// The same product and refinement with fp32 operands on COUNT leaves side by side (see leaves_block_recursive_f32): X^T only
+// (X^T + Y^T X^T needs Y in N orientation), Y turned through LDS, X turned when both orientations are wanted: 8 tile products
+// and 4 turns per leaf with one refinement step instead of 14 products.  Mixed recursion, fp32 operands: 16384 standalone matrices
+// of C = 64 100 -> 84 us (bf16 A, 8192: 51 -> 34 us), 4096 of C = 128 109 -> 88 us, C = 16 (32768) 35 -> 20 us; from keys, 8192 of
+// C = 64 60 -> 55 us, a call of 128 10.8 -> 8.4 us.
+// patch: COUNT * XPOSE_FLOATS floats.
+template <int COUNT> __device__ __forceinline__ void turn_tiles(const v4f (&in)[COUNT], v4f (&out)[COUNT], float* patch, Lane ln)
+{
+#pragma unroll
+    for (int d = 0; d < COUNT; ++d)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) patch[d * XPOSE_FLOATS + (4 * ln.q + r) * XPOSE_LD + ln.n] = in[d][r];
+    leaf_lds_sync();
+#pragma unroll
+    for (int d = 0; d < COUNT; ++d) out[d] = *reinterpret_cast<const v4f*>(&patch[d * XPOSE_FLOATS + ln.n * XPOSE_LD + 4 * ln.q]);
+    leaf_lds_sync();
+}
+
+template <int COUNT>
+__device__ __forceinline__ void leaves_neumann_f32(const v4f (&LN)[COUNT], const v4f (&LT)[COUNT], v4f (&XN)[COUNT], v4f (&XT)[COUNT],
+                                                   float* patch, Lane ln, int r)
+{
+    // x^T y added to acc, the leaves taking turns
+    const auto products = [](const v4f (&x)[COUNT], const v4f (&y)[COUNT], v4f (&acc)[COUNT]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int d = 0; d < COUNT; ++d) acc[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[d][k], y[d][k], acc[d], 0, 0, 0);
+    };
+    const v4f id = identity_tile(ln);
+    v4f YN[COUNT], YT[COUNT];
+#pragma unroll
+    for (int d = 0; d < COUNT; ++d) {
+        YN[d] = LN[d];
+        YT[d] = LT[d];
+        XT[d] = id - LT[d];
+    }
+#pragma unroll
+    for (int it = 0; it < 3; ++it) {
+        v4f Y2[COUNT], X2[COUNT];
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) Y2[d] = zero4();
+        products(YT, YN, Y2);                                   // Y Y
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) {
+            YN[d] = Y2[d];
+            X2[d] = XT[d];
+        }
+        products(YN, XT, X2);                                   // (X + X Y)^T = X^T + Y^T X^T
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) XT[d] = X2[d];
+        if (it < 2) turn_tiles<COUNT>(YN, YT, patch, ln);
+    }
+    turn_tiles<COUNT>(XT, XN, patch, ln);
+#pragma unroll 1
+    for (int s = 0; s < r; ++s) {
+        v4f P[COUNT], X2[COUNT];
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) P[d] = zero4();
+        products(LN, XT, P);
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) {
+            P[d] = id - XT[d] - P[d];                           // R^T = I - X^T - L^T X^T
+            X2[d] = XT[d];
+        }
+        products(XN, P, X2);                                    // (X + R X)^T = X^T + X^T R^T
+#pragma unroll
+        for (int d = 0; d < COUNT; ++d) XT[d] = X2[d];
+        turn_tiles<COUNT>(XT, XN, patch, ln);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Leaves by forward substitution in fp32 vector arithmetic (the direct method of paper Sec. 3.1
 // as the start X0 of Alg. 4 at b0 = 16).  Four leaves at a time: lane group q solves leaf q, lane
@@ -315,7 +387,7 @@ __device__ __forceinline__ void block_recursive(const ASrc& A, v4f (&Tt)[NB * (N
             leafN[2 * p + 1] = transpose_tile(X[tix(1, 1)], patch, ln);
             Tt[tix(2 * p + 1, 2 * p)] = blockT ? X[tix(1, 0)] : transpose_tile(X[tix(1, 0)], patch, ln);
         }
-    } else if constexpr (OP == OP_F32 && LEAF == LEAF_BLOCK_RECURSIVE && PATCHES > 1) {
+    } else if constexpr (OP == OP_F32 && (LEAF == LEAF_BLOCK_RECURSIVE || LEAF == LEAF_NEUMANN) && PATCHES > 1) {
         constexpr int PER = PATCHES < NB ? PATCHES : NB;
         static_assert(NB % PER == 0, "the leaves go in equal groups");
 #pragma unroll
@@ -326,7 +398,10 @@ __device__ __forceinline__ void block_recursive(const ASrc& A, v4f (&Tt)[NB * (N
                 LN[d] = A.template get<false>(PER * pass + d, PER * pass + d);
                 LT[d] = A.template get<true>(PER * pass + d, PER * pass + d);
             }
-            leaves_block_recursive_f32<PER>(LN, LT, XN, XT, patch, ln);
+            if constexpr (LEAF == LEAF_BLOCK_RECURSIVE)
+                leaves_block_recursive_f32<PER>(LN, LT, XN, XT, patch, ln);
+            else
+                leaves_neumann_f32<PER>(LN, LT, XN, XT, patch, ln, leaf_r);
 #pragma unroll
             for (int d = 0; d < PER; ++d) {
                 leafN[PER * pass + d] = XN[d];

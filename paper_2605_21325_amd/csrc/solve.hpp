@@ -224,8 +224,11 @@ __device__ __forceinline__ void invert_and_apply(const ASrc& src, RhsX<OP, NB>& 
     v4f Tm[NT];  // T orientation: Tm[tix(i, j)][r] = T[16 i + n][16 j + 4 q + r], exact unit diagonal, zeros above it
     {
         constexpr int LEAF = METHOD == M_MIXED ? LEAF_NEUMANN : LEAF_BLOCK_RECURSIVE;
-        // (fp32 leaves side by side at C = 64; at C <= 32 these kernels are bound by memory and were 5 % slower with them)
-        block_recursive<OP, NB, ROOT_T, LEAF, NB >= 4 ? 4 : 1>(src, Tm, lds, ln, aux, [&]() {
+        // fp32 leaves side by side: four at C = 64 and 128 with the blocked recursion; two with the mixed one, whose leaves take more
+        // registers (four: one wavefront per SIMD, 8 % slower than one at a time; the same with two and two right-hand sides
+        // beside packed tiles of A); one at C <= 32 (bound by memory, 5 % slower)
+        constexpr int PATCHES = NB < 4 ? 1 : METHOD != M_MIXED ? 4 : (NRHS == 2 && PackedSource<ASrc>::value) ? 1 : 2;
+        block_recursive<OP, NB, ROOT_T, LEAF, PATCHES>(src, Tm, lds, ln, aux, [&]() {
             if constexpr (ISSUE_FROM < NB && IN_MERGE) x.issue(0, ISSUE_FROM, NB);
         });
         if constexpr (ISSUE_FROM < NB && !IN_MERGE) x.issue(0, ISSUE_FROM, NB);
