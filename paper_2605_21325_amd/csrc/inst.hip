@@ -1,7 +1,6 @@
 // Kernel instantiations for one (C = 16 * TRIINV_INST_NB, operand type TRIINV_INST_OP) pair: the
-// matrix-core methods, or -- with TRIINV_INST_FWD=1 -- forward substitution alone (its fully
-// unrolled code is the slowest to compile, so it gets translation units of its own; the gated
-// keys of the per-channel kernel still use TRIINV_INST_OP as their operand type).
+// matrix-core methods, or -- with TRIINV_INST_FWD=1 -- forward substitution alone, which has no operand type
+// of its own (the gated keys of the per-channel kernel still use TRIINV_INST_OP as theirs).
 #include "dispatch.hpp"
 #include "kernels.hpp"
 #if TRIINV_INST_NB == 8 && !TRIINV_INST_FWD

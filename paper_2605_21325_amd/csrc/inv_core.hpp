@@ -66,7 +66,7 @@ __device__ __forceinline__ void leaf_block_recursive(v4f LN, v4f LT, v4f& XN, v4
 // N orientation only and turns it through LDS (a patch per leaf, so that the leaves' turns overlap), and the level b = 2
 // contracts only the two of four instructions whose slots (rows 4q + r) hold non-zeros: r = 0, 1 are the even blocks of
 // size 2, r = 2, 3 the odd ones.  20 instructions per leaf instead of 48.  Standalone blocked recursion, 4099 matrices of
-// C = 64: 27 -> 20 us (bf16 A, 8192: 49 -> 31 us), 4096 of C = 128 107 -> 85 us, C = 16 (32768) 31 -> 18 us; from keys, 128 of C = 64
+// C = 64: 27 -> 20 us (bf16 A, 8192: 49 -> 31 us), 4096 of C = 128 107 -> 85 us, C = 16 (32768) 31 -> 18 us; from keys, 32 of C = 64
 // 10.8 -> 8.1 us, 8192 54 -> 53 us (bound by memory; four leaves side by side instead of two, waiting for all keys: 55 us).
 // patch: COUNT * XPOSE_FLOATS floats.
 constexpr int XPOSE_LD = 20;
@@ -162,7 +162,7 @@ __device__ __forceinline__ void leaf_neumann(v4f LN, v4f LT, v4f& XN, v4f& XT, L
 // (X^T + Y^T X^T needs Y in N orientation), Y turned through LDS, X turned when both orientations are wanted: 8 tile products
 // and 4 turns per leaf with one refinement step instead of 14 products.  Mixed recursion, fp32 operands: 16384 standalone matrices
 // of C = 64 100 -> 84 us (bf16 A, 8192: 51 -> 34 us), 4096 of C = 128 109 -> 88 us, C = 16 (32768) 35 -> 20 us; from keys, 8192 of
-// C = 64 60 -> 55 us, a call of 128 10.8 -> 8.4 us.
+// C = 64 60 -> 55 us, a call of 32 10.8 -> 8.4 us.
 // patch: COUNT * XPOSE_FLOATS floats.
 template <int COUNT> __device__ __forceinline__ void turn_tiles(const v4f (&in)[COUNT], v4f (&out)[COUNT], float* patch, Lane ln)
 {

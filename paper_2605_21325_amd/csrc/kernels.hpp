@@ -685,7 +685,8 @@ __device__ __forceinline__ void build_A_scalar_any_dk(PreA<NB>& out, const void*
 // matrix (the cache-policy bits are an argument of the builtin, and the compiler, which sees the
 // instruction, keeps the wait states a wide store needs before its data registers are rewritten;
 // offsets outside the matrix would be dropped by the hardware's range check).  The 4-byte stores of
-// forward substitution keep the plain non-temporal hint (partial lines written through measured slower).
+// whole rows one by one (forward substitution at C = 16 and its shuffle form) keep the plain non-temporal hint (partial lines written
+// through measured slower).
 constexpr int CACHE_SC0_SC1_NT = 1 | 2 | 16;  // gfx950 buffer-instruction cache-policy bits: sc0, nt, sc1
 
 // One output matrix: its first byte and its element type (OP_F32, or OP_F16 / OP_BF16 when the caller
@@ -846,7 +847,7 @@ __device__ __forceinline__ void store_result(Out Tm, const v4f (&Tt)[NB * (NB + 
 // in fp32 matrix-core products.  A row of A is needed only for its own row of T, so T takes A's place in registers.
 // Row by row throughout, a matrix of C = 128 took 10144 dependent multiply-adds and 2536 LDS broadcasts per lane, with A in
 // 36 KB of LDS and therefore one wavefront per SIMD; this way 112 tile products, two wavefronts, and it is bound by memory.
-// 2048 fused matrices of C = 128 140 -> 42 us, one call of 64: 63 -> 15 us; standalone fp32 135 -> 83 us (4096 matrices);
+// 2048 fused matrices of C = 128 140 -> 42 us, a call of 32: 63 -> 15 us; standalone fp32 135 -> 83 us (4096 matrices);
 // C = 64 fused 69 -> 53 us, standalone 53 -> 44 us (8192).  Error against 64 bits 1.5e-7 -> 1.4e-7 and 8.4e-8 -> 6.2e-8
 // below the diagonal, 5.4e-7 -> 5.8e-7 on correlated keys without decay.
 // ---------------------------------------------------------------------------------------------
@@ -1309,7 +1310,7 @@ template <int OP> __device__ __forceinline__ v4f turned(v4f x, Opnd<OP_BF16> id_
 // right factor is read from LDS once for both of the wave's rows; 16-bit operands contract two tiles per instruction; the
 // first iteration from I / C is a scaling.  The critical wave issues 51 matrix instructions per iteration instead of
 // 111 (16-bit operands); what is left is LDS reads, packing and two barriers.  4096 fused matrices, bf16 operands 235 -> 205 us,
-// standalone 222 -> 187 us; 2048 with fp32 operands 341 -> 248 us (still matrix-core bound), standalone 668 -> 473 us.
+// standalone 222 -> 187 us; 1024 with fp32 operands 341 -> 248 us (still matrix-core bound), 2048 standalone 668 -> 473 us.
 template <int OP, int W>
 __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char* lds, Lane ln, int n_iter, int w)
 {
