@@ -36,8 +36,8 @@ typedef enum { TRIINV_F32 = 0, TRIINV_F16 = 1, TRIINV_BF16 = 2 } triinv_dtype;
 
 /* Inversion methods. */
 typedef enum {
-    /* Forward substitution in fp32, 16 rows at a time: the 16 x 16 diagonal blocks row by row in vector arithmetic,
-     * the products of a tile row with the rows above it in fp32 matrix-core products; the direct, stable baseline
+    /* Forward substitution in fp32, 16 rows at a time: the products of a tile row with the rows above it in fp32
+     * matrix-core products, the rows of the tile row one by one in vector arithmetic; the direct, stable baseline
      * (the role of the vectorised column sweep, paper Sec. 3.1).  Ignores op_dtype.  (TRIINV_FLAG_FWD_SHUFFLE: the
      * row-by-row form without matrix products.) */
     TRIINV_FWD_SUBST = 0,
