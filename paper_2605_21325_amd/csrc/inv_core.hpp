@@ -601,55 +601,44 @@ __device__ __forceinline__ void neumann(const ASrc& A, v4f (&Xt)[NB * (NB + 1) /
 //     bits 1.01e-7 -> 0.97e-7 and 4.1e-8 -> 3.4e-8 (below the diagonal).
 // ---------------------------------------------------------------------------------------------
 
-// 16-bit operands: tile rows / columns 2 p and 2 p + 1 side by side; the tile of a pair that lies above the diagonal is zero.
+// 16-bit operands: tile rows / columns 2 p and 2 p + 1 side by side.
 template <int OP, int NB> struct NsOperands {
     static constexpr int NP = (NB + 1) / 2;
     typedef PairOp<OP> Left[NB][NP];   // [tile row][pair of tile columns]
     typedef PairOp<OP> Right[NP];      // one tile column: [pair of tile rows]
     static __device__ __forceinline__ void set_left(Left& l, int i, int k, Opnd<OP> x) { l[i][k / 2].set(k & 1, x); }
-    static __device__ __forceinline__ void clear(Left& l)
-    {
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-            if (i % 2 == 0) l[i][i / 2].set(1, Opnd<OP>{});
-    }
     // operands of tile column j from its tiles v[i], i >= j
     static __device__ __forceinline__ void set_right(Right& r, int j, const v4f (&v)[NB])
     {
 #pragma unroll
-        for (int i = 0; i < 2 * NP; ++i)
-            if (i / 2 >= j / 2) r[i / 2].set(i & 1, i >= j && i < NB ? pack<OP>(v[i]) : Opnd<OP>{});
+        for (int i = 0; i < NB; ++i)
+            if (i >= j) r[i / 2].set(i & 1, pack<OP>(v[i]));
     }
     // acc[i] += sum over k of left(i, k) right(k, j), i >= j; the tile rows take turns, so that consecutive instructions
     // belong to different sums
     static __device__ __forceinline__ void product(const Left& l, const Right& r, int j, v4f (&acc)[NB])
     {
+        v4f odd[NB];
 #pragma unroll
         for (int p = 0; p < NP; ++p)
 #pragma unroll
             for (int i = 0; i < NB; ++i)
-                if (i >= j && p >= j / 2 && p <= i / 2) acc[i] = tn_pair<OP>(l[i][p], r[p], acc[i]);
+                if (i >= j) pair_term<OP>(p, i, j, l[i][p], r[p], acc[i], odd[i]);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            if (i >= j && mixed_terms(i, j)) acc[i] += odd[i];
     }
-    // Columns 2 p and 2 p + 1 of X are turned together, before the later one is used: its products read the whole pair
-    // (against a zero, so the other half has to be there and finite).
-    static constexpr bool TURN_PAIRS = NB > 1;
     // left(i, j) <- the transpose of tile i of the right column j
-    static __device__ __forceinline__ void transpose(Left& l, const Right& r, int i, int j, const PairOp<OP>& id)
+    static __device__ __forceinline__ void transpose(Left& l, const Right& r, int i, int j, Opnd<OP> id)
     {
-        set_left(l, i, j, pack<OP>(tn<OP>(r[i / 2].get(i & 1), id.get(0), zero4())));
+        set_left(l, i, j, pack<OP>(tn<OP>(r[i / 2].get(i & 1), id, zero4())));
     }
-    static __device__ __forceinline__ PairOp<OP> identity(Lane ln)
-    {
-        PairOp<OP> id;
-        id.set(0, pack<OP>(identity_tile(ln)));
-        id.set(1, Opnd<OP>{});
-        return id;
-    }
+    static __device__ __forceinline__ Opnd<OP> identity(Lane ln) { return pack<OP>(identity_tile(ln)); }
     static __device__ __forceinline__ void put_left(Left& l, int i, int j, v4f at) { set_left(l, i, j, pack<OP>(at)); }
     // the (rounded) value of left(i, j) in N orientation
-    static __device__ __forceinline__ v4f value_n(const Left& l, int i, int j, const PairOp<OP>& id)
+    static __device__ __forceinline__ v4f value_n(const Left& l, int i, int j, Opnd<OP> id)
     {
-        return tn<OP>(l[i][j / 2].get(j & 1), id.get(0), zero4());
+        return tn<OP>(l[i][j / 2].get(j & 1), id, zero4());
     }
 };
 
@@ -657,14 +646,12 @@ template <int OP, int NB> struct NsOperands {
 template <int NB> struct NsOperands<OP_F32, NB> {
     typedef Split3 Left[NB * (NB + 1) / 2];
     typedef Split3 Right[NB];
-    static __device__ __forceinline__ void clear(Left&) {}
     static __device__ __forceinline__ void set_right(Right& r, int j, const v4f (&v)[NB])
     {
 #pragma unroll
         for (int i = 0; i < NB; ++i)
             if (i >= j) r[i] = split3(v[i]);
     }
-    static constexpr bool TURN_PAIRS = false;
     static __device__ __forceinline__ void product(const Left& l, const Right& r, int j, v4f (&acc)[NB])
     {
         v4f cross[NB];
@@ -707,7 +694,6 @@ __device__ __forceinline__ void newton_schulz(const ASrc& A, v4f (&Xn)[NB * (NB 
     constexpr float X0 = 1.f / (16 * NB);
     typename Ops::Left Al;
     const auto id = Ops::identity(ln);
-    Ops::clear(Al);
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -719,28 +705,17 @@ __device__ __forceinline__ void newton_schulz(const ASrc& A, v4f (&Xn)[NB * (NB 
 #pragma unroll 1
     for (int it = 1; it < n_iter; ++it) {
         typename Ops::Left Xl;
-        Ops::clear(Xl);
 #pragma unroll
         for (int j = NB - 1; j >= 0; --j) {
             v4f col[NB];
             typename Ops::Right x, y;
-            if (!Ops::TURN_PAIRS || (j & 1)) {
 #pragma unroll
-                for (int c = Ops::TURN_PAIRS ? j - 1 : j; c <= j; ++c) {
+            for (int i = 0; i < NB; ++i)
+                if (i >= j) col[i] = Xn[tix(i, j)];
+            Ops::set_right(x, j, col);
 #pragma unroll
-                    for (int i = 0; i < NB; ++i)
-                        if (i >= c) col[i] = Xn[tix(i, c)];
-                    Ops::set_right(x, c, col);
-#pragma unroll
-                    for (int i = 0; i < NB; ++i)
-                        if (i >= c) Ops::transpose(Xl, x, i, c, id);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < NB; ++i)
-                    if (i >= j) col[i] = Xn[tix(i, j)];
-                Ops::set_right(x, j, col);
-            }
+            for (int i = 0; i < NB; ++i)
+                if (i >= j) Ops::transpose(Xl, x, i, j, id);
             Ops::product(Al, x, j, col);  // Y = X + A X
             Ops::set_right(y, j, col);
 #pragma unroll

@@ -1407,37 +1407,26 @@ template <int OP> constexpr int ns128_lds_bytes()
 template <int W> __host__ __device__ constexpr int n128_slot(int i, int k) { return i == W ? k : (W + 1) + k; }
 
 // The wave's two tile rows as left operands, and one tile column as right operand.  16-bit operands: pairs of tiles for the
-// 32-deep instructions (a tile above the diagonal is zero); fp32: tile by tile.
-template <int OP, int W> struct Ns128Operands {
-    static constexpr bool PAIRED = OP != OP_F32;
-    static constexpr int NP = PAIRED ? 4 : 8;                                   // slots along a tile row
-    struct Slot {
-        Opnd<OP> lo, hi;                                                        // (hi: PAIRED only)
-    };
-    typedef Slot Left[2][NP];                                                   // rows W and 7 - W
-    typedef Slot Right[NP];
-    static __device__ __forceinline__ void put(Slot* row, int k, Opnd<OP> x)
+// 32-deep instructions; fp32: tile by tile.
+template <int OP> struct Ns128Operands {
+    typedef PairOp<OP> Row[4];
+    static __device__ __forceinline__ void put(Row& row, int k, Opnd<OP> x) { row[k / 2].set(k & 1, x); }
+    static __device__ __forceinline__ v4f product(const Row& l, const Row& r, int i, int j, v4f acc)
     {
-        if (!PAIRED) row[k].lo = x;
-        else if (k & 1) row[k / 2].hi = x;
-        else row[k / 2].lo = x;
+        v4f odd;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) pair_term<OP>(p, i, j, l[p], r[p], acc, odd);
+        return mixed_terms(i, j) ? acc + odd : acc;
     }
-    static __device__ __forceinline__ v4f product(const Slot* l, const Slot* r, int i, int j, v4f acc)
+};
+template <> struct Ns128Operands<OP_F32> {
+    typedef Opnd<OP_F32> Row[8];
+    static __device__ __forceinline__ void put(Row& row, int k, Opnd<OP_F32> x) { row[k] = x; }
+    static __device__ __forceinline__ v4f product(const Row& l, const Row& r, int i, int j, v4f acc)
     {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {
-            if constexpr (PAIRED) {
-                if (p < j / 2 || p > i / 2) continue;
-                PairOp<OP> x, y;
-                x.set(0, l[p].lo);
-                x.set(1, l[p].hi);
-                y.set(0, r[p].lo);
-                y.set(1, r[p].hi);
-                acc = tn_pair<OP>(x, y, acc);
-            } else {
-                if (p >= j && p <= i) acc = tn<OP>(l[p].lo, r[p].lo, acc);
-            }
-        }
+        for (int k = 0; k < 8; ++k)
+            if (k >= j && k <= i) acc = tn<OP_F32>(l[k], r[k], acc);
         return acc;
     }
 };
@@ -1464,7 +1453,7 @@ template <int OP, int W>
 __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char* lds, Lane ln, int n_iter, int w)
 {
     typedef MailTiles<OP> Mail;
-    typedef Ns128Operands<OP, W> Ops;
+    typedef Ns128Operands<OP> Ops;
     constexpr int ROW[2] = {W, 7 - W};
     constexpr float X0 = 1.f / 128.f;
     char* const X = lds;
@@ -1472,7 +1461,7 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
     const v4f unit = identity_tile(ln);
     const Opnd<OP> id = pack<OP>(unit);
     const Opnd<OP_BF16> id_bf16 = pack<OP_BF16>(unit);
-    typename Ops::Left Al = {};
+    typename Ops::Row Al[2];
     v4f Xn[9];
 #pragma unroll
     for (int s = 0; s < 9; ++s) {
@@ -1491,17 +1480,15 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
 #pragma unroll 1
     for (int it = 1; it < n_iter; ++it) {
         // a tile column j of a matrix in LDS, rows j .. 7 - W
-        const auto column = [&](const char* base, int j, typename Ops::Right& r) {
+        const auto column = [&](const char* base, int j, typename Ops::Row& r) {
 #pragma unroll
-            for (int k = 0; k < N128_NB; ++k) {
-                if (k > (Ops::PAIRED ? (7 - W) | 1 : 7 - W) || k < (Ops::PAIRED ? j & ~1 : j)) continue;
-                Ops::put(r, k, k >= j && k <= 7 - W ? Mail::get(base, tix(k, j), ln) : Opnd<OP>{});
-            }
+            for (int k = 0; k < N128_NB; ++k)
+                if (k >= j && k <= 7 - W) Ops::put(r, k, Mail::get(base, tix(k, j), ln));
         };
         // Y(i,j) = X(i,j) + sum_k A(i,k) X(k,j) on this wave's rows
 #pragma unroll
         for (int j = 0; j <= 7 - W; ++j) {
-            typename Ops::Right x;
+            typename Ops::Row x;
             column(X, j, x);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -1510,14 +1497,14 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
                 Mail::put(Y, tix(ROW[h], j), pack<OP>(Ops::product(Al[h], x, ROW[h], j, Xn[s])), ln);
             }
         }
-        typename Ops::Left Xl = {};
+        typename Ops::Row Xl[2];
 #pragma unroll
         for (int s = 0; s < 9; ++s) Ops::put(Xl[s <= W ? 0 : 1], n128_col<W>(s), pack<OP>(turned<OP>(Xn[s], id_bf16, id)));
         __syncthreads();  // Y complete; nobody reads X from LDS any more in this iteration
         // X(i,j) <- 2 X(i,j) - sum_k X(i,k) Y(k,j)
 #pragma unroll
         for (int j = 0; j <= 7 - W; ++j) {
-            typename Ops::Right y;
+            typename Ops::Row y;
             column(Y, j, y);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {

@@ -197,6 +197,27 @@ template <int OP> __device__ __forceinline__ v4f tn_pair(PairOp<OP> x, PairOp<OP
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, x.u), __builtin_bit_cast(v8bf, y.u), acc, 0, 0, 0);
 }
 
+// The terms k = 2 p, 2 p + 1 of a tile (i, j) of a product of lower triangular matrices, sum over j <= k <= i.  Where both are
+// terms: one 32-deep instruction into acc.  Where one is: a 16-deep one, into `odd` if the tile has pairs too (mixed_terms;
+// started from zero here, to be added to acc at the end), into acc otherwise.  A 32-deep instruction with a zero in place of the
+// other tile would take as long, but that tile's partner is a real one, from outside the sum: where it is not finite, its
+// product with zero is NaN.
+__host__ __device__ constexpr bool has_pairs(int i, int j) { return (i + 1) / 2 > (j + 1) / 2; }
+__host__ __device__ constexpr bool mixed_terms(int i, int j) { return has_pairs(i, j) && (j % 2 == 1 || i % 2 == 0); }
+template <int OP> __device__ __forceinline__ void pair_term(int p, int i, int j, const PairOp<OP>& x, const PairOp<OP>& y, v4f& acc, v4f& odd)
+{
+    const bool low = j <= 2 * p && 2 * p <= i, high = j <= 2 * p + 1 && 2 * p + 1 <= i;
+    if (low && high)
+        acc = tn_pair<OP>(x, y, acc);
+    else if (low || high) {
+        const bool first = p == j / 2 && j % 2 == 1;  // (the other single term, if there is one, is the last)
+        if (mixed_terms(i, j))
+            odd = tn<OP>(x.get(high), y.get(high), first || j % 2 == 0 ? zero4() : odd);
+        else
+            acc = tn<OP>(x.get(high), y.get(high), acc);
+    }
+}
+
 // An fp32 tile as the sum of three bf16 tiles, x = h + m + l: h = bf16(x), m = bf16(x - h), l = x - h - m, which is exact
 // (24 = 3 x 8 bits; both differences are exact, and what remains after m has at most 8 bits).  The product of two such
 // tiles is hh + hm + mh + hl + lh + mm up to terms below 2^-26 |x| |y| (an fp32 product rounds at 2^-24), all of

@@ -1019,6 +1019,29 @@ def test_non_finite_entry_reaches_only_the_rows_that_depend_on_it_forward(C):
             assert not torch.isfinite(T[m, i, j])
 
 
+@pytest.mark.parametrize("op", _OPS, ids=lambda o: tri.DTYPE_NAMES[o])
+@pytest.mark.parametrize("C", [32, 64, 128])
+def test_non_finite_entry_reaches_only_the_tiles_that_depend_on_it(C, op):
+    """The matrix-product methods, an infinite or NaN entry below the diagonal in tile (I, J) of 16 x 16: tile rows above I and tile
+    columns right of J of the result do not depend on it and are those of the matrix without it, bit for bit."""
+    NB = C // 16
+    A = torch.tril(torch.randn(1, C, C, generator=torch.Generator().manual_seed(11)) * 0.1, -1)
+    tiles = [(I, J) for I in range(NB) for J in range(I + 1)]
+    pos = [(16 * I + 9, 16 * J + 4) for I, J in tiles]
+    M, Z = A.repeat(2 * len(pos), 1, 1), A.repeat(len(pos), 1, 1)
+    for m, (i, j) in enumerate(pos):
+        Z[m, i, j] = 0
+        M[m, i, j], M[m + len(pos), i, j] = float("inf"), float("nan")
+    for method in (tri.NEWTON_SCHULZ, tri.NEUMANN, tri.BLOCK_RECURSIVE, tri.MIXED, tri.MIXED_B32, tri.BLOCK_DIRECT):
+        for in_dt in (torch.float32, torch.bfloat16):
+            T = tri.tri_inv_ex(M.to(in_dt).to(DEV), method=method, op_dtype=op).cpu()
+            want = tri.tri_inv_ex(Z.to(in_dt).to(DEV), method=method, op_dtype=op).cpu()
+            for m in range(2 * len(pos)):
+                (I, J), w = tiles[m % len(pos)], want[m % len(pos)]
+                assert torch.equal(T[m, :16 * I], w[:16 * I]), (tri.METHOD_NAMES[method], in_dt, I, J, "rows above")
+                assert torch.equal(T[m, :, 16 * J + 16:], w[:, 16 * J + 16:]), (tri.METHOD_NAMES[method], in_dt, I, J, "columns right")
+
+
 # ------------------------------------------------------------------ forward substitution by wavefront shuffles
 @pytest.mark.parametrize("dt", [torch.float32, torch.float16, torch.bfloat16])
 def test_forward_substitution_shuffle_variant(cases, dt):
