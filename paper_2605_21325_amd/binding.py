@@ -7,6 +7,7 @@ missing or cannot be loaded, importing a symbol from it raises.
 """
 from __future__ import annotations
 
+import array
 import ctypes
 import os
 from typing import Optional
@@ -36,6 +37,7 @@ def flag_iters(n: int) -> int:
 
 GATE_SCALAR, GATE_PER_CHANNEL, GATE_NONE = 0, 1, 2
 OK = 0
+ERR_BAD_C = -2
 
 METHOD_NAMES = {FWD_SUBST: "fwd_subst", BLOCK_RECURSIVE: "block_recursive", NEUMANN: "neumann", MIXED: "mixed",
                 BLOCK_DIRECT: "block_direct", NEWTON_SCHULZ: "newton_schulz", MIXED_B32: "mixed_b32"}
@@ -209,6 +211,8 @@ def varlen_chunk_offsets(seqlens, C: int):
     cu_s, cu_c = [0], [0]
     for n in seqlens:
         n = int(n)
+        if n < 0:
+            raise ValueError(f"negative sequence length {n}")
         cu_s.append(cu_s[-1] + n)
         cu_c.append(cu_c[-1] + (n + C - 1) // C)
     return cu_s, cu_c
@@ -218,30 +222,38 @@ def _chunk_offsets(K: torch.Tensor, seqlens, C: int, stream):
     """(device addresses of cu_seqlens and cu_chunks, number of sequences, total chunks, tensors to keep alive) for packed
     sequences of the given lengths.  The offsets of up to 900 sequences travel as kernel arguments on the launch stream, behind
     which the caller's kernel follows: copying two host lists to the device waited for the device twice a call (76 against
-    41 us for 48 sequences).  Where that does not apply (another device, a stream that is no torch stream, lengths that are no plain
-    non-negative integers) they are copied."""
+    41 us for 48 sequences).  For tensors of another device, on a stream object of another library, and for more sequences they are
+    copied.  ValueError: a negative length, or lengths that do not sum to the tokens there are."""
     total = K.shape[0]
     if not isinstance(seqlens, (list, tuple)):
         seqlens = list(seqlens)
     n = len(seqlens)
+    st = OK
     if n <= 900 and K.is_cuda and K.device.index == torch.cuda.current_device() and (
             stream is None or (isinstance(stream, torch.cuda.Stream) and stream.device == K.device)):
         try:
-            lens = (ctypes.c_int64 * n)(*seqlens)
-        except TypeError:
-            lens = (ctypes.c_int64 * n)(*[int(x) for x in seqlens])
-        if stream is None:
-            cu = torch.empty(2 * (n + 1), dtype=torch.int64, device=K.device)
-        else:
-            with torch.cuda.stream(stream):  # the memory belongs to the stream that writes and reads it
+            try:
+                lens = array.array("q", seqlens)
+            except TypeError:
+                lens = array.array("q", [int(x) for x in seqlens])
+        except OverflowError:  # no 64-bit number: refused with the other wrong sums below
+            lens = None
+        if lens is not None:
+            if stream is None:
                 cu = torch.empty(2 * (n + 1), dtype=torch.int64, device=K.device)
-        chunks = ctypes.c_int64()
-        st = lib().triinv_detail_chunk_offsets(lens, n, C, total, cu.data_ptr(), ctypes.byref(chunks), _stream_ptr(stream))
-        if st == OK:
-            return cu.data_ptr(), cu.data_ptr() + 8 * (n + 1), n, chunks.value, (cu,)
+            else:
+                with torch.cuda.stream(stream):  # the memory belongs to the stream that writes and reads it
+                    cu = torch.empty(2 * (n + 1), dtype=torch.int64, device=K.device)
+            chunks = ctypes.c_int64()
+            st = lib().triinv_detail_chunk_offsets(lens.buffer_info()[0], n, C, total, cu.data_ptr(), ctypes.byref(chunks),
+                                                   _stream_ptr(stream))
+            if st == OK:
+                return cu.data_ptr(), cu.data_ptr() + 8 * (n + 1), n, chunks.value, (cu,)
     cu_s, cu_c = varlen_chunk_offsets(seqlens, C)
     if cu_s[-1] != total:
         raise ValueError(f"sequence lengths sum to {cu_s[-1]}, K holds {total} tokens")
+    if st not in (OK, ERR_BAD_C):  # (the entry point itself reports a chunk size there is no kernel for)
+        raise TriInvError(st, "offsets of the packed sequences")
     cu_seqlens = torch.tensor(cu_s, dtype=torch.int64, device=K.device)
     cu_chunks = torch.tensor(cu_c, dtype=torch.int64, device=K.device)
     return cu_seqlens.data_ptr(), cu_chunks.data_ptr(), len(cu_s) - 1, cu_c[-1], (cu_seqlens, cu_chunks)

@@ -238,3 +238,15 @@ def test_chunk_offsets_helper_refuses_before_any_launch(L):
     assert f((ctypes.c_int64 * 901)(), 901, 64, 0, P, ctypes.byref(out), None) == -5
     assert f(lens, 2, 64, 7, None, ctypes.byref(out), None) == -5
     assert out.value == -1
+
+
+def test_negative_sequence_lengths_are_refused():
+    """With the right sum too: the offsets of such lengths would name tokens of other sequences."""
+    import torch
+    for lens in ([2, -1, 3], [-4, 8]):
+        with pytest.raises(ValueError, match="negative"):
+            tri.varlen_chunk_offsets(lens, 64)
+        with pytest.raises(ValueError, match="negative"):
+            tri.gdn_chunk_tri_inv_varlen(torch.zeros(4, 1, 64), torch.zeros(4, 1), None, lens, 64, gate_kind=tri.GATE_NONE)
+        with pytest.raises(ValueError, match="negative"):
+            tri.gdn_chunk_tri_solve_varlen(torch.zeros(4, 1, 64), torch.zeros(4, 1), None, torch.zeros(4, 1, 8), lens, 64, gate_kind=tri.GATE_NONE)

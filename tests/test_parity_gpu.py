@@ -918,11 +918,66 @@ def test_packed_sequences_by_either_route():
     S = tri.gdn_chunk_tri_inv_varlen(K, beta, None, few, C, gate_kind=tri.GATE_NONE, stream=side)
     torch.cuda.synchronize()
     assert torch.equal(S, T)
-    for wrong in (few + [1], [2716] + few[1:], [2715, 70, -1, 132]):
-        if sum(wrong) == total:
-            continue
+    for wrong in (few + [1], [2716] + few[1:], [2715, 70, -1, 132], [1] * 905 + [-1, total - 904], [total + 2 ** 64]):
         with pytest.raises(ValueError):
             tri.gdn_chunk_tri_inv_varlen(K, beta, None, wrong, C, gate_kind=tri.GATE_NONE)
+    with pytest.raises(tri.TriInvError) as e:
+        tri.gdn_chunk_tri_inv_varlen(K, beta, None, few, 48, gate_kind=tri.GATE_NONE)
+    assert e.value.status == -2
+
+
+def test_packed_sequences_report_a_failing_offsets_launch(monkeypatch):
+    """A launch of the offsets kernel that the runtime refuses is reported, not taken for a reason to copy them instead."""
+    class Refused:
+        def __getattr__(self, name):
+            return (lambda *a: -8) if name == "triinv_detail_chunk_offsets" else getattr(lib, name)
+    lib = tri.lib()
+    monkeypatch.setattr(tri.binding, "_lib", Refused())
+    K, beta = torch.zeros(128, 2, 64, dtype=torch.bfloat16, device=DEV), torch.zeros(128, 2, device=DEV)
+    with pytest.raises(tri.TriInvError) as e:
+        tri.gdn_chunk_tri_inv_varlen(K, beta, None, [100, 28], 64, gate_kind=tri.GATE_NONE)
+    assert e.value.status == -8
+
+
+def test_packed_sequences_replay_from_a_captured_graph():
+    """The packed-sequence calls recorded into a graph with given results: the offsets' buffer comes from the graph's memory, so that
+    replays are right after the result's own reference to it is gone (eager calls into the same results, and allocations in
+    between, overwrite what was freed)."""
+    C, H, lens = 64, 3, [70, 0, 1, 130, 64, 7]
+    total = sum(lens)
+    gen = torch.Generator().manual_seed(17)
+    def inputs():
+        K = torch.nn.functional.normalize(torch.randn(total, H, 64, generator=gen), dim=-1).bfloat16().to(DEV)
+        return K, torch.rand(total, H, generator=gen).to(DEV), torch.randn(total, H, 72, generator=gen).bfloat16().to(DEV)
+    ins = [inputs() for _ in range(3)]
+    K, beta, X = (t.clone() for t in ins[0])
+    inv = lambda T=None: tri.gdn_chunk_tri_inv_varlen(K, beta, None, lens, C, T=T, gate_kind=tri.GATE_NONE)
+    solve = lambda W=None: tri.gdn_chunk_tri_solve_varlen(K, beta, None, X, lens, C, row_scale=beta, W=W, gate_kind=tri.GATE_NONE)
+    T, W = inv(), solve()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        inv(T)
+        solve(W)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        inv(T)
+        solve(W)
+    for rep in range(6):
+        for dst, src in zip((K, beta, X), ins[rep % 3]):
+            dst.copy_(src)
+        inv(T)
+        solve(W)
+        junk = [torch.full((14,), -1 - i, dtype=torch.int64, device=DEV) for i in range(50)]
+        T.fill_(7.0)
+        W.fill_(7.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(T, inv()) and torch.equal(W, solve()), f"replay {rep} differs from the eager call"
+        assert all(bool((j == -1 - i).all()) for i, j in enumerate(junk)), "a replay wrote memory that is not the graph's"
 
 
 # ------------------------------------------------------------------ every element of a given A in its place
