@@ -679,11 +679,11 @@ template <int NB> struct NsOperands<OP_F32, NB> {
                              pack<OP_BF16>(tn<OP_BF16>(r[i].l(), id, zero4())));
     }
     static __device__ __forceinline__ Opnd<OP_BF16> identity(Lane ln) { return pack<OP_BF16>(identity_tile(ln)); }
-    static __device__ __forceinline__ void put_left(Left& l, int i, int j, v4f at) { l[tix(i, j)] = split3(at); }
+    static __device__ __forceinline__ void put_left(Left& l, int i, int j, v4f at) { l[tix(i, j)] = split3_any(at); }
     static __device__ __forceinline__ v4f value_n(const Left& l, int i, int j, const Opnd<OP_BF16>& id)
     {
         const Split3& s = l[tix(i, j)];
-        return tn<OP_BF16>(s.l(), id, tn<OP_BF16>(s.m(), id, tn<OP_BF16>(s.h(), id, zero4())));  // h + m + l, exact in this order
+        return tn<OP_BF16>(s.h(), id, tn<OP_BF16>(s.m(), id, tn<OP_BF16>(s.l(), id, zero4())));  // exact in this order, the smallest first
     }
 };
 

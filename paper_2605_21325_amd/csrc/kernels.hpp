@@ -1431,12 +1431,12 @@ template <> struct Ns128Operands<OP_F32> {
     }
 };
 
-// The transpose of a tile, exact: by products with the identity.
-template <int OP> __device__ __forceinline__ v4f turned(v4f x, Opnd<OP_BF16> id_bf16, Opnd<OP> id)
+// The transpose of a tile, exact (see Split3; ANY: for values beyond the largest bf16 too): by products with the identity.
+template <int OP, bool ANY = false> __device__ __forceinline__ v4f turned(v4f x, Opnd<OP_BF16> id_bf16, Opnd<OP> id)
 {
     if constexpr (OP == OP_F32) {
-        const Split3 s = split3(x);
-        return tn<OP_BF16>(s.l(), id_bf16, tn<OP_BF16>(s.m(), id_bf16, tn<OP_BF16>(s.h(), id_bf16, zero4())));
+        const Split3 s = ANY ? split3_any(x) : split3(x);
+        return tn<OP_BF16>(s.h(), id_bf16, tn<OP_BF16>(s.m(), id_bf16, tn<OP_BF16>(s.l(), id_bf16, zero4())));
     } else {
         return tn<OP>(pack<OP>(x), id, zero4());  // (of the rounded tile)
     }
@@ -1469,7 +1469,7 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
         Ops::put(Al[s <= W ? 0 : 1], j, At[s]);
         v4f a;
         if constexpr (OP == OP_F32)
-            a = turned<OP>(At[s].x, id_bf16, id);
+            a = turned<OP, true>(At[s].x, id_bf16, id);
         else
             a = tn<OP>(At[s], id, zero4());
         if (i == j) a += unit;

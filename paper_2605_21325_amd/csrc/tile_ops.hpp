@@ -219,11 +219,13 @@ template <int OP> __device__ __forceinline__ void pair_term(int p, int i, int j,
 }
 
 // An fp32 tile as the sum of three bf16 tiles, x = h + m + l: h = bf16(x), m = bf16(x - h), l = x - h - m, which is exact
-// (24 = 3 x 8 bits; both differences are exact, and what remains after m has at most 8 bits).  The product of two such
-// tiles is hh + hm + mh + hl + lh + mm up to terms below 2^-26 |x| |y| (an fp32 product rounds at 2^-24), all of
-// it accumulated in fp32: three 32-deep bf16 instructions of 16 cycles against four 16x16x4 fp32 instructions of 32.
-// Splitting costs 22 vector instructions a tile, so it pays where an operand is used several times.  Values above
-// 3.39e38 (the largest bf16) do not split.
+// (24 = 3 x 8 bits; both differences are exact, and what remains after m has at most 8 bits) for |x| between 2^-110, below
+// which l runs into bf16's smallest subnormal, and 3.39e38, the largest bf16, above which h is infinite and the sum NaN
+// (split3_any takes every finite x).  The product of two such tiles is hh + hm + mh + hl + lh + mm, accumulated in fp32; what is
+// left out, ml + lm + ll, is at most 2^-24 |x| |y| (|m| <= 2^-8 |x|, |l| <= 2^-17 |x|; both at once is rare: root mean square 2^-27.5
+// over random mantissas), where an fp32 multiply-add rounds its sum, not the product.  Whole iterations are no less accurate for it (see
+// newton_schulz): three 32-deep bf16 instructions of 16 cycles against four 16x16x4 fp32 instructions of 32.
+// Splitting costs 22 vector instructions a tile, so it pays where an operand is used several times.
 // The parts sit side by side in the order m h l, so that two overlapping windows of either operand feed the instructions:
 //   (m h) . (m h) = mm + hh,   (m h) . (h l) = mh + hl,   (h l) . (m h) = hm + lh.
 typedef uint32_t v6u __attribute__((ext_vector_type(6)));
@@ -251,6 +253,18 @@ __device__ __forceinline__ v4f minus_bf16(v4f x, Opnd<OP_BF16> y)
 __device__ __forceinline__ Split3 split3(v4f x)
 {
     const Opnd<OP_BF16> h = pack<OP_BF16>(x);
+    x = minus_bf16(x, h);
+    const Opnd<OP_BF16> m = pack<OP_BF16>(x);
+    return join3(m, h, pack<OP_BF16>(minus_bf16(x, m)));
+}
+// The same for values beyond the largest bf16: h is that one then, and m takes what is left.
+__device__ __forceinline__ Split3 split3_any(v4f x)
+{
+    constexpr float MAX_BF16 = 0x1.fep127f;
+    v4f c;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) c[r] = __builtin_amdgcn_fmed3f(x[r], -MAX_BF16, MAX_BF16);
+    const Opnd<OP_BF16> h = pack<OP_BF16>(c);
     x = minus_bf16(x, h);
     const Opnd<OP_BF16> m = pack<OP_BF16>(x);
     return join3(m, h, pack<OP_BF16>(minus_bf16(x, m)));

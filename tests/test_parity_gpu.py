@@ -883,6 +883,25 @@ def test_newton_schulz_iterates(C, op):
             assert err <= (TOL[op] if op != tri.F16 or k != 1 else 1e-1), (C, m, k, err)
 
 
+@pytest.mark.parametrize("C", [16, 32, 64, 128])
+def test_newton_schulz_takes_entries_beyond_the_largest_bf16(C):
+    """fp32 operands: entries between the largest bf16 (3.39e38) and the largest fp32 number, whose leading part alone would round to
+    infinity.  A single one per matrix, the first two iterates (X0 A X0 = A / C^2, and 4 (1 - 3 / (2 C)) of it; later ones
+    approach -A and overflow in 2 X)."""
+    from oracle import methods
+    pos = [(i, j) for i in (1, 9, C - 1) for j in (0, i - 1, i // 2)]
+    A = torch.zeros(len(pos), C, C)
+    for m, (i, j) in enumerate(pos):
+        A[m, i, j] = (3.4028234e38, -3.395e38, 3.3953e38)[m % 3]
+    for iters in (1, 2):
+        T = tri.tri_inv_ex(A.to(DEV), method=tri.NEWTON_SCHULZ, op_dtype=tri.F32, flags=tri.flag_iters(iters)).cpu().double().numpy()
+        for m, (i, j) in enumerate(pos):
+            want = methods.newton_schulz_closed_form(A[m].double().numpy(), iters)[i, j]
+            assert abs(T[m, i, j] / want - 1) < 1e-6, (C, iters, i, j, T[m, i, j], want)
+            T[m, i, j] = 0
+        assert np.array_equal(T, np.broadcast_to(np.eye(C), T.shape))
+
+
 # ------------------------------------------------------------------ packed sequences: the offsets' way to the device
 @pytest.mark.parametrize("n_seq", [0, 1, 228, 229, 230, 459, 900])
 def test_chunk_offsets_by_kernel_arguments(n_seq):
