@@ -868,7 +868,10 @@ def test_sixteen_bit_result_argument_errors():
 def test_newton_schulz_iterates(C, op):
     """The m-th iterate, converged or not, against its closed form X_m = T (I - R0^(2^m)) in 64 bits (strictly lower part: the
     stored diagonal is exactly 1): m = 1 is the start that is written down directly, m = 2 the first full iteration.  The
-    entries of A span eight orders of magnitude, so that every part of a split operand counts."""
+    entries of A span eight orders of magnitude.  With fp32 operands every row is held to 5e-7 of its own norm (a norm over the matrix
+    would be that of its large rows): products of fp32 accuracy give at most 2e-7; in an emulation of the split
+    products, leaving out the third part of one operand gives 3.5e-6 and more from m = 2 on, of both 4.8e-6, and keeping three of
+    the six products 4.8e-6 (C = 16, 32, 64)."""
     from oracle import methods
     A = si.random_strict_lower(5, C, 0.15, seed=23)
     A[1] *= 1e-4
@@ -879,6 +882,9 @@ def test_newton_schulz_iterates(C, op):
         for k in range(A.shape[0]):
             want = np.tril(methods.newton_schulz_closed_form(np.tril(A[k].numpy().astype(np.float64), -1), m), -1)
             err = np.linalg.norm(got[k] - want) / np.linalg.norm(want)
+            if op == tri.F32:
+                rows = np.linalg.norm(got[k] - want, axis=1)[1:] / np.linalg.norm(want, axis=1)[1:]
+                assert rows.max() <= 5e-7, (C, m, k, int(rows.argmax()) + 1, rows.max())
             # fp16: the start (I + A) / C^2 times entries of 1e-5 lies among the subnormal operands
             assert err <= (TOL[op] if op != tri.F16 or k != 1 else 1e-1), (C, m, k, err)
 
@@ -1016,6 +1022,23 @@ def test_input_elements_in_place(C, dt):
         want[m, i, j] = -A[m, i, j]
     for method in (tri.BLOCK_RECURSIVE, tri.FWD_SUBST):
         T = tri.tri_inv_ex(A.to(dt).to(DEV), method=method, op_dtype={torch.float32: tri.F32, torch.float16: tri.F16, torch.bfloat16: tri.BF16}[dt])
+        assert torch.equal(T.cpu(), want), (C, dt, tri.METHOD_NAMES[method])
+
+
+@pytest.mark.parametrize("dt", [torch.float16, torch.bfloat16], ids=["f16", "bf16"])
+@pytest.mark.parametrize("C", [16, 32, 64, 128])
+def test_smallest_input_elements(C, dt):
+    """fp16 A with subnormal entries (bf16: the smallest normal ones), fp32 operands: a single entry below the diagonal,
+    (I + A)^-1 = I - A exactly.  In one of the two orientations a tile is turned by a matrix product with the identity, which must
+    not flush them."""
+    bits = [1, 2, 3, 0x155, 0x2aa, 0x3ff] if dt == torch.float16 else [0x80, 0x81, 0x155]
+    pos = [(i, j) for i in range(1, C) for j in (0, i // 2, i - 1)]
+    A = torch.zeros(len(pos), C, C, dtype=dt)
+    for m, (i, j) in enumerate(pos):
+        A[m, i, j] = torch.tensor(bits[m % len(bits)] | (-0x8000 if m % 2 else 0), dtype=torch.int16).view(dt)
+    want = torch.eye(C) - A.float()
+    for method in (tri.BLOCK_RECURSIVE, tri.MIXED, tri.NEUMANN, tri.FWD_SUBST):
+        T = tri.tri_inv_ex(A.to(DEV), method=method, op_dtype=tri.F32)
         assert torch.equal(T.cpu(), want), (C, dt, tri.METHOD_NAMES[method])
 
 
