@@ -40,7 +40,7 @@ constexpr int OP = TRIINV_INST_OP;
 template <int METHOD, bool REFINE = false> static int go_tri(const TriInvArgs& a)
 {
     TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv<IN, OP, NB, METHOD, REFINE>), dim3((unsigned)a.n_mat), dim3(64), 0,
-                                                   a.stream, a.A, a.T, a.n_mat, a.iters, a.out_dt))
+                                                   a.stream, a.A, a.T, a.n_mat, a.in_dt, a.iters, a.out_dt))
 }
 
 // Fused matrix-core kernels at C <= 64 run four matrices (adjacent heads) per workgroup.

@@ -73,6 +73,51 @@ template <int NB, int IN> struct GlobalA {
     }
 };
 
+// The same with the element type known at run time only, for kernels that read most tiles twice (fp32 A; for a 16-bit one see
+// LoadedA16).  Each tile is then loaded in a block of its own, behind a branch that the whole wavefront takes: the
+// compiler can neither move all loads to the start, where they cost the Neumann product a wavefront per SIMD, nor put off a second
+// reading until the tile has left the caches.  (Scheduling fences between typed loads: 533 and 210 us where this takes 460 and 161.)
+template <int NB> struct GlobalAnyA {
+    static constexpr bool kFromMemory = true;
+    static constexpr bool kHoldsKeys = false;
+    const void* base;
+    int dt;
+    Lane ln;
+    template <bool TR> __device__ __forceinline__ v4f get(int i, int j) const
+    {
+        constexpr int C = 16 * NB;
+        const int64_t off = TR ? (int64_t)(16 * i + ln.n) * C + 16 * j + 4 * ln.q : (int64_t)(16 * i + 4 * ln.q) * C + 16 * j + ln.n;
+        v4f v;
+        if (dt == OP_F32) {
+            const float* const p = static_cast<const float*>(base) + off;
+            if constexpr (TR) {
+                v = *reinterpret_cast<const v4f*>(p);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v[r] = p[r * C];
+            }
+        } else {
+            const uint16_t* const p = static_cast<const uint16_t*>(base) + off;
+            uint16_t u[4];
+            if constexpr (TR) {
+                const v2u w = *reinterpret_cast<const v2u*>(p);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) u[r] = (uint16_t)(r & 1 ? w[r / 2] >> 16 : w[r / 2] & 0xffff);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) u[r] = p[r * C];
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = dt == OP_F16 ? f16_to_f32(u[r]) : bf16_to_f32(u[r]);
+        }
+        if (i == j) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = (TR ? ln.n > 4 * ln.q + r : 4 * ln.q + r > ln.n) ? v[r] : 0.f;
+        }
+        return v;
+    }
+};
+
 // ---------------------------------------------------------------------------------------------
 // Tile source 2: A built from the keys.  S = K_c K_c^T on the matrix cores with the stored key
 // values as operands (16x16x32 for 16-bit keys, 16x16x4 for fp32 keys), then
@@ -1184,7 +1229,7 @@ template <int OP, int NB, int METHOD, bool REFINE, bool PER_CHANNEL = false> con
 
 template <int IN, int OP, int NB, int METHOD, bool REFINE = false>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_tri_inv(
-    typename TriInvPointers<METHOD>::in A, typename TriInvPointers<METHOD>::out T, int64_t n_mat, int aux, int out_dt)
+    typename TriInvPointers<METHOD>::in A, typename TriInvPointers<METHOD>::out T, int64_t n_mat, int in_dt, int aux, int out_dt)
 {
     constexpr int C = 16 * NB;
     __shared__ __attribute__((aligned(16))) float lds[core_lds_floats<NB, METHOD>()];
@@ -1197,6 +1242,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_pe
         LoadedA16<IN, OP, NB> src;
         src.load(base, ln);
         invert_and_store<OP, NB, METHOD, LoadedA16<IN, OP, NB>, REFINE>(src, Tm, lds, ln, aux);
+    } else if constexpr (NB == 4 ? (METHOD == M_NEUMANN || (REFINE && METHOD != M_NEWTON_SCHULZ)) : (NB == 2 && METHOD == M_MIXED32 && OP == OP_F32 && REFINE)) {
+        // the Neumann product wants every tile in both orientations, the refinement step most of them a second time (GlobalAnyA; the
+        // same with the loads early or typed: C = 64, 32768 matrices, Neumann 460 against 505 us with fp32 operands, 117 against 126
+        // with 16-bit ones and a 16-bit result; refinement after the blocked recursion 217 against 295 and 168 against 190, after the
+        // direct leaves in fp32 207 against 279; b0 = 32 at C = 32 501 against 575.  Newton-Schulz reads A once, at C = 128 the
+        // step is a kernel of its own, and at C = 32 the other methods hold all of A: 1.0 to 1.4 times as fast typed)
+        invert_and_store<OP, NB, METHOD, GlobalAnyA<NB>, REFINE>(GlobalAnyA<NB>{static_cast<const char*>(A) + m * C * C * (in_dt == OP_F32 ? 4 : 2), in_dt, ln}, Tm, lds, ln, aux);
     } else if constexpr (REFINE || (METHOD == M_BLOCK_DIRECT && NB == 8)) {
         // tile by tile: the refinement step wants every tile once more, in both orientations; the direct leaves at C = 128 do
         // little enough before the merges to gain nothing from the early loads (84 us against 85, 4096 matrices)
