@@ -37,9 +37,21 @@ constexpr int OP = TRIINV_INST_OP;
     default: { constexpr int IN = OP_BF16; CALL; }    \
     }
 
+// Unused dynamic LDS of the standalone kernels at C = 32 with an fp32 A and an fp32 result, where they are bound by the memory system:
+// at most twelve wavefronts per compute unit (nineteen with the refinement step) instead of 32.  131072 matrices, 16-bit
+// operands, without / with: blocked 182 / 170 us, direct leaves 180 / 166 (fp32 operands too), Neumann 176 / 170, mixed 177 / 172,
+// b0 = 32 178 / 167; refined, blocked 196 / 190.  With fp32 operands the other methods are bound by their products (0.7 to 0.9 times as
+// fast with it), and so is a 16-bit result's smaller traffic.
+template <int METHOD, bool REFINE> static unsigned tri_pad_bytes(const TriInvArgs& a)
+{
+    if (NB != 2 || a.in_dt != OP_F32 || a.out_dt != OP_F32 || METHOD == M_NEWTON_SCHULZ || METHOD == M_FWD) return 0u;
+    if (REFINE) return OP != OP_F32 && (METHOD == M_BLOCK || METHOD == M_MIXED) ? 5824u : 0u;
+    return OP != OP_F32 || METHOD == M_BLOCK_DIRECT ? 10496u : 0u;
+}
+
 template <int METHOD, bool REFINE = false> static int go_tri(const TriInvArgs& a)
 {
-    TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv<IN, OP, NB, METHOD, REFINE>), dim3((unsigned)a.n_mat), dim3(64), 0,
+    TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv<IN, OP, NB, METHOD, REFINE>), dim3((unsigned)a.n_mat), dim3(64), tri_pad_bytes<METHOD, REFINE>(a),
                                                    a.stream, a.A, a.T, a.n_mat, a.in_dt, a.iters, a.out_dt))
 }
 
@@ -120,10 +132,17 @@ int CAT(launch_tri_inv_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const Tr
 // Unused dynamic LDS that keeps a compute unit (160 KB of LDS) at two workgroups = two wavefronts per SIMD for the
 // 16-bit-operand recursions at C = 64, and at four at C = 32.  Those kernels are bound by the memory system, not by latency:
 // with more wavefronts resident they measured 2-4 % slower (more requests queued at the memory controllers, none served
-// sooner).
-template <int METHOD> constexpr unsigned occupancy_pad_bytes()
+// sooner).  At C = 16, with 512 bytes of keys a row (128 fp32 channels), the blocked, the mixed recursion and the Neumann product are
+// held to four too (0.94 to 0.96 of the time without; with fewer bytes up to 1.3 times).
+constexpr unsigned FOUR_WORKGROUPS = 33792u;  // of LDS in all
+template <int KD, int METHOD, int DKS> constexpr unsigned occupancy_pad_bytes()
 {
-    return ((NB == 4 || NB == 2) && WPB == 4 && OP != OP_F32 && (METHOD == M_BLOCK || METHOD == M_MIXED || METHOD == M_MIXED32 || METHOD == M_BLOCK_DIRECT)) ? 24576u : 0u;
+    constexpr bool recursion = METHOD == M_BLOCK || METHOD == M_MIXED || METHOD == M_MIXED32 || METHOD == M_BLOCK_DIRECT;
+    if (WPB != 4 || OP == OP_F32) return 0u;
+    if ((NB == 4 || NB == 2) && recursion) return 24576u;
+    if (NB == 1 && KD == OP_F32 && DKS == 8 && (METHOD == M_BLOCK || METHOD == M_MIXED || METHOD == M_NEUMANN))
+        return FOUR_WORKGROUPS - 4u * WPB * core_lds_floats<NB, METHOD>();
+    return 0u;
 }
 
 template <int KD, int METHOD, int DKS, bool REFINE = false> static int go_gdn(const GdnArgs& a)
@@ -140,7 +159,7 @@ template <int KD, int METHOD, int DKS, bool REFINE = false> static int go_gdn(co
     else
 #endif
         return launch_kernel(a.dry, k_gdn_tri_inv<KD, OP, NB, METHOD, DKS, REFINE, WPB>, dim3((unsigned)((a.n_mat + WPB - 1) / WPB)),
-                             dim3(64 * WPB), occupancy_pad_bytes<METHOD>(), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k,
+                             dim3(64 * WPB), occupancy_pad_bytes<KD, METHOD, DKS>(), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k,
                              a.iters, a.out_dt, WPB > 1 ? head_spread(a.H) : 0);
 }
 
@@ -201,6 +220,17 @@ template <int KD, int DKS> static int gdn_method(const GdnArgs& a)
     }
 }
 
+// The same for the per-channel gate: four workgroups at C = 32, and at C = 16 from 512 bytes of keys and gate a row on (16-bit
+// operands: 768 bytes 205 -> 197 us, 1024 159 -> 150; 384 bytes 0.87 to 0.94 times as fast with it).  fp32 operands only with the
+// direct leaves at C = 16 and fp32 keys (0.96 -> 1.01); the others are bound by their products.
+template <int METHOD> static unsigned kda_pad_bytes(const GdnArgs& a)
+{
+    if (NB > 2 || WPB != 4 || METHOD == M_FWD || METHOD == M_BUILD_A) return 0u;
+    const bool many = NB == 2 || a.d_k * ((a.k_dt == OP_F32 ? 4 : 2) + 4) >= 512;
+    const bool bound = OP != OP_F32 || (NB == 1 && METHOD == M_BLOCK_DIRECT && a.k_dt == OP_F32);
+    return many && bound ? FOUR_WORKGROUPS - 4u * WPB * core_lds_floats<NB, METHOD>() : 0u;
+}
+
 template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
 {
 #if TRIINV_INST_NB == 8 && !TRIINV_INST_FWD
@@ -210,8 +240,8 @@ template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
                              a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt);
     else
 #endif
-        return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, WPB, REFINE>, dim3((unsigned)((a.n_mat + WPB - 1) / WPB)), dim3(64 * WPB), 0,
-                             a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt,
+        return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, WPB, REFINE>, dim3((unsigned)((a.n_mat + WPB - 1) / WPB)), dim3(64 * WPB),
+                             kda_pad_bytes<METHOD>(a), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt,
                              WPB > 1 ? head_spread(a.H) : 0);
 }
 

@@ -1308,13 +1308,23 @@ __device__ __forceinline__ int64_t fused_matrix_index(int64_t n_chunk, int H, in
     return head_group_swizzle(blockIdx.x, n_chunk, H / WPB) * WPB + w;
 }
 
+// The same for the fused kernels.  At C = 32 the Neumann product, and the direct leaves with fp32 operands, keep the patch that fits
+// C = 128: it holds a compute unit to four workgroups, and the compiler then spends more registers on loads in flight.
+// 32768 matrices of d_k = 128, bf16 keys, a patch of their own size / this: Neumann fp32 32.3 / 29.5 us, direct leaves 18.6 / 17.5;
+// 131072, Neumann 16-bit 62 / 60, fp32 keys 138 / 126.  (Neumann, 16-bit operands, 64 fp32 channels: 0.92 times as fast with it.)
+template <int KD, int OP, int NB, int METHOD, int DKS> constexpr int gdn_lds_floats()
+{
+    constexpr bool large = METHOD == M_NEUMANN ? !(OP != OP_F32 && KD == OP_F32 && DKS == 4) : METHOD == M_BLOCK_DIRECT && OP == OP_F32;
+    return NB == 2 && large ? STORE_LDS_FLOATS : core_lds_floats<NB, METHOD>();
+}
+
 template <int KD, int OP, int NB, int METHOD, int DKS, bool REFINE = false, int WPB = 1>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_gdn_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt, int spread)
 {
     constexpr int C = 16 * NB;
-    constexpr int CORE = core_lds_floats<NB, METHOD>();
+    constexpr int CORE = gdn_lds_floats<KD, OP, NB, METHOD, DKS>();
     constexpr int GATE = gate_lds_floats<NB>();
     constexpr int PER_WAVE = CORE > GATE ? CORE : GATE;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
