@@ -61,6 +61,22 @@ __device__ __forceinline__ void leaf_block_recursive(v4f LN, v4f LT, v4f& XN, v4
     }
 }
 
+constexpr int XPOSE_LD = 20;
+constexpr int XPOSE_FLOATS = 16 * XPOSE_LD;
+
+// out = in^T, tile by tile, through LDS (a patch per tile, so that the turns overlap).  patch: COUNT * XPOSE_FLOATS floats.
+template <int COUNT> __device__ __forceinline__ void turn_tiles(const v4f (&in)[COUNT], v4f (&out)[COUNT], float* patch, Lane ln)
+{
+#pragma unroll
+    for (int d = 0; d < COUNT; ++d)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) patch[d * XPOSE_FLOATS + (4 * ln.q + r) * XPOSE_LD + ln.n] = in[d][r];
+    leaf_lds_sync();
+#pragma unroll
+    for (int d = 0; d < COUNT; ++d) out[d] = *reinterpret_cast<const v4f*>(&patch[d * XPOSE_FLOATS + ln.n * XPOSE_LD + 4 * ln.q]);
+    leaf_lds_sync();
+}
+
 // The same recursion with fp32 operands on COUNT leaves at a time, level by level.  An fp32 tile product is four instructions of 32
 // cycles, so the leaves, not the merges, are most of a matrix's matrix-core time: here a level forms X - D_o (A D_e) in
 // N orientation only and turns it through LDS (a patch per leaf, so that the leaves' turns overlap), and the level b = 2
@@ -69,9 +85,6 @@ __device__ __forceinline__ void leaf_block_recursive(v4f LN, v4f LT, v4f& XN, v4
 // C = 64: 27 -> 20 us (bf16 A, 8192: 49 -> 31 us), 4096 of C = 128 107 -> 85 us, C = 16 (32768) 31 -> 18 us; from keys, 32 of C = 64
 // 10.8 -> 8.1 us, 8192 54 -> 53 us (bound by memory; four leaves side by side instead of two, waiting for all keys: 55 us).
 // patch: COUNT * XPOSE_FLOATS floats.
-constexpr int XPOSE_LD = 20;
-constexpr int XPOSE_FLOATS = 16 * XPOSE_LD;
-
 template <int COUNT>
 __device__ __forceinline__ void leaves_block_recursive_f32(const v4f (&LN)[COUNT], const v4f (&LT)[COUNT], v4f (&XN)[COUNT], v4f (&XT)[COUNT],
                                                            float* patch, Lane ln)
@@ -110,14 +123,7 @@ __device__ __forceinline__ void leaves_block_recursive_f32(const v4f (&LN)[COUNT
             for (int d = 0; d < COUNT; ++d)
                 if (lb > 1 || r >= 2)  // X - D_o A D_e
                     XN[d] = __builtin_amdgcn_mfma_f32_16x16x4f32(ko[r] ? XT[d][r] : 0.f, P[d][r], XN[d], 0, 0, 0);
-#pragma unroll
-        for (int d = 0; d < COUNT; ++d)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) patch[d * XPOSE_FLOATS + (4 * ln.q + r) * XPOSE_LD + ln.n] = XN[d][r];
-        leaf_lds_sync();
-#pragma unroll
-        for (int d = 0; d < COUNT; ++d) XT[d] = *reinterpret_cast<const v4f*>(&patch[d * XPOSE_FLOATS + ln.n * XPOSE_LD + 4 * ln.q]);
-        leaf_lds_sync();
+        turn_tiles<COUNT>(XN, XT, patch, ln);
     }
 }
 
@@ -164,18 +170,6 @@ __device__ __forceinline__ void leaf_neumann(v4f LN, v4f LT, v4f& XN, v4f& XT, L
 // of C = 64 100 -> 84 us (bf16 A, 8192: 51 -> 34 us), 4096 of C = 128 109 -> 88 us, C = 16 (32768) 35 -> 20 us; from keys, 8192 of
 // C = 64 60 -> 55 us, a call of 32 10.8 -> 8.4 us.
 // patch: COUNT * XPOSE_FLOATS floats.
-template <int COUNT> __device__ __forceinline__ void turn_tiles(const v4f (&in)[COUNT], v4f (&out)[COUNT], float* patch, Lane ln)
-{
-#pragma unroll
-    for (int d = 0; d < COUNT; ++d)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) patch[d * XPOSE_FLOATS + (4 * ln.q + r) * XPOSE_LD + ln.n] = in[d][r];
-    leaf_lds_sync();
-#pragma unroll
-    for (int d = 0; d < COUNT; ++d) out[d] = *reinterpret_cast<const v4f*>(&patch[d * XPOSE_FLOATS + ln.n * XPOSE_LD + 4 * ln.q]);
-    leaf_lds_sync();
-}
-
 template <int COUNT>
 __device__ __forceinline__ void leaves_neumann_f32(const v4f (&LN)[COUNT], const v4f (&LT)[COUNT], v4f (&XN)[COUNT], v4f (&XT)[COUNT],
                                                    float* patch, Lane ln, int r)
@@ -586,19 +580,20 @@ __device__ __forceinline__ void neumann(const ASrc& A, v4f (&Xt)[NB * (NB + 1) /
 // X lives in N orientation (fp32).  Column j of tiles of Y = X + A X needs column j of X only, and column j of X Y the
 // columns j and up of X as a left factor, so the iteration runs over the columns from the last to the first and turns each
 // into its left form (T orientation) just before changing it.  That form comes from the packed tiles by one product
-// with the identity each, exact for 16-bit values: two products per iteration instead of the three that
+// with the identity each, exact for finite 16-bit values: two products per iteration instead of the three that
 // updating X in both orientations takes, and half of the state.
 // The first iteration from X0 = I / C is a scaling, X1 = 2/C I - (I + A) / C^2, and is written down directly.
 // Result: Xn, every tile in N orientation.
 //
-// What bounds it is the matrix cores (16 cycles a 16-bit instruction, whether it contracts 16 or 32 deep) and the vector
-// instructions between them, which at two wavefronts per SIMD hardly overlap:
-//   16-bit operands: one 32-deep instruction contracts two adjacent tiles: 28 instructions + 10 transposes per iteration at
-//     C = 64 instead of 60.  8 192 fused matrices of C = 64, bf16: 73 -> 58 us; standalone 60 -> 48 us.
-//   fp32 operands: three 32-deep bf16 instructions per tile product on values split into three bf16 parts (Split3)
-//     instead of four 16x16x4 fp32 instructions of 32 cycles: 150 instructions of 16 cycles per iteration instead of 240 of
-//     32.  The same matrices: 346 -> 188 us (matrix cores 0.90 -> 0.49 busy), standalone 352 -> 185 us; error against 64
-//     bits 1.01e-7 -> 0.97e-7 and 4.1e-8 -> 3.4e-8 (below the diagonal).
+// What bounds it is the vector instructions and the matrix cores (16 cycles a 16-bit instruction, whether it contracts 16 or
+// 32 deep) in turn, which at two wavefronts per SIMD hardly overlap:
+//   16-bit operands (vector unit 0.53-0.62 busy, matrix cores 0.45-0.54): a 32-deep instruction contracts two adjacent tiles, a
+//     16-deep one a tile without a partner in its sum: 28 instructions + 10 transposes per iteration at C = 64 instead of 60.
+//     8 192 fused matrices of C = 64, bf16: 73 -> 58 us; standalone 60 -> 48 us.
+//   fp32 operands (vector 0.72, matrix 0.50): three 32-deep bf16 instructions per tile product on values split into three bf16
+//     parts (Split3) instead of four 16x16x4 fp32 instructions of 32 cycles: 150 instructions of 16 cycles per iteration instead of
+//     240 of 32.  The same matrices: 344 -> 194-204 us, standalone 348 -> 177 us, with the refinement step (one wavefront per SIMD)
+//     405 -> 258 us and 365 -> 247 us; error against 64 bits 1.01e-7 -> 0.97e-7 and 4.1e-8 -> 3.4e-8 (below the diagonal).
 // ---------------------------------------------------------------------------------------------
 
 // 16-bit operands: tile rows / columns 2 p and 2 p + 1 side by side.

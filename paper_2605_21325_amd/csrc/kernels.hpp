@@ -345,10 +345,11 @@ template <int NB, int METHOD> struct LoadedA {  // fp32 elements
 
 // 16-bit elements.  A lane loads 16 bytes of a row, two lane groups' share of a tile: two swaps between the lane groups per
 // register pair (v_permlane16_swap, v_permlane32_swap) make T-orientation tiles of two neighbours out of them, which are
-// matrix-core operands as they stand.  The N orientation is a product with the identity, exact for 16-bit values.  Loaded
-// tile by tile (8 bytes a lane, 2 bytes in N orientation, 32-byte row pieces, each level of the recursion
-// waiting for its own) the same kernels took: bf16 A, blocked recursion, 8192 matrices of C = 128, bf16 result 137 against
-// 87 us, fp32 result 178 against 137; 16384 of C = 64, bf16 result 56 against 47, fp32 77 against 71; C = 16 18.2 against 11.3.
+// matrix-core operands as they stand.  The N orientation is a product with the identity, exact for finite values (an infinity or
+// NaN makes its row of the tile NaN, as the products it goes into would).  Loaded tile by tile (8 bytes a lane, 2 bytes in N
+// orientation, 32-byte row pieces, each level of the recursion waiting for its own) the same kernels took: bf16 A, blocked
+// recursion, 8192 matrices of C = 128, bf16 result 137 against 87 us, fp32 result 178 against 137; 16384 of C = 64, bf16 result
+// 56 against 47, fp32 77 against 71; C = 16 18.2 against 11.3.
 template <int IN, int OP, int NB> struct LoadedA16 {
     static constexpr int C = 16 * NB;
     static constexpr bool kFromMemory = true;
@@ -908,10 +909,11 @@ __device__ __forceinline__ void store_result(Out Tm, const v4f (&Tt)[NB * (NB + 
 // 1.19e-7 on the former; that inverse also spreads an infinity or NaN of A over rows above its own, where here only rows that
 // depend on it see it.
 //
-// Bound by memory at C <= 64, at C = 128 by the instructions of its two wavefronts per SIMD (4300 vector, 480 matrix).
-// 2048 fused matrices of C = 128: 49 us (row by row throughout, 10144 dependent multiply-adds and 2536 LDS broadcasts a lane, one
-// wavefront per SIMD: 140; with the block's inverse 42), a call of 32: 21 (63, 15); standalone fp32, 4096 matrices 95 us (135, 85);
-// C = 64 fused, 16384: 99 us (123, 101), standalone 45 us (54, 44; 8192).
+// Bound by memory at C <= 64, at C = 128 by the serial rows of its two wavefronts per SIMD (4519 vector and 480 matrix instructions a
+// matrix; vector unit 0.35, matrix cores 0.25 busy).  2048 fused matrices of C = 128: 42.7 us (row by row throughout, 10144
+// dependent multiply-adds and 2536 LDS broadcasts a lane, one wavefront per SIMD: 140; with the block's inverse 41.7), on the
+// workload of correlated keys, 8192, 192 us (167 with the inverse); a call of 32: 21 us (63, 15); standalone fp32, 8192 matrices
+// 179 us (262); C = 64 fused, 16384: 93-100 us (125, 101), standalone 45 us (54, 44; 8192).
 // ---------------------------------------------------------------------------------------------
 
 // Four registers against the four lane groups: x[p] of lane group q <- x[q] of lane group p.
@@ -1162,7 +1164,7 @@ template <int NB, int METHOD> constexpr int core_lds_floats()
     return store_lds_floats<NB>() > small ? store_lds_floats<NB>() : small;
 }
 
-// REFINE: one iterative-refinement step after a matrix-product method (C = 64 only).
+// REFINE: one iterative-refinement step after a matrix-product method (C <= 64; at C = 128 a kernel of its own).
 template <int OP, int NB, int METHOD, class ASrc, bool REFINE = false>
 __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float* lds, Lane ln, int aux = 0)
 {
