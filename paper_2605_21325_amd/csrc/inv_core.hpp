@@ -592,7 +592,7 @@ __device__ __forceinline__ void neumann(const ASrc& A, v4f (&Xt)[NB * (NB + 1) /
 //     8 192 fused matrices of C = 64, bf16: 73 -> 58 us; standalone 60 -> 48 us.
 //   fp32 operands (vector 0.72, matrix 0.50): three 32-deep bf16 instructions per tile product on values split into three bf16
 //     parts (Split3) instead of four 16x16x4 fp32 instructions of 32 cycles: 150 instructions of 16 cycles per iteration instead of
-//     240 of 32.  The same matrices: 344 -> 194-204 us, standalone 348 -> 177 us, with the refinement step (one wavefront per SIMD)
+//     240 of 32.  The same matrices: 344 -> 192-213 us from card to card, standalone 348 -> 177 us, with the refinement step (one wavefront per SIMD)
 //     405 -> 258 us and 365 -> 247 us; error against 64 bits 1.01e-7 -> 0.97e-7 and 4.1e-8 -> 3.4e-8 (below the diagonal).
 // ---------------------------------------------------------------------------------------------
 
