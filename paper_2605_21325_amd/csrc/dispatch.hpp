@@ -56,6 +56,24 @@ struct SolveArgs {
 // The chunk stride of the few-heads workgroup map of the fused kernels (0 = the many-heads map): see fused_matrix_index.
 inline int head_spread(int H) { return H >= 8 ? 0 : (H >= 4 ? 1 : 4 / H); }
 
+// Grid of the fused kernels that put `waves` wavefronts, a matrix each, into a workgroup.  Up to two matrices per compute unit (256 of
+// them) a workgroup holds one: four wavefronts would load their keys and store their results through one compute unit while
+// others have nothing to do.  Kernel time at C = 64, four / one to a workgroup: 256 matrices 6.4 / 5.4 us (bf16), 16.1 / 11.6
+// (per-channel gate), 13.9 / 11.7 (fp32 keys and operands), applied to two right-hand sides 11.2 / 9.3; 512 6.5 / 6.0 and 17.1 / 13.3; 1024
+// 7.6 / 7.5 and 18.2 / 18.8; 1536 9.3 / 12.2.
+constexpr int ONE_WAVE_PER_GROUP = -1;  // in place of the spread
+constexpr int64_t FEW_MATRICES = 512;
+struct FusedGrid {
+    unsigned groups, threads;
+    int spread;
+    bool few() const { return spread == ONE_WAVE_PER_GROUP; }
+};
+inline FusedGrid fused_grid(int64_t n_mat, int H, int waves)
+{
+    if (waves > 1 && n_mat <= FEW_MATRICES) return {(unsigned)n_mat, 64u, ONE_WAVE_PER_GROUP};
+    return {(unsigned)((n_mat + waves - 1) / waves), 64u * waves, waves > 1 ? head_spread(H) : 0};
+}
+
 // Launcher return codes.
 enum : int { LAUNCHED = 0, NOT_BUILT = 1, LAUNCH_FAILED = 2 };
 

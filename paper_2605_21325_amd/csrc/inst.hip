@@ -158,9 +158,12 @@ template <int KD, int METHOD, int DKS, bool REFINE = false> static int go_gdn(co
                                    a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
     else
 #endif
-        return launch_kernel(a.dry, k_gdn_tri_inv<KD, OP, NB, METHOD, DKS, REFINE, WPB>, dim3((unsigned)((a.n_mat + WPB - 1) / WPB)),
-                             dim3(64 * WPB), occupancy_pad_bytes<KD, METHOD, DKS>(), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k,
-                             a.iters, a.out_dt, WPB > 1 ? head_spread(a.H) : 0);
+    {
+        const FusedGrid f = fused_grid(a.n_mat, a.H, WPB);
+        return launch_kernel(a.dry, k_gdn_tri_inv<KD, OP, NB, METHOD, DKS, REFINE, WPB>, dim3(f.groups), dim3(f.threads),
+                             f.few() ? 0u : occupancy_pad_bytes<KD, METHOD, DKS>(), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk,
+                             a.map, a.H, a.d_k, a.iters, a.out_dt, f.spread);
+    }
 }
 
 template <int KD, int DKS> static int gdn_method(const GdnArgs& a)
@@ -240,9 +243,12 @@ template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
                              a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt);
     else
 #endif
-        return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, WPB, REFINE>, dim3((unsigned)((a.n_mat + WPB - 1) / WPB)), dim3(64 * WPB),
-                             kda_pad_bytes<METHOD>(a), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt,
-                             WPB > 1 ? head_spread(a.H) : 0);
+    {
+        const FusedGrid f = fused_grid(a.n_mat, a.H, WPB);
+        return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, WPB, REFINE>, dim3(f.groups), dim3(f.threads),
+                             f.few() ? 0u : kda_pad_bytes<METHOD>(a), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt,
+                             a.iters, a.out_dt, f.spread);
+    }
 }
 
 static int kda_method(const GdnArgs& a)

@@ -12,6 +12,7 @@
 // (inv_core.hpp).  csrc/chunk_map.hpp says where a chunk's tokens are.
 #pragma once
 #include "chunk_map.hpp"
+#include "dispatch.hpp"
 #include "inv_core.hpp"
 
 namespace triinv {
@@ -1283,6 +1284,7 @@ __device__ __forceinline__ int64_t head_group_swizzle(int64_t bid, int64_t n_gro
 // slower, with 10 % higher read latency and 4.5x the DRAM credit stalls.  Instead a workgroup takes ONE head of WPB chunks
 // S chunks apart (S = max(1, 4 / H), so its four key regions are at least 64 KB apart), and the S * H workgroups that share
 // those 4 S chunks run back to back on one XCD.  Chunks beyond the last full group of 4 S keep the plain order.
+// spread = ONE_WAVE_PER_GROUP (few matrices, see fused_grid): workgroups of one wavefront, in plain order.
 // The waves never synchronise with each other.  Returns chunk id * H + head, or -1 for a wave without a matrix.
 template <int WPB>
 __device__ __forceinline__ int64_t fused_matrix_index(int64_t n_chunk, int H, int64_t n_mat, int spread)
@@ -1303,8 +1305,8 @@ __device__ __forceinline__ int64_t fused_matrix_index(int64_t n_chunk, int H, in
         const int64_t m = (full + (bid - full)) * WPB + w;             // the tail: WPB consecutive matrices per workgroup
         return m < n_mat ? m : -1;
     }
-    if (H % WPB != 0) {
-        const int64_t m = (int64_t)blockIdx.x * WPB + w;
+    if (H % WPB != 0 || (WPB > 1 && spread == ONE_WAVE_PER_GROUP)) {
+        const int64_t m = (int64_t)blockIdx.x * (WPB > 1 && spread == ONE_WAVE_PER_GROUP ? 1 : WPB) + w;
         return m < n_mat ? m : -1;
     }
     return head_group_swizzle(blockIdx.x, n_chunk, H / WPB) * WPB + w;

@@ -74,14 +74,15 @@ template <int KD, int METHOD, int DKS> static int go_gdn(const SolveArgs& a)
     if constexpr (!SINGLE_ON_TWO_WAVES)
 #endif
     {
-    const dim3 grid((unsigned)((f.n_mat + WPB - 1) / WPB)), block(64 * WPB);
+    const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
+    const dim3 grid(shape.groups), block(shape.threads);
     if (a.n_rhs == 1) {
         return launch_kernel(f.dry, k_gdn_tri_solve<KD, OP, NB, METHOD, DKS, WPB, XPOS, 1>, grid, block, 0, f.stream, f.K, f.beta, f.g,
-                           rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters, WPB > 1 ? head_spread(f.H) : 0);
+                           rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters, shape.spread);
     }
     if constexpr (HAS_PAIR) {
         return launch_kernel(f.dry, k_gdn_tri_solve<KD, OP, NB, METHOD, DKS, WPB, XPOS, 2>, grid, block, 0, f.stream, f.K, f.beta, f.g,
-                           rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters, WPB > 1 ? head_spread(f.H) : 0);
+                           rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters, shape.spread);
     }
     return 1;
     }
@@ -107,14 +108,15 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
     return launch_kernel(f.dry, k_kda_tri_solve_c128<OP, METHOD, 2>, dim3((unsigned)f.n_mat), dim3(128), 0, f.stream, f.K, f.beta, f.g,
                          rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
 #else
-    const dim3 grid((unsigned)((f.n_mat + WPB - 1) / WPB)), block(64 * WPB);
+    const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
+    const dim3 grid(shape.groups), block(shape.threads);
     if (a.n_rhs == 1) {
         return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 1>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
-                           f.map, f.H, f.d_k, f.k_dt, f.iters, WPB > 1 ? head_spread(f.H) : 0);
+                           f.map, f.H, f.d_k, f.k_dt, f.iters, shape.spread);
     }
     if constexpr (HAS_PAIR) {
         return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 2>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
-                           f.map, f.H, f.d_k, f.k_dt, f.iters, WPB > 1 ? head_spread(f.H) : 0);
+                           f.map, f.H, f.d_k, f.k_dt, f.iters, shape.spread);
     }
     return 1;
 #endif
