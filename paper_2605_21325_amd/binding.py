@@ -48,6 +48,13 @@ EXPORTS = ("tri_inv", "tri_inv_ex", "gdn_chunk_tri_inv", "gdn_chunk_tri_inv_ex",
 
 _lib: Optional[ctypes.CDLL] = None
 
+# Native argument handling of plain calls (csrc/fastcall.cpp): it answers None to whatever it does not take, and the call goes through
+# the Python code below, which reports what is wrong with it.  In use for the library it was connected to.
+# Host time of a call, Python / native: tri_inv_ex 5.5 / 4.1 us, gdn_chunk_tri_inv_ex 7.1 / 4.6, gdn_chunk_tri_solve 7.2 / 4.4,
+# gdn_chunk_tri_solve_multi 12 / 5.6.
+_fast = None
+_fast_lib = object()
+
 
 class TriInvError(RuntimeError):
     def __init__(self, status: int, where: str):
@@ -90,7 +97,22 @@ def lib() -> ctypes.CDLL:
         L.triinv_version.argtypes = []
         L.triinv_version.restype = i32
         _lib = L
+        _connect(L)
     return _lib
+
+
+def _connect(L: ctypes.CDLL) -> None:
+    global _fast, _fast_lib
+    if _raw_stream is None or _device_index is None:
+        return
+    try:
+        from . import _fastcall
+    except ImportError:  # not built, or for another torch
+        return
+    _fastcall.connect(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        L.tri_inv_ex, L.gdn_chunk_tri_inv_ex, L.gdn_chunk_tri_inv_varlen, L.gdn_chunk_tri_solve_multi, L.gdn_chunk_tri_solve_varlen,
+        L.triinv_detail_chunk_offsets)))
+    _fast, _fast_lib = _fastcall, L
 
 
 def status_string(status: int) -> str:
@@ -135,6 +157,10 @@ def _dev(t: torch.Tensor, name: str) -> int:
 def tri_inv(A: torch.Tensor, T: Optional[torch.Tensor] = None, method: int = BLOCK_RECURSIVE) -> torch.Tensor:
     """T = (I + strict_lower(A))^{-1};  A [n_mat, C, C] fp32/fp16/bf16 on the GPU.  Short form of
     the C-ABI: operands in A's own type, default stream."""
+    if _lib is _fast_lib and A.is_cuda:
+        r = _fast.tri_inv(_device_index(), 0, A, T, method, -1, 0, None)
+        if r is not None:
+            return r
     n_mat, C, _ = A.shape
     if T is None:
         T = torch.empty((n_mat, C, C), dtype=torch.float32, device=A.device)
@@ -161,6 +187,11 @@ def _out(T: Optional[torch.Tensor], out_dtype: Optional[torch.dtype], shape, dev
 def tri_inv_ex(A: torch.Tensor, T: Optional[torch.Tensor] = None, method: int = BLOCK_RECURSIVE,
                op_dtype: Optional[int] = None, stream=None, flags: int = 0,
                out_dtype: Optional[torch.dtype] = None) -> torch.Tensor:
+    if _lib is _fast_lib and stream is None and A.is_cuda:
+        dev = _device_index()
+        r = _fast.tri_inv(dev, _raw_stream(dev), A, T, method, -1 if op_dtype is None else op_dtype, flags, out_dtype)
+        if r is not None:
+            return r
     n_mat, C, _ = A.shape
     T, flags = _out(T, out_dtype, (n_mat, C, C), A.device, flags)
     in_dt = dtype_code(A.dtype)
@@ -180,6 +211,10 @@ def gdn_chunk_tri_inv(K: torch.Tensor, beta: torch.Tensor, g: torch.Tensor, C: i
                       T: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Fused build + invert, short form: bf16 keys [B, Tlen, H, d_k], scalar gate, blocked
     recursion with bf16 operands, default stream."""
+    if _lib is _fast_lib and K.is_cuda and K.dtype == torch.bfloat16:
+        r = _fast.gdn_inv(_device_index(), 0, K, beta, g, C, T, GATE_SCALAR, BLOCK_RECURSIVE, BF16, 0, None)
+        if r is not None:
+            return r
     B, Tlen, H, d_k = K.shape
     if K.dtype != torch.bfloat16:
         raise TypeError("the short form takes bf16 keys; use gdn_chunk_tri_inv_ex")
@@ -195,6 +230,11 @@ def gdn_chunk_tri_inv_ex(K: torch.Tensor, beta: torch.Tensor, g: Optional[torch.
                          T: Optional[torch.Tensor] = None, gate_kind: int = GATE_SCALAR,
                          method: int = BLOCK_RECURSIVE, op_dtype: int = BF16, stream=None, flags: int = 0,
                          out_dtype: Optional[torch.dtype] = None) -> torch.Tensor:
+    if _lib is _fast_lib and stream is None and K.is_cuda:
+        dev = _device_index()
+        r = _fast.gdn_inv(dev, _raw_stream(dev), K, beta, g, C, T, gate_kind, method, op_dtype, flags, out_dtype)
+        if r is not None:
+            return r
     B, Tlen, H, d_k = K.shape
     T, flags = _out(T, out_dtype, (_n_mat(K, C), C, C), K.device, flags)
     gp = None if g is None else _dev(g, "g")
@@ -265,6 +305,11 @@ def gdn_chunk_tri_inv_varlen(K: torch.Tensor, beta: torch.Tensor, g: Optional[to
                              out_dtype: Optional[torch.dtype] = None) -> torch.Tensor:
     """Fused build + invert on packed variable-length sequences: K [total_tokens, H, d_k], beta
     [total_tokens, H], g [total_tokens, H] (or [total_tokens, H, d_k]); seqlens = host sequence of lengths."""
+    if _lib is _fast_lib and stream is None and K.is_cuda:
+        dev = _device_index()
+        r = _fast.gdn_inv_varlen(dev, _raw_stream(dev), K, beta, g, seqlens, C, T, gate_kind, method, op_dtype, flags, out_dtype)
+        if r is not None:
+            return r
     total, H, d_k = K.shape
     cu_s, cu_c, n_seq, n_chunk, keep = _chunk_offsets(K, seqlens, C, stream)
     T, flags = _out(T, out_dtype, (n_chunk * H, C, C), K.device, flags)
@@ -297,6 +342,11 @@ def gdn_chunk_tri_solve(K: torch.Tensor, beta: torch.Tensor, g: Optional[torch.T
                         gate_kind: int = GATE_SCALAR, method: int = BLOCK_RECURSIVE, stream=None, flags: int = 0) -> torch.Tensor:
     """W = (I + A)^{-1} diag(row_scale) X chunk by chunk: K [B, Tlen, H, d_k], X and W [B, Tlen, H, d_x]; the element type
     of X is the operand type of every product."""
+    if _lib is _fast_lib and stream is None and K.is_cuda:
+        dev = _device_index()
+        r = _fast.gdn_solve(dev, _raw_stream(dev), K, beta, g, (X,), C, (row_scale,), None if W is None else (W,), gate_kind, method, flags)
+        if r is not None:
+            return r[0]
     B, Tlen, H, d_k = K.shape
     d_x = X.shape[-1]
     if X.shape[:3] != K.shape[:3]:
@@ -319,6 +369,11 @@ def gdn_chunk_tri_solve_varlen(K: torch.Tensor, beta: torch.Tensor, g: Optional[
                                row_scale: Optional[torch.Tensor] = None, W: Optional[torch.Tensor] = None,
                                gate_kind: int = GATE_SCALAR, method: int = BLOCK_RECURSIVE, stream=None, flags: int = 0) -> torch.Tensor:
     """gdn_chunk_tri_solve on packed sequences: K [total, H, d_k], X and W [total, H, d_x]; seqlens = host sequence of lengths."""
+    if _lib is _fast_lib and stream is None and K.is_cuda:
+        dev = _device_index()
+        r = _fast.gdn_solve_varlen(dev, _raw_stream(dev), K, beta, g, X, seqlens, C, row_scale, W, gate_kind, method, flags)
+        if r is not None:
+            return r
     total, H, d_k = K.shape
     d_x = X.shape[-1]
     if tuple(X.shape[:2]) != (total, H):
@@ -344,6 +399,11 @@ def gdn_chunk_tri_solve_multi(K: torch.Tensor, beta: torch.Tensor, g: Optional[t
                               gate_kind: int = GATE_SCALAR, method: int = BLOCK_RECURSIVE, stream=None, flags: int = 0):
     """W_k = (I + A)^{-1} diag(row_scales[k]) Xs[k] for one or two right-hand sides sharing one inversion per chunk.
     Xs: sequence of [B, Tlen, H, d_x_k] tensors of one element type; row_scales: sequence of [B, Tlen, H] tensors or None."""
+    if _lib is _fast_lib and stream is None and K.is_cuda:
+        dev = _device_index()
+        r = _fast.gdn_solve(dev, _raw_stream(dev), K, beta, g, Xs, C, row_scales, Ws, gate_kind, method, flags)
+        if r is not None:
+            return r
     B, Tlen, H, d_k = K.shape
     n = len(Xs)
     if row_scales is None:

@@ -2,7 +2,8 @@
 
 One translation unit per (C, operand type) pair plus the C-ABI file, compiled in parallel and
 linked into paper_2605_21325_amd/libtriinv.so.  Packed-fp32 code generation is switched off
-for every device compile.
+for every device compile.  Beside it the host compiler builds the binding's native argument
+handling, paper_2605_21325_amd/_fastcall.so.
 """
 from __future__ import annotations
 
@@ -11,12 +12,14 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libtriinv.so")
+FASTCALL = os.path.join(HERE, "_fastcall.so")
 RESOURCES = os.path.join(HERE, "kernel_resources.json")  # registers / scratch / LDS of every kernel, from the compiler
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -69,13 +72,28 @@ def _compile(unit):
     return out, _parse_resources(r.stderr)
 
 
+def build_fastcall() -> str:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{sysconfig.get_paths()['include']}",
+           f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL,
+           f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"{cmd[0]} failed for fastcall.cpp:\n{r.stderr[-4000:]}")
+    return FASTCALL
+
+
 def build(force: bool = False, jobs: int = 0) -> str:
-    if not force and os.path.exists(LIB) and os.path.getmtime(LIB) >= _sources_mtime():
+    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _sources_mtime() for f in (LIB, FASTCALL)):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     jobs = jobs or min(len(UNITS), os.cpu_count() or 4, 16)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        fastcall = ex.submit(build_fastcall)
         results = list(ex.map(_compile, UNITS))
+        fastcall.result()
     objs = [o for o, _ in results]
     resources = {}
     for _, res in results:

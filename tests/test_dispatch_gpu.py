@@ -44,3 +44,120 @@ def test_few_matrices_give_the_bits_of_a_larger_call(C, H, gate):
         assert torch.equal(w, W[:, :n * C])
         w1, w2 = tri.gdn_chunk_tri_solve_multi(k, b, gg, [x, x], C, row_scales=[b, None], gate_kind=gate)
         assert torch.equal(w1, w)
+
+
+# Plain calls are marshalled natively, all others in Python: same results, same exceptions, and the native route takes no call that the
+# other refuses.
+def _calls():
+    K, beta, g = make_inputs(130, 4, 64, tri.GATE_SCALAR, B=2)
+    X = torch.randn(2, 130, 4, 72, device=DEV).bfloat16()
+    A = torch.tril(torch.randn(5, 64, 64, device=DEV), -1) * 0.05
+    P, pb, pg, px = K[0].contiguous(), beta[0].contiguous(), g[0].contiguous(), X[0].contiguous()
+    lens = [64, 1, 65]
+    new = lambda *s, dt=torch.float32: torch.zeros(*s, device=DEV, dtype=dt)
+    bf = torch.bfloat16
+    calls = {
+        "tri_inv": lambda: tri.tri_inv(A),
+        "tri_inv into T": lambda: tri.tri_inv(A, new(5, 64, 64), method=tri.FWD_SUBST),
+        "tri_inv_ex": lambda: tri.tri_inv_ex(A, op_dtype=tri.F16, out_dtype=torch.float16),
+        "tri_inv_ex refined": lambda: tri.tri_inv_ex(A, flags=tri.FLAG_REFINE1),
+        "no matrices": lambda: tri.tri_inv_ex(A[:0]),
+        "short form": lambda: tri.gdn_chunk_tri_inv(K, beta, g, 64),
+        "inv": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, g, 32, op_dtype=tri.F32),
+        "inv into T": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, None, 128, T=new(16, 128, 128, dt=bf), gate_kind=tri.GATE_NONE, out_dtype=bf),
+        "inv on a stream": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, g, 64, stream=torch.cuda.current_stream()),
+        "solve": lambda: tri.gdn_chunk_tri_solve(K, beta, g, X, 64, row_scale=beta),
+        "solve into W": lambda: tri.gdn_chunk_tri_solve(K, beta, g, X, 64, W=torch.empty_like(X), method=tri.MIXED),
+        "two sides": lambda: tri.gdn_chunk_tri_solve_multi(K, beta, g, [X, X * 2], 64, row_scales=[None, beta]),
+        "two sides into W": lambda: tri.gdn_chunk_tri_solve_multi(K, beta, g, (X, X * 2), 64, Ws=(torch.empty_like(X), torch.empty_like(X))),
+        "packed": lambda: tri.gdn_chunk_tri_inv_varlen(P, pb, pg, lens, 64),
+        "packed, lengths in a tensor": lambda: tri.gdn_chunk_tri_inv_varlen(P, pb, pg, torch.tensor(lens), 64),
+        "packed solve": lambda: tri.gdn_chunk_tri_solve_varlen(P, pb, pg, px, lens, 64, row_scale=pb),
+        "packed solve into W": lambda: tri.gdn_chunk_tri_solve_varlen(P, pb, pg, px, tuple(lens), 64, W=torch.empty_like(px)),
+        # refused
+        "chunk size": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, g, 48),
+        "no gate": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, None, 64),
+        "method": lambda: tri.tri_inv_ex(A, method=99),
+        "flags": lambda: tri.tri_inv_ex(A, flags=1 << 20),
+        "element type": lambda: tri.tri_inv_ex(A.double()),
+        "keys of the short form": lambda: tri.gdn_chunk_tri_inv(K.float(), beta, g, 64),
+        "result type": lambda: tri.tri_inv_ex(A, T=new(5, 64, 64), out_dtype=bf),
+        "result type unknown": lambda: tri.tri_inv_ex(A, out_dtype=torch.int32),
+        "not contiguous": lambda: tri.gdn_chunk_tri_inv_ex(K.transpose(0, 1), beta, g, 64),
+        "on the host": lambda: tri.gdn_chunk_tri_inv_ex(K, beta.cpu(), g, 64),
+        "dimensions": lambda: tri.gdn_chunk_tri_inv_ex(K[0], beta, g, 64),
+        "overlap": lambda: tri.tri_inv_ex(A, T=A),
+        "X of another shape": lambda: tri.gdn_chunk_tri_solve(K, beta, g, X[:, 1:].contiguous(), 64),
+        "d_x": lambda: tri.gdn_chunk_tri_solve(K, beta, g, X[..., :4].contiguous(), 64),
+        "three sides": lambda: tri.gdn_chunk_tri_solve_multi(K, beta, g, [X] * 3, 64),
+        "no sides": lambda: tri.gdn_chunk_tri_solve_multi(K, beta, g, [], 64),
+        "sides of two types": lambda: tri.gdn_chunk_tri_solve_multi(K, beta, g, [X, X.float()], 64),
+        "scales missing": lambda: tri.gdn_chunk_tri_solve_multi(K, beta, g, [X, X], 64, row_scales=[beta]),
+        "lengths too short": lambda: tri.gdn_chunk_tri_inv_varlen(P, pb, pg, [64, 1], 64),
+        "negative length": lambda: tri.gdn_chunk_tri_inv_varlen(P, pb, pg, [64, -1, 67], 64),
+        "length beyond 64 bits": lambda: tri.gdn_chunk_tri_solve_varlen(P, pb, pg, px, [1 << 70, 130], 64),
+    }
+    return calls
+
+
+def test_native_and_python_marshalling_agree(monkeypatch):
+    calls = _calls()
+    tri.lib()
+    assert tri.binding._fast is not None, "the native argument handling is not built"
+
+    def outcome(f):
+        try:
+            r = f()
+        except Exception as e:  # noqa: BLE001 (whatever it is, the other route has to raise it too)
+            return type(e), str(e)
+        torch.cuda.synchronize()
+        return r
+
+    for name, call in calls.items():
+        taken = []
+        with monkeypatch.context() as m:
+            m.setattr(tri.binding, "_fast", _Watch(tri.binding._fast, taken))
+            native = outcome(call)
+        with monkeypatch.context() as m:
+            m.setattr(tri.binding, "_fast_lib", object())
+            python = outcome(call)
+        if isinstance(python, tuple) and isinstance(python[0], type):
+            assert native == python and not any(taken), name
+            continue
+        assert type(native) is type(python), name
+        for a, b in zip(*(x if isinstance(x, (list, tuple)) else [x] for x in (native, python))):
+            assert a.dtype == b.dtype and torch.equal(a, b), name
+            assert hasattr(a, "_triinv_keepalive") == hasattr(b, "_triinv_keepalive"), name
+        assert any(taken) == (name not in ("inv on a stream", "packed, lengths in a tensor")), name
+
+
+class _Watch:
+    """The native module; `taken` collects whether it answered each call."""
+    def __init__(self, module, taken):
+        self.module, self.taken = module, taken
+
+    def __getattr__(self, name):
+        def call(*a):
+            r = getattr(self.module, name)(*a)
+            self.taken.append(r is not None)
+            return r
+        return call
+
+
+def test_native_marshalling_runs_on_the_current_stream():
+    K, beta, g = make_inputs(4096, 16, 128, tri.GATE_SCALAR)
+    X = torch.randn(1, 4096, 16, 128, device=DEV).bfloat16()
+    want = tri.gdn_chunk_tri_inv_ex(K, beta, g, 64)
+    want_w = tri.gdn_chunk_tri_solve(K, beta, g, X, 64)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    K2, beta2, g2, X2 = (torch.zeros_like(x) for x in (K, beta, g, X))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        for dst, src in ((K2, K), (beta2, beta), (g2, g), (X2, X)):
+            torch.cuda._sleep(200000)
+            dst.copy_(src)
+        T = tri.gdn_chunk_tri_inv_ex(K2, beta2, g2, 64)
+        W = tri.gdn_chunk_tri_solve(K2, beta2, g2, X2, 64)
+    s.synchronize()
+    assert torch.equal(T, want) and torch.equal(W, want_w)
