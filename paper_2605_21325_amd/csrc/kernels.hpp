@@ -503,14 +503,144 @@ template <bool K16> __device__ __forceinline__ void widen_key8(const RawKey8<K16
 // its second half is still cached when needed (requested one k-step apart, lines were found
 // evicted in between and fetched from HBM twice).
 // Kc / gc: element (chunk row 0, this head, channel 0); row_stride in elements (same for both).
-// GATED = false: no per-channel gate; the stored keys themselves are the operands (OPG = their type,
-// exact products) and gc is not read -- the any-d_k path of the scalar / no-gate kinds.
+// The C <= 64 form.  The loads of a k-step's gate rows (and, every other k-step, of the next line of keys) go out before the k-step
+// ahead of them is computed: one after the other, four k-steps were four round trips to memory, most of a call of few matrices.  The
+// anchor rows are rows of the chunk, the ones that lanes n = 0 load anyway, and reach the others through LDS.
+// Kernel time, bf16 keys of d_k = 128, C = 64, loads in the k-step itself / a step ahead: 256 matrices 11.6 / 10.9 us, 1024 18.5 / 15.6, 16384
+// 214 / 201; one right-hand side, 1024 20.6 / 17.8; fp32 operands, 1024 27.3 / 24.5, d_k = 256 30.0 / 23.8.
+template <int OPG, int NB, int METHOD, bool K16>
+__device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int d_k,
+                                                        Lane ln, int valid, float* tab)
+{
+    constexpr float LOG2E = 1.44269504088896340736f;
+    constexpr int STEPS = K16 ? 2 : 1;
+    const int n_step = d_k / 32;
+    int rowc[NB];
+    float keep[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int row = 16 * i + ln.n;
+        rowc[i] = row < valid ? row : valid - 1;
+        keep[i] = row < valid ? 1.f : 0.f;
+    }
+    const auto load_keys = [&](RawKey8<K16> (&raw)[STEPS][NB], int s) {
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+                if (s + t < n_step) raw[t][i] = load_key8<K16>(Kc, (int64_t)rowc[i] * row_stride + 32 * (s + t) + 8 * ln.q);
+    };
+    const auto load_gates = [&](v4f (&G)[NB][2], int s) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const float* const p = gc + (int64_t)rowc[i] * row_stride + 32 * s + 8 * ln.q;
+            G[i][0] = *reinterpret_cast<const v4f*>(p);
+            G[i][1] = *reinterpret_cast<const v4f*>(p + 4);
+        }
+    };
+    // Per row group (q): the anchors of its 8 channels, then the pairs' factors (see the k-step).
+    constexpr int NP = NB * (NB - 1) / 2, NE = 8 * NP;
+    float* const anc = tab + ln.q * (8 * NB + NE);
+    float* const fac = anc + 8 * NB;
+
+    RawKey8<K16> raw[STEPS][NB];
+    v4f G[NB][2];
+    load_keys(raw, 0);
+    load_gates(G, 0);
+    for (int s0 = 0; s0 < n_step; s0 += STEPS) {
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+            const int s = s0 + t;
+            if (s >= n_step) break;
+            if (ln.n == 0) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    *reinterpret_cast<v4f*>(&anc[8 * i]) = G[i][0];
+                    *reinterpret_cast<v4f*>(&anc[8 * i + 4]) = G[i][1];
+                }
+            }
+            v4f G_next[NB][2];
+            RawKey8<K16> raw_next[STEPS][NB];
+            if (s + 1 < n_step) {
+                if (t == STEPS - 1) load_keys(raw_next, s + 1);
+                load_gates(G_next, s + 1);
+            }
+            wave_lds_sync();
+            // With e_i = (g_i - a_I) log2 e (row i, its tile row's anchor a_I), u_i = k_i 2^(e_i) is the left factor of every
+            // tile in tile row I and v_j = k_j 2^(-e_j) the right factor of the diagonal tile (J, J).  The right factor of
+            // tile (I, J), J < I, differs from v_j by 2^((a_I - a_J) log2 e), which depends on the channel only, not on the
+            // row: those NB (NB - 1) / 2 x 32 factors are computed once per k-step by the whole wave (through LDS: the 16
+            // lanes of a row group need the same; each computes a share of the table) instead
+            // of once per row: 67 exponentials per lane and k-step at C = 64 instead of 112, and no subtraction or scaling
+            // of the exponent per pair either.
+            if constexpr (NP > 0) {
+#pragma unroll
+                for (int k = 0; k < (NE + 15) / 16; ++k) {
+                    const int e = ln.n + 16 * k, p = e >> 3, r = e & 7;
+                    if (e < NE) {  // pair p = (hi, lo), hi > lo, in the order (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
+                        const int hi = p >= 3 ? 3 : (p >= 1 ? 2 : 1), lo = p - hi * (hi - 1) / 2;
+                        fac[e] = __builtin_amdgcn_exp2f((anc[8 * hi + r] - anc[8 * lo + r]) * LOG2E);
+                    }
+                }
+                wave_lds_sync();
+            }
+            GOp<OPG> ppi[NB];
+            float v[NB][8];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                float kv[8], u[8];
+                widen_key8<K16>(raw[t][i], is_f16, kv);
+                const v4f a0 = *reinterpret_cast<const v4f*>(&anc[8 * i]), a1 = *reinterpret_cast<const v4f*>(&anc[8 * i + 4]);
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const float kk = kv[r] * keep[i];
+                    const float e = (G[i][r / 4][r % 4] - (r < 4 ? a0[r] : a1[r - 4])) * LOG2E;
+                    u[r] = kk * __builtin_amdgcn_exp2f(e);
+                    v[i][r] = kk * __builtin_amdgcn_exp2f(-e);
+                }
+                ppi[i] = gpack<OPG>(u);
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j <= i; ++j) {
+                    float dn[8];
+                    if (i == j) {
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) dn[r] = v[j][r];
+                    } else {
+                        const int p = i * (i - 1) / 2 + j;
+                        const v4f f0 = *reinterpret_cast<const v4f*>(&fac[8 * p]), f1 = *reinterpret_cast<const v4f*>(&fac[8 * p + 4]);
+#pragma unroll
+                        for (int r = 0; r < 8; ++r) dn[r] = v[j][r] * (r < 4 ? f0[r] : f1[r - 4]);
+                    }
+                    const GOp<OPG> pmj = gpack<OPG>(dn);
+                    if (need_tile<NB, METHOD>(i, j, false)) out.n[tix(i, j)] = gstep<OPG>(ppi[i], pmj, out.n[tix(i, j)]);
+                    if (need_tile<NB, METHOD>(i, j, true)) out.t[tix(i, j)] = gstep<OPG>(pmj, ppi[i], out.t[tix(i, j)]);
+                }
+            wave_lds_sync();  // (anchors and factors are rewritten by the next k-step)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                G[i][0] = G_next[i][0];
+                G[i][1] = G_next[i][1];
+                if (t == STEPS - 1) {
+#pragma unroll
+                    for (int k = 0; k < STEPS; ++k) raw[k][i] = raw_next[k][i];
+                }
+            }
+        }
+    }
+}
+
+// The general form: C = 128 and, with GATED = false, no per-channel gate (the stored keys themselves are the operands, OPG = their type,
+// exact products, and gc is not read): the any-d_k path of the scalar / no-gate kinds.
 template <int OPG, int NB, int METHOD, bool K16, bool GATED = true>
 __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc,
                                                       int64_t row_stride, int d_k, Lane ln, int valid, float* tab = nullptr)
 {
+    if constexpr (GATED && NB <= 4) return accumulate_gated_gram64<OPG, NB, METHOD, K16>(out, Kc, is_f16, gc, row_stride, d_k, ln, valid, tab);
     constexpr int C = 16 * NB;
-    constexpr float LOG2E = 1.44269504088896340736f;
+    [[maybe_unused]] constexpr float LOG2E = 1.44269504088896340736f;
     constexpr int STEPS = (K16 && NB <= 4) ? 2 : 1;  // C = 128 has no registers to spare for the pairing
     // rows beyond the chunk's real tokens read the last real one (valid addresses, finite exponents)
     // and contribute zero keys; the anchor is a real row too
@@ -534,83 +664,6 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
         for (int t = 0; t < STEPS; ++t) {
             if (s0 + t >= d_k / 32) break;
             const int ch = 32 * (s0 + t) + 8 * ln.q;
-            if constexpr (GATED && NB <= 4) {
-                // gate rows and tile-row anchors of this k-step, all loads first
-                v4f G[NB][2], An[NB][2];
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    const int64_t off = (int64_t)rowc[i] * row_stride + ch;
-                    G[i][0] = *reinterpret_cast<const v4f*>(gc + off);
-                    G[i][1] = *reinterpret_cast<const v4f*>(gc + off + 4);
-                    const int ar = 16 * i < valid ? 16 * i : valid - 1;
-                    An[i][0] = *reinterpret_cast<const v4f*>(gc + (int64_t)ar * row_stride + ch);
-                    An[i][1] = *reinterpret_cast<const v4f*>(gc + (int64_t)ar * row_stride + ch + 4);
-                }
-                // With e_i = (g_i - a_I) log2 e (row i, its tile row's anchor a_I), u_i = k_i 2^(e_i) is the left factor of every
-                // tile in tile row I and v_j = k_j 2^(-e_j) the right factor of the diagonal tile (J, J).  The right factor of
-                // tile (I, J), J < I, differs from v_j by 2^((a_I - a_J) log2 e), which depends on the channel only, not on the
-                // row: those NB (NB - 1) / 2 x 32 factors are computed once per k-step by the whole wave (through LDS: the 16
-                // lanes of a row group hold the same anchors; one writes them, each computes a share of the table) instead
-                // of once per row: 67 exponentials per lane and k-step at C = 64 instead of 112, and no subtraction or scaling
-                // of the exponent per pair either.
-                constexpr int NP = NB * (NB - 1) / 2, NE = 8 * NP;
-                float* anc = tab + ln.q * (8 * NB + NE);  // [NB][8] anchors, then [NP][8] factors, per row group
-                float* fac = anc + 8 * NB;
-                if constexpr (NP > 0) {
-                    if (ln.n == 0) {
-#pragma unroll
-                        for (int i = 0; i < NB; ++i) {
-                            *reinterpret_cast<v4f*>(&anc[8 * i]) = An[i][0];
-                            *reinterpret_cast<v4f*>(&anc[8 * i + 4]) = An[i][1];
-                        }
-                    }
-                    wave_lds_sync();
-#pragma unroll
-                    for (int k = 0; k < (NE + 15) / 16; ++k) {
-                        const int e = ln.n + 16 * k, p = e >> 3, r = e & 7;
-                        if (e < NE) {  // pair p = (hi, lo), hi > lo, in the order (1,0) (2,0) (2,1) (3,0) (3,1) (3,2)
-                            const int hi = p >= 3 ? 3 : (p >= 1 ? 2 : 1), lo = p - hi * (hi - 1) / 2;
-                            fac[e] = __builtin_amdgcn_exp2f((anc[8 * hi + r] - anc[8 * lo + r]) * LOG2E);
-                        }
-                    }
-                    wave_lds_sync();
-                }
-                GOp<OPG> ppi[NB];
-                float v[NB][8];
-#pragma unroll
-                for (int i = 0; i < NB; ++i) {
-                    float kv[8], u[8];
-                    widen_key8<K16>(raw[t][i], is_f16, kv);
-#pragma unroll
-                    for (int r = 0; r < 8; ++r) {
-                        const float kk = kv[r] * keep[i];
-                        const float e = (G[i][r / 4][r % 4] - An[i][r / 4][r % 4]) * LOG2E;
-                        u[r] = kk * __builtin_amdgcn_exp2f(e);
-                        v[i][r] = kk * __builtin_amdgcn_exp2f(-e);
-                    }
-                    ppi[i] = gpack<OPG>(u);
-                }
-#pragma unroll
-                for (int i = 0; i < NB; ++i)
-#pragma unroll
-                    for (int j = 0; j <= i; ++j) {
-                        float dn[8];
-                        if (i == j) {
-#pragma unroll
-                            for (int r = 0; r < 8; ++r) dn[r] = v[j][r];
-                        } else {
-                            const int p = i * (i - 1) / 2 + j;
-                            const v4f f0 = *reinterpret_cast<const v4f*>(&fac[8 * p]), f1 = *reinterpret_cast<const v4f*>(&fac[8 * p + 4]);
-#pragma unroll
-                            for (int r = 0; r < 8; ++r) dn[r] = v[j][r] * (r < 4 ? f0[r] : f1[r - 4]);
-                        }
-                        const GOp<OPG> pmj = gpack<OPG>(dn);
-                        if (need_tile<NB, METHOD>(i, j, false)) out.n[tix(i, j)] = gstep<OPG>(ppi[i], pmj, out.n[tix(i, j)]);
-                        if (need_tile<NB, METHOD>(i, j, true)) out.t[tix(i, j)] = gstep<OPG>(pmj, ppi[i], out.t[tix(i, j)]);
-                    }
-                if constexpr (NP > 0) wave_lds_sync();  // (the table is rewritten by the next k-step)
-                continue;
-            }
             GOp<OPG> pp[NB], pm[NB];
             if constexpr (GATED) {
                 const v4f a0 = *reinterpret_cast<const v4f*>(gc + (int64_t)anchor * row_stride + ch);
@@ -1222,12 +1275,15 @@ template <> struct TriInvPointers<M_FWD> {
 };
 
 // Wavefronts per SIMD the register allocator has to leave room for.  Newton-Schulz with fp32 operands at C = 64 needs two:
-// its matrix-core and its vector instructions take about the same time and overlap only between wavefronts.  So does forward
-// substitution at C = 128 (255 registers this way).  With the per-channel gate it holds A beside the
-// running keys and factors and would spill.
+// its matrix-core and its vector instructions take about the same time and overlap only between wavefronts (with the refinement step it
+// does not fit).  So does forward substitution at C = 128 (255 registers this way; with the per-channel gate it holds A beside the
+// running keys and factors and would spill), and the per-channel kernels at C = 64, whose loads a step ahead take some methods just
+// beyond 256.
 template <int OP, int NB, int METHOD, bool REFINE, bool PER_CHANNEL = false> constexpr int min_waves_per_simd()
 {
-    return ((METHOD == M_NEWTON_SCHULZ && OP == OP_F32 && NB == 4 && !REFINE) || (METHOD == M_FWD && NB == 8 && !PER_CHANNEL)) ? 2 : 1;
+    constexpr bool split = METHOD == M_NEWTON_SCHULZ && OP == OP_F32;
+    if (NB == 4) return (split || PER_CHANNEL) && !(split && REFINE) ? 2 : 1;
+    return METHOD == M_FWD && NB == 8 && !PER_CHANNEL ? 2 : 1;
 }
 
 template <int IN, int OP, int NB, int METHOD, bool REFINE = false>
