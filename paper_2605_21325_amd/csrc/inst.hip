@@ -244,9 +244,10 @@ template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
     else
 #endif
     {
-        const FusedGrid f = fused_grid(a.n_mat, a.H, WPB);
+        const FusedGrid f = kda_team<OP, NB, METHOD, REFINE>() ? team_grid(a.n_mat, a.H, a.d_k, WPB) : fused_grid(a.n_mat, a.H, WPB);
+        constexpr int TILES = gram_tiles<NB, REFINE ? METHOD + WITH_REFINE : METHOD>();
         return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, WPB, REFINE>, dim3(f.groups), dim3(f.threads),
-                             f.few() ? 0u : kda_pad_bytes<METHOD>(a), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt,
+                             f.few() ? team_bytes(f.threads / 64, TILES) : kda_pad_bytes<METHOD>(a), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt,
                              a.iters, a.out_dt, f.spread);
     }
 }
@@ -311,8 +312,9 @@ static int kda_method(const GdnArgs& a)
 // recursion from directly solved blocks at C = 128.
 template <int KD, int METHOD> static int go_any_dk(const GdnArgs& a)
 {
-    return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD>, dim3((unsigned)a.n_mat), dim3(64), 0, a.stream, a.K, a.beta,
-                       a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
+    const int team = any_dk_team<NB>() > 1 ? team_waves(a.n_mat, a.d_k) : 1;
+    return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD>, dim3((unsigned)a.n_mat), dim3(64 * team),
+                         team_bytes(team, gram_tiles<NB, METHOD>()), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt, team);
 }
 
 template <int KD> static int any_dk_method(const GdnArgs& a)

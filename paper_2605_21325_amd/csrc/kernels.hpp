@@ -503,18 +503,70 @@ template <bool K16> __device__ __forceinline__ void widen_key8(const RawKey8<K16
 // its second half is still cached when needed (requested one k-step apart, lines were found
 // evicted in between and fetched from HBM twice).
 // Kc / gc: element (chunk row 0, this head, channel 0); row_stride in elements (same for both).
+constexpr int GATES_AHEAD_MATRICES = 8192;
+// The k-steps (of 32 channels) a wavefront takes.
+struct Steps {
+    int begin, end;
+};
+
+// With few matrices the wavefronts of a workgroup form one matrix together: each takes a share of the channels (the Gram products of
+// the channel loops are most of such a call: exponentials, and fp32 matrix instructions, beside which nothing else runs), the
+// first adds the others' tiles to its own and goes on alone.  256 matrices of C = 64, d_k = 128, one wavefront / four: per-channel gate
+// 10.9 / 8.7 us, with fp32 operands 19.3 / 12.0, applied to two right-hand sides 15.6 / 13.0; d_k = 256, fp32 keys and operands 22.6 / 12.8,
+// bf16 8.0 / 7.4.  512 matrices: 11.8 / 10.8, 20.5 / 16.5, 17.4 / 15.7, 24 / 16.3, 8.9 / 8.4.
+struct Team {
+    int w, size;   // this wavefront, their number (1: no team); never more than there are k-steps
+    float* tiles;  // LDS: (size - 1) * gram_tiles<NB, METHOD>() * 256 floats
+    __device__ __forceinline__ Steps share(int n_step) const { return Steps{w * n_step / size, (w + 1) * n_step / size}; }
+};
+template <int NB, int METHOD> __host__ __device__ constexpr int gram_tiles()
+{
+    int n = 0;
+    for (int i = 0; i < NB; ++i)
+        for (int j = 0; j <= i; ++j) n += (need_tile<NB, METHOD>(i, j, false) ? 1 : 0) + (need_tile<NB, METHOD>(i, j, true) ? 1 : 0);
+    return n;
+}
+// False for the wavefronts that are done.
+template <int NB, int METHOD> __device__ __forceinline__ bool team_sum(PreA<NB>& out, const Team& team, Lane ln)
+{
+    if (team.size == 1) return true;
+    constexpr int COUNT = gram_tiles<NB, METHOD>();
+    v4f* const slots = reinterpret_cast<v4f*>(team.tiles) + 16 * ln.q + ln.n;  // [wavefront - 1][tile][lane]
+    const auto each = [&](auto f) {
+        int n = 0;
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int j = 0; j <= i; ++j) {
+                if (need_tile<NB, METHOD>(i, j, false)) f(out.n[tix(i, j)], n++);
+                if (need_tile<NB, METHOD>(i, j, true)) f(out.t[tix(i, j)], n++);
+            }
+    };
+    if (team.w > 0) each([&](v4f& t, int n) { slots[((team.w - 1) * COUNT + n) * 64] = t; });
+    __syncthreads();
+    if (team.w > 0) return false;
+#pragma unroll 1
+    for (int w = 1; w < team.size; ++w) each([&](v4f& t, int n) { t += slots[((w - 1) * COUNT + n) * 64]; });
+    return true;
+}
+
 // The C <= 64 form.  The loads of a k-step's gate rows (and, every other k-step, of the next line of keys) go out before the k-step
 // ahead of them is computed: one after the other, four k-steps were four round trips to memory, most of a call of few matrices.  The
 // anchor rows are rows of the chunk, the ones that lanes n = 0 load anyway, and reach the others through LDS.
 // Kernel time, bf16 keys of d_k = 128, C = 64, loads in the k-step itself / a step ahead: 256 matrices 11.6 / 10.9 us, 1024 18.5 / 15.6, 16384
 // 214 / 201; one right-hand side, 1024 20.6 / 17.8; fp32 operands, 1024 27.3 / 24.5, d_k = 256 30.0 / 23.8.
+// ahead = false: not so, for calls that fill the chip many times over and keep fewer bytes of keys than of gates in flight this way
+// (fp32 keys, fp32 operands at C = 32).  C = 16 has wavefronts enough without.
 template <int OPG, int NB, int METHOD, bool K16>
-__device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int d_k,
-                                                        Lane ln, int valid, float* tab)
+__device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, Steps steps,
+                                                        Lane ln, int valid, float* tab, bool ahead)
 {
     constexpr float LOG2E = 1.44269504088896340736f;
     constexpr int STEPS = K16 ? 2 : 1;
-    const int n_step = d_k / 32;
+    constexpr bool KEYS_AHEAD = K16 && (NB == 4 || (NB == 2 && OPG != OP_F32));  // elsewhere they would cost a wavefront per SIMD
+    if (KEYS_AHEAD) ahead = true;
+    if (NB == 1 || METHOD == M_NEWTON_SCHULZ + WITH_REFINE) ahead = false;       // (which has no registers left for them)
+    const int n_step = steps.end;
     int rowc[NB];
     float keep[NB];
 #pragma unroll
@@ -545,9 +597,9 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
 
     RawKey8<K16> raw[STEPS][NB];
     v4f G[NB][2];
-    load_keys(raw, 0);
-    load_gates(G, 0);
-    for (int s0 = 0; s0 < n_step; s0 += STEPS) {
+    if (KEYS_AHEAD) load_keys(raw, steps.begin);
+    load_gates(G, steps.begin);
+    for (int s0 = steps.begin; s0 < n_step; s0 += STEPS) {
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
             const int s = s0 + t;
@@ -561,9 +613,10 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
             }
             v4f G_next[NB][2];
             RawKey8<K16> raw_next[STEPS][NB];
+            if (!KEYS_AHEAD && t == 0) load_keys(raw, s);
             if (s + 1 < n_step) {
-                if (t == STEPS - 1) load_keys(raw_next, s + 1);
-                load_gates(G_next, s + 1);
+                if (KEYS_AHEAD && t == STEPS - 1) load_keys(raw_next, s + 1);
+                if (ahead) load_gates(G_next, s + 1);
             }
             wave_lds_sync();
             // With e_i = (g_i - a_I) log2 e (row i, its tile row's anchor a_I), u_i = k_i 2^(e_i) is the left factor of every
@@ -619,11 +672,12 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
                     if (need_tile<NB, METHOD>(i, j, true)) out.t[tix(i, j)] = gstep<OPG>(pmj, ppi[i], out.t[tix(i, j)]);
                 }
             wave_lds_sync();  // (anchors and factors are rewritten by the next k-step)
+            if (!ahead && s + 1 < n_step) load_gates(G_next, s + 1);
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
                 G[i][0] = G_next[i][0];
                 G[i][1] = G_next[i][1];
-                if (t == STEPS - 1) {
+                if (KEYS_AHEAD && t == STEPS - 1) {
 #pragma unroll
                     for (int k = 0; k < STEPS; ++k) raw[k][i] = raw_next[k][i];
                 }
@@ -636,9 +690,9 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
 // exact products, and gc is not read): the any-d_k path of the scalar / no-gate kinds.
 template <int OPG, int NB, int METHOD, bool K16, bool GATED = true>
 __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc,
-                                                      int64_t row_stride, int d_k, Lane ln, int valid, float* tab = nullptr)
+                                                      int64_t row_stride, Steps steps, Lane ln, int valid, float* tab = nullptr, bool ahead = true)
 {
-    if constexpr (GATED && NB <= 4) return accumulate_gated_gram64<OPG, NB, METHOD, K16>(out, Kc, is_f16, gc, row_stride, d_k, ln, valid, tab);
+    if constexpr (GATED && NB <= 4) return accumulate_gated_gram64<OPG, NB, METHOD, K16>(out, Kc, is_f16, gc, row_stride, steps, ln, valid, tab, ahead);
     constexpr int C = 16 * NB;
     [[maybe_unused]] constexpr float LOG2E = 1.44269504088896340736f;
     constexpr int STEPS = (K16 && NB <= 4) ? 2 : 1;  // C = 128 has no registers to spare for the pairing
@@ -653,16 +707,16 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
         keep[i] = row < valid ? 1.f : 0.f;
     }
     const int anchor = C / 2 < valid ? C / 2 : valid - 1;
-    for (int s0 = 0; s0 < d_k / 32; s0 += STEPS) {
+    for (int s0 = steps.begin; s0 < steps.end; s0 += STEPS) {
         RawKey8<K16> raw[STEPS][NB];
 #pragma unroll
         for (int t = 0; t < STEPS; ++t)
 #pragma unroll
             for (int i = 0; i < NB; ++i)
-                if (s0 + t < d_k / 32) raw[t][i] = load_key8<K16>(Kc, (int64_t)rowc[i] * row_stride + 32 * (s0 + t) + 8 * ln.q);
+                if (s0 + t < steps.end) raw[t][i] = load_key8<K16>(Kc, (int64_t)rowc[i] * row_stride + 32 * (s0 + t) + 8 * ln.q);
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
-            if (s0 + t >= d_k / 32) break;
+            if (s0 + t >= steps.end) break;
             const int ch = 32 * (s0 + t) + 8 * ln.q;
             GOp<OPG> pp[NB], pm[NB];
             if constexpr (GATED) {
@@ -708,8 +762,8 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
 }
 
 template <int OPG, int NB, int METHOD>
-__device__ __forceinline__ void build_A_per_channel(PreA<NB>& out, const void* Kc, int kd, const float* gc, int64_t row_stride,
-                                                    const float* bc, int64_t tok_stride, int d_k, float* lds, Lane ln, int valid)
+__device__ __forceinline__ bool build_A_per_channel(PreA<NB>& out, const void* Kc, int kd, const float* gc, int64_t row_stride,
+                                                    const float* bc, int64_t tok_stride, int d_k, float* lds, Lane ln, int valid, const Team& team, bool ahead)
 {
     constexpr int C = 16 * NB;
 #pragma unroll
@@ -720,9 +774,10 @@ __device__ __forceinline__ void build_A_per_channel(PreA<NB>& out, const void* K
             out.t[tix(i, j)] = zero4();
         }
     if (kd == OP_F32)
-        accumulate_gated_gram<OPG, NB, METHOD, false>(out, Kc, false, gc, row_stride, d_k, ln, valid, lds);
+        accumulate_gated_gram<OPG, NB, METHOD, false>(out, Kc, false, gc, row_stride, team.share(d_k / 32), ln, valid, lds, ahead);
     else
-        accumulate_gated_gram<OPG, NB, METHOD, true>(out, Kc, kd == OP_F16, gc, row_stride, d_k, ln, valid, lds);
+        accumulate_gated_gram<OPG, NB, METHOD, true>(out, Kc, kd == OP_F16, gc, row_stride, team.share(d_k / 32), ln, valid, lds, ahead);
+    if (!team_sum<NB, METHOD>(out, team, ln)) return false;
     // beta_i row scaling and the strictly-lower mask
     const int l = 16 * ln.q + ln.n;
 #pragma unroll
@@ -742,13 +797,14 @@ __device__ __forceinline__ void build_A_per_channel(PreA<NB>& out, const void* K
             }
     }
     wave_lds_sync();
+    return true;
 }
 
 // Scalar / no-gate kinds for any d_k (multiple of 32): Gram tiles accumulated 32 channels at a time
 // in a run-time loop with the stored keys as operands, then the scalar gate.  KD = type of K.
 template <int KD, int NB, int METHOD>
-__device__ __forceinline__ void build_A_scalar_any_dk(PreA<NB>& out, const void* Kc, int64_t row_stride, const float* bc,
-                                                      const float* gc, int64_t tok_stride, int d_k, float* lds, Lane ln, int valid)
+__device__ __forceinline__ bool build_A_scalar_any_dk(PreA<NB>& out, const void* Kc, int64_t row_stride, const float* bc,
+                                                      const float* gc, int64_t tok_stride, int d_k, float* lds, Lane ln, int valid, const Team& team)
 {
 #pragma unroll
     for (int i = 0; i < NB; ++i)
@@ -757,7 +813,8 @@ __device__ __forceinline__ void build_A_scalar_any_dk(PreA<NB>& out, const void*
             out.n[tix(i, j)] = zero4();
             out.t[tix(i, j)] = zero4();
         }
-    accumulate_gated_gram<KD, NB, METHOD, KD != OP_F32, false>(out, Kc, KD == OP_F16, nullptr, row_stride, d_k, ln, valid);
+    accumulate_gated_gram<KD, NB, METHOD, KD != OP_F32, false>(out, Kc, KD == OP_F16, nullptr, row_stride, team.share(d_k / 32), ln, valid);
+    if (!team_sum<NB, METHOD>(out, team, ln)) return false;
     GateVec<NB> gate;
     gate.load(bc, gc, tok_stride, lds, ln, valid);
 #pragma unroll
@@ -767,6 +824,7 @@ __device__ __forceinline__ void build_A_scalar_any_dk(PreA<NB>& out, const void*
             if (need_tile<NB, METHOD>(i, j, false)) out.n[tix(i, j)] = gate.template apply<false>(i, j, out.n[tix(i, j)], ln);
             if (need_tile<NB, METHOD>(i, j, true)) out.t[tix(i, j)] = gate.template apply<true>(i, j, out.t[tix(i, j)], ln);
         }
+    return true;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1218,6 +1276,16 @@ template <int NB, int METHOD> constexpr int core_lds_floats()
     return store_lds_floats<NB>() > small ? store_lds_floats<NB>() : small;
 }
 
+// The team of this wavefront in a workgroup of `size` of them; its tiles are in the launch's dynamic LDS.
+__device__ __forceinline__ Team this_team(int size)
+{
+    extern __shared__ __attribute__((aligned(16))) float team_tiles[];
+    return Team{size > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0, size, team_tiles};
+}
+template <int NB> constexpr int any_dk_team() { return NB <= 4 ? TEAM_WAVES : 1; }
+// (Newton-Schulz at C = 64, with fp32 operands or the refinement step, has no register left for it)
+template <int OP, int NB, int METHOD, bool REFINE> constexpr bool kda_team() { return !(METHOD == M_NEWTON_SCHULZ && NB == 4 && (OP == OP_F32 || REFINE)); }
+
 // REFINE: one iterative-refinement step after a matrix-product method (C <= 64; at C = 128 a kernel of its own).
 template <int OP, int NB, int METHOD, class ASrc, bool REFINE = false>
 __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float* lds, Lane ln, int aux = 0)
@@ -1340,7 +1408,7 @@ __device__ __forceinline__ int64_t head_group_swizzle(int64_t bid, int64_t n_gro
 // slower, with 10 % higher read latency and 4.5x the DRAM credit stalls.  Instead a workgroup takes ONE head of WPB chunks
 // S chunks apart (S = max(1, 4 / H), so its four key regions are at least 64 KB apart), and the S * H workgroups that share
 // those 4 S chunks run back to back on one XCD.  Chunks beyond the last full group of 4 S keep the plain order.
-// spread = ONE_WAVE_PER_GROUP (few matrices, see fused_grid): workgroups of one wavefront, in plain order.
+// spread = ONE_WAVE_PER_GROUP or ONE_TEAM_PER_GROUP (few matrices, see fused_grid): a workgroup has one matrix, in plain order.
 // The waves never synchronise with each other.  Returns chunk id * H + head, or -1 for a wave without a matrix.
 template <int WPB>
 __device__ __forceinline__ int64_t fused_matrix_index(int64_t n_chunk, int H, int64_t n_mat, int spread)
@@ -1361,8 +1429,8 @@ __device__ __forceinline__ int64_t fused_matrix_index(int64_t n_chunk, int H, in
         const int64_t m = (full + (bid - full)) * WPB + w;             // the tail: WPB consecutive matrices per workgroup
         return m < n_mat ? m : -1;
     }
-    if (H % WPB != 0 || (WPB > 1 && spread == ONE_WAVE_PER_GROUP)) {
-        const int64_t m = (int64_t)blockIdx.x * (WPB > 1 && spread == ONE_WAVE_PER_GROUP ? 1 : WPB) + w;
+    if (H % WPB != 0 || (WPB > 1 && spread < 0)) {
+        const int64_t m = WPB > 1 && spread < 0 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * WPB + w;
         return m < n_mat ? m : -1;
     }
     return head_group_swizzle(blockIdx.x, n_chunk, H / WPB) * WPB + w;
@@ -1406,10 +1474,11 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
 }
 
 // Fused kernel of the scalar / no-gate kinds for head dimensions without a specialised build.
+// team: wavefronts that form a matrix together (see Team), the workgroup's size.
 template <int KD, int OP, int NB, int METHOD>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+__global__ __launch_bounds__(64 * any_dk_team<NB>()) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
-                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt)
+                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt, int team)
 {
     constexpr int C = 16 * NB;
     constexpr int CORE = core_lds_floats<NB, METHOD>();
@@ -1423,9 +1492,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(min_waves_pe
     const Lane ln = lane_id();
     const int64_t esz = (KD == OP_F32) ? 4 : 2;
     PreA<NB> src;
-    build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz,
-                                          (int64_t)H * d_k, beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln,
-                                          pos.valid);
+    if (!build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
+                                               beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid,
+                                               this_team(any_dk_team<NB>() > 1 ? team : 1)))
+        return;
     invert_and_store<OP, NB, METHOD, PreA<NB>, false>(src, out_matrix(T, m, C, out_dt), lds, ln, aux);
 }
 
@@ -1450,9 +1520,11 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
     const int64_t esz = (k_dt == OP_F32) ? 4 : 2;
     const int64_t e0 = (tok0 * H + h) * (int64_t)d_k;  // element offset of (token 0, head h, channel 0)
     PreA<NB> src;
-    build_A_per_channel<OP, NB, REFINE ? METHOD + WITH_REFINE : METHOD>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0,
-                                                                        (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, lds, ln,
-                                                                        pos.valid);
+    if (!build_A_per_channel<OP, NB, REFINE ? METHOD + WITH_REFINE : METHOD>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0,
+                                                                             (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, lds, ln, pos.valid,
+                                                                             this_team(WPB > 1 && kda_team<OP, NB, METHOD, REFINE>() && spread == ONE_TEAM_PER_GROUP ? (int)blockDim.x / 64 : 1),
+                                                                             n_chunk * H <= GATES_AHEAD_MATRICES))
+        return;
     invert_and_store<OP, NB, METHOD, PreA<NB>, REFINE>(src, out_matrix(T, m, C, out_dt), lds, ln, aux);
 }
 

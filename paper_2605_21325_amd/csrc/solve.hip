@@ -108,14 +108,15 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
     return launch_kernel(f.dry, k_kda_tri_solve_c128<OP, METHOD, 2>, dim3((unsigned)f.n_mat), dim3(128), 0, f.stream, f.K, f.beta, f.g,
                          rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
 #else
-    const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
+    const FusedGrid shape = team_grid(f.n_mat, f.H, f.d_k, WPB);
+    const unsigned lds = shape.few() ? team_bytes(shape.threads / 64, gram_tiles<NB, METHOD>()) : 0u;
     const dim3 grid(shape.groups), block(shape.threads);
     if (a.n_rhs == 1) {
-        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 1>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
+        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 1>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
                            f.map, f.H, f.d_k, f.k_dt, f.iters, shape.spread);
     }
     if constexpr (HAS_PAIR) {
-        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 2>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
+        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 2>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
                            f.map, f.H, f.d_k, f.k_dt, f.iters, shape.spread);
     }
     return 1;
@@ -127,13 +128,15 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
 template <int KD, int METHOD> static int go_any_dk(const SolveArgs& a)
 {
     const GdnArgs& f = a.f;
-    const dim3 grid((unsigned)f.n_mat), block(64);
+    const int team = team_waves(f.n_mat, f.d_k);
+    const dim3 grid((unsigned)f.n_mat), block(64 * team);
+    const unsigned lds = team_bytes(team, gram_tiles<NB, METHOD>());
     if (a.n_rhs == 1)
-        return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, 1>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
-                           f.map, f.H, f.d_k, f.iters);
+        return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, 1>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
+                           f.map, f.H, f.d_k, f.iters, team);
     else
-        return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, 2>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
-                             f.map, f.H, f.d_k, f.iters);
+        return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, 2>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
+                             f.map, f.H, f.d_k, f.iters, team);
 }
 
 template <int KD> static int any_dk_method(const SolveArgs& a)

@@ -357,8 +357,10 @@ __global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restri
     const int64_t esz = (k_dt == OP_F32) ? 4 : 2;
     const int64_t e0 = (tok0 * H + h) * (int64_t)d_k;
     PreA<NB> src;
-    build_A_per_channel<OP, NB, METHOD>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0, (int64_t)H * d_k,
-                                        beta + tok0 * H + h, H, d_k, lds, ln, pos.valid);
+    if (!build_A_per_channel<OP, NB, METHOD>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0, (int64_t)H * d_k, beta + tok0 * H + h, H, d_k,
+                                             lds, ln, pos.valid, this_team(WPB > 1 && spread == ONE_TEAM_PER_GROUP ? (int)blockDim.x / 64 : 1),
+                                             n_chunk * H <= GATES_AHEAD_MATRICES))
+        return;
     RhsX<OP, NB> x;  // after the Gram passes, which need the registers
     x.init(rhs.r[0], tok0, h, H, pos.valid, ln);
     auto next_rhs = [&](int k) {
@@ -372,9 +374,9 @@ __global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restri
 // Scalar / no-gate kinds for head dimensions without a specialised build (any multiple of 32): the channel-loop Gram of
 // the storing kernel, then the same recursion and products.  One wavefront per workgroup.
 template <int KD, int OP, int NB, int METHOD, int NRHS>
-__global__ __launch_bounds__(64) void k_gdn_any_dk_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
+__global__ __launch_bounds__(64 * any_dk_team<NB>()) void k_gdn_any_dk_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
                                                              const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
-                                                             int H, int d_k, int aux)
+                                                             int H, int d_k, int aux, int team)
 {
     constexpr int C = 16 * NB;
     constexpr int CORE = SOLVE_LDS_FLOATS;
@@ -388,8 +390,9 @@ __global__ __launch_bounds__(64) void k_gdn_any_dk_tri_solve(const void* __restr
     const Lane ln = lane_id();
     const int64_t esz = (KD == OP_F32) ? 4 : 2;
     PreA<NB> src;
-    build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
-                                          beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid);
+    if (!build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
+                                               beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid, this_team(team)))
+        return;
     RhsX<OP, NB> x;
     x.init(rhs.r[0], tok0, h, H, pos.valid, ln);
     auto next_rhs = [&](int k) {
