@@ -55,9 +55,10 @@ __host__ __device__ constexpr int c128_pair(int i, int j) { return i * (i - 1) /
 // per row: 69 exponentials per lane and k-step instead of 144.
 // Kc / gc: element (chunk row 0, this head, channel 0); row_stride in elements (the same for both).
 // tab: this wave's ANCHOR_FLOATS floats of LDS.
-template <int OP, int METHOD, bool K16, int W>
+// under_way(): called once the first k-step's gate rows are requested.
+template <int OP, int METHOD, bool K16, int W, bool AHEAD, class Hook>
 __device__ __forceinline__ void c128_kda_gram(char* xchg, float* tab, PreA<4>& pre, v4f (&a21)[4][2], const void* Kc, bool is_f16,
-                                              const float* gc, int64_t row_stride, int d_k, Lane ln, int valid)
+                                              const float* gc, int64_t row_stride, int d_k, Lane ln, int valid, Hook under_way)
 {
     constexpr float LOG2E = 1.44269504088896340736f;
     constexpr int STEPS = K16 ? 2 : 1;  // 16-bit keys: both k-steps of a 128-byte line of keys are requested together
@@ -65,15 +66,6 @@ __device__ __forceinline__ void c128_kda_gram(char* xchg, float* tab, PreA<4>& p
     GOp<OP>* xb = reinterpret_cast<GOp<OP>*>(xchg);
     float* anc = tab + ln.q * 40;            // [5][8]: anchors of tile rows 0..3 of this half, then the chunk's row 64
     float* fac = tab + 160 + ln.q * 80;      // [10][8]: pairs (i > j) by c128_pair, then the off-diagonal block's four
-    int rowc[4];
-    float keep[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = 64 * W + 16 * i + ln.n;
-        rowc[i] = row < valid ? row : valid - 1;
-        keep[i] = row < valid ? 1.f : 0.f;
-    }
-    const int mid = 64 < valid ? 64 : valid - 1;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -87,41 +79,56 @@ __device__ __forceinline__ void c128_kda_gram(char* xchg, float* tab, PreA<4>& p
         for (int d = 0; d < 2; ++d) a21[b][d] = zero4();
 
     const int n_step = d_k / 32;
+    // element offset of this lane's row of tile row i (4: the chunk's row 64), formed where it is used: kept from step to step the
+    // addresses of keys and gates are 40 registers
+    const auto row_offset = [&](int i) {
+        int row = i < 4 ? 64 * W + 16 * i + ln.n : 64;
+        row = row < valid ? row : valid - 1;
+        asm volatile("" : "+v"(row));
+        return (int64_t)row * row_stride + 8 * ln.q;
+    };
+    const auto load_keys = [&](RawKey8<K16> (&raw)[STEPS][4], int s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int64_t off = row_offset(i) + 32 * s;
+#pragma unroll
+            for (int t = 0; t < STEPS; ++t)
+                if (s + t < n_step) raw[t][i] = load_key8<K16>(Kc, off + 32 * t);
+        }
+    };
+    const auto load_gates = [&](v4f (&G)[4][2], v4f& mid, int s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float* const p = gc + row_offset(i) + 32 * s;
+            G[i][0] = *reinterpret_cast<const v4f*>(p);
+            G[i][1] = *reinterpret_cast<const v4f*>(p + 4);
+        }
+        if (W == 0) mid = *reinterpret_cast<const v4f*>(gc + row_offset(4) + 32 * s + 4 * (ln.n & 1));
+    };
+    // The gate rows of the next k-step are on their way while one is computed (AHEAD).  The anchors are rows that lanes n = 0 load (see
+    // accumulate_gated_gram64); the top wave loads the chunk's row 64 as well, half a row group's channels in lanes n = 0 and n = 1 each.
+    RawKey8<K16> raw[STEPS][4];
+    v4f G[4][2], mid = zero4();
+    load_gates(G, mid, 0);
+    under_way();
     for (int s0 = 0; s0 < n_step; s0 += STEPS) {
-        RawKey8<K16> raw[STEPS][4];
-#pragma unroll
-        for (int t = 0; t < STEPS; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (s0 + t < n_step) raw[t][i] = load_key8<K16>(Kc, (int64_t)rowc[i] * row_stride + 32 * (s0 + t) + 8 * ln.q);
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
             const int s = s0 + t;
             if (s >= n_step) break;
-            const int ch = 32 * s + 8 * ln.q;
-            // gate rows, tile-row anchors and the chunk's row 64 for this k-step, all loads first
-            v4f G[4][2], An[5][2];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int64_t off = (int64_t)rowc[i] * row_stride + ch;
-                G[i][0] = *reinterpret_cast<const v4f*>(gc + off);
-                G[i][1] = *reinterpret_cast<const v4f*>(gc + off + 4);
-                const int ar = 64 * W + 16 * i < valid ? 64 * W + 16 * i : valid - 1;
-                An[i][0] = *reinterpret_cast<const v4f*>(gc + (int64_t)ar * row_stride + ch);
-                An[i][1] = *reinterpret_cast<const v4f*>(gc + (int64_t)ar * row_stride + ch + 4);
-            }
-            An[4][0] = *reinterpret_cast<const v4f*>(gc + (int64_t)mid * row_stride + ch);
-            An[4][1] = *reinterpret_cast<const v4f*>(gc + (int64_t)mid * row_stride + ch + 4);
-            // the channel-only factors: anchors to LDS (every lane of a row group holds the same values; one writes), five
-            // table entries per lane, back through LDS
             if (ln.n == 0) {
 #pragma unroll
-                for (int i = 0; i < 5; ++i) {
-                    *reinterpret_cast<v4f*>(&anc[8 * i]) = An[i][0];
-                    *reinterpret_cast<v4f*>(&anc[8 * i + 4]) = An[i][1];
+                for (int i = 0; i < (W == 0 ? 4 : 5); ++i) {
+                    *reinterpret_cast<v4f*>(&anc[8 * i]) = G[i & 3][0];  // (the bottom wave's first row is the chunk's row 64)
+                    *reinterpret_cast<v4f*>(&anc[8 * i + 4]) = G[i & 3][1];
                 }
             }
+            if (W == 0 && ln.n < 2) *reinterpret_cast<v4f*>(&anc[32 + 4 * ln.n]) = mid;
+            if (t == 0) load_keys(raw, s);
+            v4f G_next[4][2], mid_next;
+            if (AHEAD && s + 1 < n_step) load_gates(G_next, mid_next, s + 1);
             wave_lds_sync();
+            // the channel-only factors: five table entries per lane from the anchors, through LDS
 #pragma unroll
             for (int k = 0; k < 5; ++k) {
                 const int e = ln.n + 16 * k, p = e >> 3, r = e & 7;
@@ -140,17 +147,22 @@ __device__ __forceinline__ void c128_kda_gram(char* xchg, float* tab, PreA<4>& p
             // factor of the off-diagonal block, which goes to the other wave
             GOp<OP> ppi[4], mine[4];
             float v[4][8];
+            if (64 * W + 64 > valid) {  // wave-uniform: rows beyond a short chunk's last token become zero keys
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (64 * W + 16 * i + ln.n >= valid) raw[t][i] = RawKey8<K16>{};
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 float kv[8], u[8], m[8];
                 widen_key8<K16>(raw[t][i], is_f16, kv);
+                const v4f a0 = *reinterpret_cast<const v4f*>(&anc[8 * i]), a1 = *reinterpret_cast<const v4f*>(&anc[8 * i + 4]);
                 const v4f f0 = *reinterpret_cast<const v4f*>(&fac[8 * (6 + i)]), f1 = *reinterpret_cast<const v4f*>(&fac[8 * (6 + i) + 4]);
 #pragma unroll
                 for (int r = 0; r < 8; ++r) {
-                    const float kk = kv[r] * keep[i];
-                    const float e = (G[i][r / 4][r % 4] - An[i][r / 4][r % 4]) * LOG2E;
-                    u[r] = kk * __builtin_amdgcn_exp2f(e);
-                    v[i][r] = kk * __builtin_amdgcn_exp2f(-e);
+                    const float e = (G[i][r / 4][r % 4] - (r < 4 ? a0[r] : a1[r - 4])) * LOG2E;
+                    u[r] = kv[r] * __builtin_amdgcn_exp2f(e);
+                    v[i][r] = kv[r] * __builtin_amdgcn_exp2f(-e);
                     m[r] = (W == 1 ? u[r] : v[i][r]) * (r < 4 ? f0[r] : f1[r - 4]);
                 }
                 ppi[i] = gpack<OP>(u);
@@ -190,11 +202,19 @@ __device__ __forceinline__ void c128_kda_gram(char* xchg, float* tab, PreA<4>& p
                     for (int b = 0; b < 4; ++b) a21[b][o - 2] = gstep<OP>(dn_d, mine[b], a21[b][o - 2]);
                 }
             }
+            if (!AHEAD && s + 1 < n_step) load_gates(G_next, mid_next, s + 1);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                G[i][0] = G_next[i][0];
+                G[i][1] = G_next[i][1];
+            }
+            if (W == 0) mid = mid_next;
         }
     }
 }
 
-template <int OP, int METHOD, int W>
+// AHEAD: gate rows a k-step ahead (see c128_kda_gram); b0 = 32 with 16-bit operands has no registers left for them.
+template <int OP, int METHOD, bool K16, int W, bool AHEAD = METHOD != M_MIXED32 || OP == OP_F32 || !K16>
 __device__ __forceinline__ void c128_kda_invert(char* lds, const void* Kc, int kd, const float* gc, int64_t row_stride, const float* bc,
                                                 int64_t tok_stride, int d_k, int valid, int aux, Lane ln, v4f (&D)[10], v4f (&Wc)[2][4])
 {
@@ -205,7 +225,7 @@ __device__ __forceinline__ void c128_kda_invert(char* lds, const void* Kc, int k
     Opnd<OP>* t22_lds = reinterpret_cast<Opnd<OP>*>(lds + LY::T22);
     Opnd<OP>* t11_lds = reinterpret_cast<Opnd<OP>*>(lds + LY::T11);
     Opnd<OP>* a21_lds = reinterpret_cast<Opnd<OP>*>(lds + LY::XCHG);  // after the Gram passes: [b][d][lane], 16 packed tiles of A21
-    // beta of this lane's two tokens: in flight during the Gram passes
+    // beta of this lane's two tokens, requested ahead of everything else and left in LDS while the first keys are on their way
     float raw_b[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -214,13 +234,11 @@ __device__ __forceinline__ void c128_kda_invert(char* lds, const void* Kc, int k
     }
     PreA<4> pre;
     v4f acc21[4][2];
-    if (kd == OP_F32)
-        c128_kda_gram<OP, METHOD, false, W>(lds + LY::XCHG, tab, pre, acc21, Kc, false, gc, row_stride, d_k, ln, valid);
-    else
-        c128_kda_gram<OP, METHOD, true, W>(lds + LY::XCHG, tab, pre, acc21, Kc, kd == OP_F16, gc, row_stride, d_k, ln, valid);
+    c128_kda_gram<OP, METHOD, K16, W, AHEAD>(lds + LY::XCHG, tab, pre, acc21, Kc, kd == OP_F16, gc, row_stride, d_k, ln, valid, [&]() {
+        small[lane] = raw_b[0];
+        small[lane + 64] = raw_b[1];
+    });
     // beta_i row scaling and the strictly-lower mask
-    small[lane] = raw_b[0];
-    small[lane + 64] = raw_b[1];
     wave_lds_sync();
     Opnd<OP> a21[4][4];
 #pragma unroll
@@ -269,8 +287,10 @@ __device__ __forceinline__ void c128_kda_invert(char* lds, const void* Kc, int k
 
 // Fused kernel, per-channel gate, C = 128, any d_k (multiple of 32): blocked, mixed (b0 = 16, 32) and direct-leaf
 // recursion.  One workgroup of two wavefronts per matrix.
-template <int OP, int METHOD>
-__global__ __launch_bounds__(128) void k_kda_tri_inv_c128(const void* __restrict__ K, const float* __restrict__ beta,
+// K16: 16-bit keys (a kernel for either: with a branch for both in one the code of two key types and two wavefronts, 60 to 130 KB, does not
+// fit the 64 KB that two compute units keep of it).
+template <int OP, int METHOD, bool K16>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 1 : 2))) void k_kda_tri_inv_c128(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T, int64_t n_chunk,
                                                           ChunkMap map, int H, int d_k, int k_dt, int aux, int out_dt)
 {
@@ -284,16 +304,15 @@ __global__ __launch_bounds__(128) void k_kda_tri_inv_c128(const void* __restrict
     const int64_t tok0 = pos.tok0;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const Lane ln = lane_id();
-    const int64_t esz = (k_dt == OP_F32) ? 4 : 2;
     const int64_t e0 = (tok0 * H + h) * (int64_t)d_k;
-    const void* Kc = static_cast<const char*>(K) + e0 * esz;
+    const void* Kc = static_cast<const char*>(K) + e0 * (K16 ? 2 : 4);
     const Out Tm = out_matrix(T, m, C, out_dt);
     v4f D[10], Wc[2][4];
     if (w == 0) {
-        c128_kda_invert<OP, METHOD, 0>(lds, Kc, k_dt, g + e0, (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, pos.valid, aux, ln, D, Wc);
+        c128_kda_invert<OP, METHOD, K16, 0>(lds, Kc, k_dt, g + e0, (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, pos.valid, aux, ln, D, Wc);
         c128_store_result<0>(reinterpret_cast<v4f*>(lds + LY::MAIL), reinterpret_cast<float*>(lds + LY::STRIPS), Tm, D, Wc, ln);
     } else {
-        c128_kda_invert<OP, METHOD, 1>(lds, Kc, k_dt, g + e0, (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, pos.valid, aux, ln, D, Wc);
+        c128_kda_invert<OP, METHOD, K16, 1>(lds, Kc, k_dt, g + e0, (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, pos.valid, aux, ln, D, Wc);
         c128_store_result<1>(reinterpret_cast<v4f*>(lds + LY::MAIL), reinterpret_cast<float*>(lds + LY::STRIPS) + STORE_LDS_FLOATS, Tm, D,
                              Wc, ln);
     }
