@@ -9,10 +9,10 @@ namespace triinv {
 
 template <int OP, int METHOD, int NRHS> struct C128KdaSolveLds {
     typedef C128KdaLds<OP, METHOD> INV;
-    static constexpr int TILES = 0;  // after the recursion, in place of everything it kept: one set of 36 tiles per right-hand side
+    static constexpr int TILES = 0;  // after the recursion, in place of everything it kept
     static constexpr bool BY_ROWS = NRHS == 1;  // one right-hand side: split by rows (c128_apply_rows)
     static constexpr int XTOP = TileLds<OP>::BYTES;
-    static constexpr int APPLY = BY_ROWS ? XTOP + 16 * 64 * 16 : NRHS * TileLds<OP>::BYTES;
+    static constexpr int APPLY = BY_ROWS ? XTOP + 16 * 64 * 16 : c128_tile_sets<OP, NRHS>() * TileLds<OP>::BYTES;
     static constexpr int SCALE = INV::BYTES > APPLY ? INV::BYTES : APPLY;  // 128 floats per wave
     static constexpr int BYTES = SCALE + 2 * 128 * 4;
 };

@@ -258,10 +258,17 @@ template <int OP> struct TileLds {
     }
 };
 
+// Sets of published tiles for two right-hand sides: one each, published before the one barrier, with 16-bit operands.  fp32 tiles take
+// turns on one: two sets are 93 KB, one workgroup per compute unit and half of its SIMDs idle, and the registers that hold the inverse until
+// the second side's turn are there (220 with 16-bit keys; one wavefront per SIMD has 512).  Two sets / turns, d_k = d_x = 128: 1024
+// chunks 159 / 105 us, 2048 321 / 197; per-channel gate 240 / 132 and 492 / 261; 256 chunks 43 / 43 and 63 / 62.
+template <int OP, int NRHS> constexpr int c128_tile_sets() { return OP == OP_F32 ? 1 : NRHS; }
+
 template <int KD, int OP, int DKS, int METHOD, int NRHS> struct C128SolveLds {
     typedef C128Lds<KD, OP, DKS, METHOD, false> INV;
-    static constexpr int TILES = 0;  // after the recursion, in place of the keys: one set of 36 tiles per right-hand side
-    static constexpr int SCALE = INV::BYTES > NRHS * TileLds<OP>::BYTES ? INV::BYTES : NRHS * TileLds<OP>::BYTES;  // 128 floats per wave
+    static constexpr int TILES = 0;  // after the recursion, in place of the keys
+    static constexpr int TILE_BYTES = c128_tile_sets<OP, NRHS>() * TileLds<OP>::BYTES;
+    static constexpr int SCALE = INV::BYTES > TILE_BYTES ? INV::BYTES : TILE_BYTES;  // 128 floats per wave
     static constexpr int BYTES = SCALE + 2 * 128 * 4;
 };
 
@@ -332,10 +339,10 @@ __device__ __forceinline__ void c128_publish_tiles(typename TileLds<OP>::elem* s
 
 // The inverse (D: this wave's diagonal block, Wc: its two tile columns of the off-diagonal block, as the recursion leaves
 // them) applied to NRHS right-hand sides.  The sides share the inverse: its tiles are published once per right-hand side
-// (their columns scaled by that side's s), all sets before the one barrier, so that nothing of the inverse stays in
-// registers afterwards.  x: initialised for the first right-hand side, its first column group (W) already requested
+// (their columns scaled by that side's s), with 16-bit operands all sets before the one barrier, so that nothing of the inverse stays in
+// registers afterwards (see c128_tile_sets).  x: initialised for the first right-hand side, its first column group (W) already requested
 // (taken by value: through a reference its row registers ended up in scratch memory for fp32 operands).
-// tiles_lds: NRHS * TileLds<OP>::BYTES that both waves are done with when they arrive here (a barrier comes first);
+// tiles_lds: c128_tile_sets * TileLds<OP>::BYTES that both waves are done with when they arrive here (a barrier comes first);
 // scale_lds: 128 floats per wave.
 template <int OP, int W, int NRHS>
 __device__ __forceinline__ void c128_apply(char* tiles_lds, char* scale_lds, v4f (&D)[10], v4f (&Wc)[2][4], const float (&raw_s)[NRHS][2],
@@ -347,14 +354,16 @@ __device__ __forceinline__ void c128_apply(char* tiles_lds, char* scale_lds, v4f
     elem* tiles = reinterpret_cast<elem*>(tiles_lds);
     float* sc = reinterpret_cast<float*>(scale_lds) + 128 * W;
     constexpr int VEC = RhsHalf<OP>::VEC;
-    __syncthreads();  // nobody reads what the recursion kept where the tiles go
-#pragma unroll
-    for (int k = 0; k < NRHS; ++k) {
+    constexpr int SETS = c128_tile_sets<OP, NRHS>();
+    const auto publish = [&](int k) {
         float s_n[8];
         v4f s_q[4];
         c128_scale_patterns(sc, raw_s[k], s_n, s_q, ln);
-        c128_publish_tiles<OP, W>(tiles + k * 36 * TL::TILE_ELEMS, D, Wc, s_n, s_q, ln);
-    }
+        c128_publish_tiles<OP, W>(tiles + k % SETS * 36 * TL::TILE_ELEMS, D, Wc, s_n, s_q, ln);
+    };
+    __syncthreads();  // nobody reads what the recursion kept where the tiles go
+#pragma unroll
+    for (int k = 0; k < SETS; ++k) publish(k);
     __syncthreads();  // every tile is in LDS
 #pragma unroll
     for (int k = 0; k < NRHS; ++k) {
@@ -362,6 +371,11 @@ __device__ __forceinline__ void c128_apply(char* tiles_lds, char* scale_lds, v4f
             x.init(rhs.r[k], tok0, h, H, valid, ln);
             __builtin_amdgcn_sched_barrier(0);
             if (W < x.n_group()) x.issue(W);
+            if (SETS == 1) {
+                __syncthreads();  // the first side's tiles have been read
+                publish(k);
+                __syncthreads();
+            }
         }
         const int n_group = x.n_group();
 #pragma unroll 1
@@ -378,7 +392,7 @@ __device__ __forceinline__ void c128_apply(char* tiles_lds, char* scale_lds, v4f
             // no longer knows that it reads LDS, and the generic loads it then uses wait for every store of W before them)
             int hide = 0;
             asm volatile("" : "+v"(hide));
-            const elem* set = tiles + k * 36 * TL::TILE_ELEMS + hide;
+            const elem* set = tiles + k % SETS * 36 * TL::TILE_ELEMS + hide;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 v4f acc[VEC];

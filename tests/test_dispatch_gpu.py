@@ -193,3 +193,16 @@ def test_teams_of_wavefronts_in_the_channel_loops(C, d_k, k_dtype, op):
                     w = tri.gdn_chunk_tri_solve(*cut, C, gate_kind=gate)
                     rows = tokens if tokens < C else tokens // C * C
                     assert (w[:, :rows] - W[:, :rows]).abs().max() <= 2 * tol * W.abs().max()
+
+
+# Two right-hand sides at C = 128 with fp32 operands take turns on one set of published tiles: each side as if it were the only one.
+@pytest.mark.parametrize("gate", GATES)
+@pytest.mark.parametrize("k_dtype,d_k", [(torch.bfloat16, 128), (torch.float32, 64)])
+@pytest.mark.parametrize("T,d_x", [(128, 64), (300, 128), (131, 200), (7, 8)])
+def test_two_fp32_sides_at_c128(T, d_x, k_dtype, d_k, gate):
+    K, beta, g = make_inputs(T, 3, d_k, gate, k_dtype)
+    X1, X2 = (torch.randn(1, T, 3, w, device=DEV) for w in (d_x, 40))
+    W1, W2 = tri.gdn_chunk_tri_solve_multi(K, beta, g, [X1, X2], 128, row_scales=[beta, None], gate_kind=gate)
+    for X, s, W in ((X1, beta, W1), (X2, None, W2)):
+        one = tri.gdn_chunk_tri_solve(K, beta, g, X, 128, row_scale=s, gate_kind=gate)
+        assert (W - one).abs().max() <= 3e-6 * one.abs().max()  # the same fp32 products, summed tile by tile in another order
