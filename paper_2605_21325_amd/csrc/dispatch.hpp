@@ -67,6 +67,10 @@ constexpr int64_t FEW_MATRICES = 512;
 // four wavefronts, each with a share of its k-steps (32 channels).
 constexpr int TEAM_WAVES = 4;
 inline int team_waves(int64_t n_mat, int d_k) { return n_mat > FEW_MATRICES ? 1 : d_k / 32 < TEAM_WAVES ? d_k / 32 : TEAM_WAVES; }
+// fp32 keys of 128 channels go the same way at C = 64 although that head dimension has a kernel of its own: their Gram products are fp32
+// matrix instructions, 6 of the 11.5 us of such a call.  Up to one team per compute unit: 256 matrices 11.7 / 10.5 us (own kernel / team; bf16
+// operands 9.8 / 8.8, one right-hand side applied 17.9 / 16.5), 512 12.8 / 12.8; with 64 channels, two to a team, 9.4 / 9.3 and 9.9 / 11.8.
+inline bool fp32_keys_by_team(int64_t n_mat, int d_k, int C) { return C == 64 && d_k == 128 && n_mat <= FEW_MATRICES / 2; }
 inline unsigned team_bytes(int waves, int tiles) { return (unsigned)(waves - 1) * (unsigned)tiles * 1024u; }
 struct FusedGrid {
     unsigned groups, threads;

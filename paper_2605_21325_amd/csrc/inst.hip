@@ -349,6 +349,9 @@ int CAT(launch_gdn_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const GdnArg
     return 1;
 #else
     if (a.k_dt == OP_F32) {
+#if TRIINV_INST_NB <= 4
+        if (fp32_keys_by_team(a.n_mat, a.d_k, 16 * NB) && !a.refine) return any_dk_method<OP_F32>(a);
+#endif
         if (a.d_k == 64) return gdn_method<OP_F32, 4>(a);
 #if TRIINV_INST_NB <= 4
         if (a.d_k == 128) return gdn_method<OP_F32, 8>(a);

@@ -65,7 +65,6 @@ template <int KD, int METHOD, int DKS> static int go_gdn(const SolveArgs& a)
                                        f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters)
                        : launch_kernel(f.dry, k_gdn_tri_solve_c128_rows<KD, OP, METHOD, DKS, true>, dim3((unsigned)f.n_mat), dim3(128), 0,
                                        f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
-    // (fp32 operands: the two sets of fp32 tiles take 93 KB of LDS, one workgroup per compute unit)
     if (a.n_rhs == 2)
         return f.g ? launch_kernel(f.dry, k_gdn_tri_solve_c128<KD, OP, METHOD, DKS, 2, false>, dim3((unsigned)f.n_mat), dim3(128), 0, f.stream,
                                    f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters)
@@ -160,6 +159,9 @@ int CAT(launch_solve_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP)(const SolveArgs& a
         return 1;
     }
     if (f.k_dt == OP_F32) {
+#if TRIINV_INST_NB <= 4
+        if (fp32_keys_by_team(f.n_mat, f.d_k, 16 * NB)) return any_dk_method<OP_F32>(a);
+#endif
         if (f.d_k == 64) return gdn_method<OP_F32, 4>(a);
 #if TRIINV_INST_NB <= 4
         if (f.d_k == 128) return gdn_method<OP_F32, 8>(a);
