@@ -313,9 +313,15 @@ static int kda_method(const GdnArgs& a)
 // recursion from directly solved blocks at C = 128.
 template <int KD, int METHOD> static int go_any_dk(const GdnArgs& a)
 {
-    const int team = any_dk_team<NB>() > 1 ? team_waves(a.n_mat, a.d_k) : 1;
-    return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD>, dim3((unsigned)a.n_mat), dim3(64 * team),
-                         team_bytes(team, gram_tiles<NB, METHOD>()), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt, team);
+    if constexpr (NB <= 4) {
+        const int team = team_waves(a.n_mat, a.d_k);
+        if (team > 1)
+            return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, true>, dim3((unsigned)a.n_mat), dim3(64 * team),
+                                 team_bytes(team, gram_tiles<NB, METHOD>()), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters,
+                                 a.out_dt);
+    }
+    return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, false>, dim3((unsigned)a.n_mat), dim3(64), 0, a.stream, a.K, a.beta,
+                       a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
 }
 
 template <int KD> static int any_dk_method(const GdnArgs& a)

@@ -556,7 +556,7 @@ template <int NB, int METHOD> __device__ __forceinline__ bool team_sum(PreA<NB>&
 // Kernel time, bf16 keys of d_k = 128, C = 64, loads in the k-step itself / a step ahead: 256 matrices 11.6 / 10.9 us, 1024 18.5 / 15.6, 16384
 // 214 / 201; one right-hand side, 1024 20.6 / 17.8; fp32 operands, 1024 27.3 / 24.5, d_k = 256 30.0 / 23.8.
 // ahead = false: not so, for calls that fill the chip many times over and keep fewer bytes of keys than of gates in flight this way
-// (fp32 keys, fp32 operands at C = 32).  C = 16 has wavefronts enough without.
+// (fp32 keys, fp32 operands at C = 32).  C = 16 has a form of its own, accumulate_gated_gram16.
 template <int OPG, int NB, int METHOD, bool K16>
 __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, Steps steps,
                                                         Lane ln, int valid, float* tab, bool ahead)
@@ -565,7 +565,7 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
     constexpr int STEPS = K16 ? 2 : 1;
     constexpr bool KEYS_AHEAD = K16 && (NB == 4 || (NB == 2 && OPG != OP_F32));  // elsewhere they would cost a wavefront per SIMD
     if (KEYS_AHEAD) ahead = true;
-    if (NB == 1 || METHOD == M_NEWTON_SCHULZ + WITH_REFINE) ahead = false;       // (which has no registers left for them)
+    if (METHOD == M_NEWTON_SCHULZ + WITH_REFINE) ahead = false;                  // (which has no registers left for them)
     const int n_step = steps.end;
     int rowc[NB];
     float keep[NB];
@@ -626,7 +626,7 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
             // lanes of a row group need the same; each computes a share of the table) instead
             // of once per row: 67 exponentials per lane and k-step at C = 64 instead of 112, and no subtraction or scaling
             // of the exponent per pair either.
-            if constexpr (NP > 0) {
+            {
 #pragma unroll
                 for (int k = 0; k < (NE + 15) / 16; ++k) {
                     const int e = ln.n + 16 * k, p = e >> 3, r = e & 7;
@@ -686,13 +686,51 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
     }
 }
 
+// C = 16: one tile row, whose only anchor every lane loads, and wavefronts enough to hide the loads of one behind the others' work (through
+// LDS and a step ahead as above, 1792 matrices of d_k = 256: 11.8 us against 10.6).
+template <int OPG, int METHOD, bool K16>
+__device__ __forceinline__ void accumulate_gated_gram16(PreA<1>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, Steps steps,
+                                                        Lane ln, int valid)
+{
+    constexpr float LOG2E = 1.44269504088896340736f;
+    constexpr int STEPS = K16 ? 2 : 1;
+    const int64_t row = (int64_t)(ln.n < valid ? ln.n : valid - 1) * row_stride + 8 * ln.q;
+    const float keep = ln.n < valid ? 1.f : 0.f;
+    for (int s0 = steps.begin; s0 < steps.end; s0 += STEPS) {
+        RawKey8<K16> raw[STEPS];
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t)
+            if (s0 + t < steps.end) raw[t] = load_key8<K16>(Kc, row + 32 * (s0 + t));
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+            if (s0 + t >= steps.end) break;
+            const float *const g = gc + row + 32 * (s0 + t), *const a = gc + 8 * ln.q + 32 * (s0 + t);
+            const v4f G[2] = {*reinterpret_cast<const v4f*>(g), *reinterpret_cast<const v4f*>(g + 4)};
+            const v4f A[2] = {*reinterpret_cast<const v4f*>(a), *reinterpret_cast<const v4f*>(a + 4)};
+            float kv[8], up[8], dn[8];
+            widen_key8<K16>(raw[t], is_f16, kv);
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const float kk = kv[r] * keep;
+                const float e = (G[r / 4][r % 4] - A[r / 4][r % 4]) * LOG2E;
+                up[r] = kk * __builtin_amdgcn_exp2f(e);
+                dn[r] = kk * __builtin_amdgcn_exp2f(-e);
+            }
+            const GOp<OPG> u = gpack<OPG>(up), v = gpack<OPG>(dn);
+            if (need_tile<1, METHOD>(0, 0, false)) out.n[0] = gstep<OPG>(u, v, out.n[0]);
+            if (need_tile<1, METHOD>(0, 0, true)) out.t[0] = gstep<OPG>(v, u, out.t[0]);
+        }
+    }
+}
+
 // The general form: C = 128 and, with GATED = false, no per-channel gate (the stored keys themselves are the operands, OPG = their type,
 // exact products, and gc is not read): the any-d_k path of the scalar / no-gate kinds.
 template <int OPG, int NB, int METHOD, bool K16, bool GATED = true>
 __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc,
                                                       int64_t row_stride, Steps steps, Lane ln, int valid, float* tab = nullptr, bool ahead = true)
 {
-    if constexpr (GATED && NB <= 4) return accumulate_gated_gram64<OPG, NB, METHOD, K16>(out, Kc, is_f16, gc, row_stride, steps, ln, valid, tab, ahead);
+    if constexpr (GATED && NB == 1) return accumulate_gated_gram16<OPG, METHOD, K16>(out, Kc, is_f16, gc, row_stride, steps, ln, valid);
+    else if constexpr (GATED && NB <= 4) return accumulate_gated_gram64<OPG, NB, METHOD, K16>(out, Kc, is_f16, gc, row_stride, steps, ln, valid, tab, ahead);
     constexpr int C = 16 * NB;
     [[maybe_unused]] constexpr float LOG2E = 1.44269504088896340736f;
     constexpr int STEPS = (K16 && NB <= 4) ? 2 : 1;  // C = 128 has no registers to spare for the pairing
@@ -1282,7 +1320,6 @@ __device__ __forceinline__ Team this_team(int size)
     extern __shared__ __attribute__((aligned(16))) float team_tiles[];
     return Team{size > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0, size, team_tiles};
 }
-template <int NB> constexpr int any_dk_team() { return NB <= 4 ? TEAM_WAVES : 1; }
 // (Newton-Schulz at C = 64, with fp32 operands or the refinement step, has no register left for it)
 template <int OP, int NB, int METHOD, bool REFINE> constexpr bool kda_team() { return !(METHOD == M_NEWTON_SCHULZ && NB == 4 && (OP == OP_F32 || REFINE)); }
 
@@ -1474,11 +1511,12 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
 }
 
 // Fused kernel of the scalar / no-gate kinds for head dimensions without a specialised build.
-// team: wavefronts that form a matrix together (see Team), the workgroup's size.
-template <int KD, int OP, int NB, int METHOD>
-__global__ __launch_bounds__(64 * any_dk_team<NB>()) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+// TEAM: the workgroup's wavefronts form a matrix together (see Team; a kernel of its own: the other one lost 5 to 13 % of its speed with the
+// choice at run time).
+template <int KD, int OP, int NB, int METHOD, bool TEAM>
+__global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
-                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt, int team)
+                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt)
 {
     constexpr int C = 16 * NB;
     constexpr int CORE = core_lds_floats<NB, METHOD>();
@@ -1494,7 +1532,7 @@ __global__ __launch_bounds__(64 * any_dk_team<NB>()) __attribute__((amdgpu_waves
     PreA<NB> src;
     if (!build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
                                                beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid,
-                                               this_team(any_dk_team<NB>() > 1 ? team : 1)))
+                                               this_team(TEAM ? (int)blockDim.x / 64 : 1)))
         return;
     invert_and_store<OP, NB, METHOD, PreA<NB>, false>(src, out_matrix(T, m, C, out_dt), lds, ln, aux);
 }

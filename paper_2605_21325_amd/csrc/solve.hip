@@ -125,18 +125,17 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
 
 #if TRIINV_INST_NB <= 4
 // Head dimensions other than 64 / 128 (scalar / no-gate kinds), C <= 64.
-template <int KD, int METHOD> static int go_any_dk(const SolveArgs& a)
+template <int KD, int METHOD, int NRHS, bool TEAM> static int launch_any_dk(const SolveArgs& a, int team)
 {
     const GdnArgs& f = a.f;
-    const int team = team_waves(f.n_mat, f.d_k);
-    const dim3 grid((unsigned)f.n_mat), block(64 * team);
-    const unsigned lds = team_bytes(team, gram_tiles<NB, METHOD>());
-    if (a.n_rhs == 1)
-        return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, 1>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
-                           f.map, f.H, f.d_k, f.iters, team);
-    else
-        return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, 2>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
-                             f.map, f.H, f.d_k, f.iters, team);
+    return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, NRHS, TEAM>, dim3((unsigned)f.n_mat), dim3(64 * team),
+                         team_bytes(team, gram_tiles<NB, METHOD>()), f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
+}
+template <int KD, int METHOD> static int go_any_dk(const SolveArgs& a)
+{
+    const int team = team_waves(a.f.n_mat, a.f.d_k);
+    if (a.n_rhs == 1) return team > 1 ? launch_any_dk<KD, METHOD, 1, true>(a, team) : launch_any_dk<KD, METHOD, 1, false>(a, 1);
+    return team > 1 ? launch_any_dk<KD, METHOD, 2, true>(a, team) : launch_any_dk<KD, METHOD, 2, false>(a, 1);
 }
 
 template <int KD> static int any_dk_method(const SolveArgs& a)

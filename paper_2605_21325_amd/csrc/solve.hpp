@@ -373,10 +373,10 @@ __global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restri
 
 // Scalar / no-gate kinds for head dimensions without a specialised build (any multiple of 32): the channel-loop Gram of
 // the storing kernel, then the same recursion and products.  One wavefront per workgroup.
-template <int KD, int OP, int NB, int METHOD, int NRHS>
-__global__ __launch_bounds__(64 * any_dk_team<NB>()) void k_gdn_any_dk_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
+template <int KD, int OP, int NB, int METHOD, int NRHS, bool TEAM>
+__global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) void k_gdn_any_dk_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
                                                              const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
-                                                             int H, int d_k, int aux, int team)
+                                                             int H, int d_k, int aux)
 {
     constexpr int C = 16 * NB;
     constexpr int CORE = SOLVE_LDS_FLOATS;
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(64 * any_dk_team<NB>()) void k_gdn_any_dk_tri_solve
     const int64_t esz = (KD == OP_F32) ? 4 : 2;
     PreA<NB> src;
     if (!build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
-                                               beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid, this_team(team)))
+                                               beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid, this_team(TEAM ? (int)blockDim.x / 64 : 1)))
         return;
     RhsX<OP, NB> x;
     x.init(rhs.r[0], tok0, h, H, pos.valid, ln);
