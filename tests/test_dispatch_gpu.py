@@ -206,3 +206,18 @@ def test_two_fp32_sides_at_c128(T, d_x, k_dtype, d_k, gate):
     for X, s, W in ((X1, beta, W1), (X2, None, W2)):
         one = tri.gdn_chunk_tri_solve(K, beta, g, X, 128, row_scale=s, gate_kind=gate)
         assert (W - one).abs().max() <= 3e-6 * one.abs().max()  # the same fp32 products, summed tile by tile in another order
+
+
+# The offsets of packed sequences travel as arguments of three sizes (up to 15, 63 and 229 sequences) and, beyond, of several launches.
+@pytest.mark.parametrize("n_seq", [1, 15, 16, 63, 64, 229, 230, 500])
+def test_offsets_of_packed_sequences_in_blocks(n_seq):
+    lens = [1 + (7 * i) % 37 for i in range(n_seq)]
+    K, beta, g = (x[0] for x in make_inputs(sum(lens), 2, 64, tri.GATE_SCALAR))
+    T = tri.gdn_chunk_tri_inv_varlen(K, beta, g, lens, 16)
+    start = chunk = 0
+    for n in lens:
+        part = [x[start:start + n][None].clone() for x in (K, beta, g)]  # (16-byte aligned)
+        one = tri.gdn_chunk_tri_inv_ex(*part, 16)
+        assert torch.equal(T[chunk:chunk + one.shape[0]], one)
+        start, chunk = start + n, chunk + one.shape[0]
+    assert chunk == T.shape[0]
