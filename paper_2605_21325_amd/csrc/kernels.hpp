@@ -503,6 +503,7 @@ template <bool K16> __device__ __forceinline__ void widen_key8(const RawKey8<K16
 // its second half is still cached when needed (requested one k-step apart, lines were found
 // evicted in between and fetched from HBM twice).
 // Kc / gc: element (chunk row 0, this head, channel 0); row_stride in elements (same for both).
+// (fp32 keys, C = 64, gate rows ahead / not: 8192 matrices 123 / 126 us, 16384 250 / 242)
 constexpr int GATES_AHEAD_MATRICES = 8192;
 // The k-steps (of 32 channels) a wavefront takes.
 struct Steps {
