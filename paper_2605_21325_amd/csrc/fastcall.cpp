@@ -4,7 +4,10 @@
 // A function returns the result, or None when anything about its arguments is not plain (no exact torch.Tensor on the current
 // device, not contiguous, another number of dimensions or element type, a chunk size there is no kernel for, an argument of the
 // wrong kind) or when the C-ABI refused the call.  Nothing has been launched then, and the caller goes through the Python route, which
-// raises what there is to raise: this file has no error messages of its own.
+// raises what there is to raise: this file has no error messages of its own.  The same goes for C++ exceptions: libtorch throws them for
+// tensors that do not have what they are asked for, and none may pass the C boundary to the interpreter.
+//
+// Device -1 stands for host memory: not for the library, whose kernels cannot read it, but for tests with a stand-in for the C-ABI.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <ATen/core/Tensor.h>
@@ -57,8 +60,8 @@ public:
         if (!ok_ || (none && o == Py_None)) return {};
         if (!THPVariable_CheckExact(o)) return fail(), at::Tensor();
         at::Tensor t = THPVariable_Unpack(o);
-        if (!t.is_cuda() || t.get_device() != device_ || t.layout() != at::kStrided || !t.is_contiguous() || (dims >= 0 && t.dim() != dims) ||
-            code_of(t.scalar_type()) < 0)
+        if ((device_ < 0 ? !t.is_cpu() : !t.is_cuda() || t.get_device() != device_) || t.is_nested() || t.layout() != at::kStrided ||
+            !t.is_contiguous() || (dims >= 0 && t.dim() != dims) || code_of(t.scalar_type()) < 0)
             return fail(), at::Tensor();
         return t;
     }
@@ -334,7 +337,18 @@ PyObject* connect(PyObject*, PyObject* const* v, Py_ssize_t n)
     Py_RETURN_NONE;
 }
 
-#define TRIINV_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr}
+// f with its exceptions turned into None.
+template <PyObject* (*f)(PyObject*, PyObject* const*, Py_ssize_t)> PyObject* guarded(PyObject* self, PyObject* const* v, Py_ssize_t n) noexcept
+{
+    try {
+        return f(self, v, n);
+    } catch (...) {
+        PyErr_Clear();  // (an exception that came from Python code may have left its error set)
+        return none();
+    }
+}
+
+#define TRIINV_METHOD(f) {#f, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<f>)), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {TRIINV_METHOD(connect), TRIINV_METHOD(tri_inv), TRIINV_METHOD(gdn_inv), TRIINV_METHOD(gdn_solve),
                          TRIINV_METHOD(gdn_inv_varlen), TRIINV_METHOD(gdn_solve_varlen), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

@@ -1,0 +1,111 @@
+"""The binding's native argument handling (csrc/fastcall.cpp) without a GPU: host tensors (device -1) and a stand-in for the C-ABI that
+records the calls it gets."""
+import ctypes
+import importlib.util
+import os
+import shutil
+
+import pytest
+import torch
+
+import paper_2605_21325_amd as tri
+from paper_2605_21325_amd import build as tri_build
+
+# as in csrc/fastcall.cpp, struct Abi
+P, I, L, U = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64, ctypes.c_uint32
+ABI = {
+    "tri_inv_ex": (P, P, L, I, I, I, I, P, U),
+    "inv_ex": (P, P, P, P, I, L, I, I, I, I, I, I, I, P, U),
+    "inv_varlen": (P, P, P, P, P, P, I, L, L, I, I, I, I, I, I, I, P, U),
+    "solve_multi": (P, P, P, I, P, P, P, P, I, L, I, I, I, I, I, I, I, P, U),
+    "solve_varlen": (P, P, P, P, P, P, P, P, I, L, L, I, I, I, I, I, I, I, I, P, U),
+    "offsets": (P, I, I, L, P, P, P),
+}
+
+
+class Native:
+    """The module, connected to the stand-in.  calls: (function, arguments) as they arrive; status: what the stand-in answers."""
+    def __init__(self, path):
+        spec = importlib.util.spec_from_file_location("_fastcall", path)
+        self.module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(self.module)
+        self.calls, self.status, self.keep = [], 0, []
+        for name, types in ABI.items():
+            self.keep.append(ctypes.CFUNCTYPE(I, *types)(lambda *a, name=name: self.answer(name, a)))
+        self.module.connect(*(ctypes.cast(f, P).value for f in self.keep))
+
+    def answer(self, name, args):
+        self.calls.append((name, args))
+        if name == "offsets":
+            lens, n, C, total, _, n_chunk, _ = args
+            lens = ctypes.cast(lens, ctypes.POINTER(L))[:n]
+            if sum(lens) != total:
+                return -5
+            ctypes.cast(n_chunk, ctypes.POINTER(L))[0] = sum(-(-x // C) for x in lens)
+            return 0
+        return self.status
+
+
+@pytest.fixture
+def native(tmp_path):
+    if not os.path.exists(tri_build.FASTCALL):
+        tri_build.build_fastcall()
+    copy = str(tmp_path / "_fastcall.so")  # a copy: the module a process has connected to the library stays as it is
+    shutil.copy(tri_build.FASTCALL, copy)
+    return Native(copy)
+
+
+def tri_inv(n, A, T=None, method=1, op=None, flags=0, out=None):
+    return n.module.tri_inv(-1, 0, A, T, method, op, flags, out)
+
+
+def gdn_inv(n, K, beta, g, C=64, T=None):
+    return n.module.gdn_inv(-1, 0, K, beta, g, C, T, tri.GATE_SCALAR, 1, tri.BF16, 0, None)
+
+
+def keys(*shape):
+    return torch.randn(*shape).bfloat16(), torch.rand(shape[:-1]), -torch.rand(shape[:-1])
+
+
+def nested(*shapes, dtype=torch.float32):
+    return torch.nested.nested_tensor([torch.randn(s, dtype=dtype) for s in shapes])
+
+
+def test_plain_calls_reach_the_library(native):
+    A = torch.randn(3, 64, 64)
+    T = tri_inv(native, A, op=tri.F32)
+    assert T.shape == A.shape and T.dtype == torch.float32
+    (name, a), = native.calls
+    assert (name, a[0], a[1], a[2:7]) == ("tri_inv_ex", A.data_ptr(), T.data_ptr(), (3, 64, tri.F32, 1, tri.F32))
+    K, beta, g = keys(2, 130, 4, 64)
+    assert gdn_inv(native, K, beta, g).shape == (24, 64, 64)
+    native.status = -9  # refused: None, and the Python route reports it
+    assert tri_inv(native, A, op=tri.F32) is None
+
+
+# libtorch throws when a nested tensor is asked for a size: nothing of that may reach the interpreter as a C++ exception (it ends the
+# process), and no nested tensor is taken, whatever its parts' shapes.
+@pytest.mark.filterwarnings("ignore:The PyTorch API of nested tensors")
+@pytest.mark.parametrize("shapes", [((64, 64), (32, 32)), ((64, 64), (64, 64))], ids=["ragged", "uniform"])
+def test_nested_tensors_are_left_to_the_python_route(native, shapes):
+    assert tri_inv(native, nested(*shapes), op=tri.F32) is None
+    assert tri_inv(native, torch.randn(2, 64, 64), T=nested(*shapes), op=tri.F32) is None
+    K, beta, g = keys(2, 130, 4, 64)
+    ragged = nested((130, 4, 64), (shapes[1][0] + 66, 4, 64), dtype=torch.bfloat16)
+    assert gdn_inv(native, ragged, beta, g) is None
+    solve = lambda K, X, W=None: native.module.gdn_solve(-1, 0, K, beta, g, (X,), 64, None, None if W is None else (W,), 0, 1, 0)
+    assert solve(K, ragged) is None and solve(ragged, K) is None and solve(K, K, ragged) is None
+    packed = nested((100, 64), (shapes[1][0] + 36, 64), dtype=torch.bfloat16)
+    assert native.module.gdn_inv_varlen(-1, 0, packed, beta, g, [200], 64, None, 0, 1, 2, 0, None) is None
+    P, b = torch.randn(200, 4, 64).bfloat16(), torch.rand(200, 4)
+    assert native.module.gdn_solve_varlen(-1, 0, P, b, b, packed, [200], 64, None, None, 0, 1, 0) is None
+    assert native.module.gdn_solve_varlen(-1, 0, P, b, b, P, [200], 64, None, packed, 0, 1, 0) is None
+    assert not native.calls
+
+
+@pytest.mark.filterwarnings("ignore")
+def test_tensors_of_a_functional_transform_are_left_to_the_python_route(native):
+    A, seen = torch.randn(2, 3, 64, 64), []
+    torch.func.vmap(lambda a: (seen.append(tri_inv(native, a, op=tri.F32)), a)[1])(A)
+    torch.func.jvp(lambda a: (seen.append(tri_inv(native, a, op=tri.F32)), a)[1], (A[0],), (A[0],))
+    assert seen == [None, None] and not native.calls
