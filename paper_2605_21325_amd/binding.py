@@ -158,7 +158,7 @@ def tri_inv(A: torch.Tensor, T: Optional[torch.Tensor] = None, method: int = BLO
     """T = (I + strict_lower(A))^{-1};  A [n_mat, C, C] fp32/fp16/bf16 on the GPU.  Short form of
     the C-ABI: operands in A's own type, default stream."""
     if _lib is _fast_lib and A.is_cuda:
-        r = _fast.tri_inv(_device_index(), 0, A, T, method, -1, 0, None)
+        r = _fast.tri_inv(_device_index(), 0, A, T, method, None, 0, None)
         if r is not None:
             return r
     n_mat, C, _ = A.shape
@@ -189,7 +189,7 @@ def tri_inv_ex(A: torch.Tensor, T: Optional[torch.Tensor] = None, method: int = 
                out_dtype: Optional[torch.dtype] = None) -> torch.Tensor:
     if _lib is _fast_lib and stream is None and A.is_cuda:
         dev = _device_index()
-        r = _fast.tri_inv(dev, _raw_stream(dev), A, T, method, -1 if op_dtype is None else op_dtype, flags, out_dtype)
+        r = _fast.tri_inv(dev, _raw_stream(dev), A, T, method, op_dtype, flags, out_dtype)
         if r is not None:
             return r
     n_mat, C, _ = A.shape

@@ -53,6 +53,8 @@ public:
         return x;
     }
     int small() { return narrow(integer()); }
+    // None stands for `otherwise`
+    int small_or(int otherwise) { return ok_ && *v_ == Py_None ? (next(), otherwise) : small(); }
     // a contiguous tensor on the device of the call, with `dims` dimensions (any number: -1); none: None may stand for it (undefined tensor)
     at::Tensor tensor(int dims, bool none = false) { return as_tensor(next(), dims, none); }
     at::Tensor as_tensor(PyObject* o, int dims, bool none = false)
@@ -125,24 +127,23 @@ template <class F> bool unlocked(F f)
 
 PyObject* none() { Py_RETURN_NONE; }
 
-// (device, stream, A, T, method, op_dtype or -1 for A's own, flags, out_dtype)
+// (device, stream, A, T, method, op_dtype or None for A's own, flags, out_dtype)
 PyObject* tri_inv(PyObject*, PyObject* const* v, Py_ssize_t n)
 {
     Args a(v, n, 8);
     a.device_and_stream();
     const at::Tensor A = a.tensor(3);
     at::Tensor T = a.tensor(-1, true);
-    const int method = a.small(), op = a.small();
+    const int in = A.defined() ? code_of(A.scalar_type()) : -1, method = a.small(), op = a.small_or(in);
     uint32_t flags = (uint32_t)a.small();
     bool given;
     const at::ScalarType type = a.dtype(given);
     if (!a.ok() || !chunk_ok((int)A.size(1)) || A.size(2) != A.size(1)) return none();
     const int64_t n_mat = A.size(0), C = A.size(1);
     if (T.defined() && T.numel() != A.numel()) return none();
-    const int in = code_of(A.scalar_type());
     if (!unlocked([&] {
             return result(T, {n_mat, C, C}, type, given, A, flags) &&
-                   abi.tri_inv_ex(A.data_ptr(), T.data_ptr(), n_mat, (int)C, in, method, op < 0 ? in : op, a.stream(), flags) == 0;
+                   abi.tri_inv_ex(A.data_ptr(), T.data_ptr(), n_mat, (int)C, in, method, op, a.stream(), flags) == 0;
         }))
         return none();
     return THPVariable_Wrap(T);

@@ -74,13 +74,16 @@ def _calls():
         "packed, lengths in a tensor": lambda: tri.gdn_chunk_tri_inv_varlen(P, pb, pg, torch.tensor(lens), 64),
         "packed solve": lambda: tri.gdn_chunk_tri_solve_varlen(P, pb, pg, px, lens, 64, row_scale=pb),
         "packed solve into W": lambda: tri.gdn_chunk_tri_solve_varlen(P, pb, pg, px, tuple(lens), 64, W=torch.empty_like(px)),
-        # refused
+    }
+    refused = {
         "chunk size": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, g, 48),
         "no gate": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, None, 64),
         "method": lambda: tri.tri_inv_ex(A, method=99),
         "flags": lambda: tri.tri_inv_ex(A, flags=1 << 20),
         "element type": lambda: tri.tri_inv_ex(A.double()),
         "keys of the short form": lambda: tri.gdn_chunk_tri_inv(K.float(), beta, g, 64),
+        "operand type": lambda: tri.tri_inv_ex(A, op_dtype=-1),
+        "operand type of keys": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, g, 64, op_dtype=-7),
         "result type": lambda: tri.tri_inv_ex(A, T=new(5, 64, 64), out_dtype=bf),
         "result type unknown": lambda: tri.tri_inv_ex(A, out_dtype=torch.int32),
         "not contiguous": lambda: tri.gdn_chunk_tri_inv_ex(K.transpose(0, 1), beta, g, 64),
@@ -97,11 +100,11 @@ def _calls():
         "negative length": lambda: tri.gdn_chunk_tri_inv_varlen(P, pb, pg, [64, -1, 67], 64),
         "length beyond 64 bits": lambda: tri.gdn_chunk_tri_solve_varlen(P, pb, pg, px, [1 << 70, 130], 64),
     }
-    return calls
+    return calls, refused
 
 
 def test_native_and_python_marshalling_agree(monkeypatch):
-    calls = _calls()
+    calls, refused = _calls()
     tri.lib()
     assert tri.binding._fast is not None, "the native argument handling is not built"
 
@@ -113,7 +116,7 @@ def test_native_and_python_marshalling_agree(monkeypatch):
         torch.cuda.synchronize()
         return r
 
-    for name, call in calls.items():
+    for name, call in {**calls, **refused}.items():
         taken = []
         with monkeypatch.context() as m:
             m.setattr(tri.binding, "_fast", _Watch(tri.binding._fast, taken))
@@ -121,7 +124,9 @@ def test_native_and_python_marshalling_agree(monkeypatch):
         with monkeypatch.context() as m:
             m.setattr(tri.binding, "_fast_lib", object())
             python = outcome(call)
-        if isinstance(python, tuple) and isinstance(python[0], type):
+        raised = isinstance(python, tuple) and isinstance(python[0], type)
+        assert raised == (name in refused), name
+        if raised:
             assert native == python and not any(taken), name
             continue
         assert type(native) is type(python), name

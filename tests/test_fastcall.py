@@ -109,3 +109,12 @@ def test_tensors_of_a_functional_transform_are_left_to_the_python_route(native):
     torch.func.vmap(lambda a: (seen.append(tri_inv(native, a, op=tri.F32)), a)[1])(A)
     torch.func.jvp(lambda a: (seen.append(tri_inv(native, a, op=tri.F32)), a)[1], (A[0],), (A[0],))
     assert seen == [None, None] and not native.calls
+
+
+# Only None asks for the matrices' own type; every number goes to the library, which refuses those that name no type.
+def test_operand_type_of_given_matrices(native):
+    A = torch.randn(2, 64, 64).bfloat16()
+    for op, want in ((None, tri.BF16), (tri.F32, tri.F32), (-1, -1), (-7, -7), (3, 3)):
+        native.calls.clear()
+        tri_inv(native, A, op=op)
+        assert native.calls[0][1][6] == want
