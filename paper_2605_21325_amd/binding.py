@@ -154,16 +154,23 @@ def _dev(t: torch.Tensor, name: str) -> int:
     return t.data_ptr()
 
 
+def _fp32_sized(T: torch.Tensor) -> None:
+    """The short forms write fp32: elements of 16 bits would leave the result half as much room as it takes."""
+    if T.element_size() < 4:
+        raise TypeError(f"T is {T.dtype}, the short form writes fp32; use the _ex form")
+
+
 def tri_inv(A: torch.Tensor, T: Optional[torch.Tensor] = None, method: int = BLOCK_RECURSIVE) -> torch.Tensor:
     """T = (I + strict_lower(A))^{-1};  A [n_mat, C, C] fp32/fp16/bf16 on the GPU.  Short form of
     the C-ABI: operands in A's own type, default stream."""
     if _lib is _fast_lib and A.is_cuda:
-        r = _fast.tri_inv(_device_index(), 0, A, T, method, None, 0, None)
+        r = _fast.tri_inv(_device_index(), 0, A, T, method, None, 0, torch.float32)
         if r is not None:
             return r
     n_mat, C, _ = A.shape
     if T is None:
         T = torch.empty((n_mat, C, C), dtype=torch.float32, device=A.device)
+    _fp32_sized(T)
     st = lib().tri_inv(_dev(A, "A"), _dev(T, "T"), n_mat, C, dtype_code(A.dtype), method)
     if st != OK:
         raise TriInvError(st, "tri_inv")
@@ -212,7 +219,7 @@ def gdn_chunk_tri_inv(K: torch.Tensor, beta: torch.Tensor, g: torch.Tensor, C: i
     """Fused build + invert, short form: bf16 keys [B, Tlen, H, d_k], scalar gate, blocked
     recursion with bf16 operands, default stream."""
     if _lib is _fast_lib and K.is_cuda and K.dtype == torch.bfloat16:
-        r = _fast.gdn_inv(_device_index(), 0, K, beta, g, C, T, GATE_SCALAR, BLOCK_RECURSIVE, BF16, 0, None)
+        r = _fast.gdn_inv(_device_index(), 0, K, beta, g, C, T, GATE_SCALAR, BLOCK_RECURSIVE, BF16, 0, torch.float32)
         if r is not None:
             return r
     B, Tlen, H, d_k = K.shape
@@ -220,6 +227,7 @@ def gdn_chunk_tri_inv(K: torch.Tensor, beta: torch.Tensor, g: torch.Tensor, C: i
         raise TypeError("the short form takes bf16 keys; use gdn_chunk_tri_inv_ex")
     if T is None:
         T = torch.empty((_n_mat(K, C), C, C), dtype=torch.float32, device=K.device)
+    _fp32_sized(T)
     st = lib().gdn_chunk_tri_inv(_dev(K, "K"), _dev(beta, "beta"), _dev(g, "g"), _dev(T, "T"), B, Tlen, H, d_k, C)
     if st != OK:
         raise TriInvError(st, "gdn_chunk_tri_inv")

@@ -82,6 +82,8 @@ def _calls():
         "flags": lambda: tri.tri_inv_ex(A, flags=1 << 20),
         "element type": lambda: tri.tri_inv_ex(A.double()),
         "keys of the short form": lambda: tri.gdn_chunk_tri_inv(K.float(), beta, g, 64),
+        "16-bit T of the short forms": lambda: tri.tri_inv(A, T=new(5, 64, 64, dt=bf)),
+        "16-bit T of the short forms, keys": lambda: tri.gdn_chunk_tri_inv(K, beta, g, 64, T=new(24, 64, 64, dt=torch.float16)),
         "operand type": lambda: tri.tri_inv_ex(A, op_dtype=-1),
         "operand type of keys": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, g, 64, op_dtype=-7),
         "result type": lambda: tri.tri_inv_ex(A, T=new(5, 64, 64), out_dtype=bf),

@@ -118,3 +118,28 @@ def test_operand_type_of_given_matrices(native):
         native.calls.clear()
         tri_inv(native, A, op=op)
         assert native.calls[0][1][6] == want
+
+
+# The short forms write fp32, so neither route takes a T of 16-bit elements (the Python route would write past its end).
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_short_forms_refuse_a_result_of_16_bits(monkeypatch, native, dtype):
+    A = torch.randn(2, 64, 64)
+    K, beta, g = keys(1, 128, 2, 64)
+    T = torch.zeros(4, 64, 64, dtype=dtype)
+    answers = []
+
+    class Watch:  # as the binding calls it, for host tensors
+        def __getattr__(self, name):
+            def call(dev, stream, *a):
+                answers.append(getattr(native.module, name)(-1, 0, *a))
+                return answers[-1]
+            return call
+
+    monkeypatch.setattr(tri.binding, "_fast", Watch())
+    monkeypatch.setattr(tri.binding, "_fast_lib", tri.binding._lib)
+    monkeypatch.setattr(tri.binding, "_device_index", lambda: 0)
+    monkeypatch.setattr(torch.Tensor, "is_cuda", property(lambda t: True))
+    for call in (lambda: tri.tri_inv(A, T=T[:2]), lambda: tri.gdn_chunk_tri_inv(K, beta, g, 64, T=T)):
+        with pytest.raises(TypeError, match="writes fp32"):
+            call()
+    assert answers == [None, None] and not native.calls
