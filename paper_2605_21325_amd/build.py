@@ -3,7 +3,8 @@
 One translation unit per (C, operand type) pair plus the C-ABI file, compiled in parallel and
 linked into paper_2605_21325_amd/libtriinv.so.  Packed-fp32 code generation is switched off
 for every device compile.  Beside it the host compiler builds the binding's native argument
-handling, paper_2605_21325_amd/_fastcall.so.
+handling, paper_2605_21325_amd/_fastcall.so, from Python's and torch's headers; the binding does without it
+where that fails.
 """
 from __future__ import annotations
 
@@ -13,6 +14,7 @@ import re
 import subprocess
 import sys
 import sysconfig
+import warnings
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -85,15 +87,24 @@ def build_fastcall() -> str:
     return FASTCALL
 
 
+def _current(path: str) -> bool:
+    return os.path.exists(path) and os.path.getmtime(path) >= _sources_mtime()
+
+
 def build(force: bool = False, jobs: int = 0) -> str:
-    if not force and all(os.path.exists(f) and os.path.getmtime(f) >= _sources_mtime() for f in (LIB, FASTCALL)):
+    if force or not _current(FASTCALL):
+        try:
+            build_fastcall()
+        except Exception as e:  # no host compiler, no headers: slower calls, the same results
+            if os.path.exists(FASTCALL):
+                os.remove(FASTCALL)  # of older sources
+            warnings.warn(f"the native argument handling is not built: {e}")
+    if not force and _current(LIB):
         return LIB
     os.makedirs(OBJ, exist_ok=True)
     jobs = jobs or min(len(UNITS), os.cpu_count() or 4, 16)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        fastcall = ex.submit(build_fastcall)
         results = list(ex.map(_compile, UNITS))
-        fastcall.result()
     objs = [o for o, _ in results]
     resources = {}
     for _, res in results:

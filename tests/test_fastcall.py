@@ -143,3 +143,24 @@ def test_short_forms_refuse_a_result_of_16_bits(monkeypatch, native, dtype):
         with pytest.raises(TypeError, match="writes fp32"):
             call()
     assert answers == [None, None] and not native.calls
+
+
+# The library does not need the native argument handling: where that does not compile, the build says so and links the library.
+def test_the_library_is_built_without_the_native_argument_handling(monkeypatch, tmp_path):
+    done = []
+    monkeypatch.setattr(tri_build, "FASTCALL", str(tmp_path / "_fastcall.so"))
+    open(tri_build.FASTCALL, "w").close()
+    os.utime(tri_build.FASTCALL, (0, 0))
+    monkeypatch.setattr(tri_build, "LIB", str(tmp_path / "libtriinv.so"))
+    monkeypatch.setattr(tri_build, "RESOURCES", str(tmp_path / "resources.json"))
+    monkeypatch.setattr(tri_build, "OBJ", str(tmp_path / "obj"))
+    monkeypatch.setattr(tri_build, "HIPCC", "true")  # the link
+    monkeypatch.setattr(tri_build, "_compile", lambda unit: (done.append(unit), (str(tmp_path / "unit.o"), {}))[1])
+    monkeypatch.setenv("CXX", "false")
+    with pytest.warns(UserWarning, match="native argument handling is not built"):
+        assert tri_build.build() == tri_build.LIB
+    assert len(done) == len(tri_build.UNITS) and not os.path.exists(tri_build.FASTCALL)  # (one of older sources is not left either)
+    open(tri_build.LIB, "w").close()
+    with pytest.warns(UserWarning, match="native argument handling is not built"):
+        tri_build.build()
+    assert len(done) == len(tri_build.UNITS)  # the library is current: it is not compiled again
