@@ -107,7 +107,10 @@ def _connect(L: ctypes.CDLL) -> None:
         return
     try:
         from . import _fastcall
-    except ImportError:  # not built, or for another torch
+    except ImportError:  # not built
+        return
+    from .build import fastcall_stamp
+    if getattr(_fastcall, "BUILT_FOR", None) != fastcall_stamp():  # its inlined torch headers would misread this torch's tensors
         return
     _fastcall.connect(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.tri_inv_ex, L.gdn_chunk_tri_inv_ex, L.gdn_chunk_tri_inv_varlen, L.gdn_chunk_tri_solve_multi, L.gdn_chunk_tri_solve_varlen,

@@ -74,12 +74,18 @@ def _compile(unit):
     return out, _parse_resources(r.stderr)
 
 
+def fastcall_stamp() -> str:
+    """The Python and the torch whose headers a module is built from: it reads their objects through inline functions."""
+    import torch
+    return f"triinv fastcall, Python {sys.hexversion:08x}, torch {torch.__version__} {torch.version.git_version}"
+
+
 def build_fastcall() -> str:
     import torch
     root = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f"-I{sysconfig.get_paths()['include']}",
-           f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL,
+           f'-DTRIINV_BUILT_FOR="{fastcall_stamp()}"', f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", os.path.join(CSRC, "fastcall.cpp"), "-o", FASTCALL,
            f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -91,8 +97,15 @@ def _current(path: str) -> bool:
     return os.path.exists(path) and os.path.getmtime(path) >= _sources_mtime()
 
 
+def _fastcall_current() -> bool:
+    if not _current(FASTCALL):
+        return False
+    with open(FASTCALL, "rb") as f:
+        return fastcall_stamp().encode() in f.read()
+
+
 def build(force: bool = False, jobs: int = 0) -> str:
-    if force or not _current(FASTCALL):
+    if force or not _fastcall_current():
         try:
             build_fastcall()
         except Exception as e:  # no host compiler, no headers: slower calls, the same results

@@ -356,4 +356,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fastcall", nullptr, -1, methods, 
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fastcall() { return PyModule_Create(&module); }
+// BUILT_FOR: the Python and the torch whose headers this was compiled with; the binding compares them with the ones it runs in.
+PyMODINIT_FUNC PyInit__fastcall()
+{
+    PyObject* const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "BUILT_FOR", TRIINV_BUILT_FOR) != 0) return Py_DECREF(m), nullptr;
+    return m;
+}

@@ -4,6 +4,8 @@ import ctypes
 import importlib.util
 import os
 import shutil
+import sys
+import types
 
 import pytest
 import torch
@@ -48,7 +50,7 @@ class Native:
 
 @pytest.fixture
 def native(tmp_path):
-    if not os.path.exists(tri_build.FASTCALL):
+    if not tri_build._fastcall_current():
         tri_build.build_fastcall()
     copy = str(tmp_path / "_fastcall.so")  # a copy: the module a process has connected to the library stays as it is
     shutil.copy(tri_build.FASTCALL, copy)
@@ -164,3 +166,21 @@ def test_the_library_is_built_without_the_native_argument_handling(monkeypatch, 
     with pytest.warns(UserWarning, match="native argument handling is not built"):
         tri_build.build()
     assert len(done) == len(tri_build.UNITS)  # the library is current: it is not compiled again
+
+
+# The module reads Python's and torch's objects as their headers lay them out: one of another build is neither connected nor kept.
+def test_a_module_built_for_another_torch_is_not_used(monkeypatch, native):
+    module = types.ModuleType("paper_2605_21325_amd._fastcall")
+    module.connect = lambda *a: connected.append(a)
+    connected = []
+    monkeypatch.setattr(tri, "_fastcall", module, raising=False)
+    monkeypatch.setitem(sys.modules, module.__name__, module)
+    for name, value in (("_raw_stream", int), ("_device_index", int), ("_fast", None), ("_fast_lib", None)):
+        monkeypatch.setattr(tri.binding, name, value)
+    for stamp, taken in ((None, False), (tri_build.fastcall_stamp() + "1", False), (native.module.BUILT_FOR, True)):
+        module.BUILT_FOR = stamp
+        tri.binding._connect(tri.lib())
+        assert bool(connected) == taken and (tri.binding._fast is module) == taken, stamp
+    assert tri_build._fastcall_current()
+    monkeypatch.setattr(torch.version, "git_version", "another")
+    assert not tri_build._fastcall_current()
