@@ -19,7 +19,10 @@
  *     detected on the host before anything is launched, so a failing call does no GPU work;
  *   - T is dense row-major [n_mat][C][C], fp32 unless a TRIINV_FLAG_OUT_* bit asks for a 16-bit
  *     result, completely overwritten: exact 0 above the diagonal and exact 1 on it;
- *   - non-finite input values are not errors; they propagate inside their own matrix only.
+ *   - non-finite input values are not errors; they propagate inside their own matrix only;
+ *   - a matrix's result does not depend on the other matrices of its call, nor on their number: the same chunk gives
+ *     the same bits alone, in a batch and in a share of it (few matrices run on other launch shapes and kernels, which
+ *     form the same sums in the same order).
  */
 #ifndef TRIINV_H
 #define TRIINV_H

@@ -61,17 +61,18 @@ inline int head_spread(int H) { return H >= 8 ? 0 : (H >= 4 ? 1 : 4 / H); }
 // others have nothing to do.  Kernel time at C = 64, four / one to a workgroup: 256 matrices 6.4 / 5.4 us (bf16), 16.1 / 11.6
 // (per-channel gate), 13.9 / 11.7 (fp32 keys and operands), applied to two right-hand sides 11.2 / 9.3; 512 6.5 / 6.0 and 17.1 / 13.3; 1024
 // 7.6 / 7.5 and 18.2 / 18.8; 1536 9.3 / 12.2.
-constexpr int ONE_WAVE_PER_GROUP = -1, ONE_TEAM_PER_GROUP = -2;  // in place of the spread
+constexpr int ONE_WAVE_PER_GROUP = -1;  // in place of the spread
 constexpr int64_t FEW_MATRICES = 512;
 // The channel loops (per-channel gate, head dimensions without a kernel of their own) share a matrix of such a call between up to
-// four wavefronts, each with a share of its k-steps (32 channels).
+// four wavefronts, one per k-step (32 channels) where there are fewer.
 constexpr int TEAM_WAVES = 4;
 inline int team_waves(int64_t n_mat, int d_k) { return n_mat > FEW_MATRICES ? 1 : d_k / 32 < TEAM_WAVES ? d_k / 32 : TEAM_WAVES; }
 // fp32 keys of 128 channels go the same way at C = 64 although that head dimension has a kernel of its own: their Gram products are fp32
-// matrix instructions, 6 of the 11.5 us of such a call.  Up to one team per compute unit: 256 matrices 11.7 / 10.5 us (own kernel / team; bf16
-// operands 9.8 / 8.8, one right-hand side applied 17.9 / 16.5), 512 12.8 / 12.8; with 64 channels, two to a team, 9.4 / 9.3 and 9.9 / 11.8.
-inline bool fp32_keys_by_team(int64_t n_mat, int d_k, int C) { return C == 64 && d_k == 128 && n_mat <= FEW_MATRICES / 2; }
-inline unsigned team_bytes(int waves, int tiles) { return (unsigned)(waves - 1) * (unsigned)tiles * 1024u; }
+// matrix instructions, 6 of the 11.7 us of such a call, and each diagonal tile's products are formed once there.  Up to one team per compute unit:
+// 256 matrices 11.8 / 10.0 us (own kernel / team; bf16 operands 9.7 / 8.1, one right-hand side applied 17.3 / 15.8), 512 12.6 / 12.4 and
+// 10.8 / 10.4.  Not with 64 channels, two wavefronts to a team: 256 matrices 8.9 / 9.2 and 7.3 / 7.2, 512 10.1 / 10.9 and 8.0 / 8.8.
+constexpr int FP32_KEYS_TEAM_DK = 128;
+inline bool fp32_keys_by_team(int64_t n_mat, int d_k, int C) { return C == 64 && d_k == FP32_KEYS_TEAM_DK && n_mat <= FEW_MATRICES / 2; }
 struct FusedGrid {
     unsigned groups, threads;
     int spread;
@@ -81,12 +82,6 @@ inline FusedGrid fused_grid(int64_t n_mat, int H, int waves)
 {
     if (waves > 1 && n_mat <= FEW_MATRICES) return {(unsigned)n_mat, 64u, ONE_WAVE_PER_GROUP};
     return {(unsigned)((n_mat + waves - 1) / waves), 64u * waves, waves > 1 ? head_spread(H) : 0};
-}
-inline FusedGrid team_grid(int64_t n_mat, int H, int d_k, int waves)
-{
-    const int team = team_waves(n_mat, d_k);
-    if (waves > 1 && team > 1) return {(unsigned)n_mat, 64u * team, ONE_TEAM_PER_GROUP};
-    return fused_grid(n_mat, H, waves);
 }
 
 // Launcher return codes.

@@ -245,11 +245,15 @@ template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
     else
 #endif
     {
-        const FusedGrid f = kda_team<OP, NB, METHOD, REFINE>() ? team_grid(a.n_mat, a.H, a.d_k, WPB) : fused_grid(a.n_mat, a.H, WPB);
-        constexpr int TILES = gram_tiles<NB, REFINE ? METHOD + WITH_REFINE : METHOD>();
-        return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, WPB, REFINE>, dim3(f.groups), dim3(f.threads),
-                             f.few() ? team_bytes(f.threads / 64, TILES) : kda_pad_bytes<METHOD>(a), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt,
-                             a.iters, a.out_dt, f.spread);
+        if constexpr (kda_team<OP, NB, METHOD, REFINE>()) {
+            const int team = team_waves(a.n_mat, a.d_k);
+            if (team > 1)
+                return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, 1, REFINE, true>, dim3((unsigned)a.n_mat), dim3(64 * team), 0, a.stream, a.K, a.beta,
+                                     a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt, 0);
+        }
+        const FusedGrid f = fused_grid(a.n_mat, a.H, WPB);
+        return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, WPB, REFINE>, dim3(f.groups), dim3(f.threads), f.few() ? 0u : kda_pad_bytes<METHOD>(a),
+                             a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt, f.spread);
     }
 }
 
@@ -317,7 +321,7 @@ template <int KD, int METHOD> static int go_any_dk(const GdnArgs& a)
         const int team = team_waves(a.n_mat, a.d_k);
         if (team > 1)
             return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, true>, dim3((unsigned)a.n_mat), dim3(64 * team),
-                                 team_bytes(team, gram_tiles<NB, METHOD>()), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters,
+                                 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters,
                                  a.out_dt);
     }
     return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, false>, dim3((unsigned)a.n_mat), dim3(64), 0, a.stream, a.K, a.beta,

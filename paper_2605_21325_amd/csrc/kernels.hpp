@@ -503,63 +503,18 @@ template <bool K16> __device__ __forceinline__ void widen_key8(const RawKey8<K16
 // its second half is still cached when needed (requested one k-step apart, lines were found
 // evicted in between and fetched from HBM twice).
 // Kc / gc: element (chunk row 0, this head, channel 0); row_stride in elements (same for both).
-// (fp32 keys, C = 64, gate rows ahead / not: 8192 matrices 123 / 126 us, 16384 250 / 242)
-constexpr int GATES_AHEAD_MATRICES = 8192;
-// The k-steps (of 32 channels) a wavefront takes.
-struct Steps {
-    int begin, end;
-};
-
-// With few matrices the wavefronts of a workgroup form one matrix together: each takes a share of the channels (the Gram products of
-// the channel loops are most of such a call: exponentials, and fp32 matrix instructions, beside which nothing else runs), the
-// first adds the others' tiles to its own and goes on alone.  256 matrices of C = 64, d_k = 128, one wavefront / four: per-channel gate
-// 10.9 / 8.7 us, with fp32 operands 19.3 / 12.0, applied to two right-hand sides 15.6 / 13.0; d_k = 256, fp32 keys and operands 22.6 / 12.8,
-// bf16 8.0 / 7.4.  512 matrices: 11.8 / 10.8, 20.5 / 16.5, 17.4 / 15.7, 24 / 16.3, 8.9 / 8.4.
-struct Team {
-    int w, size;   // this wavefront, their number (1: no team); never more than there are k-steps
-    float* tiles;  // LDS: (size - 1) * gram_tiles<NB, METHOD>() * 256 floats
-    __device__ __forceinline__ Steps share(int n_step) const { return Steps{w * n_step / size, (w + 1) * n_step / size}; }
-};
-template <int NB, int METHOD> __host__ __device__ constexpr int gram_tiles()
-{
-    int n = 0;
-    for (int i = 0; i < NB; ++i)
-        for (int j = 0; j <= i; ++j) n += (need_tile<NB, METHOD>(i, j, false) ? 1 : 0) + (need_tile<NB, METHOD>(i, j, true) ? 1 : 0);
-    return n;
-}
-// False for the wavefronts that are done.
-template <int NB, int METHOD> __device__ __forceinline__ bool team_sum(PreA<NB>& out, const Team& team, Lane ln)
-{
-    if (team.size == 1) return true;
-    constexpr int COUNT = gram_tiles<NB, METHOD>();
-    v4f* const slots = reinterpret_cast<v4f*>(team.tiles) + 16 * ln.q + ln.n;  // [wavefront - 1][tile][lane]
-    const auto each = [&](auto f) {
-        int n = 0;
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-#pragma unroll
-            for (int j = 0; j <= i; ++j) {
-                if (need_tile<NB, METHOD>(i, j, false)) f(out.n[tix(i, j)], n++);
-                if (need_tile<NB, METHOD>(i, j, true)) f(out.t[tix(i, j)], n++);
-            }
-    };
-    if (team.w > 0) each([&](v4f& t, int n) { slots[((team.w - 1) * COUNT + n) * 64] = t; });
-    __syncthreads();
-    if (team.w > 0) return false;
-#pragma unroll 1
-    for (int w = 1; w < team.size; ++w) each([&](v4f& t, int n) { t += slots[((w - 1) * COUNT + n) * 64]; });
-    return true;
-}
-
+//
 // The C <= 64 form.  The loads of a k-step's gate rows (and, every other k-step, of the next line of keys) go out before the k-step
 // ahead of them is computed: one after the other, four k-steps were four round trips to memory, most of a call of few matrices.  The
 // anchor rows are rows of the chunk, the ones that lanes n = 0 load anyway, and reach the others through LDS.
 // Kernel time, bf16 keys of d_k = 128, C = 64, loads in the k-step itself / a step ahead: 256 matrices 11.6 / 10.9 us, 1024 18.5 / 15.6, 16384
 // 214 / 201; one right-hand side, 1024 20.6 / 17.8; fp32 operands, 1024 27.3 / 24.5, d_k = 256 30.0 / 23.8.
 // ahead = false: not so, for calls that fill the chip many times over and keep fewer bytes of keys than of gates in flight this way
-// (fp32 keys, fp32 operands at C = 32).  C = 16 has a form of its own, accumulate_gated_gram16.
+// (fp32 keys, fp32 operands at C = 32): fp32 keys, C = 64, gate rows ahead / not, 8192 matrices 123 / 126 us, 16384 250 / 242.  C = 16 has a
+// form of its own, accumulate_gated_gram16.
+constexpr int GATES_AHEAD_MATRICES = 8192;
 template <int OPG, int NB, int METHOD, bool K16>
-__device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, Steps steps,
+__device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step,
                                                         Lane ln, int valid, float* tab, bool ahead)
 {
     constexpr float LOG2E = 1.44269504088896340736f;
@@ -567,7 +522,6 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
     constexpr bool KEYS_AHEAD = K16 && (NB == 4 || (NB == 2 && OPG != OP_F32));  // elsewhere they would cost a wavefront per SIMD
     if (KEYS_AHEAD) ahead = true;
     if (METHOD == M_NEWTON_SCHULZ + WITH_REFINE) ahead = false;                  // (which has no registers left for them)
-    const int n_step = steps.end;
     int rowc[NB];
     float keep[NB];
 #pragma unroll
@@ -598,9 +552,9 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
 
     RawKey8<K16> raw[STEPS][NB];
     v4f G[NB][2];
-    if (KEYS_AHEAD) load_keys(raw, steps.begin);
-    load_gates(G, steps.begin);
-    for (int s0 = steps.begin; s0 < n_step; s0 += STEPS) {
+    if (KEYS_AHEAD) load_keys(raw, 0);
+    load_gates(G, 0);
+    for (int s0 = 0; s0 < n_step; s0 += STEPS) {
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
             const int s = s0 + t;
@@ -690,21 +644,21 @@ __device__ __forceinline__ void accumulate_gated_gram64(PreA<NB>& out, const voi
 // C = 16: one tile row, whose only anchor every lane loads, and wavefronts enough to hide the loads of one behind the others' work (through
 // LDS and a step ahead as above, 1792 matrices of d_k = 256: 11.8 us against 10.6).
 template <int OPG, int METHOD, bool K16>
-__device__ __forceinline__ void accumulate_gated_gram16(PreA<1>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, Steps steps,
+__device__ __forceinline__ void accumulate_gated_gram16(PreA<1>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step,
                                                         Lane ln, int valid)
 {
     constexpr float LOG2E = 1.44269504088896340736f;
     constexpr int STEPS = K16 ? 2 : 1;
     const int64_t row = (int64_t)(ln.n < valid ? ln.n : valid - 1) * row_stride + 8 * ln.q;
     const float keep = ln.n < valid ? 1.f : 0.f;
-    for (int s0 = steps.begin; s0 < steps.end; s0 += STEPS) {
+    for (int s0 = 0; s0 < n_step; s0 += STEPS) {
         RawKey8<K16> raw[STEPS];
 #pragma unroll
         for (int t = 0; t < STEPS; ++t)
-            if (s0 + t < steps.end) raw[t] = load_key8<K16>(Kc, row + 32 * (s0 + t));
+            if (s0 + t < n_step) raw[t] = load_key8<K16>(Kc, row + 32 * (s0 + t));
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
-            if (s0 + t >= steps.end) break;
+            if (s0 + t >= n_step) break;
             const float *const g = gc + row + 32 * (s0 + t), *const a = gc + 8 * ln.q + 32 * (s0 + t);
             const v4f G[2] = {*reinterpret_cast<const v4f*>(g), *reinterpret_cast<const v4f*>(g + 4)};
             const v4f A[2] = {*reinterpret_cast<const v4f*>(a), *reinterpret_cast<const v4f*>(a + 4)};
@@ -728,10 +682,10 @@ __device__ __forceinline__ void accumulate_gated_gram16(PreA<1>& out, const void
 // exact products, and gc is not read): the any-d_k path of the scalar / no-gate kinds.
 template <int OPG, int NB, int METHOD, bool K16, bool GATED = true>
 __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc,
-                                                      int64_t row_stride, Steps steps, Lane ln, int valid, float* tab = nullptr, bool ahead = true)
+                                                      int64_t row_stride, int n_step, Lane ln, int valid, float* tab = nullptr, bool ahead = true)
 {
-    if constexpr (GATED && NB == 1) return accumulate_gated_gram16<OPG, METHOD, K16>(out, Kc, is_f16, gc, row_stride, steps, ln, valid);
-    else if constexpr (GATED && NB <= 4) return accumulate_gated_gram64<OPG, NB, METHOD, K16>(out, Kc, is_f16, gc, row_stride, steps, ln, valid, tab, ahead);
+    if constexpr (GATED && NB == 1) return accumulate_gated_gram16<OPG, METHOD, K16>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid);
+    else if constexpr (GATED && NB <= 4) return accumulate_gated_gram64<OPG, NB, METHOD, K16>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid, tab, ahead);
     constexpr int C = 16 * NB;
     [[maybe_unused]] constexpr float LOG2E = 1.44269504088896340736f;
     constexpr int STEPS = (K16 && NB <= 4) ? 2 : 1;  // C = 128 has no registers to spare for the pairing
@@ -746,16 +700,16 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
         keep[i] = row < valid ? 1.f : 0.f;
     }
     const int anchor = C / 2 < valid ? C / 2 : valid - 1;
-    for (int s0 = steps.begin; s0 < steps.end; s0 += STEPS) {
+    for (int s0 = 0; s0 < n_step; s0 += STEPS) {
         RawKey8<K16> raw[STEPS][NB];
 #pragma unroll
         for (int t = 0; t < STEPS; ++t)
 #pragma unroll
             for (int i = 0; i < NB; ++i)
-                if (s0 + t < steps.end) raw[t][i] = load_key8<K16>(Kc, (int64_t)rowc[i] * row_stride + 32 * (s0 + t) + 8 * ln.q);
+                if (s0 + t < n_step) raw[t][i] = load_key8<K16>(Kc, (int64_t)rowc[i] * row_stride + 32 * (s0 + t) + 8 * ln.q);
 #pragma unroll
         for (int t = 0; t < STEPS; ++t) {
-            if (s0 + t >= steps.end) break;
+            if (s0 + t >= n_step) break;
             const int ch = 32 * (s0 + t) + 8 * ln.q;
             GOp<OPG> pp[NB], pm[NB];
             if constexpr (GATED) {
@@ -800,9 +754,295 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
     }
 }
 
-template <int OPG, int NB, int METHOD>
+// With few matrices up to four wavefronts of a workgroup form one matrix together.  What is spread over them: the channels, where the
+// operands of the products are made (exponentials), each wavefront one k-step (32 channels) of a round; and the products (fp32 matrix
+// instructions, beside which nothing else runs), each wavefront some of the tiles, over all channels.  Between the two the operands go
+// through LDS.  Every tile's products are added in one chain in the order of the channels, with the same operands as in the
+// loops of one wavefront: a matrix's bits do not depend on how many others its call has.
+// Bound by the one wavefront's recursion that follows, and by these products where they are fp32.  256 matrices of C = 64, d_k = 128, one
+// wavefront / four: per-channel gate 10.8 / 8.5 us, with fp32 operands 19.2 / 12.8, applied to two right-hand sides 14.6 / 12.3, forward
+// substitution 17.9 / 12.5; d_k = 256 without a gate, fp32 keys and operands 22.4 / 12.0, bf16 8.1 / 7.2.  512 matrices: 12.1 / 11.0, 20.3 / 16.8,
+// 17.5 / 15.9, 19.4 / 15.7, 24.6 / 16.0, 9.2 / 8.2.  (Each wavefront all the products of its own channels and the first adding the sums, another
+// order: 8.6, 12.5, 12.3, -, 12.9, 7.4; 11.2, 16.5, 15.8, -, 16.3, 8.5.)
+struct Team {
+    int w, size;  // this wavefront, their number: four, or two or three where there are no more k-steps
+    char* lds;    // TeamLds::BYTES
+};
+// The products a method asks for: tile (i, j) in N or T orientation.  Without a gate both operands are the keys, and a diagonal tile is its
+// own transpose: one product serves both.
+template <int NB, int METHOD, bool GATED> struct GramProducts {
+    static constexpr int count_()
+    {
+        int n = 0;
+        for (int i = 0; i < NB; ++i)
+            for (int j = 0; j <= i; ++j) n += !GATED && i == j ? 1 : (need_tile<NB, METHOD>(i, j, false) ? 1 : 0) + (need_tile<NB, METHOD>(i, j, true) ? 1 : 0);
+        return n;
+    }
+    static constexpr int COUNT = count_();
+    int code[COUNT] = {};  // left tile row | right operand << 8 | T orientation << 16
+    constexpr GramProducts()
+    {
+        int n = 0;
+        for (int i = 0; i < NB; ++i)
+            for (int j = 0; j <= i; ++j)
+                for (int tr = 0; tr < 2; ++tr)
+                    if (!GATED && i == j ? tr == 0 : need_tile<NB, METHOD>(i, j, tr == 1)) code[n++] = i | (i * (i + 1) / 2 + j) << 8 | j << 24 | tr << 16;
+    }
+};
+// A k-step's operands in LDS, 16 bytes of a lane to a plane of 64 lanes.  Left: NB of them.  Right: without a gate the same.  With a gate, 16-bit
+// operands: one per tile; fp32: the factor that depends on the row, one per tile row, the other one (channels only) in the table.
+template <int OPG, int NB, bool GATED> struct TeamLds {
+    static constexpr int PLANE = 1024, PLANES = OPG == OP_F32 ? 2 : 1, PAIRS = NB * (NB - 1) / 2;
+    static constexpr int RIGHT = NB * PLANES * PLANE;
+    static constexpr int TABLE = RIGHT + (GATED ? (OPG == OP_F32 ? NB * 2 : NB * (NB + 1) / 2) * PLANE : 0);
+    static constexpr int STEP = TABLE + (GATED ? 4 * 8 * (NB + PAIRS) * 4 : 0);
+    static constexpr int TILES = NB * (NB + 1);  // the finished tiles take the operands' place
+    static constexpr int BYTES = TEAM_WAVES * STEP > TILES * PLANE ? TEAM_WAVES * STEP : TILES * PLANE;
+};
+template <int OPG> __device__ __forceinline__ void team_write(char* p, const GOp<OPG>& o)
+{
+    if constexpr (OPG == OP_F32) {
+        *reinterpret_cast<v4f*>(p) = v4f{o.x[0], o.x[1], o.x[2], o.x[3]};
+        *reinterpret_cast<v4f*>(p + 1024) = v4f{o.x[4], o.x[5], o.x[6], o.x[7]};
+    } else {
+        *reinterpret_cast<decltype(o.x)*>(p) = o.x;
+    }
+}
+template <int OPG> __device__ __forceinline__ GOp<OPG> team_read(const char* p)
+{
+    if constexpr (OPG == OP_F32) {
+        const v4f a = *reinterpret_cast<const v4f*>(p), b = *reinterpret_cast<const v4f*>(p + 1024);
+        return GOp<OPG>{{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]}};
+    } else {
+        GOp<OPG> o;
+        o.x = *reinterpret_cast<const decltype(o.x)*>(p);
+        return o;
+    }
+}
+
+// P products per wavefront over STEPS k-steps, a group's operands on their way while the group before is multiplied.
+template <int OPG, int NB, bool GATED, int P, int STEPS> __device__ __forceinline__ void team_products(v4f (&acc)[P], const int (&code)[P], const char* lds, Lane ln)
+{
+    typedef TeamLds<OPG, NB, GATED> LY;
+    constexpr bool FACTORS = GATED && OPG == OP_F32;
+    constexpr int GROUP = OPG == OP_F32 ? 2 : 4, PER_STEP = (P + GROUP - 1) / GROUP;
+    const int lane = 16 * (16 * ln.q + ln.n);
+    GOp<OPG> left[2][GROUP], right[2][GROUP];
+    v4f factor[2][GROUP][2];
+    const auto fetch = [&](int k) {
+        const char* const at = lds + k / PER_STEP * LY::STEP;
+#pragma unroll
+        for (int g = 0; g < GROUP; ++g) {
+            const int p = k % PER_STEP * GROUP + g;
+            if (p >= P) break;
+            const int i = code[p] & 0xff, j = code[p] >> 24, tile = (code[p] >> 8) & 0xff;
+            const bool tr = !FACTORS && ((code[p] >> 16) & 1);  // (here by exchanging the addresses)
+            const int a = i * LY::PLANES * LY::PLANE, b = !GATED ? j * LY::PLANES * LY::PLANE : LY::RIGHT + (FACTORS ? j * LY::PLANES : tile) * LY::PLANE;
+            left[k & 1][g] = team_read<OPG>(at + (tr ? b : a) + lane);
+            right[k & 1][g] = team_read<OPG>(at + (tr ? a : b) + lane);
+            if constexpr (FACTORS) {  // (a diagonal tile's is 1: what is read in its place is an anchor)
+                const float* const f = reinterpret_cast<const float*>(at + LY::TABLE) + ln.q * 8 * (NB + LY::PAIRS) + 8 * (i == j ? 0 : NB + tile - i);
+                factor[k & 1][g][0] = *reinterpret_cast<const v4f*>(f);
+                factor[k & 1][g][1] = *reinterpret_cast<const v4f*>(f + 4);
+            }
+        }
+    };
+    fetch(0);
+#pragma unroll
+    for (int k = 0; k < STEPS * PER_STEP; ++k) {
+        if (k + 1 < STEPS * PER_STEP) fetch(k + 1);
+#pragma unroll
+        for (int g = 0; g < GROUP; ++g) {
+            const int p = k % PER_STEP * GROUP + g;
+            if (p >= P) break;
+            GOp<OPG>&a = left[k & 1][g], &b = right[k & 1][g];
+            if constexpr (FACTORS) {
+                if ((code[p] & 0xff) != code[p] >> 24) {
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) b.x[r] *= factor[k & 1][g][r / 4][r % 4];
+                }
+                acc[p] = (code[p] >> 16) & 1 ? gstep<OPG>(b, a, acc[p]) : gstep<OPG>(a, b, acc[p]);
+            } else {
+                acc[p] = gstep<OPG>(a, b, acc[p]);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// The tiles of one matrix by the team, complete on its first wavefront; false for the others, which are done.  Every wavefront of the
+// workgroup comes here, with the same matrix: the barriers are the workgroup's.
+// HALF_ROWS: a lane's eight channels of a k-step are 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3, not 8q .. 8q + 7 (the order of the products of the kernels
+// that keep fp32 keys in registers).
+template <int OPG, int NB, int METHOD, bool K16, bool GATED, int SIZE, bool HALF_ROWS>
+__device__ __forceinline__ bool team_gram_of(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
+                                             const Team& team)
+{
+    typedef TeamLds<OPG, NB, GATED> LY;
+    constexpr float LOG2E = 1.44269504088896340736f;
+    static constexpr GramProducts<NB, METHOD, GATED> list;
+    constexpr int COUNT = list.COUNT, P = (COUNT + SIZE - 1) / SIZE;  // products in all, at most per wavefront
+    const int lane = 16 * (16 * ln.q + ln.n);
+    char* const mine = team.lds + team.w * LY::STEP;
+    int rowc[NB];
+    float keep[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int row = 16 * i + ln.n;
+        rowc[i] = row < valid ? row : valid - 1;
+        keep[i] = row < valid ? 1.f : 0.f;
+    }
+    RawKey8<K16> raw[NB];
+    v4f G[NB][2];
+    const auto load = [&](int s) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int64_t off = (int64_t)rowc[i] * row_stride + 32 * s;
+            if constexpr (HALF_ROWS) {
+                raw[i].a = *reinterpret_cast<const v4f*>(static_cast<const float*>(Kc) + off + 4 * ln.q);
+                raw[i].b = *reinterpret_cast<const v4f*>(static_cast<const float*>(Kc) + off + 16 + 4 * ln.q);
+            } else {
+                raw[i] = load_key8<K16>(Kc, off + 8 * ln.q);
+            }
+            if constexpr (GATED) {
+                G[i][0] = *reinterpret_cast<const v4f*>(gc + off + 8 * ln.q);
+                G[i][1] = *reinterpret_cast<const v4f*>(gc + off + 8 * ln.q + 4);
+            }
+        }
+    };
+    const auto operands = [&]() {
+        if constexpr (!GATED) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                float kv[8];
+                widen_key8<K16>(raw[i], is_f16, kv);
+#pragma unroll
+                for (int r = 0; r < 8; ++r) kv[r] = !HALF_ROWS ? kv[r] * keep[i] : 16 * i + ln.n < valid ? kv[r] : 0.f;
+                team_write<OPG>(mine + i * LY::PLANES * LY::PLANE + lane, gpack<OPG>(kv));
+            }
+        } else {  // (as in accumulate_gated_gram64)
+            constexpr int NE = 8 * LY::PAIRS;
+            float* const anc = reinterpret_cast<float*>(mine + LY::TABLE) + ln.q * (8 * NB + NE);
+            float* const fac = anc + 8 * NB;
+            if (ln.n == 0) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i) {
+                    *reinterpret_cast<v4f*>(&anc[8 * i]) = G[i][0];
+                    *reinterpret_cast<v4f*>(&anc[8 * i + 4]) = G[i][1];
+                }
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int k = 0; k < (NE + 15) / 16; ++k) {
+                const int e = ln.n + 16 * k, p = e >> 3, r = e & 7;
+                if (e < NE) {
+                    const int hi = p >= 3 ? 3 : (p >= 1 ? 2 : 1), lo = p - hi * (hi - 1) / 2;
+                    fac[e] = __builtin_amdgcn_exp2f((anc[8 * hi + r] - anc[8 * lo + r]) * LOG2E);
+                }
+            }
+            wave_lds_sync();
+            float v[NB][8];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                float kv[8], u[8];
+                widen_key8<K16>(raw[i], is_f16, kv);
+                const v4f a0 = *reinterpret_cast<const v4f*>(&anc[8 * i]), a1 = *reinterpret_cast<const v4f*>(&anc[8 * i + 4]);
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const float kk = kv[r] * keep[i];
+                    const float e = (G[i][r / 4][r % 4] - (r < 4 ? a0[r] : a1[r - 4])) * LOG2E;
+                    u[r] = kk * __builtin_amdgcn_exp2f(e);
+                    v[i][r] = kk * __builtin_amdgcn_exp2f(-e);
+                }
+                team_write<OPG>(mine + i * LY::PLANES * LY::PLANE + lane, gpack<OPG>(u));
+                if constexpr (OPG == OP_F32) team_write<OPG>(mine + LY::RIGHT + i * LY::PLANES * LY::PLANE + lane, gpack<OPG>(v[i]));
+            }
+            if constexpr (OPG != OP_F32) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+#pragma unroll
+                    for (int j = 0; j <= i; ++j) {
+                        float dn[8];
+                        if (i == j) {
+#pragma unroll
+                            for (int r = 0; r < 8; ++r) dn[r] = v[j][r];
+                        } else {
+                            const int p = i * (i - 1) / 2 + j;
+                            const v4f f0 = *reinterpret_cast<const v4f*>(&fac[8 * p]), f1 = *reinterpret_cast<const v4f*>(&fac[8 * p + 4]);
+#pragma unroll
+                            for (int r = 0; r < 8; ++r) dn[r] = v[j][r] * (r < 4 ? f0[r] : f1[r - 4]);
+                        }
+                        team_write<OPG>(mine + LY::RIGHT + tix(i, j) * LY::PLANE + lane, gpack<OPG>(dn));
+                    }
+            }
+        }
+    };
+
+    const int first = team.w * COUNT / SIZE, end = (team.w + 1) * COUNT / SIZE;
+    int code[P];
+    v4f acc[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {  // (a wavefront with a product fewer does its last one twice)
+        const int k = first + p < end ? first + p : first < end ? end - 1 : 0;
+        code[p] = list.code[k];
+        acc[p] = zero4();
+    }
+    load(team.w);
+    if constexpr (SIZE < TEAM_WAVES) {  // a k-step each
+        operands();
+        __syncthreads();
+        team_products<OPG, NB, GATED, P, SIZE>(acc, code, team.lds, ln);
+        __syncthreads();  // the operands have been read
+    } else {
+#pragma unroll 1
+        for (int s0 = 0; s0 < n_step; s0 += SIZE) {
+            const int s = s0 + team.w;
+            if (s < n_step) operands();
+            if (s + SIZE < n_step) load(s + SIZE);
+            __syncthreads();
+            if (n_step - s0 >= SIZE) {
+                team_products<OPG, NB, GATED, P, SIZE>(acc, code, team.lds, ln);
+            } else {
+#pragma unroll 1
+                for (int t = 0; t < n_step - s0; ++t) team_products<OPG, NB, GATED, P, 1>(acc, code, team.lds + t * LY::STEP, ln);
+            }
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (first + p < end) *reinterpret_cast<v4f*>(team.lds + (first + p) * LY::PLANE + lane) = acc[p];
+    __syncthreads();
+    if (team.w > 0) return false;
+    int n = 0;
+    const auto next = [&]() { return *reinterpret_cast<const v4f*>(team.lds + n++ * LY::PLANE + lane); };
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            if (!GATED && i == j) {
+                out.n[tix(i, j)] = out.t[tix(i, j)] = next();
+                continue;
+            }
+            if (need_tile<NB, METHOD>(i, j, false)) out.n[tix(i, j)] = next();
+            if (need_tile<NB, METHOD>(i, j, true)) out.t[tix(i, j)] = next();
+        }
+    wave_lds_sync();
+    return true;
+}
+template <int OPG, int NB, int METHOD, bool K16, bool GATED, bool HALF_ROWS = false>
+__device__ __forceinline__ bool team_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
+                                          const Team& team)
+{
+    if (team.size == 4) return team_gram_of<OPG, NB, METHOD, K16, GATED, 4, HALF_ROWS>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid, team);
+    if (team.size == 3) return team_gram_of<OPG, NB, METHOD, K16, GATED, 3, HALF_ROWS>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid, team);
+    return team_gram_of<OPG, NB, METHOD, K16, GATED, 2, HALF_ROWS>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid, team);
+}
+
+// TEAM: formed by the workgroup's wavefronts together; false for those that are done.
+template <int OPG, int NB, int METHOD, bool TEAM>
 __device__ __forceinline__ bool build_A_per_channel(PreA<NB>& out, const void* Kc, int kd, const float* gc, int64_t row_stride,
-                                                    const float* bc, int64_t tok_stride, int d_k, float* lds, Lane ln, int valid, const Team& team, bool ahead)
+                                                    const float* bc, int64_t tok_stride, int d_k, float* lds, Lane ln, int valid, bool ahead, const Team& team)
 {
     constexpr int C = 16 * NB;
 #pragma unroll
@@ -812,11 +1052,15 @@ __device__ __forceinline__ bool build_A_per_channel(PreA<NB>& out, const void* K
             out.n[tix(i, j)] = zero4();
             out.t[tix(i, j)] = zero4();
         }
-    if (kd == OP_F32)
-        accumulate_gated_gram<OPG, NB, METHOD, false>(out, Kc, false, gc, row_stride, team.share(d_k / 32), ln, valid, lds, ahead);
-    else
-        accumulate_gated_gram<OPG, NB, METHOD, true>(out, Kc, kd == OP_F16, gc, row_stride, team.share(d_k / 32), ln, valid, lds, ahead);
-    if (!team_sum<NB, METHOD>(out, team, ln)) return false;
+    if constexpr (TEAM) {
+        if (!(kd == OP_F32 ? team_gram<OPG, NB, METHOD, false, true>(out, Kc, false, gc, row_stride, d_k / 32, ln, valid, team)
+                           : team_gram<OPG, NB, METHOD, true, true>(out, Kc, kd == OP_F16, gc, row_stride, d_k / 32, ln, valid, team)))
+            return false;
+    } else if (kd == OP_F32) {
+        accumulate_gated_gram<OPG, NB, METHOD, false>(out, Kc, false, gc, row_stride, d_k / 32, ln, valid, lds, ahead);
+    } else {
+        accumulate_gated_gram<OPG, NB, METHOD, true>(out, Kc, kd == OP_F16, gc, row_stride, d_k / 32, ln, valid, lds, ahead);
+    }
     // beta_i row scaling and the strictly-lower mask
     const int l = 16 * ln.q + ln.n;
 #pragma unroll
@@ -841,7 +1085,7 @@ __device__ __forceinline__ bool build_A_per_channel(PreA<NB>& out, const void* K
 
 // Scalar / no-gate kinds for any d_k (multiple of 32): Gram tiles accumulated 32 channels at a time
 // in a run-time loop with the stored keys as operands, then the scalar gate.  KD = type of K.
-template <int KD, int NB, int METHOD>
+template <int KD, int NB, int METHOD, bool TEAM>
 __device__ __forceinline__ bool build_A_scalar_any_dk(PreA<NB>& out, const void* Kc, int64_t row_stride, const float* bc,
                                                       const float* gc, int64_t tok_stride, int d_k, float* lds, Lane ln, int valid, const Team& team)
 {
@@ -852,8 +1096,17 @@ __device__ __forceinline__ bool build_A_scalar_any_dk(PreA<NB>& out, const void*
             out.n[tix(i, j)] = zero4();
             out.t[tix(i, j)] = zero4();
         }
-    accumulate_gated_gram<KD, NB, METHOD, KD != OP_F32, false>(out, Kc, KD == OP_F16, nullptr, row_stride, team.share(d_k / 32), ln, valid);
-    if (!team_sum<NB, METHOD>(out, team, ln)) return false;
+    if constexpr (!TEAM) {
+        accumulate_gated_gram<KD, NB, METHOD, KD != OP_F32, false>(out, Kc, KD == OP_F16, nullptr, row_stride, d_k / 32, ln, valid);
+    } else {
+        bool more = true;
+        if (KD == OP_F32 && NB == 4 && d_k == FP32_KEYS_TEAM_DK) {  // in the order of the kernel that these keys have at this size
+            if constexpr (KD == OP_F32 && NB == 4) more = team_gram<KD, NB, METHOD, false, false, true>(out, Kc, false, nullptr, row_stride, d_k / 32, ln, valid, team);
+        } else {
+            more = team_gram<KD, NB, METHOD, KD != OP_F32, false>(out, Kc, KD == OP_F16, nullptr, row_stride, d_k / 32, ln, valid, team);
+        }
+        if (!more) return false;
+    }
     GateVec<NB> gate;
     gate.load(bc, gc, tok_stride, lds, ln, valid);
 #pragma unroll
@@ -1315,14 +1568,10 @@ template <int NB, int METHOD> constexpr int core_lds_floats()
     return store_lds_floats<NB>() > small ? store_lds_floats<NB>() : small;
 }
 
-// The team of this wavefront in a workgroup of `size` of them; its tiles are in the launch's dynamic LDS.
-__device__ __forceinline__ Team this_team(int size)
-{
-    extern __shared__ __attribute__((aligned(16))) float team_tiles[];
-    return Team{size > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0, size, team_tiles};
-}
-// (Newton-Schulz at C = 64, with fp32 operands or the refinement step, has no register left for it)
-template <int OP, int NB, int METHOD, bool REFINE> constexpr bool kda_team() { return !(METHOD == M_NEWTON_SCHULZ && NB == 4 && (OP == OP_F32 || REFINE)); }
+// The team of this wavefront: its workgroup.
+__device__ __forceinline__ Team this_team(char* lds) { return Team{__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), (int)blockDim.x / 64, lds}; }
+// (Refined Newton-Schulz with fp32 operands at C = 64 takes more than 256 registers: a compute unit would hold one team of the two.)
+template <int OP, int NB, int METHOD, bool REFINE> constexpr bool kda_team() { return NB <= 4 && !(METHOD == M_NEWTON_SCHULZ && NB == 4 && OP == OP_F32 && REFINE); }
 
 // REFINE: one iterative-refinement step after a matrix-product method (C <= 64; at C = 128 a kernel of its own).
 template <int OP, int NB, int METHOD, class ASrc, bool REFINE = false>
@@ -1446,7 +1695,7 @@ __device__ __forceinline__ int64_t head_group_swizzle(int64_t bid, int64_t n_gro
 // slower, with 10 % higher read latency and 4.5x the DRAM credit stalls.  Instead a workgroup takes ONE head of WPB chunks
 // S chunks apart (S = max(1, 4 / H), so its four key regions are at least 64 KB apart), and the S * H workgroups that share
 // those 4 S chunks run back to back on one XCD.  Chunks beyond the last full group of 4 S keep the plain order.
-// spread = ONE_WAVE_PER_GROUP or ONE_TEAM_PER_GROUP (few matrices, see fused_grid): a workgroup has one matrix, in plain order.
+// spread = ONE_WAVE_PER_GROUP (few matrices, see fused_grid): a workgroup has one matrix, in plain order.
 // The waves never synchronise with each other.  Returns chunk id * H + head, or -1 for a wave without a matrix.
 template <int WPB>
 __device__ __forceinline__ int64_t fused_matrix_index(int64_t n_chunk, int H, int64_t n_mat, int spread)
@@ -1512,8 +1761,8 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
 }
 
 // Fused kernel of the scalar / no-gate kinds for head dimensions without a specialised build.
-// TEAM: the workgroup's wavefronts form a matrix together (see Team; a kernel of its own: the other one lost 5 to 13 % of its speed with the
-// choice at run time).
+// TEAM: the workgroup's wavefronts form a matrix together, its first one goes on alone (see Team; a kernel of its own: the other one lost 5 to
+// 13 % of its speed with the choice at run time).
 template <int KD, int OP, int NB, int METHOD, bool TEAM>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
@@ -1523,6 +1772,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_
     constexpr int CORE = core_lds_floats<NB, METHOD>();
     constexpr int GATE = gate_lds_floats<NB>();
     __shared__ __attribute__((aligned(16))) float lds[CORE > GATE ? CORE : GATE];
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<KD, NB, false>::BYTES : 16];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
     const int h = (int)((uint32_t)m - bc * (uint32_t)H);
@@ -1531,16 +1781,17 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_
     const Lane ln = lane_id();
     const int64_t esz = (KD == OP_F32) ? 4 : 2;
     PreA<NB> src;
-    if (!build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
+    if (!build_A_scalar_any_dk<KD, NB, METHOD, TEAM>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
                                                beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid,
-                                               this_team(TEAM ? (int)blockDim.x / 64 : 1)))
+                                               this_team(team_lds)))
         return;
     invert_and_store<OP, NB, METHOD, PreA<NB>, false>(src, out_matrix(T, m, C, out_dt), lds, ln, aux);
 }
 
 // Fused kernel for the per-channel gate: g is [B, Tlen, H, d_k]; the gated keys are rounded to OP.
-template <int OP, int NB, int METHOD, int WPB = 1, bool REFINE = false>
-__global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE, true>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
+// TEAM: WPB = 1, a workgroup of up to TEAM_WAVES wavefronts per matrix.
+template <int OP, int NB, int METHOD, int WPB = 1, bool REFINE = false, bool TEAM = false>
+__global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE, true>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int k_dt, int aux, int out_dt, int spread)
 {
@@ -1549,7 +1800,8 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
     constexpr int PER_WAVE = CORE > C ? CORE : C;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
     float* lds = lds_all + ((WPB == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * PER_WAVE;
-    const int64_t m = fused_matrix_index<WPB>(n_chunk, H, n_chunk * H, spread);
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<OP, NB, true>::BYTES : 16];
+    const int64_t m = TEAM ? (int64_t)blockIdx.x : fused_matrix_index<WPB>(n_chunk, H, n_chunk * H, spread);
     if (m < 0) return;
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
     const int h = (int)((uint32_t)m - bc * (uint32_t)H);
@@ -1559,10 +1811,9 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
     const int64_t esz = (k_dt == OP_F32) ? 4 : 2;
     const int64_t e0 = (tok0 * H + h) * (int64_t)d_k;  // element offset of (token 0, head h, channel 0)
     PreA<NB> src;
-    if (!build_A_per_channel<OP, NB, REFINE ? METHOD + WITH_REFINE : METHOD>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0,
-                                                                             (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, lds, ln, pos.valid,
-                                                                             this_team(WPB > 1 && kda_team<OP, NB, METHOD, REFINE>() && spread == ONE_TEAM_PER_GROUP ? (int)blockDim.x / 64 : 1),
-                                                                             n_chunk * H <= GATES_AHEAD_MATRICES))
+    if (!build_A_per_channel<OP, NB, REFINE ? METHOD + WITH_REFINE : METHOD, TEAM>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0,
+                                                                                   (int64_t)H * d_k, beta + tok0 * H + h, H, d_k, lds, ln, pos.valid,
+                                                                                   n_chunk * H <= GATES_AHEAD_MATRICES, this_team(team_lds)))
         return;
     invert_and_store<OP, NB, METHOD, PreA<NB>, REFINE>(src, out_matrix(T, m, C, out_dt), lds, ln, aux);
 }

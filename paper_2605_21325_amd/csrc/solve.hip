@@ -108,15 +108,19 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
     return launch_kernel(f.dry, f.k_dt == OP_F32 ? k_kda_tri_solve_c128<OP, METHOD, false, 2> : k_kda_tri_solve_c128<OP, METHOD, true, 2>,
                          dim3((unsigned)f.n_mat), dim3(128), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
 #else
-    const FusedGrid shape = team_grid(f.n_mat, f.H, f.d_k, WPB);
-    const unsigned lds = shape.few() ? team_bytes(shape.threads / 64, gram_tiles<NB, METHOD>()) : 0u;
+    const int team = team_waves(f.n_mat, f.d_k);
+    if (team > 1)
+        return launch_kernel(f.dry, a.n_rhs == 1 ? k_kda_tri_solve<OP, NB, METHOD, 1, 1, true> : k_kda_tri_solve<OP, NB, METHOD, 1, 2, true>,
+                             dim3((unsigned)f.n_mat), dim3(64 * team), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt,
+                             f.iters, 0);
+    const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
     const dim3 grid(shape.groups), block(shape.threads);
     if (a.n_rhs == 1) {
-        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 1>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
+        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 1>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
                            f.map, f.H, f.d_k, f.k_dt, f.iters, shape.spread);
     }
     if constexpr (HAS_PAIR) {
-        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 2>, grid, block, lds, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
+        return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, WPB, 2>, grid, block, 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk,
                            f.map, f.H, f.d_k, f.k_dt, f.iters, shape.spread);
     }
     return 1;
@@ -129,7 +133,7 @@ template <int KD, int METHOD, int NRHS, bool TEAM> static int launch_any_dk(cons
 {
     const GdnArgs& f = a.f;
     return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, NRHS, TEAM>, dim3((unsigned)f.n_mat), dim3(64 * team),
-                         team_bytes(team, gram_tiles<NB, METHOD>()), f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
+                         0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
 }
 template <int KD, int METHOD> static int go_any_dk(const SolveArgs& a)
 {

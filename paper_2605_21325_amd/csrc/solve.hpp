@@ -337,8 +337,9 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(1, NB 
     }
 }
 
-template <int OP, int NB, int METHOD, int WPB, int NRHS>
-__global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
+// TEAM: WPB = 1, a workgroup of up to TEAM_WAVES wavefronts forms a matrix together, its first one goes on alone.
+template <int OP, int NB, int METHOD, int WPB, int NRHS, bool TEAM = false>
+__global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) void k_kda_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
                                                             const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
                                                             int H, int d_k, int k_dt, int aux, int spread)
 {
@@ -347,7 +348,8 @@ __global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restri
     constexpr int PER_WAVE = CORE > C ? CORE : C;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
     float* lds = lds_all + ((WPB == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * PER_WAVE;
-    const int64_t m = fused_matrix_index<WPB>(n_chunk, H, n_chunk * H, spread);
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<OP, NB, true>::BYTES : 16];
+    const int64_t m = TEAM ? (int64_t)blockIdx.x : fused_matrix_index<WPB>(n_chunk, H, n_chunk * H, spread);
     if (m < 0) return;
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
     const int h = (int)((uint32_t)m - bc * (uint32_t)H);
@@ -357,9 +359,8 @@ __global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restri
     const int64_t esz = (k_dt == OP_F32) ? 4 : 2;
     const int64_t e0 = (tok0 * H + h) * (int64_t)d_k;
     PreA<NB> src;
-    if (!build_A_per_channel<OP, NB, METHOD>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0, (int64_t)H * d_k, beta + tok0 * H + h, H, d_k,
-                                             lds, ln, pos.valid, this_team(WPB > 1 && spread == ONE_TEAM_PER_GROUP ? (int)blockDim.x / 64 : 1),
-                                             n_chunk * H <= GATES_AHEAD_MATRICES))
+    if (!build_A_per_channel<OP, NB, METHOD, TEAM>(src, static_cast<const char*>(K) + e0 * esz, k_dt, g + e0, (int64_t)H * d_k, beta + tok0 * H + h, H,
+                                                   d_k, lds, ln, pos.valid, n_chunk * H <= GATES_AHEAD_MATRICES, this_team(team_lds)))
         return;
     RhsX<OP, NB> x;  // after the Gram passes, which need the registers
     x.init(rhs.r[0], tok0, h, H, pos.valid, ln);
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(64 * WPB) void k_kda_tri_solve(const void* __restri
 }
 
 // Scalar / no-gate kinds for head dimensions without a specialised build (any multiple of 32): the channel-loop Gram of
-// the storing kernel, then the same recursion and products.  One wavefront per workgroup.
+// the storing kernel, then the same recursion and products.  One wavefront per workgroup, or (TEAM) up to TEAM_WAVES that form a matrix together.
 template <int KD, int OP, int NB, int METHOD, int NRHS, bool TEAM>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) void k_gdn_any_dk_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
                                                              const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
@@ -382,6 +383,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) void k_gdn_any_dk_tri_
     constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int GATE = gate_lds_floats<NB>();
     __shared__ __attribute__((aligned(16))) float lds[CORE > GATE ? CORE : GATE];
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<KD, NB, false>::BYTES : 16];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
     const int h = (int)((uint32_t)m - bc * (uint32_t)H);
@@ -390,8 +392,8 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) void k_gdn_any_dk_tri_
     const Lane ln = lane_id();
     const int64_t esz = (KD == OP_F32) ? 4 : 2;
     PreA<NB> src;
-    if (!build_A_scalar_any_dk<KD, NB, METHOD>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
-                                               beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid, this_team(TEAM ? (int)blockDim.x / 64 : 1)))
+    if (!build_A_scalar_any_dk<KD, NB, METHOD, TEAM>(src, static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * esz, (int64_t)H * d_k,
+                                               beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, d_k, lds, ln, pos.valid, this_team(team_lds)))
         return;
     RhsX<OP, NB> x;
     x.init(rhs.r[0], tok0, h, H, pos.valid, ln);

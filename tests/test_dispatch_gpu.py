@@ -21,15 +21,15 @@ def make_inputs(T, H, d_k, gate, k_dtype=torch.bfloat16, seed=0, B=1):
     return K, beta, None if g is None else g.expand(*shape).contiguous()
 
 
-# Up to 512 matrices a workgroup holds one wavefront, above four: a matrix does not depend on the others of its call, so the same
-# chunks give the same bits on either side.
+# Up to 512 matrices a workgroup holds one wavefront, above four (with the per-channel gate: one matrix, formed by four of them): a matrix
+# does not depend on the others of its call, so the same chunks give the same bits on either side.
 @pytest.mark.parametrize("gate", GATES)
 @pytest.mark.parametrize("H", [1, 3, 4, 8])
 @pytest.mark.parametrize("C", [16, 32, 64])
 def test_few_matrices_give_the_bits_of_a_larger_call(C, H, gate):
     most = 512 // H                                   # chunks of the largest call with one wavefront to a workgroup
     T = (most + 1) * C - 5                            # ends inside a chunk
-    K, beta, g = make_inputs(T, H, 32 if gate == tri.GATE_PER_CHANNEL else 64, gate)  # (32 channels: no team, see below)
+    K, beta, g = make_inputs(T, H, 128 if gate == tri.GATE_PER_CHANNEL else 64, gate)
     X = torch.randn(1, T, H, 72, device=DEV).bfloat16()
     part = lambda x, n: None if x is None else x[:, :n * C].contiguous()
     many = [tri.gdn_chunk_tri_inv_ex(K, beta, g, C, gate_kind=gate, method=m) for m in (tri.BLOCK_RECURSIVE, tri.NEWTON_SCHULZ)]
@@ -170,36 +170,40 @@ def test_native_marshalling_runs_on_the_current_stream():
     assert torch.equal(T, want) and torch.equal(W, want_w)
 
 
-# With few matrices the channel loops share a matrix between up to four wavefronts: the partial sums add up to what one wavefront
-# gets, whatever the number of k-steps (32 channels each) and the chunk's tokens.
-@pytest.mark.parametrize("op", [tri.F32, tri.BF16])
-@pytest.mark.parametrize("k_dtype", [torch.bfloat16, torch.float32])
+# With few matrices the channel loops (per-channel gate, head dimensions without a kernel of their own; fp32 keys of 128 channels at C = 64)
+# share a matrix between up to four wavefronts.  Every method, whatever the number of k-steps (32 channels each) and the chunk's tokens,
+# gives the bits of a larger call, where one wavefront forms it.
+@pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
+@pytest.mark.parametrize("k_dtype", [torch.bfloat16, torch.float16, torch.float32], ids=str)
 @pytest.mark.parametrize("d_k", [32, 64, 96, 128, 160, 256])
 @pytest.mark.parametrize("C", [16, 32, 64])
 def test_teams_of_wavefronts_in_the_channel_loops(C, d_k, k_dtype, op):
     H = 4
+    many = 512 // H + 1
+    x_type = {tri.F32: torch.float32, tri.F16: torch.float16, tri.BF16: torch.bfloat16}[op]
     for gate in GATES:
-        many = 512 // H + 1
         K, beta, g = make_inputs(many * C - 3, H, d_k, gate, k_dtype)
-        X = torch.randn(1, many * C - 3, H, 40, device=DEV).to({tri.F32: torch.float32, tri.BF16: torch.bfloat16}[op])
-        for method in (tri.BLOCK_RECURSIVE, tri.NEWTON_SCHULZ, tri.FWD_SUBST):
-            T = tri.gdn_chunk_tri_inv_ex(K, beta, g, C, gate_kind=gate, method=method, op_dtype=op)
-            A = tri.gdn_chunk_build_A(K, beta, g, C, gate_kind=gate, op_dtype=op) if method == tri.BLOCK_RECURSIVE else None
-            W = tri.gdn_chunk_tri_solve(K, beta, g, X, C, gate_kind=gate) if method == tri.BLOCK_RECURSIVE else None
-            for n, tokens in ((1, C), (1, C - 5), (3, 2 * C + 1), (512 // H, 512 // H * C)):
-                cut = [None if x is None else x[:, :tokens].contiguous() for x in (K, beta, g, X)]
-                few = tri.gdn_chunk_tri_inv_ex(*cut[:3], C, gate_kind=gate, method=method, op_dtype=op)
-                whole, v = max(1, tokens // C) * H, min(tokens, C)  # (a short chunk: the leading block of the whole one)
-                # sums in another order: a rounding of the sum per partial sum, and of the operand where A is rounded to one
-                tol = 2e-6 if op == tri.F32 else 1.6e-2
-                assert (few[:whole, :v, :v] - T[:whole, :v, :v]).abs().max() <= tol * T[:whole].abs().max()
-                assert torch.isfinite(few).all()
-                if A is not None:
-                    a = tri.gdn_chunk_build_A(*cut[:3], C, gate_kind=gate, op_dtype=op)
-                    assert (a[:whole, :v, :v] - A[:whole, :v, :v]).abs().max() <= 4e-7
-                    w = tri.gdn_chunk_tri_solve(*cut, C, gate_kind=gate)
+        X = torch.randn(1, many * C - 3, H, 40, device=DEV).to(x_type)
+        calls = {tri.METHOD_NAMES[m]: (lambda k, b, gg, x, m=m: tri.gdn_chunk_tri_inv_ex(k, b, gg, C, gate_kind=gate, method=m, op_dtype=op))
+                 for m in tri.METHOD_NAMES if C > 16 or m != tri.MIXED_B32}
+        if gate == tri.GATE_PER_CHANNEL:
+            calls["refined"] = lambda k, b, gg, x: tri.gdn_chunk_tri_inv_ex(k, b, gg, C, gate_kind=gate, op_dtype=op, flags=tri.FLAG_REFINE1)
+        calls["A"] = lambda k, b, gg, x: tri.gdn_chunk_build_A(k, b, gg, C, gate_kind=gate, op_dtype=op)
+        for m in (tri.BLOCK_RECURSIVE, tri.MIXED):
+            calls["applied " + tri.METHOD_NAMES[m]] = lambda k, b, gg, x, m=m: tri.gdn_chunk_tri_solve(k, b, gg, x, C, gate_kind=gate, method=m)
+            calls["two sides " + tri.METHOD_NAMES[m]] = lambda k, b, gg, x, m=m: tri.gdn_chunk_tri_solve_multi(
+                k, b, gg, [x, x], C, row_scales=[b, None], gate_kind=gate, method=m)[1]
+        for name, call in calls.items():
+            every = call(K, beta, g, X)
+            for tokens in (C, C - 5, 2 * C + 1, 256 // H * C, 512 // H * C):
+                few = call(*(None if x is None else x[:, :tokens].contiguous() for x in (K, beta, g, X)))
+                if few.dim() == 4:  # applied
                     rows = tokens if tokens < C else tokens // C * C
-                    assert (w[:, :rows] - W[:, :rows]).abs().max() <= 2 * tol * W.abs().max()
+                    same = torch.equal(few[:, :rows], every[:, :rows])
+                else:
+                    whole, v = max(1, tokens // C) * H, min(tokens, C)  # (a short chunk: the leading block of the whole one)
+                    same = torch.equal(few[:whole, :v, :v], every[:whole, :v, :v])
+                assert same, (name, gate, tokens)
 
 
 # Two right-hand sides at C = 128 with fp32 operands take turns on one set of published tiles: each side as if it were the only one.
