@@ -1760,11 +1760,24 @@ def test_refinement_repairs_an_unconverged_newton_schulz():
 # ------------------------------------------------------------------ few heads: the chunk-strided workgroup map and its tail
 @pytest.mark.parametrize("H", [1, 2, 3, 4, 5, 7])
 @pytest.mark.parametrize("n_chunk", [1, 3, 4, 7, 16, 19, 33])
-def test_few_heads_workgroup_map_covers_every_matrix_once(H, n_chunk):
-    """H < 8 runs the map in which a workgroup takes one head of four chunks a stride apart; chunk counts that are not a
-    multiple of the group size end in a plain-order tail.  Every matrix must be written, with the right chunk's result,
-    for the storing kernels (scalar and per-channel gate), the applied inverse and the packed-sequence layout."""
-    C, d_k = 64, 64
+def test_few_heads_and_few_matrices_cover_every_matrix_once(H, n_chunk):
+    """Up to 512 matrices a workgroup has one of them, in plain order."""
+    assert n_chunk * H <= 512
+    every_matrix_once(H, n_chunk, 64)
+
+
+@pytest.mark.parametrize("H", [1, 2, 3, 4, 5, 7, 9])
+@pytest.mark.parametrize("beyond,C", [(0, 32), (1, 32), (3, 64), (7, 32), (16, 16)])
+def test_few_heads_workgroup_map_covers_every_matrix_once(H, beyond, C):
+    """More than 512 matrices: H < 8 runs the map in which a workgroup takes one head of four chunks a stride apart; chunk counts that
+    are not a multiple of the group size end in a plain-order tail.  (H = 9: four matrices in a row, no multiple of the heads.)"""
+    every_matrix_once(H, 512 // H + 1 + beyond, C)
+
+
+def every_matrix_once(H, n_chunk, C):
+    """Every matrix must be written, with the right chunk's result, for the storing kernels (scalar and per-channel gate), the applied
+    inverse and the packed-sequence layout."""
+    d_k = 64
     for idx in (1, 3):
         w = si.workload(idx, B=1, Tlen=n_chunk * C - 5, H=H, C=C, d_k=d_k)
         inp = si.make_inputs(w)
@@ -1779,7 +1792,7 @@ def test_few_heads_workgroup_map_covers_every_matrix_once(H, n_chunk):
         tri.gdn_chunk_tri_solve(K, beta, g, rhs["X"].to(DEV), C, W=W, gate_kind=w.gate_kind)
         check_solve(W, oracle.gdn_chunk_tri_solve(inp["K"], inp["beta"], inp["g"], rhs["X"], None, w.gate_kind, C), 2e-2,
                     f"solve H={H} n_chunk={n_chunk} cfg{idx}", C=C)
-    # packed sequences: the same tensors read as two sequences
+    # packed sequences: the same tensors read as two sequences (a chunk more where both end inside one)
     w = si.workload(1, B=1, Tlen=n_chunk * C - 5, H=H, C=C, d_k=d_k)
     inp = si.make_inputs(w)
     total = w.Tlen
@@ -1795,3 +1808,8 @@ def test_few_heads_workgroup_map_covers_every_matrix_once(H, n_chunk):
     Kp, bp = inp["K"][0].contiguous(), inp["beta"][0].contiguous()
     T = tri.gdn_chunk_tri_inv_varlen(Kp.to(DEV), bp.to(DEV), g.to(DEV), seqlens, C)
     check(T, oracle.gdn_chunk_tri_inv_varlen(Kp, bp, g, seqlens, 0, C), 2e-2, f"varlen H={H} n_chunk={n_chunk}")
+    X = torch.randn(total, H, 40, generator=gen).bfloat16()
+    W = torch.full(X.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+    tri.gdn_chunk_tri_solve_varlen(Kp.to(DEV), bp.to(DEV), g.to(DEV), X.to(DEV), seqlens, C, W=W)
+    check_solve(W[None], oracle.gdn_chunk_tri_solve_varlen(Kp, bp, g, X, None, seqlens, 0, C)[None], 2e-2, f"solve varlen H={H} n_chunk={n_chunk}",
+                C=C, seqlens=seqlens)
