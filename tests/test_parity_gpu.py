@@ -297,6 +297,25 @@ def test_fp32_keys_with_128_channels(C, mo):
     assert bool((guard[n_mat] == 7.0).all()), "wrote past the last matrix"
 
 
+# The same calls with more matrices than the launch shapes and kernels for few of them take (512).
+@pytest.mark.parametrize("mo", FP32_KEY_METHODS, ids=ids)
+@pytest.mark.parametrize("gate,d_k,C,k_dtype", [("scalar", 128, 64, "f32"), ("scalar", 96, 64, "bf16"), ("scalar", 160, 32, "f32"), ("scalar", 96, 16, "bf16"),
+                                                ("channel", 128, 64, "bf16"), ("channel", 96, 32, "f32"), ("channel", 64, 16, "bf16")])
+def test_channel_loops_and_fp32_keys_in_larger_calls(gate, d_k, C, k_dtype, mo):
+    method, op = mo
+    if C == 16 and method == tri.MIXED_B32:
+        pytest.skip("b0 = 32 needs C >= 32")
+    w = si.workload(3 if gate == "channel" else 1, B=1, Tlen=173 * C + 7, H=3, C=C, d_k=d_k, k_dtype=k_dtype)
+    inp = si.make_inputs(w)
+    T_ref = oracle.gdn_chunk_tri_inv_ragged(inp["K"], inp["beta"], inp["g"], w.gate_kind, C)
+    n_mat = T_ref.shape[0]
+    assert n_mat > 512
+    guard = torch.full((n_mat + 1, C, C), 7.0, device=DEV)
+    tri.gdn_chunk_tri_inv_ex(inp["K"].to(DEV), inp["beta"].to(DEV), inp["g"].to(DEV), C, T=guard[:n_mat], gate_kind=w.gate_kind, method=method, op_dtype=op)
+    check(guard[:n_mat], T_ref, TOL[op], f"{gate} d_k={d_k} C={C} {ids(mo)}", op=op, method=method, key_abs=key_abs_term(inp, w.gate_kind, C))
+    assert bool((guard[n_mat] == 7.0).all()), "wrote past the last matrix"
+
+
 def test_group_counts_that_are_not_multiples_of_eight(cases):
     # 12 (batch, chunk) groups: 8 go through the XCD-aware map, 4 keep the plain order
     inp = si.make_inputs(si.workload(1, B=1, Tlen=768, H=4))
