@@ -3,8 +3,10 @@
 //
 // A function returns the result, or None when anything about its arguments is not plain (no exact torch.Tensor on the current
 // device, not contiguous, another number of dimensions or element type, a chunk size there is no kernel for, an argument of the
-// wrong kind) or when the C-ABI refused the call.  Nothing has been launched then, and the caller goes through the Python route, which
-// raises what there is to raise: this file has no error messages of its own.  The same goes for C++ exceptions: libtorch throws them for
+// wrong kind) or when the C-ABI refused the call.  No matrix has been formed or written then, and the caller goes through the Python route,
+// which raises what there is to raise: this file has no error messages of its own.  (Packed sequences: their offsets may have been
+// written already, by a kernel on the call's stream, into a tensor that is then given back to the allocator of that stream.  Whoever gets its
+// memory next uses it behind that kernel, in a captured graph too.)  The same goes for C++ exceptions: libtorch throws them for
 // tensors that do not have what they are asked for, and none may pass the C boundary to the interpreter.
 //
 // Device -1 stands for host memory: not for the library, whose kernels cannot read it, but for tests with a stand-in for the C-ABI.
