@@ -779,7 +779,7 @@ template <int NB, int METHOD, bool GATED> struct GramProducts {
         return n;
     }
     static constexpr int COUNT = count_();
-    int code[COUNT] = {};  // left tile row | right operand << 8 | T orientation << 16
+    int code[COUNT] = {};  // i | tix(i, j) << 8 | T orientation << 16 | j << 24
     constexpr GramProducts()
     {
         int n = 0;
@@ -801,7 +801,7 @@ template <int OPG, int NB, bool GATED> struct TeamLds {
 };
 template <int OPG> __device__ __forceinline__ void team_write(char* p, const GOp<OPG>& o)
 {
-    if constexpr (OPG == OP_F32) {
+    if constexpr (OPG == OP_F32) {  // two planes
         *reinterpret_cast<v4f*>(p) = v4f{o.x[0], o.x[1], o.x[2], o.x[3]};
         *reinterpret_cast<v4f*>(p + 1024) = v4f{o.x[4], o.x[5], o.x[6], o.x[7]};
     } else {

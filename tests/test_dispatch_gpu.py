@@ -86,6 +86,8 @@ def _calls():
         "16-bit T of the short forms, keys": lambda: tri.gdn_chunk_tri_inv(K, beta, g, 64, T=new(24, 64, 64, dt=torch.float16)),
         "operand type": lambda: tri.tri_inv_ex(A, op_dtype=-1),
         "operand type of keys": lambda: tri.gdn_chunk_tri_inv_ex(K, beta, g, 64, op_dtype=-7),
+        "nested matrices": lambda: tri.tri_inv_ex(torch.nested.nested_tensor([A[0], A[1, :32, :32]])),
+        "nested keys": lambda: tri.gdn_chunk_tri_inv_ex(torch.nested.nested_tensor([K[0], K[1, :70]]), beta, g, 64),
         "result type": lambda: tri.tri_inv_ex(A, T=new(5, 64, 64), out_dtype=bf),
         "result type unknown": lambda: tri.tri_inv_ex(A, out_dtype=torch.int32),
         "not contiguous": lambda: tri.gdn_chunk_tri_inv_ex(K.transpose(0, 1), beta, g, 64),
@@ -105,6 +107,7 @@ def _calls():
     return calls, refused
 
 
+@pytest.mark.filterwarnings("ignore:The PyTorch API of nested tensors")
 def test_native_and_python_marshalling_agree(monkeypatch):
     calls, refused = _calls()
     tri.lib()
