@@ -63,14 +63,14 @@ inline int head_spread(int H) { return H >= 8 ? 0 : (H >= 4 ? 1 : 4 / H); }
 // 7.6 / 7.5 and 18.2 / 18.8; 1536 9.3 / 12.2.
 constexpr int ONE_WAVE_PER_GROUP = -1;  // in place of the spread
 constexpr int64_t FEW_MATRICES = 512;
-// The channel loops (per-channel gate, head dimensions without a kernel of their own) share a matrix of such a call between up to
-// four wavefronts, one per k-step (32 channels) where there are fewer.
+// The channel loops (per-channel gate, head dimensions without a kernel of their own) share a matrix of such a call between four
+// wavefronts where there is more than one k-step (32 channels).
 constexpr int TEAM_WAVES = 4;
-inline int team_waves(int64_t n_mat, int d_k) { return n_mat > FEW_MATRICES ? 1 : d_k / 32 < TEAM_WAVES ? d_k / 32 : TEAM_WAVES; }
+inline bool by_team(int64_t n_mat, int d_k) { return n_mat <= FEW_MATRICES && d_k > 32; }
 // fp32 keys of 128 channels go the same way at C = 64 although that head dimension has a kernel of its own: their Gram products are fp32
 // matrix instructions, 6 of the 11.7 us of such a call, and each diagonal tile's products are formed once there.  Up to one team per compute unit:
-// 256 matrices 11.8 / 10.0 us (own kernel / team; bf16 operands 9.7 / 8.1, one right-hand side applied 17.3 / 15.8), 512 12.6 / 12.4 and
-// 10.8 / 10.4.  Not with 64 channels, two wavefronts to a team: 256 matrices 8.9 / 9.2 and 7.3 / 7.2, 512 10.1 / 10.9 and 8.0 / 8.8.
+// 256 matrices 11.8 / 9.6 us (own kernel / team; bf16 operands 9.7 / 8.0, one right-hand side applied 17.3 / 15.8), 512 12.8 / 12.3 and
+// 10.7 / 10.3.  (64 channels, half the products, keep their kernel: 256 matrices 9.2 / 8.6 and 7.4 / 6.8, 512 10.1 / 10.1 and 8.1 / 8.3.)
 constexpr int FP32_KEYS_TEAM_DK = 128;
 inline bool fp32_keys_by_team(int64_t n_mat, int d_k, int C) { return C == 64 && d_k == FP32_KEYS_TEAM_DK && n_mat <= FEW_MATRICES / 2; }
 struct FusedGrid {

@@ -246,9 +246,8 @@ template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
 #endif
     {
         if constexpr (kda_team<OP, NB, METHOD, REFINE>()) {
-            const int team = team_waves(a.n_mat, a.d_k);
-            if (team > 1)
-                return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, 1, REFINE, true>, dim3((unsigned)a.n_mat), dim3(64 * team), 0, a.stream, a.K, a.beta,
+            if (by_team(a.n_mat, a.d_k))
+                return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, 1, REFINE, true>, dim3((unsigned)a.n_mat), dim3(64 * TEAM_WAVES), 0, a.stream, a.K, a.beta,
                                      a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt, 0);
         }
         const FusedGrid f = fused_grid(a.n_mat, a.H, WPB);
@@ -318,9 +317,8 @@ static int kda_method(const GdnArgs& a)
 template <int KD, int METHOD> static int go_any_dk(const GdnArgs& a)
 {
     if constexpr (NB <= 4) {
-        const int team = team_waves(a.n_mat, a.d_k);
-        if (team > 1)
-            return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, true>, dim3((unsigned)a.n_mat), dim3(64 * team),
+        if (by_team(a.n_mat, a.d_k))
+            return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, true>, dim3((unsigned)a.n_mat), dim3(64 * TEAM_WAVES),
                                  0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters,
                                  a.out_dt);
     }

@@ -754,19 +754,19 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
     }
 }
 
-// With few matrices up to four wavefronts of a workgroup form one matrix together.  What is spread over them: the channels, where the
-// operands of the products are made (exponentials), each wavefront one k-step (32 channels) of a round; and the products (fp32 matrix
+// With few matrices the four wavefronts of a workgroup form one matrix together.  What is spread over them: the channels, where the
+// operands of the products are made (exponentials), each wavefront one k-step (32 channels) of a round, if there are that many; and the products (fp32 matrix
 // instructions, beside which nothing else runs), each wavefront some of the tiles, over all channels.  Between the two the operands go
 // through LDS.  Every tile's products are added in one chain in the order of the channels, with the same operands as in the
 // loops of one wavefront: a matrix's bits do not depend on how many others its call has.
 // Bound by the one wavefront's recursion that follows, and by these products where they are fp32.  256 matrices of C = 64, d_k = 128, one
-// wavefront / four: per-channel gate 10.8 / 8.5 us, with fp32 operands 19.2 / 12.8, applied to two right-hand sides 14.6 / 12.3, forward
-// substitution 17.9 / 12.5; d_k = 256 without a gate, fp32 keys and operands 22.4 / 12.0, bf16 8.1 / 7.2.  512 matrices: 12.1 / 11.0, 20.3 / 16.8,
-// 17.5 / 15.9, 19.4 / 15.7, 24.6 / 16.0, 9.2 / 8.2.  (Each wavefront all the products of its own channels and the first adding the sums, another
+// wavefront / four: per-channel gate 10.8 / 8.2 us, with fp32 operands 19.2 / 12.7, applied to two right-hand sides 14.6 / 12.0, forward
+// substitution 17.9 / 12.1; d_k = 256 without a gate, fp32 keys and operands 22.4 / 11.8, bf16 8.1 / 6.8.  512 matrices: 12.1 / 10.2, 20.3 / 16.4,
+// 17.5 / 15.4, 19.4 / 15.2, 24.6 / 15.7, 9.2 / 7.7.  (Each wavefront all the products of its own channels and the first adding the sums, another
 // order: 8.6, 12.5, 12.3, -, 12.9, 7.4; 11.2, 16.5, 15.8, -, 16.3, 8.5.)
 struct Team {
-    int w, size;  // this wavefront, their number: four, or two or three where there are no more k-steps
-    char* lds;    // TeamLds::BYTES
+    int w;      // this wavefront of the TEAM_WAVES
+    char* lds;  // TeamLds::BYTES
 };
 // The products a method asks for: tile (i, j) in N or T orientation.  Without a gate both operands are the keys, and a diagonal tile is its
 // own transpose: one product serves both.
@@ -825,7 +825,7 @@ template <int OPG, int NB, bool GATED, int P, int STEPS> __device__ __forceinlin
 {
     typedef TeamLds<OPG, NB, GATED> LY;
     constexpr bool FACTORS = GATED && OPG == OP_F32;
-    constexpr int GROUP = OPG == OP_F32 ? 2 : 4, PER_STEP = (P + GROUP - 1) / GROUP;
+    constexpr int GROUP = OPG == OP_F32 ? 1 : 4, PER_STEP = (P + GROUP - 1) / GROUP;
     const int lane = 16 * (16 * ln.q + ln.n);
     GOp<OPG> left[2][GROUP], right[2][GROUP];
     v4f factor[2][GROUP][2];
@@ -874,14 +874,14 @@ template <int OPG, int NB, bool GATED, int P, int STEPS> __device__ __forceinlin
 // workgroup comes here, with the same matrix: the barriers are the workgroup's.
 // HALF_ROWS: a lane's eight channels of a k-step are 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3, not 8q .. 8q + 7 (the order of the products of the kernels
 // that keep fp32 keys in registers).
-template <int OPG, int NB, int METHOD, bool K16, bool GATED, int SIZE, bool HALF_ROWS>
-__device__ __forceinline__ bool team_gram_of(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
-                                             const Team& team)
+template <int OPG, int NB, int METHOD, bool K16, bool GATED, bool HALF_ROWS = false>
+__device__ __forceinline__ bool team_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
+                                          const Team& team)
 {
     typedef TeamLds<OPG, NB, GATED> LY;
     constexpr float LOG2E = 1.44269504088896340736f;
     static constexpr GramProducts<NB, METHOD, GATED> list;
-    constexpr int COUNT = list.COUNT, P = (COUNT + SIZE - 1) / SIZE;  // products in all, at most per wavefront
+    constexpr int COUNT = list.COUNT, SIZE = TEAM_WAVES, P = (COUNT + SIZE - 1) / SIZE;  // products in all, at most per wavefront
     const int lane = 16 * (16 * ln.q + ln.n);
     char* const mine = team.lds + team.w * LY::STEP;
     int rowc[NB];
@@ -987,27 +987,20 @@ __device__ __forceinline__ bool team_gram_of(PreA<NB>& out, const void* Kc, bool
         code[p] = list.code[k];
         acc[p] = zero4();
     }
-    load(team.w);
-    if constexpr (SIZE < TEAM_WAVES) {  // a k-step each
-        operands();
+    if (team.w < n_step) load(team.w);
+#pragma unroll 1
+    for (int s0 = 0; s0 < n_step; s0 += SIZE) {
+        const int s = s0 + team.w, steps = n_step - s0;
+        if (s < n_step) operands();
+        if (s + SIZE < n_step) load(s + SIZE);
         __syncthreads();
-        team_products<OPG, NB, GATED, P, SIZE>(acc, code, team.lds, ln);
-        __syncthreads();  // the operands have been read
-    } else {
-#pragma unroll 1
-        for (int s0 = 0; s0 < n_step; s0 += SIZE) {
-            const int s = s0 + team.w;
-            if (s < n_step) operands();
-            if (s + SIZE < n_step) load(s + SIZE);
-            __syncthreads();
-            if (n_step - s0 >= SIZE) {
-                team_products<OPG, NB, GATED, P, SIZE>(acc, code, team.lds, ln);
-            } else {
-#pragma unroll 1
-                for (int t = 0; t < n_step - s0; ++t) team_products<OPG, NB, GATED, P, 1>(acc, code, team.lds + t * LY::STEP, ln);
-            }
-            __syncthreads();
+        if (steps >= SIZE) {
+            team_products<OPG, NB, GATED, P, SIZE>(acc, code, team.lds, ln);
+        } else {
+            if (steps >= 2) team_products<OPG, NB, GATED, P, 2>(acc, code, team.lds, ln);
+            if (steps & 1) team_products<OPG, NB, GATED, P, 1>(acc, code, team.lds + (steps - 1) * LY::STEP, ln);
         }
+        __syncthreads();  // the operands have been read
     }
 #pragma unroll
     for (int p = 0; p < P; ++p)
@@ -1030,15 +1023,6 @@ __device__ __forceinline__ bool team_gram_of(PreA<NB>& out, const void* Kc, bool
     wave_lds_sync();
     return true;
 }
-template <int OPG, int NB, int METHOD, bool K16, bool GATED, bool HALF_ROWS = false>
-__device__ __forceinline__ bool team_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
-                                          const Team& team)
-{
-    if (team.size == 4) return team_gram_of<OPG, NB, METHOD, K16, GATED, 4, HALF_ROWS>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid, team);
-    if (team.size == 3) return team_gram_of<OPG, NB, METHOD, K16, GATED, 3, HALF_ROWS>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid, team);
-    return team_gram_of<OPG, NB, METHOD, K16, GATED, 2, HALF_ROWS>(out, Kc, is_f16, gc, row_stride, n_step, ln, valid, team);
-}
-
 // TEAM: formed by the workgroup's wavefronts together; false for those that are done.
 template <int OPG, int NB, int METHOD, bool TEAM>
 __device__ __forceinline__ bool build_A_per_channel(PreA<NB>& out, const void* Kc, int kd, const float* gc, int64_t row_stride,
@@ -1569,7 +1553,7 @@ template <int NB, int METHOD> constexpr int core_lds_floats()
 }
 
 // The team of this wavefront: its workgroup.
-__device__ __forceinline__ Team this_team(char* lds) { return Team{__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), (int)blockDim.x / 64, lds}; }
+__device__ __forceinline__ Team this_team(char* lds) { return Team{__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lds}; }
 // (Refined Newton-Schulz with fp32 operands at C = 64 takes more than 256 registers: a compute unit would hold one team of the two.)
 template <int OP, int NB, int METHOD, bool REFINE> constexpr bool kda_team() { return NB <= 4 && !(METHOD == M_NEWTON_SCHULZ && NB == 4 && OP == OP_F32 && REFINE); }
 
@@ -1789,7 +1773,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_
 }
 
 // Fused kernel for the per-channel gate: g is [B, Tlen, H, d_k]; the gated keys are rounded to OP.
-// TEAM: WPB = 1, a workgroup of up to TEAM_WAVES wavefronts per matrix.
+// TEAM: WPB = 1, a workgroup of TEAM_WAVES wavefronts per matrix.
 template <int OP, int NB, int METHOD, int WPB = 1, bool REFINE = false, bool TEAM = false>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE, true>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,

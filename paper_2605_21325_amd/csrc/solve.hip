@@ -108,10 +108,9 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
     return launch_kernel(f.dry, f.k_dt == OP_F32 ? k_kda_tri_solve_c128<OP, METHOD, false, 2> : k_kda_tri_solve_c128<OP, METHOD, true, 2>,
                          dim3((unsigned)f.n_mat), dim3(128), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
 #else
-    const int team = team_waves(f.n_mat, f.d_k);
-    if (team > 1)
+    if (by_team(f.n_mat, f.d_k))
         return launch_kernel(f.dry, a.n_rhs == 1 ? k_kda_tri_solve<OP, NB, METHOD, 1, 1, true> : k_kda_tri_solve<OP, NB, METHOD, 1, 2, true>,
-                             dim3((unsigned)f.n_mat), dim3(64 * team), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt,
+                             dim3((unsigned)f.n_mat), dim3(64 * TEAM_WAVES), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt,
                              f.iters, 0);
     const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
     const dim3 grid(shape.groups), block(shape.threads);
@@ -129,17 +128,17 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
 
 #if TRIINV_INST_NB <= 4
 // Head dimensions other than 64 / 128 (scalar / no-gate kinds), C <= 64.
-template <int KD, int METHOD, int NRHS, bool TEAM> static int launch_any_dk(const SolveArgs& a, int team)
+template <int KD, int METHOD, int NRHS, bool TEAM> static int launch_any_dk(const SolveArgs& a)
 {
     const GdnArgs& f = a.f;
-    return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, NRHS, TEAM>, dim3((unsigned)f.n_mat), dim3(64 * team),
+    return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, NRHS, TEAM>, dim3((unsigned)f.n_mat), dim3(TEAM ? 64 * TEAM_WAVES : 64),
                          0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
 }
 template <int KD, int METHOD> static int go_any_dk(const SolveArgs& a)
 {
-    const int team = team_waves(a.f.n_mat, a.f.d_k);
-    if (a.n_rhs == 1) return team > 1 ? launch_any_dk<KD, METHOD, 1, true>(a, team) : launch_any_dk<KD, METHOD, 1, false>(a, 1);
-    return team > 1 ? launch_any_dk<KD, METHOD, 2, true>(a, team) : launch_any_dk<KD, METHOD, 2, false>(a, 1);
+    const bool team = by_team(a.f.n_mat, a.f.d_k);
+    if (a.n_rhs == 1) return team ? launch_any_dk<KD, METHOD, 1, true>(a) : launch_any_dk<KD, METHOD, 1, false>(a);
+    return team ? launch_any_dk<KD, METHOD, 2, true>(a) : launch_any_dk<KD, METHOD, 2, false>(a);
 }
 
 template <int KD> static int any_dk_method(const SolveArgs& a)

@@ -337,7 +337,7 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(1, NB 
     }
 }
 
-// TEAM: WPB = 1, a workgroup of up to TEAM_WAVES wavefronts forms a matrix together, its first one goes on alone.
+// TEAM: WPB = 1, a workgroup of TEAM_WAVES wavefronts forms a matrix together, its first one goes on alone.
 template <int OP, int NB, int METHOD, int WPB, int NRHS, bool TEAM = false>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) void k_kda_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
                                                             const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) void k_kda_tri_s
 }
 
 // Scalar / no-gate kinds for head dimensions without a specialised build (any multiple of 32): the channel-loop Gram of
-// the storing kernel, then the same recursion and products.  One wavefront per workgroup, or (TEAM) up to TEAM_WAVES that form a matrix together.
+// the storing kernel, then the same recursion and products.  One wavefront per workgroup, or (TEAM) TEAM_WAVES that form a matrix together.
 template <int KD, int OP, int NB, int METHOD, int NRHS, bool TEAM>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) void k_gdn_any_dk_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
                                                              const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
