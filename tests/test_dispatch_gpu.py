@@ -174,7 +174,7 @@ def test_native_marshalling_runs_on_the_current_stream():
 
 
 # With few matrices the channel loops (per-channel gate, head dimensions without a kernel of their own; fp32 keys of 128 channels at C = 64)
-# share a matrix between up to four wavefronts.  Every method, whatever the number of k-steps (32 channels each) and the chunk's tokens,
+# share a matrix between four wavefronts.  Every method, whatever the number of k-steps (32 channels each) and the chunk's tokens,
 # gives the bits of a larger call, where one wavefront forms it.
 @pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
 @pytest.mark.parametrize("k_dtype", [torch.bfloat16, torch.float16, torch.float32], ids=str)
