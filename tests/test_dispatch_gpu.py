@@ -209,6 +209,19 @@ def test_teams_of_wavefronts_in_the_channel_loops(C, d_k, k_dtype, op):
                 assert same, (name, gate, tokens)
 
 
+# Beyond 8192 matrices some per-channel kernels no longer load gate rows a k-step ahead: the order of loads, not of sums.
+@pytest.mark.parametrize("k_dtype", [torch.bfloat16, torch.float32], ids=str)
+@pytest.mark.parametrize("C,op", [(32, tri.F32), (64, tri.BF16), (64, tri.F32)])
+def test_more_than_8192_matrices_give_the_bits_of_a_smaller_call(C, op, k_dtype):
+    H = 8
+    K, beta, g = make_inputs(1030 * C, H, 64, tri.GATE_PER_CHANNEL, k_dtype)
+    T = tri.gdn_chunk_tri_inv_ex(K, beta, g, C, gate_kind=tri.GATE_PER_CHANNEL, op_dtype=op)
+    assert T.shape[0] > 8192
+    for n in (40, 90, 1000):  # a team per matrix, a workgroup of four matrices, ahead
+        part = tri.gdn_chunk_tri_inv_ex(*(x[:, :n * C].contiguous() for x in (K, beta, g)), C, gate_kind=tri.GATE_PER_CHANNEL, op_dtype=op)
+        assert torch.equal(part, T[:n * H]), n
+
+
 # Two right-hand sides at C = 128 with fp32 operands take turns on one set of published tiles: each side as if it were the only one.
 @pytest.mark.parametrize("gate", GATES)
 @pytest.mark.parametrize("k_dtype,d_k", [(torch.bfloat16, 128), (torch.float32, 64)])
