@@ -579,21 +579,22 @@ __device__ __forceinline__ void neumann(const ASrc& A, v4f (&Xt)[NB * (NB + 1) /
 // Every iterate is a polynomial in A, hence lower triangular: the same tile structure as above.
 // X lives in N orientation (fp32).  Column j of tiles of Y = X + A X needs column j of X only, and column j of X Y the
 // columns j and up of X as a left factor, so the iteration runs over the columns from the last to the first and turns each
-// into its left form (T orientation) just before changing it.  That form comes from the packed tiles by one product
-// with the identity each, exact for finite 16-bit values: two products per iteration instead of the three that
+// into its left form (T orientation) just before changing it: the packed tiles go through LDS and come back by transposing reads
+// (Turn16), which take none of the issue slots that bound the kernel.  Two products per iteration instead of the three that
 // updating X in both orientations takes, and half of the state.
 // The first iteration from X0 = I / C is a scaling, X1 = 2/C I - (I + A) / C^2, and is written down directly.
 // Result: Xn, every tile in N orientation.
 //
 // What bounds it is the vector instructions and the matrix cores (16 cycles a 16-bit instruction, whether it contracts 16 or
-// 32 deep) in turn, which at two wavefronts per SIMD hardly overlap:
-//   16-bit operands (vector unit 0.53-0.62 busy, matrix cores 0.45-0.54): a 32-deep instruction contracts two adjacent tiles, a
-//     16-deep one a tile without a partner in its sum: 28 instructions + 10 transposes per iteration at C = 64 instead of 60.
-//     8 192 fused matrices of C = 64, bf16: 73 -> 58 us; standalone 60 -> 48 us.
-//   fp32 operands (vector 0.72, matrix 0.50): three 32-deep bf16 instructions per tile product on values split into three bf16
-//     parts (Split3) instead of four 16x16x4 fp32 instructions of 32 cycles: 150 instructions of 16 cycles per iteration instead of
-//     240 of 32.  The same matrices: 344 -> 192-213 us from card to card, standalone 348 -> 177 us, with the refinement step (one wavefront per SIMD)
-//     405 -> 258 us and 365 -> 247 us; error against 64 bits 1.01e-7 -> 0.97e-7 and 4.1e-8 -> 3.4e-8 (below the diagonal).
+// 32 deep, beside which two vector instructions fit), whose sum two wavefronts per SIMD fill:
+//   16-bit operands: a 32-deep instruction contracts two adjacent tiles, a 16-deep one a tile without a partner in its sum: 28
+//     instructions per iteration at C = 64.  8 192 fused matrices of C = 64, bf16 / fp16: 56.7 / 56.4 us, standalone 46.1 us
+//     (turned by ten products with the identity and 20 conversions more: 58.8 / 59.7 and 50.2; both orientations kept: 73 and 60).
+//   fp32 operands: three 32-deep bf16 instructions per tile product on values split into three bf16 parts (Split3) instead of four
+//     16x16x4 fp32 instructions of 32 cycles: 120 matrix and 560 vector instructions an iteration (turned by products: 150 and 680, 60 of
+//     them copies that keep a tile's parts in a row).  The same matrices: 174 us, standalone 169, with the refinement step 256 and 195
+//     (206, 195, 258 and 267 turned by products; 344 and 348 with fp32 instructions); 32768 of C = 32 149 (173); error against 64
+//     bits 9.9e-8 and 4.4e-8 (below the diagonal; fp32 instructions 1.01e-7 and 4.1e-8 ... 4.5e-8).
 // ---------------------------------------------------------------------------------------------
 
 // 16-bit operands: tile rows / columns 2 p and 2 p + 1 side by side.
@@ -623,10 +624,15 @@ template <int OP, int NB> struct NsOperands {
         for (int i = 0; i < NB; ++i)
             if (i >= j && mixed_terms(i, j)) acc[i] += odd[i];
     }
-    // left(i, j) <- the transpose of tile i of the right column j
-    static __device__ __forceinline__ void transpose(Left& l, const Right& r, int i, int j, Opnd<OP> id)
+    static constexpr int PARTS = 1;
+    static __device__ __forceinline__ void complete(Left&, int, int) {}
+    // part of tile i of a right column, and the same of left(i, j)
+    static __device__ __forceinline__ v2u part(const Right& r, int i, int) { return __builtin_bit_cast(v2u, r[i / 2].get(i & 1).x); }
+    static __device__ __forceinline__ void set_part(Left& l, int i, int j, int, v2u u)
     {
-        set_left(l, i, j, pack<OP>(tn<OP>(r[i / 2].get(i & 1), id, zero4())));
+        Opnd<OP> o;
+        o.x = __builtin_bit_cast(decltype(o.x), u);
+        set_left(l, i, j, o);
     }
     static __device__ __forceinline__ Opnd<OP> identity(Lane ln) { return pack<OP>(identity_tile(ln)); }
     static __device__ __forceinline__ void put_left(Left& l, int i, int j, v4f at) { set_left(l, i, j, pack<OP>(at)); }
@@ -668,10 +674,13 @@ template <int NB> struct NsOperands<OP_F32, NB> {
         for (int i = 0; i < NB; ++i)
             if (i >= j) acc[i] += cross[i];
     }
-    static __device__ __forceinline__ void transpose(Left& l, const Right& r, int i, int j, const Opnd<OP_BF16>& id)
+    static constexpr int PARTS = 3;
+    static __device__ __forceinline__ void complete(Left& l, int i, int j) { in_a_row(l[tix(i, j)]); }
+    static __device__ __forceinline__ v2u part(const Right& r, int i, int p) { return v2u{r[i].u[2 * p], r[i].u[2 * p + 1]}; }
+    static __device__ __forceinline__ void set_part(Left& l, int i, int j, int p, v2u u)
     {
-        l[tix(i, j)] = join3(pack<OP_BF16>(tn<OP_BF16>(r[i].m(), id, zero4())), pack<OP_BF16>(tn<OP_BF16>(r[i].h(), id, zero4())),
-                             pack<OP_BF16>(tn<OP_BF16>(r[i].l(), id, zero4())));
+        l[tix(i, j)].u[2 * p] = u[0];
+        l[tix(i, j)].u[2 * p + 1] = u[1];
     }
     static __device__ __forceinline__ Opnd<OP_BF16> identity(Lane ln) { return pack<OP_BF16>(identity_tile(ln)); }
     static __device__ __forceinline__ void put_left(Left& l, int i, int j, v4f at) { l[tix(i, j)] = split3_any(at); }
@@ -682,9 +691,13 @@ template <int NB> struct NsOperands<OP_F32, NB> {
     }
 };
 
+// patch: ns_lds_floats<OP, NB>() floats.
+template <int OP, int NB> __host__ __device__ constexpr int ns_lds_floats() { return NB * NsOperands<OP, NB>::PARTS * TURN16_BYTES / 4; }
+
 template <int OP, int NB, class ASrc>
-__device__ __forceinline__ void newton_schulz(const ASrc& A, v4f (&Xn)[NB * (NB + 1) / 2], int n_iter, Lane ln)
+__device__ __forceinline__ void newton_schulz(const ASrc& A, v4f (&Xn)[NB * (NB + 1) / 2], int n_iter, float* patch, Lane ln)
 {
+    const Turn16 turn(patch, ln);
     typedef NsOperands<OP, NB> Ops;
     constexpr float X0 = 1.f / (16 * NB);
     typename Ops::Left Al;
@@ -710,11 +723,23 @@ __device__ __forceinline__ void newton_schulz(const ASrc& A, v4f (&Xn)[NB * (NB 
             Ops::set_right(x, j, col);
 #pragma unroll
             for (int i = 0; i < NB; ++i)
-                if (i >= j) Ops::transpose(Xl, x, i, j, id);
+#pragma unroll
+                for (int p = 0; p < Ops::PARTS; ++p)
+                    if (i >= j) turn.put(Ops::PARTS * i + p, Ops::part(x, i, p));
+            leaf_lds_sync();
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int p = 0; p < Ops::PARTS; ++p)
+                    if (i >= j) Ops::set_part(Xl, i, j, p, turn.get(Ops::PARTS * i + p));
+            leaf_lds_sync();
             Ops::product(Al, x, j, col);  // Y = X + A X
             Ops::set_right(y, j, col);
 #pragma unroll
-            for (int i = 0; i < NB; ++i) col[i] = zero4();
+            for (int i = 0; i < NB; ++i) {
+                col[i] = zero4();
+                if (i >= j) Ops::complete(Xl, i, j);
+            }
             Ops::product(Xl, y, j, col);
 #pragma unroll
             for (int i = 0; i < NB; ++i)

@@ -1547,7 +1547,7 @@ template <int NB> constexpr int gate_lds_floats() { return 2 * 16 * NB; }
 template <int NB, int METHOD> constexpr int core_lds_floats()
 {
     if (METHOD == M_FWD) return forward_lds_floats<NB>();
-    constexpr int leaves = (NB < 4 ? NB : 4) * LEAF_STRIDE;
+    constexpr int leaves = METHOD == M_NEWTON_SCHULZ ? ns_lds_floats<OP_F32, NB>() : (NB < 4 ? NB : 4) * LEAF_STRIDE;
     constexpr int small = leaves > XPOSE_FLOATS ? leaves : XPOSE_FLOATS;
     return store_lds_floats<NB>() > small ? store_lds_floats<NB>() : small;
 }
@@ -1577,7 +1577,7 @@ __device__ __forceinline__ void invert_and_store(const ASrc& src, Out Tm, float*
         forward_substitution<NB>(src, Tm, lds, ln);
     } else if (METHOD == M_NEWTON_SCHULZ) {
         v4f Xt[NT];
-        newton_schulz<OP, NB>(src, Xt, aux, ln);  // aux = number of iterations
+        newton_schulz<OP, NB>(src, Xt, aux, lds, ln);  // aux = number of iterations
         if constexpr (REFINE) refine_once<OP, NB>(src, Xt, [](int, int) { return false; }, lds, ln);  // (turns every tile)
         store_result<NB>(Tm, Xt, [](int, int) { return REFINE; }, lds, ln);
     } else if (METHOD == M_NEUMANN) {

@@ -237,10 +237,14 @@ struct Split3 {
     __device__ __forceinline__ v8bf mh() const { return __builtin_bit_cast(v8bf, __builtin_shufflevector(u, u, 0, 1, 2, 3)); }
     __device__ __forceinline__ v8bf hl() const { return __builtin_bit_cast(v8bf, __builtin_shufflevector(u, u, 2, 3, 4, 5)); }
 };
+// Six registers in a row from here on (left alone, the compiler keeps the two windows apart and copies h: two instructions a tile).
+__device__ __forceinline__ void in_a_row(Split3& s) { asm("" : "+v"(s.u)); }
 __device__ __forceinline__ Split3 join3(Opnd<OP_BF16> m, Opnd<OP_BF16> h, Opnd<OP_BF16> l)
 {
     const v2u a = __builtin_bit_cast(v2u, m.x), b = __builtin_bit_cast(v2u, h.x), c = __builtin_bit_cast(v2u, l.x);
-    return {v6u{a[0], a[1], b[0], b[1], c[0], c[1]}};
+    Split3 s{v6u{a[0], a[1], b[0], b[1], c[0], c[1]}};
+    in_a_row(s);
+    return s;
 }
 __device__ __forceinline__ v4f minus_bf16(v4f x, Opnd<OP_BF16> y)
 {
@@ -276,6 +280,27 @@ __device__ __forceinline__ v4f tn_split(int part, Split3 x, Split3 y, v4f acc)
 {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(part == 0 ? x.hl() : x.mh(), part == 1 ? y.hl() : y.mh(), acc, 0, 0, 0);
 }
+
+// Packed 16-bit tiles turned through LDS: a tile is written as it stands, 8 bytes a lane, column n of the matrix at row n of the patch,
+// and read by the transposing read of gfx950 (ds_read_b64_tr_b16: lane n of a lane group receives element n of the four 32-byte rows
+// whose pieces the group's lanes point at, a piece each).  No arithmetic, so any bits are turned; the pieces of a row are permuted by
+// its group of four rows, so that neither access has a bank conflict.
+constexpr int TURN16_BYTES = 512;
+struct Turn16 {
+    typedef __attribute__((address_space(3))) v4s* lds_v4s;
+    char *put_at, *get_at;  // this lane's 8 bytes of tile 0
+    __device__ __forceinline__ Turn16(float* patch, Lane ln)
+    {
+        const int s = ln.n >> 2;
+        put_at = reinterpret_cast<char*>(patch) + 8 * (4 * ln.n + (ln.q ^ s));
+        get_at = reinterpret_cast<char*>(patch) + 8 * (16 * ln.q + 4 * s + ((ln.n & 3) ^ ln.q));
+    }
+    __device__ __forceinline__ void put(int tile, v2u u) const { *reinterpret_cast<v2u*>(put_at + tile * TURN16_BYTES) = u; }
+    __device__ __forceinline__ v2u get(int tile) const
+    {
+        return __builtin_bit_cast(v2u, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(get_at + tile * TURN16_BYTES)));
+    }
+};
 
 // Index of lower tile (i, j), i >= j, in a packed array of NB*(NB+1)/2 tiles.
 __host__ __device__ constexpr int tix(int i, int j) { return i * (i + 1) / 2 + j; }
