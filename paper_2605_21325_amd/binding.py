@@ -114,7 +114,7 @@ def _connect(L: ctypes.CDLL) -> None:
         return
     _fastcall.connect(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
         L.tri_inv_ex, L.gdn_chunk_tri_inv_ex, L.gdn_chunk_tri_inv_varlen, L.gdn_chunk_tri_solve_multi, L.gdn_chunk_tri_solve_varlen,
-        L.triinv_detail_chunk_offsets)))
+        L.triinv_detail_chunk_offsets, L.triinv_detail_inv_packed, L.triinv_detail_solve_packed)))
     _fast, _fast_lib = _fastcall, L
 
 

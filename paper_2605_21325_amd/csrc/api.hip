@@ -178,6 +178,50 @@ int solve_common(const void* K, const float* beta, const float* g, int n_rhs, co
     return finish(nb);
 }
 
+// The packed layout of these sequences for kernels that take a KM; false if their lengths do not go with the arguments or do not add up.
+template <class KM> bool packed_map(const int64_t* lens, int n_seq, int64_t total_tokens, int C, ChunkMap& map, int64_t& n_chunk)
+{
+    if (!chunk_size_ok(C) || !KM::bits_of(lens, n_seq)) return false;
+    int64_t sum = 0;
+    n_chunk = 0;
+    for (int s = 0; s < n_seq; ++s) {
+        sum += lens[s];
+        n_chunk += (lens[s] + C - 1) / C;
+    }
+    map = ChunkMap{total_tokens, 0u, (uint32_t)n_seq, nullptr, nullptr, lens};
+    return sum == total_tokens;
+}
+
+// Sequences packed back to back; arrays: the map has offset arrays in device memory.
+int inv_packed_common(const void* K, const float* beta, const float* g, float* T, const ChunkMap& map, int n_seq, int64_t total_chunks, bool arrays,
+                      int H, int d_k, int C, int k_dtype, int gate_kind, int method, int op_dtype, void* hip_stream, uint32_t flags)
+{
+    const int64_t total_tokens = map.Tlen;
+    if (!chunk_size_ok(C)) return TRIINV_ERR_BAD_C;
+    if (!dtype_ok(k_dtype) || !dtype_ok(op_dtype)) return TRIINV_ERR_BAD_DTYPE;
+    if (!method_ok(method)) return TRIINV_ERR_BAD_METHOD;
+    if (gate_kind < TRIINV_GATE_SCALAR || gate_kind > TRIINV_GATE_NONE) return TRIINV_ERR_BAD_METHOD;
+    if (n_seq <= 0 || H <= 0 || d_k <= 0 || total_tokens < 0 || total_chunks < 0 || d_k % 32 != 0 || d_k > 256)
+        return TRIINV_ERR_BAD_SHAPE;
+    // every chunk holds between 1 and C tokens, and a sequence wastes at most one partly filled chunk
+    if (total_chunks > total_tokens || total_chunks * C < total_tokens || total_chunks > (total_tokens + C - 1) / C + n_seq)
+        return TRIINV_ERR_BAD_SHAPE;
+    if (total_chunks > 0x7fffffffLL / H) return TRIINV_ERR_BAD_SHAPE;
+    const int64_t n_mat = total_chunks * H;
+    if (n_mat == 0) return TRIINV_OK;
+    if (arrays && (!map.cu_seqlens || !map.cu_chunks)) return TRIINV_ERR_NULL;
+    if ((reinterpret_cast<uintptr_t>(map.cu_seqlens) & 7u) || (reinterpret_cast<uintptr_t>(map.cu_chunks) & 7u)) return TRIINV_ERR_ALIGN;
+    const int st = check_fused(K, beta, g, T, (uint64_t)total_tokens * H, n_mat, H, d_k, C, k_dtype, gate_kind, method, flags);
+    if (st != TRIINV_OK) return st;
+    const uint64_t t_bytes = (uint64_t)n_mat * C * C * esize(out_dtype(flags)), cu_bytes = (uint64_t)(n_seq + 1) * 8;
+    if (arrays && (overlap(map.cu_seqlens, cu_bytes, T, t_bytes) || overlap(map.cu_chunks, cu_bytes, T, t_bytes))) return TRIINV_ERR_ALIAS;
+    if (method == TRIINV_FWD_SUBST && gate_kind != TRIINV_GATE_PER_CHANNEL) op_dtype = TRIINV_F32;
+
+    GdnArgs a{K, beta, gate_kind != TRIINV_GATE_NONE ? g : nullptr, T, n_mat, total_chunks, map, H, d_k, k_dtype, gate_kind, method,
+              static_cast<hipStream_t>(hip_stream), (flags & TRIINV_FLAG_REFINE1) != 0, method_count(method, flags, C), out_dtype(flags)};
+    return launch_fused(a, C, op_dtype);
+}
+
 // Offsets by value: written to device memory by a kernel whose arguments they are, without a copy engine or a host wait.
 // Three sizes: the runtime copies all of a launch's arguments to the device's queue, whatever of them is used
 // (a packed call of 2 to 15 sequences 9.6 -> 8.4 us of the host's time, of 48 9.8 -> 8.9).
@@ -311,30 +355,31 @@ int gdn_chunk_tri_inv_varlen(const void* K, const float* beta, const float* g, f
                              const int64_t* cu_chunks, int n_seq, int64_t total_tokens, int64_t total_chunks, int H, int d_k,
                              int C, int k_dtype, int gate_kind, int method, int op_dtype, void* hip_stream, uint32_t flags)
 {
-    if (!chunk_size_ok(C)) return TRIINV_ERR_BAD_C;
-    if (!dtype_ok(k_dtype) || !dtype_ok(op_dtype)) return TRIINV_ERR_BAD_DTYPE;
-    if (!method_ok(method)) return TRIINV_ERR_BAD_METHOD;
-    if (gate_kind < TRIINV_GATE_SCALAR || gate_kind > TRIINV_GATE_NONE) return TRIINV_ERR_BAD_METHOD;
-    if (n_seq <= 0 || H <= 0 || d_k <= 0 || total_tokens < 0 || total_chunks < 0 || d_k % 32 != 0 || d_k > 256)
-        return TRIINV_ERR_BAD_SHAPE;
-    // every chunk holds between 1 and C tokens, and a sequence wastes at most one partly filled chunk
-    if (total_chunks > total_tokens || total_chunks * C < total_tokens || total_chunks > (total_tokens + C - 1) / C + n_seq)
-        return TRIINV_ERR_BAD_SHAPE;
-    if (total_chunks > 0x7fffffffLL / H) return TRIINV_ERR_BAD_SHAPE;
-    const int64_t n_mat = total_chunks * H;
-    if (n_mat == 0) return TRIINV_OK;
-    if (!cu_seqlens || !cu_chunks) return TRIINV_ERR_NULL;
-    if ((reinterpret_cast<uintptr_t>(cu_seqlens) & 7u) || (reinterpret_cast<uintptr_t>(cu_chunks) & 7u)) return TRIINV_ERR_ALIGN;
-    const int st = check_fused(K, beta, g, T, (uint64_t)total_tokens * H, n_mat, H, d_k, C, k_dtype, gate_kind, method, flags);
-    if (st != TRIINV_OK) return st;
-    const uint64_t t_bytes = (uint64_t)n_mat * C * C * esize(out_dtype(flags)), cu_bytes = (uint64_t)(n_seq + 1) * 8;
-    if (overlap(cu_seqlens, cu_bytes, T, t_bytes) || overlap(cu_chunks, cu_bytes, T, t_bytes)) return TRIINV_ERR_ALIAS;
-    if (method == TRIINV_FWD_SUBST && gate_kind != TRIINV_GATE_PER_CHANNEL) op_dtype = TRIINV_F32;
-
     const ChunkMap map{total_tokens, 0u, (uint32_t)n_seq, cu_seqlens, cu_chunks};
-    GdnArgs a{K, beta, gate_kind != TRIINV_GATE_NONE ? g : nullptr, T, n_mat, total_chunks, map, H, d_k, k_dtype, gate_kind, method,
-              static_cast<hipStream_t>(hip_stream), (flags & TRIINV_FLAG_REFINE1) != 0, method_count(method, flags, C), out_dtype(flags)};
-    return launch_fused(a, C, op_dtype);
+    return inv_packed_common(K, beta, g, T, map, n_seq, total_chunks, true, H, d_k, C, k_dtype, gate_kind, method, op_dtype, hip_stream, flags);
+}
+
+// Used by the Python binding's native argument handling, no part of the interface in triinv.h: the varlen entry points with the lengths of the
+// sequences in a HOST array, for lengths that packed_map takes; everything else is refused before any launch.
+int triinv_detail_inv_packed(const void* K, const float* beta, const float* g, float* T, const int64_t* lens, int n_seq, int64_t total_tokens,
+                             int H, int d_k, int C, int k_dtype, int gate_kind, int method, int op_dtype, void* hip_stream, uint32_t flags)
+{
+    ChunkMap map{};
+    int64_t n_chunk;
+    if (!lengths_in_arguments(method, (flags & TRIINV_FLAG_REFINE1) != 0)) return TRIINV_ERR_UNSUPPORTED;
+    if (!packed_map<InvMap>(lens, n_seq, total_tokens, C, map, n_chunk)) return TRIINV_ERR_BAD_SHAPE;
+    return inv_packed_common(K, beta, g, T, map, n_seq, n_chunk, false, H, d_k, C, k_dtype, gate_kind, method, op_dtype, hip_stream, flags);
+}
+
+int triinv_detail_solve_packed(const void* K, const float* beta, const float* g, const void* X, const float* row_scale, void* W, const int64_t* lens,
+                               int n_seq, int64_t total_tokens, int H, int d_k, int d_x, int C, int k_dtype, int gate_kind, int method,
+                               int op_dtype, void* hip_stream, uint32_t flags)
+{
+    ChunkMap map{};
+    int64_t n_chunk;
+    if (!packed_map<SolveMap<1>>(lens, n_seq, total_tokens, C, map, n_chunk)) return TRIINV_ERR_BAD_SHAPE;
+    return solve_common(K, beta, g, 1, &X, &row_scale, &W, &d_x, (uint64_t)total_tokens, n_chunk, map, H, d_k, C, k_dtype, gate_kind, method,
+                        op_dtype, hip_stream, flags);
 }
 
 int gdn_chunk_tri_solve(const void* K, const float* beta, const float* g, const void* X, const float* row_scale, void* W, int B,

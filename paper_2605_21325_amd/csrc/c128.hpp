@@ -312,9 +312,10 @@ __device__ __forceinline__ void c128_store_result(v4f* mail, float* strip, Out T
 // run back to back on one XCD (head_group_swizzle).
 template <int KD, int OP, int METHOD, int DKS, bool NOGATE>
 __global__ __launch_bounds__(128) void k_gdn_tri_inv_c128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                          const float* __restrict__ g, float* __restrict__ T, int64_t n_chunk,
-                                                          ChunkMap map, int H, int d_k, int aux, int out_dt)
+                                                          const float* __restrict__ g, float* __restrict__ T, uint32_t n_chunk,
+                                                          InvMap map, int H, int d_k, uint8_t aux, uint8_t out_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 128;
     __shared__ __attribute__((aligned(16))) char lds[C128Lds<KD, OP, DKS, METHOD>::BYTES];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);

@@ -291,9 +291,10 @@ __device__ __forceinline__ void c128_kda_invert(char* lds, const void* Kc, int k
 // fit the 64 KB that two compute units keep of it).
 template <int OP, int METHOD, bool K16>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 1 : 2))) void k_kda_tri_inv_c128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                          const float* __restrict__ g, float* __restrict__ T, int64_t n_chunk,
-                                                          ChunkMap map, int H, int d_k, int k_dt, int aux, int out_dt)
+                                                          const float* __restrict__ g, float* __restrict__ T, uint32_t n_chunk,
+                                                          InvMap map, int H, int d_k, uint8_t k_dt, uint8_t aux, uint8_t out_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 128;
     typedef C128KdaLds<OP, METHOD> LY;
     __shared__ __attribute__((aligned(16))) char lds[LY::BYTES];

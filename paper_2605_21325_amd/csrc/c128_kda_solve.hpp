@@ -46,9 +46,10 @@ __device__ __forceinline__ void c128_kda_invert_and_apply(char* lds, const void*
 // to one or two right-hand sides.  One workgroup of two wavefronts per chunk matrix.
 template <int OP, int METHOD, bool K16, int NRHS>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 1 : 2))) void k_kda_tri_solve_c128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
+                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<NRHS == 1> map,
                                                             int H, int d_k, int k_dt, int aux)
 {
+    arguments_together(n_chunk, K, beta, g, rhs.r[0].X, map);
     constexpr int C = 128;
     __shared__ __attribute__((aligned(16))) char lds[C128KdaSolveLds<OP, METHOD, NRHS>::BYTES];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);

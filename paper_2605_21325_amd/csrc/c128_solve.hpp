@@ -536,9 +536,10 @@ __device__ __forceinline__ void c128_invert_and_apply_rows(char* lds, const void
 // split by rows (c128_apply_rows).  One workgroup of two wavefronts per chunk matrix.
 template <int KD, int OP, int METHOD, int DKS, bool NOGATE>
 __global__ __launch_bounds__(128) void k_gdn_tri_solve_c128_rows(const void* __restrict__ K, const float* __restrict__ beta,
-                                                                 const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
+                                                                 const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<true> map,
                                                                  int H, int d_k, int aux)
 {
+    arguments_together(n_chunk, K, beta, g, rhs.r[0].X, map);
     constexpr int C = 128;
     __shared__ __attribute__((aligned(16))) char lds[C128SolveRowsLds<KD, OP, DKS, METHOD>::BYTES];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
@@ -562,9 +563,10 @@ __global__ __launch_bounds__(128) void k_gdn_tri_solve_c128_rows(const void* __r
 // one or two right-hand sides.  One workgroup of two wavefronts per chunk matrix.
 template <int KD, int OP, int METHOD, int DKS, int NRHS, bool NOGATE>
 __global__ __launch_bounds__(128) void k_gdn_tri_solve_c128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
+                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<NRHS == 1> map,
                                                             int H, int d_k, int aux)
 {
+    arguments_together(n_chunk, K, beta, g, rhs.r[0].X, map);
     constexpr int C = 128;
     __shared__ __attribute__((aligned(16))) char lds[C128SolveLds<KD, OP, DKS, METHOD, NRHS>::BYTES];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);

@@ -34,6 +34,10 @@ struct Abi {
     int (*solve_varlen)(const void*, const void*, const void*, const void*, const void*, void*, const int64_t*, const int64_t*, int, int64_t,
                         int64_t, int, int, int, int, int, int, int, int, void*, uint32_t);
     int (*offsets)(const int64_t*, int, int, int64_t, int64_t*, int64_t*, void*);
+    // may be absent
+    int (*inv_packed)(const void*, const void*, const void*, void*, const int64_t*, int, int64_t, int, int, int, int, int, int, int, void*, uint32_t);
+    int (*solve_packed)(const void*, const void*, const void*, const void*, const void*, void*, const int64_t*, int, int64_t, int, int, int, int, int,
+                        int, int, int, void*, uint32_t);
 } abi;
 
 int code_of(at::ScalarType t) { return t == at::kFloat ? F32 : t == at::kHalf ? F16 : t == at::kBFloat16 ? BF16 : -1; }
@@ -246,12 +250,27 @@ bool lengths(PyObject* o, std::vector<int64_t>& lens)
     return true;
 }
 
+// Number of chunks of up to 64 sequences, whose lengths may go with the arguments of the kernel that uses them (csrc/chunk_map.hpp): one launch and
+// no offsets in memory.  false: more of them, or lengths that do not add up to the tokens there are.
+bool with_arguments(const std::vector<int64_t>& lens, int64_t total, int64_t C, int64_t& n_chunk)
+{
+    if (!abi.inv_packed || lens.empty() || lens.size() > 64) return false;
+    int64_t sum = 0;
+    n_chunk = 0;
+    for (const int64_t n : lens) {
+        if (n < 0 || n > total) return false;
+        sum += n;
+        n_chunk += (n + C - 1) / C;
+    }
+    return sum == total;
+}
+
 // The launches are asynchronous: the offsets live as long as the result.
 PyObject* with_offsets(const at::Tensor& result, const at::Tensor& cu)
 {
     PyObject* const r = THPVariable_Wrap(result);
-    PyObject* const c = r ? THPVariable_Wrap(cu) : nullptr;
-    PyObject* const keep = c ? PyTuple_Pack(1, c) : nullptr;
+    PyObject* const c = r && cu.defined() ? THPVariable_Wrap(cu) : nullptr;
+    PyObject* const keep = c ? PyTuple_Pack(1, c) : r && !cu.defined() ? PyTuple_New(0) : nullptr;
     const bool good = keep && PyObject_SetAttrString(r, "_triinv_keepalive", keep) == 0;
     Py_XDECREF(c);
     Py_XDECREF(keep);
@@ -279,6 +298,12 @@ PyObject* gdn_inv_varlen(PyObject*, PyObject* const* v, Py_ssize_t n)
     if (a.narrow(H), !a.ok()) return none();
     if (!unlocked([&] {
             int64_t n_chunk = 0;
+            if (with_arguments(lens, total, C, n_chunk)) {
+                if (!result(T, {n_chunk * H, C, C}, type, given, K, flags)) return false;
+                if (abi.inv_packed(K.data_ptr(), beta.data_ptr(), g.defined() ? g.data_ptr() : nullptr, out(T), lens.data(), (int)ns, total, (int)H,
+                                   (int)K.size(2), C, code_of(K.scalar_type()), gate, method, op, a.stream(), flags) == 0)
+                    return true;
+            }
             cu = at::empty({2 * (ns + 1)}, K.options().dtype(at::kLong));
             int64_t* const c = cu.data_ptr<int64_t>();
             if (abi.offsets(lens.data(), (int)ns, C, total, c, &n_chunk, a.stream()) != 0) return false;
@@ -310,6 +335,13 @@ PyObject* gdn_solve_varlen(PyObject*, PyObject* const* v, Py_ssize_t n)
     if (a.narrow(H), a.narrow(X.size(2)), !a.ok()) return none();
     if (!unlocked([&] {
             int64_t n_chunk = 0;
+            if (with_arguments(lens, total, C, n_chunk)) {
+                if (!W.defined()) W = at::empty(X.sizes(), X.options());
+                if (abi.solve_packed(K.data_ptr(), beta.data_ptr(), g.defined() ? g.data_ptr() : nullptr, ptr(X), scale.defined() ? scale.data_ptr() : nullptr,
+                                     out(W), lens.data(), (int)ns, total, (int)H, (int)K.size(2), (int)X.size(2), C, code_of(K.scalar_type()), gate,
+                                     method, code_of(X.scalar_type()), a.stream(), flags) == 0)
+                    return true;
+            }
             cu = at::empty({2 * (ns + 1)}, K.options().dtype(at::kLong));
             int64_t* const c = cu.data_ptr<int64_t>();
             if (abi.offsets(lens.data(), (int)ns, C, total, c, &n_chunk, a.stream()) != 0) return false;
@@ -322,12 +354,12 @@ PyObject* gdn_solve_varlen(PyObject*, PyObject* const* v, Py_ssize_t n)
     return with_offsets(W, cu);
 }
 
-// connect(addresses): the C-ABI functions in the order of Abi
+// connect(addresses): the C-ABI functions in the order of Abi, without or with the last two
 PyObject* connect(PyObject*, PyObject* const* v, Py_ssize_t n)
 {
-    void* p[6];
-    if (n != 6) return PyErr_SetString(PyExc_TypeError, "six addresses"), nullptr;
-    for (int i = 0; i < 6; ++i) {
+    void* p[8] = {};
+    if (n != 6 && n != 8) return PyErr_SetString(PyExc_TypeError, "six or eight addresses"), nullptr;
+    for (int i = 0; i < n; ++i) {
         p[i] = PyLong_AsVoidPtr(v[i]);
         if (!p[i]) return PyErr_Occurred() ? nullptr : (PyErr_SetString(PyExc_ValueError, "null address"), nullptr);
     }
@@ -337,6 +369,8 @@ PyObject* connect(PyObject*, PyObject* const* v, Py_ssize_t n)
     abi.solve_multi = reinterpret_cast<decltype(abi.solve_multi)>(p[3]);
     abi.solve_varlen = reinterpret_cast<decltype(abi.solve_varlen)>(p[4]);
     abi.offsets = reinterpret_cast<decltype(abi.offsets)>(p[5]);
+    abi.inv_packed = reinterpret_cast<decltype(abi.inv_packed)>(p[6]);
+    abi.solve_packed = reinterpret_cast<decltype(abi.solve_packed)>(p[7]);
     Py_RETURN_NONE;
 }
 

@@ -135,7 +135,7 @@ struct KdaHead128 {
     const float* gc;
     const float* bc;
 };
-__device__ __forceinline__ KdaHead128 kda_head128(const void* K, const float* beta, const float* g, int64_t n_chunk, const ChunkMap& map,
+__device__ __forceinline__ KdaHead128 kda_head128(const void* K, const float* beta, const float* g, uint32_t n_chunk, const InvMap& map,
                                                   int H, int d_k, int k_dt)
 {
     KdaHead128 o;
@@ -180,9 +180,10 @@ template <int OP> constexpr int kda128_lds_bytes(int rest)
 // Newton-Schulz, per-channel gate, C = 128, any d_k (multiple of 32).
 template <int OP>
 __global__ __launch_bounds__(256) void k_kda_tri_inv_ns128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                           const float* __restrict__ g, float* __restrict__ T, int64_t n_chunk,
-                                                           ChunkMap map, int H, int d_k, int k_dt, int n_iter, int out_dt)
+                                                           const float* __restrict__ g, float* __restrict__ T, uint32_t n_chunk,
+                                                           InvMap map, int H, int d_k, uint8_t k_dt, uint8_t n_iter, uint8_t out_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     __shared__ __attribute__((aligned(16))) char lds[kda128_lds_bytes<OP>(ns128_lds_bytes<OP>())];
     const KdaHead128 hd = kda_head128(K, beta, g, n_chunk, map, H, d_k, k_dt);
     const Lane ln = lane_id();
@@ -198,9 +199,10 @@ __global__ __launch_bounds__(256) void k_kda_tri_inv_ns128(const void* __restric
 // Neumann product, per-channel gate, C = 128.
 template <int OP>
 __global__ __launch_bounds__(256) void k_kda_tri_inv_neumann128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                                const float* __restrict__ g, float* __restrict__ T, int64_t n_chunk,
-                                                                ChunkMap map, int H, int d_k, int k_dt, int out_dt)
+                                                                const float* __restrict__ g, float* __restrict__ T, uint32_t n_chunk,
+                                                                InvMap map, int H, int d_k, uint8_t k_dt, uint8_t out_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     typedef MailTiles<OP> Mail;
     __shared__ __attribute__((aligned(16))) char lds[kda128_lds_bytes<OP>(ns128_lds_bytes<OP>())];
     const KdaHead128 hd = kda_head128(K, beta, g, n_chunk, map, H, d_k, k_dt);
@@ -219,9 +221,10 @@ __global__ __launch_bounds__(256) void k_kda_tri_inv_neumann128(const void* __re
 // leave its 36 tiles in LDS (N orientation, packed) and run the pass of refine128_run with them.
 template <int OP>
 __global__ __launch_bounds__(256) void k_kda_tri_inv_refine128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                               const float* __restrict__ g, float* T, int64_t n_chunk, ChunkMap map,
-                                                               int H, int d_k, int k_dt)
+                                                               const float* __restrict__ g, float* T, uint32_t n_chunk, InvMap map,
+                                                               int H, int d_k, uint8_t k_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     typedef MailTiles<OP> Mail;
     constexpr int Y_BYTES = N128_LDS_FLOATS * 4;  // refine128_run's copy of the first result; the key exchange comes before it
     __shared__ __attribute__((aligned(16))) char lds[kda128_lds_bytes<OP>(Y_BYTES) + Mail::BYTES];

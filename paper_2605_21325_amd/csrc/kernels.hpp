@@ -1720,8 +1720,9 @@ template <int KD, int OP, int NB, int METHOD, int DKS> constexpr int gdn_lds_flo
 template <int KD, int OP, int NB, int METHOD, int DKS, bool REFINE = false, int WPB = 1>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_gdn_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
-                                                          int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt, int spread)
+                                                          uint32_t n_chunk, InvMapIf<lengths_in_arguments(METHOD, REFINE)> map, int H, int d_k, uint8_t aux, uint8_t out_dt, int8_t spread)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 16 * NB;
     constexpr int CORE = gdn_lds_floats<KD, OP, NB, METHOD, DKS>();
     constexpr int GATE = gate_lds_floats<NB>();
@@ -1750,8 +1751,9 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_wa
 template <int KD, int OP, int NB, int METHOD, bool TEAM>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, false>()))) void k_gdn_any_dk_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
-                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int aux, int out_dt)
+                                                           uint32_t n_chunk, InvMap map, int H, int d_k, uint8_t aux, uint8_t out_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 16 * NB;
     constexpr int CORE = core_lds_floats<NB, METHOD>();
     constexpr int GATE = gate_lds_floats<NB>();
@@ -1777,8 +1779,9 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_
 template <int OP, int NB, int METHOD, int WPB = 1, bool REFINE = false, bool TEAM = false>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE, true>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
-                                                          int64_t n_chunk, ChunkMap map, int H, int d_k, int k_dt, int aux, int out_dt, int spread)
+                                                          uint32_t n_chunk, InvMap map, int H, int d_k, uint8_t k_dt, uint8_t aux, uint8_t out_dt, int8_t spread)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 16 * NB;
     constexpr int CORE = core_lds_floats<NB, METHOD>();
     constexpr int PER_WAVE = CORE > C ? CORE : C;
@@ -2222,9 +2225,10 @@ __global__ __launch_bounds__(256) void k_tri_inv_refine128(const void* __restric
 
 template <int KD, int OP, int DKS>
 __global__ __launch_bounds__(256) void k_gdn_tri_inv_refine128(const void* __restrict__ K, const float* __restrict__ beta,
-                                                               const float* __restrict__ g, float* T, int64_t n_chunk,
-                                                               ChunkMap map, int H, int d_k)
+                                                               const float* __restrict__ g, float* T, uint32_t n_chunk,
+                                                               InvMap map, int H, int d_k)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 128;
     __shared__ __attribute__((aligned(16))) float Y[N128_LDS_FLOATS];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
@@ -2262,8 +2266,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F3
 template <int KD, int OP, int DKS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_gdn_tri_inv_ns128(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
-                                                           int64_t n_chunk, ChunkMap map, int H, int d_k, int n_iter, int out_dt)
+                                                           uint32_t n_chunk, InvMap map, int H, int d_k, uint8_t n_iter, uint8_t out_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 128;
     typedef SharedKeys128<KD, DKS> Keys;
     constexpr int GATE_BYTES = 4 * 2 * C * 4;  // beta and g of the chunk, staged by every wave for itself
@@ -2311,8 +2316,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F3
 template <int KD, int OP, int DKS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_gdn_tri_inv_neumann128(const void* __restrict__ K, const float* __restrict__ beta,
                                                                 const float* __restrict__ g, float* __restrict__ T,
-                                                                int64_t n_chunk, ChunkMap map, int H, int d_k, int out_dt)
+                                                                uint32_t n_chunk, InvMap map, int H, int d_k, uint8_t out_dt)
 {
+    arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 128;
     typedef SharedKeys128<KD, DKS> Keys;
     typedef MailTiles<OP> Mail;

@@ -75,6 +75,7 @@ template <int KD, int METHOD, int DKS> static int go_gdn(const SolveArgs& a)
     {
     const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
     const dim3 grid(shape.groups), block(shape.threads);
+    if (f.map.lens && !solve_packed<OP, NB>()) return 1;
     if (a.n_rhs == 1) {
         return launch_kernel(f.dry, k_gdn_tri_solve<KD, OP, NB, METHOD, DKS, WPB, XPOS, 1>, grid, block, 0, f.stream, f.K, f.beta, f.g,
                            rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters, shape.spread);
@@ -95,6 +96,15 @@ template <int KD, int DKS> static int gdn_method(const SolveArgs& a)
     return 1;
 }
 
+#if TRIINV_INST_NB <= 4
+template <int METHOD, int NRHS> static int launch_kda_team(const SolveArgs& a)
+{
+    const GdnArgs& f = a.f;
+    return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, 1, NRHS, true>, dim3((unsigned)f.n_mat), dim3(64 * TEAM_WAVES), 0, f.stream, f.K, f.beta,
+                         f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters, 0);
+}
+#endif
+
 template <int METHOD> static int go_kda(const SolveArgs& a)
 {
     const GdnArgs& f = a.f;
@@ -108,10 +118,7 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
     return launch_kernel(f.dry, f.k_dt == OP_F32 ? k_kda_tri_solve_c128<OP, METHOD, false, 2> : k_kda_tri_solve_c128<OP, METHOD, true, 2>,
                          dim3((unsigned)f.n_mat), dim3(128), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
 #else
-    if (by_team(f.n_mat, f.d_k))
-        return launch_kernel(f.dry, a.n_rhs == 1 ? k_kda_tri_solve<OP, NB, METHOD, 1, 1, true> : k_kda_tri_solve<OP, NB, METHOD, 1, 2, true>,
-                             dim3((unsigned)f.n_mat), dim3(64 * TEAM_WAVES), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt,
-                             f.iters, 0);
+    if (by_team(f.n_mat, f.d_k)) return a.n_rhs == 1 ? launch_kda_team<METHOD, 1>(a) : launch_kda_team<METHOD, 2>(a);
     const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
     const dim3 grid(shape.groups), block(shape.threads);
     if (a.n_rhs == 1) {
@@ -154,6 +161,7 @@ int CAT(launch_solve_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP)(const SolveArgs& a
     const GdnArgs& f = a.f;
     if (f.refine) return 1;
     if (a.n_rhs < 1 || a.n_rhs > MAX_RHS) return 1;
+    if (a.n_rhs > 1 && f.map.lens) return 1;
     if (NB <= 4 && !rows_fit_32_bits(a)) return 1;  // (H * d_x beyond 8 million elements)
     if (f.gate == G_CHANNEL) {
         if (f.method == M_BLOCK) return go_kda<M_BLOCK>(a);

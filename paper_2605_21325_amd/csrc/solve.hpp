@@ -288,11 +288,16 @@ __device__ __forceinline__ void invert_and_apply(const ASrc& src, RhsX<OP, NB>& 
 // spread: see fused_matrix_index.
 // (C = 64: at most two wavefronts per SIMD -- like the storing kernels, these run slower with more resident: 146 against
 // 138 us at three on the batched workload, 122 against 120 us with d_k = 64, whose build would otherwise fit three)
+//
+// Lengths of packed sequences in the arguments: with one right-hand side; at C = 128 with 16-bit operands, where this kernel stands in for rows
+// too long for the one on two wavefronts and fills the register file, offsets in memory.
+template <int OP, int NB> constexpr bool solve_packed() { return NB < 8 || OP == OP_F32; }
 template <int KD, int OP, int NB, int METHOD, int DKS, int WPB, int XPOS, int NRHS>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(1, NB == 4 ? 2 : 8))) void k_gdn_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
-                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
+                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<solve_packed<OP, NB>() && NRHS == 1> map,
                                                             int H, int d_k, int aux, int spread)
 {
+    arguments_together(n_chunk, K, beta, g, rhs.r[0].X, map);
     constexpr int C = 16 * NB;
     constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int GATE = gate_lds_floats<NB>();
@@ -340,9 +345,10 @@ __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(1, NB 
 // TEAM: WPB = 1, a workgroup of TEAM_WAVES wavefronts forms a matrix together, its first one goes on alone.
 template <int OP, int NB, int METHOD, int WPB, int NRHS, bool TEAM = false>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) void k_kda_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
-                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
+                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<NRHS == 1> map,
                                                             int H, int d_k, int k_dt, int aux, int spread)
 {
+    arguments_together(n_chunk, K, beta, g, rhs.r[0].X, map);
     constexpr int C = 16 * NB;
     constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int PER_WAVE = CORE > C ? CORE : C;
@@ -376,9 +382,10 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) void k_kda_tri_s
 // the storing kernel, then the same recursion and products.  One wavefront per workgroup, or (TEAM) TEAM_WAVES that form a matrix together.
 template <int KD, int OP, int NB, int METHOD, int NRHS, bool TEAM>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) void k_gdn_any_dk_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
-                                                             const float* __restrict__ g, RhsList rhs, int64_t n_chunk, ChunkMap map,
+                                                             const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<NRHS == 1> map,
                                                              int H, int d_k, int aux)
 {
+    arguments_together(n_chunk, K, beta, g, rhs.r[0].X, map);
     constexpr int C = 16 * NB;
     constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int GATE = gate_lds_floats<NB>();

@@ -240,6 +240,25 @@ def test_chunk_offsets_helper_refuses_before_any_launch(L):
     assert out.value == -1
 
 
+def test_packed_helpers_refuse_before_any_launch(L):
+    """The varlen entry points by lengths: what they do not take, and what the entry points themselves refuse."""
+    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
+    inv, solve = L.triinv_detail_inv_packed, L.triinv_detail_solve_packed
+    inv.argtypes = [vp, vp, vp, vp, vp, i32, i64, i32, i32, i32, i32, i32, i32, i32, vp, ctypes.c_uint32]
+    solve.argtypes = [vp, vp, vp, vp, vp, vp, vp, i32, i64, i32, i32, i32, i32, i32, i32, i32, i32, vp, ctypes.c_uint32]
+    def both(lens, n, total, C=64, K=P, method=1):
+        return (inv(K, P, P, P, lens, n, total, 1, 64, C, 2, 2, method, 2, None, 0),
+                solve(K, P, P, P, None, P, lens, n, total, 1, 64, 64, C, 2, 2, method, 2, None, 0))
+    lens = (i64 * 65)(*[1] * 65)
+    assert both(lens, 65, 65) == both(lens, 0, 0) == both(lens, 2, 3) == both(None, 1, 1) == both(lens, 2, 2, C=48) == (-5, -5)
+    assert both((i64 * 2)(-1, 2), 2, 1) == both((i64 * 1)(1 << 24), 1, 1 << 24) == (-5, -5)
+    assert both(lens, 2, 2, K=None) == (-1, -1)
+    assert both(lens, 2, 2, method=9) == (-4, -4)
+    assert both((i64 * 2)(), 2, 0) == (0, 0)                        # no tokens, no launch
+    for method, flags in ((2, 0), (6, 0), (1, 1)):                  # kernels that take offsets in memory only
+        assert inv(P, P, P, P, lens, 2, 2, 1, 64, 64, 2, 2, method, 2, None, flags) == -9
+
+
 def test_negative_sequence_lengths_are_refused():
     """With the right sum too: the offsets of such lengths would name tokens of other sequences."""
     import torch

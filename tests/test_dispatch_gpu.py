@@ -1,4 +1,5 @@
 """Rules that send a call to one kernel or launch shape rather than another: both sides of each line give the same result."""
+import numpy as np
 import pytest
 import torch
 
@@ -248,3 +249,34 @@ def test_offsets_of_packed_sequences_in_blocks(n_seq):
         assert torch.equal(T[chunk:chunk + one.shape[0]], one)
         start, chunk = start + n, chunk + one.shape[0]
     assert chunk == T.shape[0]
+
+
+# Packed sequences whose lengths travel as kernel arguments (the native route; 384 bits of them for inverses, 768 for the applied inverse) against
+# the offsets in memory that the Python route uses: the same bits, whatever the kernel.
+@pytest.mark.parametrize("C, gate, d_k, op", [(16, tri.GATE_SCALAR, 64, tri.BF16), (32, tri.GATE_PER_CHANNEL, 64, tri.BF16), (64, tri.GATE_SCALAR, 128, tri.F32),
+                                              (64, tri.GATE_NONE, 96, tri.BF16), (128, tri.GATE_SCALAR, 128, tri.BF16), (128, tri.GATE_PER_CHANNEL, 64, tri.BF16)])
+@pytest.mark.parametrize("n_seq, longest", [(1, 700), (2, 700), (17, 60000), (33, 2047), (33, 2048), (48, 65535), (64, 63), (64, 700), (65, 63)])
+def test_packed_lengths_as_arguments_and_in_memory(monkeypatch, C, gate, d_k, op, n_seq, longest):
+    H = 3
+    r = np.random.default_rng(n_seq)
+    lens = [min(int(x), longest) for x in r.choice([0, 1, C - 1, C, C + 1, 3 * C + 5], n_seq)]
+    lens[n_seq // 2] = longest
+    total = sum(lens)
+    gen = torch.Generator(device=DEV).manual_seed(n_seq)
+    K = torch.nn.functional.normalize(torch.randn(total, H, d_k, generator=gen, device=DEV), dim=-1).bfloat16()
+    beta = torch.rand(total, H, generator=gen, device=DEV)
+    g = None if gate == tri.GATE_NONE else -0.01 * torch.rand(total, H, *([d_k] if gate == tri.GATE_PER_CHANNEL else []), generator=gen, device=DEV)
+    X = torch.randn(total, H, 72, generator=gen, device=DEV).to(torch.float32 if op == tri.F32 else torch.bfloat16)
+    def calls():
+        T = tri.gdn_chunk_tri_inv_varlen(K, beta, g, lens, C, gate_kind=gate, op_dtype=op)
+        return T, tri.gdn_chunk_tri_solve_varlen(K, beta, g, X, lens, C, row_scale=beta, gate_kind=gate)
+    native = calls()
+    bits = longest.bit_length()
+    assert tri.binding._fast is not None
+    for r, words in zip(native, (12, 24)):
+        assert (r._triinv_keepalive == ()) == (n_seq <= 64 and n_seq * max(bits, max(lens).bit_length()) <= 32 * words)
+    monkeypatch.setattr(tri.binding, "_fast_lib", None)
+    python = calls()
+    assert len(python[0]._triinv_keepalive) == 1
+    for a, b in zip(native, python):
+        assert torch.equal(a, b)

@@ -184,3 +184,34 @@ def test_a_module_built_for_another_torch_is_not_used(monkeypatch, native):
     assert tri_build._fastcall_current()
     monkeypatch.setattr(torch.version, "git_version", "another")
     assert not tri_build._fastcall_current()
+
+
+# Up to 64 sequences are offered to the library by their lengths; what it does not take, and everything else, goes by offsets.
+@pytest.mark.parametrize("lens, taken, as_lengths", [([130, 0, 70], True, True), ([1] * 64, True, True), ([1] * 65, True, False), ([65536], False, False),
+                                                     ([100, 101], True, None)])
+def test_packed_sequences_by_lengths_or_offsets(native, lens, taken, as_lengths):
+    extra = {"inv_packed": (P, P, P, P, P, I, L, I, I, I, I, I, I, I, P, U), "solve_packed": (P, P, P, P, P, P, P, I, L, I, I, I, I, I, I, I, I, P, U)}
+    def answer(name, a):
+        native.calls.append((name, a))
+        return 0 if taken else -5
+    for name, types in extra.items():
+        native.keep.append(ctypes.CFUNCTYPE(I, *types)(lambda *a, name=name: answer(name, a)))
+    native.module.connect(*(ctypes.cast(f, P).value for f in native.keep))
+    total = 200 if as_lengths is None else sum(lens)
+    K, beta, _ = keys(total, 1, 32)
+    X = torch.randn(total, 1, 8).bfloat16()
+    T = native.module.gdn_inv_varlen(-1, 0, K, beta, None, lens, 64, None, tri.GATE_NONE, 1, tri.BF16, 0, None)
+    W = native.module.gdn_solve_varlen(-1, 0, K, beta, None, X, lens, 64, None, None, tri.GATE_NONE, 1, 0)
+    if as_lengths is None:
+        assert T is None and W is None
+        return
+    assert T.shape == (sum(-(-n // 64) for n in lens), 64, 64) and W.shape == X.shape
+    assert hasattr(T, "_triinv_keepalive") and hasattr(W, "_triinv_keepalive")
+    offered = len(lens) <= 64
+    want = (["inv_packed"] * offered + ([] if as_lengths else ["offsets", "inv_varlen"]) + ["solve_packed"] * offered
+            + ([] if as_lengths else ["offsets", "solve_varlen"]))
+    assert [name for name, _ in native.calls] == want
+    if as_lengths:
+        (_, a), (_, b) = native.calls
+        assert a[5:9] == (len(lens), total, 1, 32) and b[7:11] == (len(lens), total, 1, 32) and b[11:13] == (8, 64)
+        assert (a[0], b[0], b[3], b[5]) == (K.data_ptr(), K.data_ptr(), X.data_ptr(), W.data_ptr())
