@@ -47,6 +47,11 @@ template <int KD, int DKS> struct HalfKeys {
     }
 };
 
+// Transpose patches of a wave's 64 x 64 block: the leaves with fp32 operands go side by side, in one orientation (leaves_block_recursive_f32,
+// leaves_neumann_f32).  Per-channel gate, 3088 matrices, blocked recursion 251 -> 223 us, mixed 233 -> 226; two right-hand sides, scalar gate, 1024
+// matrices 104 -> 97 and 105 -> 99.
+template <int OP> constexpr int c128_patches() { return OP == OP_F32 ? 2 : 1; }
+
 // LDS of one workgroup: the bottom half's keys and tile rows 1..3 of the top half's (operand layout:
 // [tile row][k-step][lane], 16 bytes each), the packed tiles of T22 (all ten, T orientation: left factors) and of T11
 // that the other wave needs (N orientation: right factors), wave 0's private area (gate staging, tile transposes, leaf
@@ -66,12 +71,12 @@ template <int KD, int OP, int DKS, int METHOD, bool WITH_MAIL = true> struct C12
     static constexpr int OPND = (int)sizeof(Opnd<OP>);
     static constexpr int T22 = KEYS_END;                                   // 10 tiles
     static constexpr int T11 = T22 + 10 * 64 * OPND;                       // tiles (1,1) (2,1) (3,1) (2,2) (3,2)
-    static constexpr int PRIVATE_FLOATS = METHOD == M_BLOCK_DIRECT ? LEAF_FWD_FLOATS : XPOSE_FLOATS;
+    static constexpr int PRIVATE_FLOATS = METHOD == M_BLOCK_DIRECT ? LEAF_FWD_FLOATS : c128_patches<OP>() * XPOSE_FLOATS;
     static constexpr int PRIVATE0 = T11 + 5 * 64 * OPND;                   // wave 0's private area
     static constexpr int MAIL = PRIVATE0;                                  // (WITH_MAIL) 8 fp32 tiles, after wave 0's private use of the same bytes
     static constexpr int PRIVATE1 = PRIVATE0 + (WITH_MAIL ? 8 * 1024 : PRIVATE_FLOATS * 4);  // wave 1's private area
     static constexpr int BYTES = PRIVATE1 + PRIVATE_FLOATS * 4;
-    static_assert(XPOSE_FLOATS >= 2 * 128 && 2048 >= LEAF_FWD_FLOATS, "the private areas fit their users");
+    static_assert(XPOSE_FLOATS >= 2 * 128 && 2048 >= LEAF_FWD_FLOATS && 2048 >= PRIVATE_FLOATS, "the private areas fit their users");
     static_assert(PRIVATE0 % 16 == 0 && PRIVATE1 % 16 == 0, "16-byte accesses");
 };
 
@@ -118,7 +123,7 @@ __device__ __forceinline__ void c128_diagonal_block(const DiagSrc& diag, v4f (&D
 {
     const int lane = 16 * ln.q + ln.n;
     v4f leaves[8];
-    block_recursive<OP, 4, W == 1, c128_leaf<METHOD>()>(diag, D, small, ln, aux, NoHook(), leaves);
+    block_recursive<OP, 4, W == 1, c128_leaf<METHOD>(), c128_patches<OP>()>(diag, D, small, ln, aux, NoHook(), leaves);
     if (W == 0) {
         D[tix(3, 2)] = transpose_tile(D[tix(3, 2)], small, ln);  // the odd child of the block came out in T orientation
 #pragma unroll

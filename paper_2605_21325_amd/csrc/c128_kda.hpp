@@ -35,7 +35,7 @@ template <int OP, int METHOD> struct C128KdaLds {
     static constexpr int T11 = T22 + 10 * 64 * OPND;
     static constexpr int MAIL = T11 + 5 * 64 * OPND;                       // before the merge: wave 0's private area
     static constexpr int PRIVATE1 = MAIL + 8 * 1024;
-    static constexpr int PRIVATE1_FLOATS = METHOD == M_BLOCK_DIRECT ? LEAF_FWD_FLOATS : XPOSE_FLOATS;
+    static constexpr int PRIVATE1_FLOATS = METHOD == M_BLOCK_DIRECT ? LEAF_FWD_FLOATS : c128_patches<OP>() * XPOSE_FLOATS;
     static constexpr int ANCHORS = PRIVATE1 + PRIVATE1_FLOATS * 4;         // per wave: anchors [q][5][8], factors [q][10][8]
     static constexpr int ANCHOR_FLOATS = 4 * 5 * 8 + 4 * 10 * 8;
     static constexpr int BYTES = ANCHORS + 2 * ANCHOR_FLOATS * 4;
