@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void k_kda_tri_inv_neumann128(const void* __re
 {
     arguments_together(n_chunk, K, beta, g, T, map);
     typedef MailTiles<OP> Mail;
-    __shared__ __attribute__((aligned(16))) char lds[kda128_lds_bytes<OP>(ns128_lds_bytes<OP>())];
+    __shared__ __attribute__((aligned(16))) char lds[kda128_lds_bytes<OP>(mail128_lds_bytes<OP>())];
     const KdaHead128 hd = kda_head128(K, beta, g, n_chunk, map, H, d_k, k_dt);
     const Lane ln = lane_id();
     v4f an[9], at[9];

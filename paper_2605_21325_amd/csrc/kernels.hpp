@@ -1870,122 +1870,204 @@ template <int OP> struct MailTiles {
     }
 };
 
-template <int OP> constexpr int ns128_lds_bytes()
+// Two sets of tiles, later the four store patches.
+template <int OP> constexpr int mail128_lds_bytes()
 {
     return 2 * MailTiles<OP>::BYTES > 4 * STORE_LDS_FLOATS * 4 ? 2 * MailTiles<OP>::BYTES : 4 * STORE_LDS_FLOATS * 4;
+}
+
+// The tiles of Newton-Schulz: each part of a tile (fp32 operands: the three of Split3) in the order of Turn16, so that it is read as it was
+// written, by any wave, or transposed.
+template <int OP> struct TurnTiles {
+    static constexpr int PARTS = OP == OP_F32 ? 3 : 1;
+    static constexpr int BYTES = N128_NT * PARTS * TURN16_BYTES;
+    Turn16 at;
+    __device__ __forceinline__ TurnTiles(char* base, Lane ln) : at(reinterpret_cast<float*>(base), ln) {}
+    __device__ __forceinline__ void put(int tile, int part, v2u u) const { at.put(tile * PARTS + part, u); }
+    template <bool TR> __device__ __forceinline__ v2u get(int tile, int part) const
+    {
+        return TR ? at.get(tile * PARTS + part) : *reinterpret_cast<const v2u*>(at.put_at + (tile * PARTS + part) * TURN16_BYTES);
+    }
+};
+// X and Y: 16-bit operands a set each, fp32 ones a set for both in turns (a second one of 54 KB would leave a compute unit one workgroup).
+template <int OP> constexpr int ns128_lds_bytes()
+{
+    constexpr int tiles = (OP == OP_F32 ? 1 : 2) * TurnTiles<OP>::BYTES;
+    return tiles > 4 * STORE_LDS_FLOATS * 4 ? tiles : 4 * STORE_LDS_FLOATS * 4;
 }
 
 template <int W> __host__ __device__ constexpr int n128_slot(int i, int k) { return i == W ? k : (W + 1) + k; }
 
 // The wave's two tile rows as left operands, and one tile column as right operand.  16-bit operands: pairs of tiles for the
-// 32-deep instructions; fp32: tile by tile.
+// 32-deep instructions; fp32: tile by tile, each split into three bf16 parts (see Split3).
 template <int OP> struct Ns128Operands {
     typedef PairOp<OP> Row[4];
     static __device__ __forceinline__ void put(Row& row, int k, Opnd<OP> x) { row[k / 2].set(k & 1, x); }
-    static __device__ __forceinline__ v4f product(const Row& l, const Row& r, int i, int j, v4f acc)
+    template <bool TR> static __device__ __forceinline__ void get(Row& row, int k, const TurnTiles<OP>& tiles, int tile)
     {
-        v4f odd;
+        Opnd<OP> o;
+        o.x = __builtin_bit_cast(decltype(o.x), tiles.template get<TR>(tile, 0));
+        put(row, k, o);
+    }
+    static __device__ __forceinline__ void publish(const TurnTiles<OP>& tiles, int tile, v4f x)
+    {
+        tiles.put(tile, 0, __builtin_bit_cast(v2u, pack<OP>(x).x));
+    }
+    // acc[h] += sum over k of l[h](k) times tile (k, j) of the tiles, for the rows i = W and 7 - W that have a column j
+    template <int W> static __device__ __forceinline__ void products(const Row (&l)[2], const TurnTiles<OP>& tiles, int j, v4f (&acc)[2])
+    {
+        Row r;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) pair_term<OP>(p, i, j, l[p], r[p], acc, odd);
-        return mixed_terms(i, j) ? acc + odd : acc;
+        for (int k = 0; k < N128_NB; ++k)
+            if (k >= j && k <= 7 - W) get<false>(r, k, tiles, tix(k, j));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int i = h == 0 ? W : 7 - W;
+            if (j > i) continue;
+            v4f odd;
+#pragma unroll
+            for (int p = 0; p < 4; ++p) pair_term<OP>(p, i, j, l[h][p], r[p], acc[h], odd);
+            if (mixed_terms(i, j)) acc[h] += odd;
+        }
     }
 };
 template <> struct Ns128Operands<OP_F32> {
-    typedef Opnd<OP_F32> Row[8];
-    static __device__ __forceinline__ void put(Row& row, int k, Opnd<OP_F32> x) { row[k] = x; }
-    static __device__ __forceinline__ v4f product(const Row& l, const Row& r, int i, int j, v4f acc)
+    typedef Split3 Row[8];
+    static __device__ __forceinline__ void put(Row& row, int k, Opnd<OP_F32> x) { row[k] = split3_any(x.x); }
+    template <bool TR> static __device__ __forceinline__ void get(Row& row, int k, const TurnTiles<OP_F32>& tiles, int tile)
     {
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (k >= j && k <= i) acc = tn<OP_F32>(l[k], r[k], acc);
-        return acc;
+        for (int p = 0; p < 3; ++p) {
+            const v2u u = tiles.get<TR>(tile, p);
+            row[k].u[2 * p] = u[0];
+            row[k].u[2 * p + 1] = u[1];
+        }
+    }
+    static __device__ __forceinline__ void publish(const TurnTiles<OP_F32>& tiles, int tile, v4f x)
+    {
+        const Split3 s = split3(x);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) tiles.put(tile, p, v2u{s.u[2 * p], s.u[2 * p + 1]});
+    }
+    template <int W> static __device__ __forceinline__ void products(const Row (&l)[2], const TurnTiles<OP_F32>& tiles, int j, v4f (&acc)[2])
+    {
+        v4f cross[2] = {zero4(), zero4()};
+#pragma unroll
+        for (int k = 0; k < N128_NB; ++k) {
+            if (k < j || k > 7 - W) continue;
+            Row r;
+            get<false>(r, k, tiles, tix(k, j));
+#pragma unroll
+            for (int part = 0; part < 3; ++part)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (k > (h == 0 ? W : 7 - W)) continue;
+                    if (part < 2)
+                        cross[h] = tn_split(part, l[h][k], r[k], cross[h]);
+                    else
+                        acc[h] = tn_split(part, l[h][k], r[k], acc[h]);
+                }
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            if (j <= (h == 0 ? W : 7 - W)) acc[h] += cross[h];
     }
 };
 
-// The transpose of a tile, exact (see Split3; ANY: for values beyond the largest bf16 too): by products with the identity.
-template <int OP, bool ANY = false> __device__ __forceinline__ v4f turned(v4f x, Opnd<OP_BF16> id_bf16, Opnd<OP> id)
+// The transpose of a tile, exact (see Split3; for values beyond the largest bf16 too): by products with the identity.
+template <int OP> __device__ __forceinline__ v4f turned(Opnd<OP> x, Opnd<OP_BF16> id_bf16, Opnd<OP> id)
 {
     if constexpr (OP == OP_F32) {
-        const Split3 s = ANY ? split3_any(x) : split3(x);
+        const Split3 s = split3_any(x.x);
         return tn<OP_BF16>(s.h(), id_bf16, tn<OP_BF16>(s.m(), id_bf16, tn<OP_BF16>(s.l(), id_bf16, zero4())));
     } else {
-        return tn<OP>(pack<OP>(x), id, zero4());  // (of the rounded tile)
+        return tn<OP>(x, id, zero4());
     }
 }
 
 // At: this wave's nine tiles of A in T orientation (slot order of n128_row / n128_col).  lds: ns128_lds_bytes<OP>() bytes
 // that no wave uses for anything else any more.
-// X is kept in N orientation only and turned once per iteration (exactly, by products with the identity); a tile column of the
-// right factor is read from LDS once for both of the wave's rows; 16-bit operands contract two tiles per instruction; the
-// first iteration from I / C is a scaling.  The critical wave issues 51 matrix instructions per iteration instead of
-// 111 (16-bit operands); what is left is LDS reads, packing and two barriers.  4096 fused matrices, bf16 operands 235 -> 205 us,
-// standalone 222 -> 187 us; 1024 with fp32 operands 341 -> 248 us (still matrix-core bound), 2048 standalone 668 -> 473 us.
+// X is kept in N orientation only; its left form is read back from the wave's own tiles in LDS by transposing reads; a tile column of the
+// right factor is read from LDS once for both of the wave's rows; 16-bit operands contract two tiles per instruction, fp32 ones are split
+// into three bf16 parts; the first iteration from I / C is a scaling.
+// Bound by latency: LDS reads a column at a time and two (fp32: four) barriers an iteration.  1024 fused matrices with fp32 operands, by fp32
+// instructions / split 245.6 / 183.8 us, standalone 240.9 / 180.2, 16 of them 73 / 70, error against 64 bits 1.34e-7 / 1.32e-7 (standalone 8.6e-8 / 5.8e-8);
+// X turned by products with the identity / by LDS reads: 4096 bf16 188 / 173, 2048 standalone 96 / 86.
 template <int OP, int W>
 __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char* lds, Lane ln, int n_iter, int w)
 {
-    typedef MailTiles<OP> Mail;
     typedef Ns128Operands<OP> Ops;
+    constexpr bool ONE_SET = OP == OP_F32;
     constexpr int ROW[2] = {W, 7 - W};
     constexpr float X0 = 1.f / 128.f;
-    char* const X = lds;
-    char* const Y = lds + Mail::BYTES;
+    const TurnTiles<OP> X(lds, ln), Y(lds + (ONE_SET ? 0 : TurnTiles<OP>::BYTES), ln);
     const v4f unit = identity_tile(ln);
-    const Opnd<OP> id = pack<OP>(unit);
-    const Opnd<OP_BF16> id_bf16 = pack<OP_BF16>(unit);
     typename Ops::Row Al[2];
     v4f Xn[9];
+    {
+        const Opnd<OP> id = pack<OP>(unit);
+        const Opnd<OP_BF16> id_bf16 = pack<OP_BF16>(unit);
 #pragma unroll
-    for (int s = 0; s < 9; ++s) {
-        const int i = n128_row<W>(s), j = n128_col<W>(s);
-        Ops::put(Al[s <= W ? 0 : 1], j, At[s]);
-        v4f a;
-        if constexpr (OP == OP_F32)
-            a = turned<OP, true>(At[s].x, id_bf16, id);
-        else
-            a = tn<OP>(At[s], id, zero4());
-        if (i == j) a += unit;
-        Xn[s] = (i == j ? 2.f * X0 : 0.f) * unit - X0 * X0 * a;
-        Mail::put(X, tix(i, j), pack<OP>(Xn[s]), ln);
+        for (int s = 0; s < 9; ++s) {
+            const int i = n128_row<W>(s), j = n128_col<W>(s);
+            Ops::put(Al[s <= W ? 0 : 1], j, At[s]);
+            v4f a = turned<OP>(At[s], id_bf16, id);
+            if (i == j) a += unit;
+            Xn[s] = (i == j ? 2.f * X0 : 0.f) * unit - X0 * X0 * a;
+            Ops::publish(X, tix(i, j), Xn[s]);
+        }
     }
     __syncthreads();
 #pragma unroll 1
     for (int it = 1; it < n_iter; ++it) {
-        // a tile column j of a matrix in LDS, rows j .. 7 - W
-        const auto column = [&](const char* base, int j, typename Ops::Row& r) {
-#pragma unroll
-            for (int k = 0; k < N128_NB; ++k)
-                if (k >= j && k <= 7 - W) Ops::put(r, k, Mail::get(base, tix(k, j), ln));
-        };
         // Y(i,j) = X(i,j) + sum_k A(i,k) X(k,j) on this wave's rows
+        v4f Yn[9];
 #pragma unroll
         for (int j = 0; j <= 7 - W; ++j) {
-            typename Ops::Row x;
-            column(X, j, x);
+            v4f y[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (j <= ROW[h]) y[h] = Xn[n128_slot<W>(ROW[h], j)];
+            Ops::template products<W>(Al, X, j, y);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (j > ROW[h]) continue;
-                const int s = n128_slot<W>(ROW[h], j);
-                Mail::put(Y, tix(ROW[h], j), pack<OP>(Ops::product(Al[h], x, ROW[h], j, Xn[s])), ln);
+                if (ONE_SET)
+                    Yn[n128_slot<W>(ROW[h], j)] = y[h];
+                else
+                    Ops::publish(Y, tix(ROW[h], j), y[h]);
             }
+            __builtin_amdgcn_sched_barrier(0);  // (the next column's tiles and X's left form would not fit beside this one's)
         }
         typename Ops::Row Xl[2];
 #pragma unroll
-        for (int s = 0; s < 9; ++s) Ops::put(Xl[s <= W ? 0 : 1], n128_col<W>(s), pack<OP>(turned<OP>(Xn[s], id_bf16, id)));
-        __syncthreads();  // Y complete; nobody reads X from LDS any more in this iteration
+        for (int s = 0; s < 9; ++s) Ops::template get<true>(Xl[s <= W ? 0 : 1], n128_col<W>(s), X, tix(n128_row<W>(s), n128_col<W>(s)));
+        __syncthreads();  // nobody reads X from LDS any more in this iteration; two sets: Y complete
+        if (ONE_SET) {
+#pragma unroll
+            for (int s = 0; s < 9; ++s) Ops::publish(Y, tix(n128_row<W>(s), n128_col<W>(s)), Yn[s]);
+            __syncthreads();  // Y complete
+        }
         // X(i,j) <- 2 X(i,j) - sum_k X(i,k) Y(k,j)
 #pragma unroll
         for (int j = 0; j <= 7 - W; ++j) {
-            typename Ops::Row y;
-            column(Y, j, y);
+            v4f xy[2] = {zero4(), zero4()};
+            Ops::template products<W>(Xl, Y, j, xy);
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (j > ROW[h]) continue;
                 const int s = n128_slot<W>(ROW[h], j);
-                Xn[s] = 2.f * Xn[s] - Ops::product(Xl[h], y, ROW[h], j, zero4());
-                Mail::put(X, tix(ROW[h], j), pack<OP>(Xn[s]), ln);
+                Xn[s] = 2.f * Xn[s] - xy[h];
+                if (!ONE_SET) Ops::publish(X, tix(ROW[h], j), Xn[s]);
             }
+            if (ONE_SET) __builtin_amdgcn_sched_barrier(0);
         }
-        __syncthreads();  // X complete; nobody reads Y any more
+        __syncthreads();  // nobody reads Y any more; two sets: X complete
+        if (ONE_SET && it + 1 < n_iter) {
+#pragma unroll
+            for (int s = 0; s < 9; ++s) Ops::publish(X, tix(n128_row<W>(s), n128_col<W>(s)), Xn[s]);
+            __syncthreads();  // X complete
+        }
     }
     // X and Y in LDS are dead: their memory becomes the four store patches
     n128_store<W, false>(Tm, Xn, reinterpret_cast<float*>(lds) + w * STORE_LDS_FLOATS, ln);
@@ -2298,7 +2380,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F3
 template <int IN, int OP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_tri_inv_neumann128(const void* A, float* T, int64_t n_mat, int out_dt)  // may run in place
 {
-    __shared__ __attribute__((aligned(16))) char lds[ns128_lds_bytes<OP>()];
+    __shared__ __attribute__((aligned(16))) char lds[mail128_lds_bytes<OP>()];
     const int64_t m = blockIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Lane ln = lane_id();
