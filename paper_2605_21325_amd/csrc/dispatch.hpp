@@ -67,6 +67,11 @@ constexpr int64_t FEW_MATRICES = 512;
 // wavefronts where there is more than one k-step (32 channels).
 constexpr int TEAM_WAVES = 4;
 inline bool by_team(int64_t n_mat, int d_k) { return n_mat <= FEW_MATRICES && d_k > 32; }
+// C = 128, head dimensions without a kernel of their own (fp32 keys of 128 channels with fp32 operands and forward substitution among them): up to one team per
+// compute unit.  256 matrices, one wavefront / a team: fp32 keys, d_k = 128, forward substitution 40.9 / 28.2 us (8 of them 40.9 / 27.3), blocked recursion
+// with fp32 operands 44.3 / 27.5, d_k = 256, 16-bit operands, mixed 61.9 / 28.6 (172, blocked: 54.4 / 21.1); bf16 keys, d_k = 256 16.6 / 13.3, d_k = 96 17.7 /
+// 17.5.  512, two teams a compute unit: 45.3 / 35.5, 48.4 / 54.0, 60.6 / 44.4 (blocked), 20.9 / 25.9.
+inline bool by_team128(int64_t n_mat, int d_k) { return n_mat <= FEW_MATRICES / 2 && d_k > 32; }
 // fp32 keys of 128 channels go the same way at C = 64 although that head dimension has a kernel of its own: their Gram products are fp32
 // matrix instructions, 6 of the 11.7 us of such a call, and each diagonal tile's products are formed once there.  Up to one team per compute unit:
 // 256 matrices 11.8 / 9.6 us (own kernel / team; bf16 operands 9.7 / 8.0, one right-hand side applied 17.3 / 15.8), 512 12.8 / 12.3 and

@@ -316,12 +316,9 @@ static int kda_method(const GdnArgs& a)
 // recursion from directly solved blocks at C = 128.
 template <int KD, int METHOD> static int go_any_dk(const GdnArgs& a)
 {
-    if constexpr (NB <= 4) {
-        if (by_team(a.n_mat, a.d_k))
-            return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, true>, dim3((unsigned)a.n_mat), dim3(64 * TEAM_WAVES),
-                                 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters,
-                                 a.out_dt);
-    }
+    if (NB <= 4 ? by_team(a.n_mat, a.d_k) : by_team128(a.n_mat, a.d_k))
+        return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, true>, dim3((unsigned)a.n_mat), dim3(64 * TEAM_WAVES), 0, a.stream, a.K,
+                             a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
     return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, false>, dim3((unsigned)a.n_mat), dim3(64), 0, a.stream, a.K, a.beta,
                        a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
 }

@@ -766,7 +766,7 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
 // order: 8.6, 12.5, 12.3, -, 12.9, 7.4; 11.2, 16.5, 15.8, -, 16.3, 8.5.)
 struct Team {
     int w;      // this wavefront of the TEAM_WAVES
-    char* lds;  // TeamLds::BYTES
+    char* lds;  // team_lds_bytes()
 };
 // The products a method asks for: tile (i, j) in N or T orientation.  Without a gate both operands are the keys, and a diagonal tile is its
 // own transpose: one product serves both.
@@ -796,9 +796,13 @@ template <int OPG, int NB, bool GATED> struct TeamLds {
     static constexpr int RIGHT = NB * PLANES * PLANE;
     static constexpr int TABLE = RIGHT + (GATED ? (OPG == OP_F32 ? NB * 2 : NB * (NB + 1) / 2) * PLANE : 0);
     static constexpr int STEP = TABLE + (GATED ? 4 * 8 * (NB + PAIRS) * 4 : 0);
-    static constexpr int TILES = NB * (NB + 1);  // the finished tiles take the operands' place
-    static constexpr int BYTES = TEAM_WAVES * STEP > TILES * PLANE ? TEAM_WAVES * STEP : TILES * PLANE;
 };
+// With METHOD's products, of which the finished ones take the operands' place.
+template <int OPG, int NB, int METHOD, bool GATED> constexpr int team_lds_bytes()
+{
+    constexpr int steps = TEAM_WAVES * TeamLds<OPG, NB, GATED>::STEP, tiles = GramProducts<NB, METHOD, GATED>::COUNT * TeamLds<OPG, NB, GATED>::PLANE;
+    return steps > tiles ? steps : tiles;
+}
 template <int OPG> __device__ __forceinline__ void team_write(char* p, const GOp<OPG>& o)
 {
     if constexpr (OPG == OP_F32) {  // two planes
@@ -1758,7 +1762,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_
     constexpr int CORE = core_lds_floats<NB, METHOD>();
     constexpr int GATE = gate_lds_floats<NB>();
     __shared__ __attribute__((aligned(16))) float lds[CORE > GATE ? CORE : GATE];
-    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<KD, NB, false>::BYTES : 16];
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? team_lds_bytes<KD, NB, METHOD, false>() : 16];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
     const int h = (int)((uint32_t)m - bc * (uint32_t)H);
@@ -1787,7 +1791,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) __attribute__((a
     constexpr int PER_WAVE = CORE > C ? CORE : C;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
     float* lds = lds_all + ((WPB == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * PER_WAVE;
-    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<OP, NB, true>::BYTES : 16];
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? team_lds_bytes<OP, NB, REFINE ? METHOD + WITH_REFINE : METHOD, true>() : 16];
     const int64_t m = TEAM ? (int64_t)blockIdx.x : fused_matrix_index<WPB>(n_chunk, H, n_chunk * H, spread);
     if (m < 0) return;
     const uint32_t bc = (uint32_t)m / (uint32_t)H;

@@ -354,7 +354,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) void k_kda_tri_s
     constexpr int PER_WAVE = CORE > C ? CORE : C;
     __shared__ __attribute__((aligned(16))) float lds_all[WPB * PER_WAVE];
     float* lds = lds_all + ((WPB == 1) ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * PER_WAVE;
-    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<OP, NB, true>::BYTES : 16];
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? team_lds_bytes<OP, NB, METHOD, true>() : 16];
     const int64_t m = TEAM ? (int64_t)blockIdx.x : fused_matrix_index<WPB>(n_chunk, H, n_chunk * H, spread);
     if (m < 0) return;
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
@@ -390,7 +390,7 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) void k_gdn_any_dk_tri_
     constexpr int CORE = SOLVE_LDS_FLOATS;
     constexpr int GATE = gate_lds_floats<NB>();
     __shared__ __attribute__((aligned(16))) float lds[CORE > GATE ? CORE : GATE];
-    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? TeamLds<KD, NB, false>::BYTES : 16];
+    __shared__ __attribute__((aligned(16))) char team_lds[TEAM ? team_lds_bytes<KD, NB, METHOD, false>() : 16];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
     const int h = (int)((uint32_t)m - bc * (uint32_t)H);

@@ -280,3 +280,22 @@ def test_packed_lengths_as_arguments_and_in_memory(monkeypatch, C, gate, d_k, op
     assert len(python[0]._triinv_keepalive) == 1
     for a, b in zip(native, python):
         assert torch.equal(a, b)
+
+
+# C = 128, head dimensions without a kernel of their own: up to 256 matrices four wavefronts form one (and its diagonal tiles once), above one wavefront:
+# the same bits.  fp32 keys of 128 channels with fp32 operands go this way too; "mixed" builds A first.
+@pytest.mark.parametrize("k_dtype, d_k", [(torch.float32, 128), (torch.float32, 256), (torch.bfloat16, 96), (torch.float16, 160)])
+@pytest.mark.parametrize("method, op", [(tri.FWD_SUBST, tri.F32), (tri.BLOCK_RECURSIVE, tri.F32), (tri.BLOCK_DIRECT, tri.BF16), (tri.MIXED, tri.F32)])
+def test_teams_of_large_chunks_give_the_bits_of_a_larger_call(method, op, k_dtype, d_k):
+    C, H, most = 128, 4, 64
+    T = (most + 1) * C - 5
+    K, beta, g = make_inputs(T, H, d_k, tri.GATE_SCALAR, k_dtype)
+    many = tri.gdn_chunk_tri_inv_ex(K, beta, g, C, method=method, op_dtype=op)
+    for tokens in (1, C, 3 * C + 17, most * C):
+        k, b, gg = (x[:, :tokens].contiguous() for x in (K, beta, g))
+        few = tri.gdn_chunk_tri_inv_ex(k, b, gg, C, method=method, op_dtype=op)
+        whole = tokens // C * H
+        assert torch.equal(few[:whole], many[:whole]), tokens
+        if tokens % C:  # the short last chunk: the leading block of the whole one
+            v = tokens % C
+            assert torch.equal(few[whole:, :v, :v], many[whole:whole + H, :v, :v]), tokens
