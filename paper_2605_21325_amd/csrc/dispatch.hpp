@@ -72,12 +72,18 @@ inline bool by_team(int64_t n_mat, int d_k) { return n_mat <= FEW_MATRICES && d_
 // with fp32 operands 44.3 / 27.5, d_k = 256, 16-bit operands, mixed 61.9 / 28.6 (172, blocked: 54.4 / 21.1); bf16 keys, d_k = 256 16.6 / 13.3, d_k = 96 17.7 /
 // 17.5.  512, two teams a compute unit: 45.3 / 35.5, 48.4 / 54.0, 60.6 / 44.4 (blocked), 20.9 / 25.9.
 inline bool by_team128(int64_t n_mat, int d_k) { return n_mat <= FEW_MATRICES / 2 && d_k > 32; }
-// fp32 keys of 128 channels go the same way at C = 64 although that head dimension has a kernel of its own: their Gram products are fp32
+// fp32 keys of 128 channels go the same way at C = 64 (methods without a team64 kernel) although that head dimension has a kernel of its own: their Gram products are fp32
 // matrix instructions, 6 of the 11.7 us of such a call, and each diagonal tile's products are formed once there.  Up to one team per compute unit:
 // 256 matrices 11.8 / 9.6 us (own kernel / team; bf16 operands 9.7 / 8.0, one right-hand side applied 17.3 / 15.8), 512 12.8 / 12.3 and
 // 10.7 / 10.3.  (64 channels, half the products, keep their kernel: 256 matrices 9.2 / 8.6 and 7.4 / 6.8, 512 10.1 / 10.1 and 8.1 / 8.3.)
 constexpr int FP32_KEYS_TEAM_DK = 128;
 inline bool fp32_keys_by_team(int64_t n_mat, int d_k, int C) { return C == 64 && d_k == FP32_KEYS_TEAM_DK && n_mat <= FEW_MATRICES / 2; }
+// C = 64, d_k = 64 or 128, blocked, mixed and direct-leaf recursion: four wavefronts to a matrix from the keys to the store (team64.hpp), up to three
+// teams per compute unit; the direct leaves, whose one chain of vector instructions nothing shortens, up to one.  One wavefront to a matrix / a team: 8
+// matrices bf16 4.9 / 4.0 us, fp32 keys and operands 8.9 / 5.2; 256: 5.1 / 4.4, fp32 operands 7.4 / 5.2, fp32 keys and operands of 128 channels (whose
+// tiles a team formed before too) 9.5 / 6.7, direct leaves 5.0 / 4.9; 512: 5.6 / 5.3, 8.0 / 6.6, 12.4 / 9.3, 5.8 / 5.9; 768: 6.8 / 6.3, 9.2 / 8.1; 1024:
+// 7.6 / 8.3, 10.0 / 10.2, 15.6 / 17.3.
+inline bool by_team64(int64_t n_mat, bool direct) { return n_mat <= (direct ? 256 : 768); }
 struct FusedGrid {
     unsigned groups, threads;
     int spread;

@@ -8,6 +8,9 @@
 #include "c128_kda.hpp"
 #include "kda128.hpp"
 #endif
+#if TRIINV_INST_NB == 4 && !TRIINV_INST_FWD
+#include "team64.hpp"
+#endif
 
 #ifndef TRIINV_INST_NB
 #error "compile with -DTRIINV_INST_NB=1|2|4|8 -DTRIINV_INST_OP=0|1|2 [-DTRIINV_INST_FWD=1]"
@@ -159,6 +162,13 @@ template <int KD, int METHOD, int DKS, bool REFINE = false> static int go_gdn(co
     else
 #endif
     {
+#if TRIINV_INST_NB == 4 && !TRIINV_INST_FWD
+        if constexpr (!REFINE && team64_method<METHOD>()) {
+            if (by_team64(a.n_mat, METHOD == M_BLOCK_DIRECT))
+                return launch_kernel(a.dry, k_gdn_tri_inv_team64<KD, OP, METHOD, DKS>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.K, a.beta, a.g, a.T,
+                                     a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
+        }
+#endif
         const FusedGrid f = fused_grid(a.n_mat, a.H, WPB);
         return launch_kernel(a.dry, k_gdn_tri_inv<KD, OP, NB, METHOD, DKS, REFINE, WPB>, dim3(f.groups), dim3(f.threads),
                              f.few() ? 0u : occupancy_pad_bytes<KD, METHOD, DKS>(), a.stream, a.K, a.beta, a.g, a.T, a.n_chunk,
@@ -245,6 +255,13 @@ template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
     else
 #endif
     {
+#if TRIINV_INST_NB == 4 && !TRIINV_INST_FWD
+        if constexpr (!REFINE && team64_method<METHOD>()) {
+            if (by_team(a.n_mat, a.d_k))
+                return launch_kernel(a.dry, k_kda_tri_inv_team64<OP, METHOD>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk,
+                                     a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt);
+        } else
+#endif
         if constexpr (kda_team<OP, NB, METHOD, REFINE>()) {
             if (by_team(a.n_mat, a.d_k))
                 return launch_kernel(a.dry, k_kda_tri_inv<OP, NB, METHOD, 1, REFINE, true>, dim3((unsigned)a.n_mat), dim3(64 * TEAM_WAVES), 0, a.stream, a.K, a.beta,
@@ -316,6 +333,13 @@ static int kda_method(const GdnArgs& a)
 // recursion from directly solved blocks at C = 128.
 template <int KD, int METHOD> static int go_any_dk(const GdnArgs& a)
 {
+#if TRIINV_INST_NB == 4 && !TRIINV_INST_FWD
+    if constexpr (team64_method<METHOD>()) {
+        if (by_team(a.n_mat, a.d_k))
+            return launch_kernel(a.dry, k_gdn_any_dk_tri_inv_team64<KD, OP, METHOD>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.K, a.beta, a.g, a.T,
+                                 a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
+    } else
+#endif
     if (NB <= 4 ? by_team(a.n_mat, a.d_k) : by_team128(a.n_mat, a.d_k))
         return launch_kernel(a.dry, k_gdn_any_dk_tri_inv<KD, OP, NB, METHOD, true>, dim3((unsigned)a.n_mat), dim3(64 * TEAM_WAVES), 0, a.stream, a.K,
                              a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
@@ -355,7 +379,9 @@ int CAT(launch_gdn_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const GdnArg
 #else
     if (a.k_dt == OP_F32) {
 #if TRIINV_INST_NB <= 4
-        if (fp32_keys_by_team(a.n_mat, a.d_k, 16 * NB) && !a.refine) return any_dk_method<OP_F32>(a);
+        const bool team64 = NB == 4 && !TRIINV_INST_FWD && by_team64(a.n_mat, a.method == M_BLOCK_DIRECT) &&
+                            (a.method == M_BLOCK || a.method == M_MIXED || a.method == M_BLOCK_DIRECT);
+        if (fp32_keys_by_team(a.n_mat, a.d_k, 16 * NB) && !a.refine && !team64) return any_dk_method<OP_F32>(a);
 #endif
         if (a.d_k == 64) return gdn_method<OP_F32, 4>(a);
 #if TRIINV_INST_NB <= 4

@@ -780,6 +780,19 @@ template <int NB, int METHOD, bool GATED> struct GramProducts {
     }
     static constexpr int COUNT = count_();
     int code[COUNT] = {};  // i | tix(i, j) << 8 | T orientation << 16 | j << 24
+    // the product of tile (i, j) in this orientation
+    static constexpr int find(int i, int j, bool tr)
+    {
+        int n = 0;
+        for (int a = 0; a < NB; ++a)
+            for (int b = 0; b <= a; ++b)
+                for (int t = 0; t < 2; ++t) {
+                    if (!(!GATED && a == b ? t == 0 : need_tile<NB, METHOD>(a, b, t == 1))) continue;
+                    if (a == i && b == j && (t == (tr ? 1 : 0) || (!GATED && a == b))) return n;
+                    ++n;
+                }
+        return -1;
+    }
     constexpr GramProducts()
     {
         int n = 0;
@@ -874,13 +887,13 @@ template <int OPG, int NB, bool GATED, int P, int STEPS> __device__ __forceinlin
     }
 }
 
-// The tiles of one matrix by the team, complete on its first wavefront; false for the others, which are done.  Every wavefront of the
-// workgroup comes here, with the same matrix: the barriers are the workgroup's.
+// The products of one matrix by the team, left in LDS in the order of GramProducts (team_product).  Every wavefront of the workgroup comes here, with the
+// same matrix: the barriers are the workgroup's, the last one behind the products.
 // HALF_ROWS: a lane's eight channels of a k-step are 4q .. 4q + 3 and 16 + 4q .. 16 + 4q + 3, not 8q .. 8q + 7 (the order of the products of the kernels
 // that keep fp32 keys in registers).
 template <int OPG, int NB, int METHOD, bool K16, bool GATED, bool HALF_ROWS = false>
-__device__ __forceinline__ bool team_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
-                                          const Team& team)
+__device__ __forceinline__ void team_gram_products(const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
+                                                   const Team& team)
 {
     typedef TeamLds<OPG, NB, GATED> LY;
     constexpr float LOG2E = 1.44269504088896340736f;
@@ -1010,9 +1023,23 @@ __device__ __forceinline__ bool team_gram(PreA<NB>& out, const void* Kc, bool is
     for (int p = 0; p < P; ++p)
         if (first + p < end) *reinterpret_cast<v4f*>(team.lds + (first + p) * LY::PLANE + lane) = acc[p];
     __syncthreads();
+}
+
+// Product k of those.
+template <int OPG, int NB, bool GATED> __device__ __forceinline__ v4f team_product(const Team& team, int k, Lane ln)
+{
+    return *reinterpret_cast<const v4f*>(team.lds + k * TeamLds<OPG, NB, GATED>::PLANE + 16 * (16 * ln.q + ln.n));
+}
+
+// All tiles, complete on the team's first wavefront; false for the others, which are done.
+template <int OPG, int NB, int METHOD, bool K16, bool GATED, bool HALF_ROWS = false>
+__device__ __forceinline__ bool team_gram(PreA<NB>& out, const void* Kc, bool is_f16, const float* gc, int64_t row_stride, int n_step, Lane ln, int valid,
+                                          const Team& team)
+{
+    team_gram_products<OPG, NB, METHOD, K16, GATED, HALF_ROWS>(Kc, is_f16, gc, row_stride, n_step, ln, valid, team);
     if (team.w > 0) return false;
     int n = 0;
-    const auto next = [&]() { return *reinterpret_cast<const v4f*>(team.lds + n++ * LY::PLANE + lane); };
+    const auto next = [&]() { return team_product<OPG, NB, GATED>(team, n++, ln); };
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
@@ -1180,10 +1207,9 @@ template <int NB> __device__ __forceinline__ void zero_strip_patch(float* lds, L
 }
 
 // Strip i, which lies in the patch as 16 plain rows, to memory.  ZEROED: the patch holds zeros right of tile i.
-template <int NB, bool ZEROED> __device__ __forceinline__ void flush_strip(Out Tm, int i, const float* lds, Lane ln)
+template <int NB, bool ZEROED, int LD = store_ld<NB>()> __device__ __forceinline__ void flush_strip(Out Tm, int i, const float* lds, Lane ln)
 {
     constexpr int C = 16 * NB;
-    constexpr int LD = store_ld<NB>();
     const int lane = 16 * ln.q + ln.n;
     const __amdgpu_buffer_rsrc_t out = matrix_buffer(Tm, C);
     wave_lds_sync();
@@ -1217,35 +1243,39 @@ template <int NB, bool ZEROED> __device__ __forceinline__ void flush_strip(Out T
     wave_lds_sync();
 }
 
+// Tile (i, j) of strip i into the patch, in T orientation or not; a diagonal tile gets `diag` on its diagonal and zeros above.
+template <int LD> __device__ __forceinline__ void strip_tile(float* lds, int i, int j, v4f v, bool is_t, Lane ln, float diag = 1.f)
+{
+    if (is_t) {  // v[r] = T[16i + n][16j + 4q + r]
+        if (i == j) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int rr = ln.n, cc = 4 * ln.q + r;
+                v[r] = (rr == cc) ? diag : ((rr > cc) ? v[r] : 0.f);
+            }
+        }
+        *reinterpret_cast<v4f*>(&lds[ln.n * LD + 16 * j + 4 * ln.q]) = v;
+    } else {     // v[r] = T[16i + 4q + r][16j + n]
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int rr = 4 * ln.q + r, cc = ln.n;
+            float x = v[r];
+            if (i == j) x = (rr == cc) ? diag : ((rr > cc) ? x : 0.f);
+            lds[rr * LD + 16 * j + cc] = x;
+        }
+    }
+}
+
 // One strip: tiles (i, 0..i) in row[0..i], tile j in T orientation when row_is_t(j).
 // ZEROED: the patch holds zeros right of tile i (zero_strip_patch, then strips in ascending order).
 template <int NB, bool ZEROED = false, class RowIsT>
 __device__ __forceinline__ void store_strip(Out Tm, int i, const v4f (&row)[NB], RowIsT row_is_t, float* lds, Lane ln,
                                             float diag = 1.f)
 {
-    constexpr int LD = store_ld<NB>();
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         if (j > i) break;
-        v4f v = row[j];
-        if (row_is_t(j)) {  // v[r] = T[16i + n][16j + 4q + r]
-            if (i == j) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int rr = ln.n, cc = 4 * ln.q + r;
-                    v[r] = (rr == cc) ? diag : ((rr > cc) ? v[r] : 0.f);
-                }
-            }
-            *reinterpret_cast<v4f*>(&lds[ln.n * LD + 16 * j + 4 * ln.q]) = v;
-        } else {            // v[r] = T[16i + 4q + r][16j + n]
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int rr = 4 * ln.q + r, cc = ln.n;
-                float x = v[r];
-                if (i == j) x = (rr == cc) ? diag : ((rr > cc) ? x : 0.f);
-                lds[rr * LD + 16 * j + cc] = x;
-            }
-        }
+        strip_tile<store_ld<NB>()>(lds, i, j, row[j], row_is_t(j), ln, diag);
     }
     flush_strip<NB, ZEROED>(Tm, i, lds, ln);
 }
