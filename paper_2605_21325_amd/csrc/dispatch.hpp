@@ -84,6 +84,9 @@ inline bool fp32_keys_by_team(int64_t n_mat, int d_k, int C) { return C == 64 &&
 // tiles a team formed before too) 9.5 / 6.7, direct leaves 5.0 / 4.9; 512: 5.6 / 5.3, 8.0 / 6.6, 12.4 / 9.3, 5.8 / 5.9; 768: 6.8 / 6.3, 9.2 / 8.1; 1024:
 // 7.6 / 8.3, 10.0 / 10.2, 15.6 / 17.3.
 inline bool by_team64(int64_t n_mat, bool direct) { return n_mat <= (direct ? 256 : 768); }
+// Applied to right-hand sides (team64_solve.hpp).  One / two of 128 columns, 256 matrices: bf16 6.7 / 5.3 and 8.9 / 6.5, fp32 operands 12.7 / 7.5 and 18.9 /
+// 10.7; 512: 7.6 / 7.1, 9.9 / 9.1, 14.4 / 11.5; 768: 9.1 / 8.9, 11.5 / 16.0, 17.0 / 16.0, 25.4 / 28.2.
+inline bool solve_by_team64(int64_t n_mat) { return n_mat <= FEW_MATRICES; }
 struct FusedGrid {
     unsigned groups, threads;
     int spread;

@@ -4,6 +4,8 @@
 #include "solve.hpp"
 #if TRIINV_INST_NB == 8
 #include "c128_kda_solve.hpp"
+#elif TRIINV_INST_NB == 4
+#include "team64_solve.hpp"
 #endif
 
 #ifndef TRIINV_INST_NB
@@ -73,6 +75,13 @@ template <int KD, int METHOD, int DKS> static int go_gdn(const SolveArgs& a)
     if constexpr (!SINGLE_ON_TWO_WAVES)
 #endif
     {
+#if TRIINV_INST_NB == 4
+    if (solve_by_team64(f.n_mat))
+        return a.n_rhs == 1 ? launch_kernel(f.dry, k_gdn_tri_solve_team64<KD, OP, METHOD, DKS, 1>, dim3((unsigned)f.n_mat), dim3(256), 0, f.stream, f.K, f.beta,
+                                            f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters)
+                            : launch_kernel(f.dry, k_gdn_tri_solve_team64<KD, OP, METHOD, DKS, 2>, dim3((unsigned)f.n_mat), dim3(256), 0, f.stream, f.K, f.beta,
+                                            f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
+#endif
     const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
     const dim3 grid(shape.groups), block(shape.threads);
     if (f.map.lens && !solve_packed<OP, NB>()) return 1;
@@ -100,8 +109,13 @@ template <int KD, int DKS> static int gdn_method(const SolveArgs& a)
 template <int METHOD, int NRHS> static int launch_kda_team(const SolveArgs& a)
 {
     const GdnArgs& f = a.f;
+#if TRIINV_INST_NB == 4
+    return launch_kernel(f.dry, k_kda_tri_solve_team64<OP, METHOD, NRHS>, dim3((unsigned)f.n_mat), dim3(256), 0, f.stream, f.K, f.beta, f.g, rhs_of(a),
+                         f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
+#else
     return launch_kernel(f.dry, k_kda_tri_solve<OP, NB, METHOD, 1, NRHS, true>, dim3((unsigned)f.n_mat), dim3(64 * TEAM_WAVES), 0, f.stream, f.K, f.beta,
                          f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters, 0);
+#endif
 }
 #endif
 
@@ -141,11 +155,24 @@ template <int KD, int METHOD, int NRHS, bool TEAM> static int launch_any_dk(cons
     return launch_kernel(f.dry, k_gdn_any_dk_tri_solve<KD, OP, NB, METHOD, NRHS, TEAM>, dim3((unsigned)f.n_mat), dim3(TEAM ? 64 * TEAM_WAVES : 64),
                          0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
 }
+#if TRIINV_INST_NB == 4
+template <int KD, int METHOD, int NRHS> static int launch_any_dk_team64(const SolveArgs& a)
+{
+    const GdnArgs& f = a.f;
+    return launch_kernel(f.dry, k_gdn_any_dk_tri_solve_team64<KD, OP, METHOD, NRHS>, dim3((unsigned)f.n_mat), dim3(256), 0, f.stream, f.K, f.beta, f.g, rhs_of(a),
+                         f.n_chunk, f.map, f.H, f.d_k, f.iters);
+}
+#endif
 template <int KD, int METHOD> static int go_any_dk(const SolveArgs& a)
 {
     const bool team = by_team(a.f.n_mat, a.f.d_k);
+#if TRIINV_INST_NB == 4
+    if (team) return a.n_rhs == 1 ? launch_any_dk_team64<KD, METHOD, 1>(a) : launch_any_dk_team64<KD, METHOD, 2>(a);
+    return a.n_rhs == 1 ? launch_any_dk<KD, METHOD, 1, false>(a) : launch_any_dk<KD, METHOD, 2, false>(a);
+#else
     if (a.n_rhs == 1) return team ? launch_any_dk<KD, METHOD, 1, true>(a) : launch_any_dk<KD, METHOD, 1, false>(a);
     return team ? launch_any_dk<KD, METHOD, 2, true>(a) : launch_any_dk<KD, METHOD, 2, false>(a);
+#endif
 }
 
 template <int KD> static int any_dk_method(const SolveArgs& a)
@@ -169,9 +196,6 @@ int CAT(launch_solve_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP)(const SolveArgs& a
         return 1;
     }
     if (f.k_dt == OP_F32) {
-#if TRIINV_INST_NB <= 4
-        if (fp32_keys_by_team(f.n_mat, f.d_k, 16 * NB)) return any_dk_method<OP_F32>(a);
-#endif
         if (f.d_k == 64) return gdn_method<OP_F32, 4>(a);
 #if TRIINV_INST_NB <= 4
         if (f.d_k == 128) return gdn_method<OP_F32, 8>(a);

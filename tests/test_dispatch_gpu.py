@@ -299,3 +299,36 @@ def test_teams_of_large_chunks_give_the_bits_of_a_larger_call(method, op, k_dtyp
         if tokens % C:  # the short last chunk: the leading block of the whole one
             v = tokens % C
             assert torch.equal(few[whole:, :v, :v], many[whole:whole + H, :v, :v]), tokens
+
+
+# C = 64, up to 768 matrices (direct leaves 256, applied 512): four wavefronts carry one matrix through the recursion and the store too.  The bits of
+# larger calls, on chunks that end anywhere in a tile; both element types of a result.
+@pytest.mark.parametrize("gate", [tri.GATE_SCALAR, tri.GATE_NONE])
+@pytest.mark.parametrize("k_dtype, d_k", [(torch.bfloat16, 64), (torch.float16, 128), (torch.float32, 64), (torch.float32, 128)], ids=str)
+@pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
+def test_teams_through_the_recursion_give_the_bits_of_a_larger_call(op, k_dtype, d_k, gate):
+    C, H, most = 64, 3, 256                           # 768 matrices by team, 771 by a wavefront each
+    T = (most + 1) * C - 7
+    K, beta, g = make_inputs(T, H, d_k, gate, k_dtype)
+    part = lambda x, t: None if x is None else x[:, :t].contiguous()
+    x_dtype = {tri.F32: torch.float32, tri.F16: torch.float16, tri.BF16: torch.bfloat16}[op]
+    Xs = [torch.randn(1, T, H, d_x, device=DEV).to(x_dtype) for d_x in (72, 200)]
+    def calls(t):
+        k, b, gg, xs = part(K, t), part(beta, t), part(g, t), [part(x, t) for x in Xs]
+        Ts = [tri.gdn_chunk_tri_inv_ex(k, b, gg, C, gate_kind=gate, method=m, op_dtype=op, out_dtype=o, flags=f)
+              for m, o, f in ((tri.BLOCK_RECURSIVE, torch.float32, 0), (tri.MIXED, x_dtype, 0), (tri.MIXED, torch.float32, tri.flag_mxr_r(2)),
+                              (tri.BLOCK_DIRECT, torch.float32, 0))]
+        Ws = [tri.gdn_chunk_tri_solve(k, b, gg, xs[0], C, gate_kind=gate),
+              *tri.gdn_chunk_tri_solve_multi(k, b, gg, xs, C, row_scales=[b, None], gate_kind=gate, method=tri.MIXED)]
+        return Ts, Ws
+    many, applied = calls(T)
+    for t in (1, 16, 17, C - 1, C, C + 33, 85 * C, 170 * C, most * C):
+        Ts, Ws = calls(t)
+        whole, v = t // C * H, t % C
+        for a, b in zip(Ts, many):
+            assert torch.equal(a[:whole], b[:whole]), t
+            if v:
+                assert torch.equal(a[whole:, :v, :v], b[whole:whole + H, :v, :v]), t
+                assert torch.equal(a[whole:, v:, v:], torch.eye(C - v, device=DEV).to(a.dtype).expand(H, -1, -1)) and not a[whole:, v:, :v].any(), t
+        for a, b in zip(Ws, applied):
+            assert torch.equal(a, b[:, :t]), t
