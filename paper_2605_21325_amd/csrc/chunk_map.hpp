@@ -138,7 +138,7 @@ template <int C> TRIINV_HOST_DEVICE ChunkPos locate_chunk(const ChunkMap& map, u
 {
     ChunkPos p;
     int64_t left;
-    if (map.cu_seqlens == nullptr) {
+    if (__builtin_expect(map.cu_seqlens == nullptr, 1)) {
         const uint32_t s = bc / map.cps, k = bc - s * map.cps;
         p.tok0 = (int64_t)s * map.Tlen + (int64_t)k * C;
         left = map.Tlen - (int64_t)k * C;
@@ -196,7 +196,7 @@ template <int C, int WORDS> TRIINV_HOST_DEVICE ChunkPos locate_packed(const Kern
 
 template <int C, int WORDS> TRIINV_HOST_DEVICE ChunkPos locate_chunk(const KernelMap<WORDS>& map, uint32_t bc)
 {
-    return map.packed() ? locate_packed<C>(map, bc) : locate_chunk<C>(map.plain(), bc);
+    return __builtin_expect(map.packed(), 0) ? locate_packed<C>(map, bc) : locate_chunk<C>(map.plain(), bc);
 }
 template <int C> TRIINV_HOST_DEVICE ChunkPos locate_chunk(const OffsetMap& map, uint32_t bc)
 {

@@ -87,6 +87,10 @@ inline bool by_team64(int64_t n_mat, bool direct) { return n_mat <= (direct ? 25
 // Applied to right-hand sides (team64_solve.hpp).  One / two of 128 columns, 256 matrices: bf16 6.7 / 5.3 and 8.9 / 6.5, fp32 operands 12.7 / 7.5 and 18.9 /
 // 10.7; 512: 7.6 / 7.1, 9.9 / 9.1, 14.4 / 11.5; 768: 9.1 / 8.9, 11.5 / 16.0, 17.0 / 16.0, 25.4 / 28.2.
 inline bool solve_by_team64(int64_t n_mat) { return n_mat <= FEW_MATRICES; }
+// C = 128, the same, eight wavefronts to a matrix (team128.hpp), whose 112 to 150 KB of LDS let a compute unit hold one team.  Kernel of the larger calls /
+// a team: 8 matrices bf16 7.5 / 7.1 us, fp32 operands 17.6 / 9.1; 256: 9.0 / 9.0, fp16 mixed 9.3 / 8.8, fp32 operands 19.0 / 11.1, mixed 19.7 / 11.3, direct
+// leaves 17.0 / 11.1, fp32 keys of 64 channels 25.8 / 13.1, of 128 with 16-bit operands 21.7 / 14.4.
+inline bool recursion_by_team128(int64_t n_mat) { return n_mat <= 256; }
 struct FusedGrid {
     unsigned groups, threads;
     int spread;

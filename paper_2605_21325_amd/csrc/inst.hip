@@ -7,6 +7,7 @@
 #include "c128.hpp"
 #include "c128_kda.hpp"
 #include "kda128.hpp"
+#include "team128.hpp"
 #endif
 #if TRIINV_INST_NB == 4 && !TRIINV_INST_FWD
 #include "team64.hpp"
@@ -151,6 +152,11 @@ template <int KD, int METHOD, int DKS> constexpr unsigned occupancy_pad_bytes()
 template <int KD, int METHOD, int DKS, bool REFINE = false> static int go_gdn(const GdnArgs& a)
 {
 #if TRIINV_INST_NB == 8 && !TRIINV_INST_FWD
+    if constexpr (!REFINE && team64_method<METHOD>()) {
+        if (recursion_by_team128(a.n_mat))
+            return launch_kernel(a.dry, k_gdn_tri_inv_team128<KD, OP, METHOD, DKS>, dim3((unsigned)a.n_mat), dim3(512), 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk,
+                                 a.map, a.H, a.d_k, a.iters, a.out_dt);
+    }
     // C = 128, the recursions with 16-bit operands: one matrix per workgroup of two wavefronts (c128.hpp).  fp32 operands
     // keep one wavefront per matrix: their four-instruction tile products make the kernel matrix-core bound, and the
     // exchange of fp32 tiles through LDS costs more than the second wavefront returns (250 against 226 us on the stress workload).

@@ -301,13 +301,14 @@ def test_teams_of_large_chunks_give_the_bits_of_a_larger_call(method, op, k_dtyp
             assert torch.equal(few[whole:, :v, :v], many[whole:whole + H, :v, :v]), tokens
 
 
-# C = 64, up to 768 matrices (direct leaves 256, applied 512): four wavefronts carry one matrix through the recursion and the store too.  The bits of
-# larger calls, on chunks that end anywhere in a tile; both element types of a result.
+# C = 64, up to 768 matrices (direct leaves 256, applied 512): four wavefronts carry one matrix through the recursion and the store too; C = 128, up to 256:
+# eight.  The bits of larger calls, on chunks that end anywhere in a tile; both element types of a result.
+@pytest.mark.parametrize("C, most", [(64, 256), (128, 85)])  # chunks of the largest call by team, with three heads
 @pytest.mark.parametrize("gate", [tri.GATE_SCALAR, tri.GATE_NONE])
 @pytest.mark.parametrize("k_dtype, d_k", [(torch.bfloat16, 64), (torch.float16, 128), (torch.float32, 64), (torch.float32, 128)], ids=str)
 @pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
-def test_teams_through_the_recursion_give_the_bits_of_a_larger_call(op, k_dtype, d_k, gate):
-    C, H, most = 64, 3, 256                           # 768 matrices by team, 771 by a wavefront each
+def test_teams_through_the_recursion_give_the_bits_of_a_larger_call(op, k_dtype, d_k, gate, C, most):
+    H = 3
     T = (most + 1) * C - 7
     K, beta, g = make_inputs(T, H, d_k, gate, k_dtype)
     part = lambda x, t: None if x is None else x[:, :t].contiguous()
@@ -322,7 +323,8 @@ def test_teams_through_the_recursion_give_the_bits_of_a_larger_call(op, k_dtype,
               *tri.gdn_chunk_tri_solve_multi(k, b, gg, xs, C, row_scales=[b, None], gate_kind=gate, method=tri.MIXED)]
         return Ts, Ws
     many, applied = calls(T)
-    for t in (1, 16, 17, C - 1, C, C + 33, 85 * C, 170 * C, most * C):
+    for t in (1, 16, 17, C - 1, C, C + 33, C + 100, 85 * C, 170 * C, most * C):
+        if t > most * C: continue
         Ts, Ws = calls(t)
         whole, v = t // C * H, t % C
         for a, b in zip(Ts, many):
