@@ -91,6 +91,10 @@ inline bool solve_by_team64(int64_t n_mat) { return n_mat <= FEW_MATRICES; }
 // a team: 8 matrices bf16 7.5 / 7.1 us, fp32 operands 17.6 / 9.1; 256: 9.0 / 9.0, fp16 mixed 9.3 / 8.8, fp32 operands 19.0 / 11.1, mixed 19.7 / 11.3, direct
 // leaves 17.0 / 11.1, fp32 keys of 64 channels 25.8 / 13.1, of 128 with 16-bit operands 21.7 / 14.4.
 inline bool recursion_by_team128(int64_t n_mat) { return n_mat <= 256; }
+// Applied to right-hand sides (team128_solve.hpp), kernel of the larger calls / a team.  8 matrices, one side of 128 columns: bf16 11.3 / 9.8 us, fp32
+// operands 36.3 / 16.3; 256: bf16 12.2 / 10.6 (two sides 17.0 / 13.9), fp16 of 64 channels 11.3 / 10.5, fp32 operands 37.1 / 17.8 (42.6 / 27.6), fp32 keys
+// with 16-bit operands 24.4 / 16.2.
+inline bool solve_by_team128(int64_t n_mat) { return n_mat <= 256; }
 struct FusedGrid {
     unsigned groups, threads;
     int spread;

@@ -4,6 +4,7 @@
 #include "solve.hpp"
 #if TRIINV_INST_NB == 8
 #include "c128_kda_solve.hpp"
+#include "team128_solve.hpp"
 #elif TRIINV_INST_NB == 4
 #include "team64_solve.hpp"
 #endif
@@ -58,6 +59,11 @@ template <int KD, int METHOD, int DKS> static int go_gdn(const SolveArgs& a)
     // keep the one-wavefront kernel otherwise (363 against 444 us).
     constexpr bool SINGLE_ON_TWO_WAVES = (KD != OP_F32 && DKS == 2) || (KD == OP_F32 && DKS == 8);
     constexpr bool SINGLE_BY_ROWS = SINGLE_ON_TWO_WAVES || OP != OP_F32;
+    if (solve_by_team128(f.n_mat) && rows_fit_32_bits(a))
+        return a.n_rhs == 1 ? launch_kernel(f.dry, k_gdn_tri_solve_team128<KD, OP, METHOD, DKS, 1, !SINGLE_BY_ROWS>, dim3((unsigned)f.n_mat), dim3(512), 0, f.stream,
+                                            f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters)
+                            : launch_kernel(f.dry, k_gdn_tri_solve_team128<KD, OP, METHOD, DKS, 2, false>, dim3((unsigned)f.n_mat), dim3(512), 0, f.stream, f.K,
+                                            f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters);
     if (a.n_rhs == 2 || SINGLE_ON_TWO_WAVES) {
         if (!rows_fit_32_bits(a)) return 1;
     }

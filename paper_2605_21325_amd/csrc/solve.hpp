@@ -94,7 +94,7 @@ template <int OP> __device__ __forceinline__ Opnd<OP> x_operand(const XRow<OP> (
 }
 
 // The right-hand sides of one chunk and head.
-template <int OP, int NB> struct RhsX {
+template <int OP, int NB, bool BUFFERS = (NB <= 4)> struct RhsX {
     static constexpr int ESZ = OP == OP_F32 ? 4 : 2;
     static constexpr int VEC = 16 / ESZ;  // columns per lane
     static constexpr int GW = 16 * VEC;   // columns per group
@@ -103,8 +103,8 @@ template <int OP, int NB> struct RhsX {
     // checks).  With 64-bit pointers every row's load address and store address is a register pair of its own: 64
     // registers at C = 64, which cost the kernels with two right-hand sides their second wavefront per SIMD (299
     // registers against 236).
-    // C = 128 (one wavefront per chunk: the fallback for tensors too wide for 32-bit offsets) keeps the pointers.
-    static constexpr bool BUF = NB <= 4;
+    // C = 128 on one wavefront (the fallback for tensors too wide for 32-bit offsets) keeps the pointers.
+    static constexpr bool BUF = BUFFERS;
     static constexpr int CACHE_NT = 2;
     __amdgpu_buffer_rsrc_t xb, wb;
     const char* xc;      // element (chunk row 0, this head, column 0) of X

@@ -31,14 +31,15 @@ template <int KD, int OP, int METHOD, int DKS> struct Team128Lds {
     static_assert(BYTES <= 160 * 1024, "a compute unit holds one team");
 };
 
-template <int KD, int OP, int METHOD, int DKS>
+// MERGE_T: the last merge in T orientation, as block_recursive has it, else as c128_merge.  keys_loaded(): called behind the key loads.  finish(strip): what is to be
+// done with the result once all of it is there; strip: tile row w of it, 16 plain rows of STRIP_LD floats, anything right of the diagonal tile.
+template <int KD, int OP, int METHOD, int DKS, bool MERGE_T, class Hook, class Finish>
 __device__ __forceinline__ void team128_invert(char* lds, const void* Kc, int64_t row_stride, const float* bc, const float* gc, int64_t tok_stride, int valid,
-                                               int aux, Out Tm, int w, Lane ln)
+                                               int aux, int w, Lane ln, Hook keys_loaded, Finish finish)
 {
     typedef Team128Lds<KD, OP, METHOD, DKS> LY;
     typedef typename KeyVec<KD>::type kvec;
     constexpr int KSTEP = KD == OP_F32 ? 16 : 32, PER_LANE = KD == OP_F32 ? 4 : 8;
-    constexpr bool MERGE_T = OP == OP_F32;  // the last merge in T orientation (as the kernels of larger calls have it)
     const int lane = 16 * ln.q + ln.n, half = w >> 2, u = w & 3;
     Opnd<OP>* const tiles = reinterpret_cast<Opnd<OP>*>(lds) + lane;
     kvec* const keys = reinterpret_cast<kvec*>(lds + LY::KEYS) + lane;  // [(tile row * DKS + k-step) * 64]
@@ -60,6 +61,7 @@ __device__ __forceinline__ void team128_invert(char* lds, const void* Kc, int64_
     const int64_t off = (int64_t)(row < valid ? row : valid - 1) * row_stride + PER_LANE * ln.q;
 #pragma unroll
     for (int s = 0; s < DKS; ++s) own[s] = *reinterpret_cast<const kvec*>(static_cast<const char*>(Kc) + (off + KSTEP * s) * (KD == OP_F32 ? 4 : 2));
+    keys_loaded();
     if (w < 2) {
         beta[t] = t < valid ? raw_b : 0.f;
         beta[128 + t] = gc ? raw_g * 1.44269504088896340736f : 0.f;
@@ -214,7 +216,7 @@ __device__ __forceinline__ void team128_invert(char* lds, const void* Kc, int64_
         }
     }
     __syncthreads();  // the strips are complete
-    flush_strip<8, false, LY::STRIP_LD>(Tm, w, strip(w), ln);
+    finish(strip(w));
 }
 
 template <int KD, int OP, int METHOD, int DKS>
@@ -229,8 +231,10 @@ __global__ __launch_bounds__(512) void k_gdn_tri_inv_team128(const void* __restr
     const int64_t tok0 = pos.tok0;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const void* const Kc = static_cast<const char*>(K) + (tok0 * H + h) * (int64_t)d_k * (KD == OP_F32 ? 4 : 2);
-    team128_invert<KD, OP, METHOD, DKS>(lds, Kc, (int64_t)H * d_k, beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, pos.valid, aux,
-                                        out_matrix(T, m, 128, out_dt), w, lane_id());
+    const Lane ln = lane_id();
+    const Out Tm = out_matrix(T, m, 128, out_dt);
+    team128_invert<KD, OP, METHOD, DKS, OP == OP_F32>(lds, Kc, (int64_t)H * d_k, beta + tok0 * H + h, g ? g + tok0 * H + h : nullptr, H, pos.valid, aux, w, ln,
+                                                      NoHook(), [&](float* strip) { flush_strip<8, false, 128 + 4>(Tm, w, strip, ln); });
 }
 
 }  // namespace triinv
