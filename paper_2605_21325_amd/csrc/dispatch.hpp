@@ -95,6 +95,10 @@ inline bool recursion_by_team128(int64_t n_mat) { return n_mat <= 256; }
 // operands 36.3 / 16.3; 256: bf16 12.2 / 10.6 (two sides 17.0 / 13.9), fp16 of 64 channels 11.3 / 10.5, fp32 operands 37.1 / 17.8 (42.6 / 27.6), fp32 keys
 // with 16-bit operands 24.4 / 16.2.
 inline bool solve_by_team128(int64_t n_mat) { return n_mat <= 256; }
+// The per-channel gate at C = 128 (two wavefronts / a team, d_k = 128).  8 matrices bf16 14.5 / 12.1 us, fp32 keys and operands 32.4 / 19.5; 256: bf16 16.4 /
+// 14.5, applied 20.0 / 15.5 (two sides 27.2 / 19.6), fp32 operands 34.8 / 21.8, applied 49.5 / 28.2, fp16 mixed of 64 channels 11.7 / 10.7; 128 of 256 channels
+// 23.4 / 17.6, of 32 8.3 / 7.7.
+inline bool channels_by_team128(int64_t n_mat) { return n_mat <= 256; }
 struct FusedGrid {
     unsigned groups, threads;
     int spread;

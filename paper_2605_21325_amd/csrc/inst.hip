@@ -253,6 +253,11 @@ template <int METHOD> static unsigned kda_pad_bytes(const GdnArgs& a)
 template <int METHOD, bool REFINE = false> static int go_kda(const GdnArgs& a)
 {
 #if TRIINV_INST_NB == 8 && !TRIINV_INST_FWD
+    if constexpr (!REFINE && team64_method<METHOD>()) {
+        if (channels_by_team128(a.n_mat))
+            return launch_kernel(a.dry, a.k_dt == OP_F32 ? k_kda_tri_inv_team128<OP, METHOD, false> : k_kda_tri_inv_team128<OP, METHOD, true>,
+                                 dim3((unsigned)a.n_mat), dim3(512), 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt);
+    }
     // C = 128, the recursions: one matrix per workgroup of two wavefronts (c128_kda.hpp)
     if constexpr (!REFINE && (METHOD == M_BLOCK || METHOD == M_MIXED || METHOD == M_MIXED32 || METHOD == M_BLOCK_DIRECT))
         return launch_kernel(a.dry, a.k_dt == OP_F32 ? k_kda_tri_inv_c128<OP, METHOD, false> : k_kda_tri_inv_c128<OP, METHOD, true>,

@@ -131,6 +131,13 @@ template <int METHOD> static int go_kda(const SolveArgs& a)
 #if TRIINV_INST_NB == 8
     // C = 128: one chunk per workgroup of two wavefronts (c128_kda_solve.hpp)
     if (!rows_fit_32_bits(a)) return 1;
+    if (channels_by_team128(f.n_mat)) {
+        if (a.n_rhs == 1)
+            return launch_kernel(f.dry, f.k_dt == OP_F32 ? k_kda_tri_solve_team128<OP, METHOD, false, 1> : k_kda_tri_solve_team128<OP, METHOD, true, 1>,
+                                 dim3((unsigned)f.n_mat), dim3(512), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
+        return launch_kernel(f.dry, f.k_dt == OP_F32 ? k_kda_tri_solve_team128<OP, METHOD, false, 2> : k_kda_tri_solve_team128<OP, METHOD, true, 2>,
+                             dim3((unsigned)f.n_mat), dim3(512), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt, f.iters);
+    }
     if (a.n_rhs == 1)
         return launch_kernel(f.dry, f.k_dt == OP_F32 ? k_kda_tri_solve_c128<OP, METHOD, false, 1> : k_kda_tri_solve_c128<OP, METHOD, true, 1>,
                              dim3((unsigned)f.n_mat), dim3(128), 0, f.stream, f.K, f.beta, f.g, rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.k_dt,

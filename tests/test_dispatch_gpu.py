@@ -304,8 +304,9 @@ def test_teams_of_large_chunks_give_the_bits_of_a_larger_call(method, op, k_dtyp
 # C = 64, up to 768 matrices (direct leaves 256, applied 512): four wavefronts carry one matrix through the recursion and the store too; C = 128, up to 256:
 # eight.  The bits of larger calls, on chunks that end anywhere in a tile; both element types of a result.
 @pytest.mark.parametrize("C, most", [(64, 256), (128, 85)])  # chunks of the largest call by team, with three heads
-@pytest.mark.parametrize("gate", [tri.GATE_SCALAR, tri.GATE_NONE])
-@pytest.mark.parametrize("k_dtype, d_k", [(torch.bfloat16, 64), (torch.float16, 128), (torch.float32, 64), (torch.float32, 128)], ids=str)
+@pytest.mark.parametrize("gate, k_dtype, d_k", [(g, k, d) for g in (tri.GATE_SCALAR, tri.GATE_NONE, tri.GATE_PER_CHANNEL)
+                                                for k, d in ((torch.bfloat16, 64), (torch.float16, 128), (torch.float32, 64), (torch.float32, 128))]
+                         + [(tri.GATE_PER_CHANNEL, torch.bfloat16, 32), (tri.GATE_PER_CHANNEL, torch.float32, 160), (tri.GATE_PER_CHANNEL, torch.float16, 256)], ids=str)
 @pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
 def test_teams_through_the_recursion_give_the_bits_of_a_larger_call(op, k_dtype, d_k, gate, C, most):
     H = 3
