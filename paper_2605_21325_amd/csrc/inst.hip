@@ -116,6 +116,10 @@ int CAT(launch_tri_inv_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const Tr
 #if TRIINV_INST_NB <= 4
         return go_tri<M_NEWTON_SCHULZ>(a);
 #else   // A, X and X as a left factor do not fit one wave's registers at C = 128: four waves, X and Y in LDS
+        if (newton_by_eight(a.n_mat)) {
+            TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv_ns128<IN, OP, 8>), dim3((unsigned)a.n_mat), dim3(512), 0, a.stream, a.A, a.T,
+                                                           a.n_mat, a.iters, a.out_dt))
+        }
         TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv_ns128<IN, OP>), dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.A, a.T,
                                                        a.n_mat, a.iters, a.out_dt))
 #endif
@@ -224,6 +228,9 @@ template <int KD, int DKS> static int gdn_method(const GdnArgs& a)
 #if TRIINV_INST_NB <= 4
         return go_gdn<KD, M_NEWTON_SCHULZ, DKS>(a);
 #else
+        if (newton_by_eight(a.n_mat))
+            return launch_kernel(a.dry, k_gdn_tri_inv_ns128<KD, OP, DKS, 8>, dim3((unsigned)a.n_mat), dim3(512), 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk,
+                                 a.map, a.H, a.d_k, a.iters, a.out_dt);
         return launch_kernel(a.dry, k_gdn_tri_inv_ns128<KD, OP, DKS>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.K, a.beta,
                            a.g, a.T, a.n_chunk, a.map, a.H, a.d_k, a.iters, a.out_dt);
 #endif

@@ -1881,6 +1881,20 @@ __device__ __forceinline__ void n128_store(Out Tm, const v4f (&Xt)[9], float* pa
     default: { constexpr int W = 3; CALL; } break; \
     }
 
+// Eight wavefronts: two to a pair of tile rows, one for the even tile columns and one for the odd (Newton-Schulz, few matrices).  The two that share a
+// SIMD, w and w + 4, have 29 to 31 of a product's 120 tile products between them, the longest 21 (of four wavefronts 25 to 37).
+#define TRIINV_PER_HALF_WAVE(w, CALL) \
+    switch (w) {                      \
+    case 0: { constexpr int W = 0, PART = 0; CALL; } break; \
+    case 1: { constexpr int W = 0, PART = 1; CALL; } break; \
+    case 2: { constexpr int W = 1, PART = 0; CALL; } break; \
+    case 3: { constexpr int W = 1, PART = 1; CALL; } break; \
+    case 4: { constexpr int W = 3, PART = 1; CALL; } break; \
+    case 5: { constexpr int W = 3, PART = 0; CALL; } break; \
+    case 6: { constexpr int W = 2, PART = 1; CALL; } break; \
+    default: { constexpr int W = 2, PART = 0; CALL; } break; \
+    }
+
 // ---------------------------------------------------------------------------------------------
 // Newton-Schulz at C = 128 (paper Alg. 3, Eq. 8, for I + A): the same four-wavefront workgroup.
 //   X <- I / C;  n_iter times:  Y <- X + A X;  X <- 2 X - X Y.
@@ -1924,10 +1938,12 @@ template <int OP> struct TurnTiles {
     }
 };
 // X and Y: 16-bit operands a set each, fp32 ones a set for both in turns (a second one of 54 KB would leave a compute unit one workgroup).
-template <int OP> constexpr int ns128_lds_bytes()
+// Later the store patches; eight wavefronts: all eight strips of the result.
+constexpr int NS128_STRIP_LD = 128 + 4;
+template <int OP, int WAVES = 4> constexpr int ns128_lds_bytes()
 {
-    constexpr int tiles = (OP == OP_F32 ? 1 : 2) * TurnTiles<OP>::BYTES;
-    return tiles > 4 * STORE_LDS_FLOATS * 4 ? tiles : 4 * STORE_LDS_FLOATS * 4;
+    constexpr int tiles = (OP == OP_F32 ? 1 : 2) * TurnTiles<OP>::BYTES, store = WAVES == 8 ? 128 * NS128_STRIP_LD * 4 : 4 * STORE_LDS_FLOATS * 4;
+    return tiles > store ? tiles : store;
 }
 
 template <int W> __host__ __device__ constexpr int n128_slot(int i, int k) { return i == W ? k : (W + 1) + k; }
@@ -2025,15 +2041,17 @@ template <int OP> __device__ __forceinline__ v4f turned(Opnd<OP> x, Opnd<OP_BF16
 // right factor is read from LDS once for both of the wave's rows; 16-bit operands contract two tiles per instruction, fp32 ones are split
 // into three bf16 parts; the first iteration from I / C is a scaling.
 // Bound by latency: LDS reads a column at a time and two (fp32: four) barriers an iteration.  1024 fused matrices with fp32 operands, by fp32
-// instructions / split 245.6 / 183.8 us, standalone 240.9 / 180.2, 16 of them 73 / 70, error against 64 bits 1.34e-7 / 1.32e-7 (standalone 8.6e-8 / 5.8e-8);
+// instructions / split 245.6 / 183.8 us, standalone 240.9 / 180.2, 16 of them 73 / 70 (by eight wavefronts 48), error against 64 bits 1.34e-7 / 1.32e-7 (standalone 8.6e-8 / 5.8e-8);
 // X turned by products with the identity / by LDS reads: 4096 bf16 188 / 173, 2048 standalone 96 / 86.
-template <int OP, int W>
+// PART: 0, 1: of eight wavefronts, this one's columns are the even / odd ones (TRIINV_PER_HALF_WAVE); -1: all.
+template <int OP, int W, int PART = -1>
 __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char* lds, Lane ln, int n_iter, int w)
 {
     typedef Ns128Operands<OP> Ops;
     constexpr bool ONE_SET = OP == OP_F32;
     constexpr int ROW[2] = {W, 7 - W};
     constexpr float X0 = 1.f / 128.f;
+    constexpr auto mine = [](int j) { return PART < 0 || (j & 1) == PART; };
     const TurnTiles<OP> X(lds, ln), Y(lds + (ONE_SET ? 0 : TurnTiles<OP>::BYTES), ln);
     const v4f unit = identity_tile(ln);
     typename Ops::Row Al[2];
@@ -2045,6 +2063,7 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
         for (int s = 0; s < 9; ++s) {
             const int i = n128_row<W>(s), j = n128_col<W>(s);
             Ops::put(Al[s <= W ? 0 : 1], j, At[s]);
+            if (!mine(j)) continue;
             v4f a = turned<OP>(At[s], id_bf16, id);
             if (i == j) a += unit;
             Xn[s] = (i == j ? 2.f * X0 : 0.f) * unit - X0 * X0 * a;
@@ -2058,6 +2077,7 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
         v4f Yn[9];
 #pragma unroll
         for (int j = 0; j <= 7 - W; ++j) {
+            if (!mine(j)) continue;
             v4f y[2];
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -2079,12 +2099,14 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
         __syncthreads();  // nobody reads X from LDS any more in this iteration; two sets: Y complete
         if (ONE_SET) {
 #pragma unroll
-            for (int s = 0; s < 9; ++s) Ops::publish(Y, tix(n128_row<W>(s), n128_col<W>(s)), Yn[s]);
+            for (int s = 0; s < 9; ++s)
+                if (mine(n128_col<W>(s))) Ops::publish(Y, tix(n128_row<W>(s), n128_col<W>(s)), Yn[s]);
             __syncthreads();  // Y complete
         }
         // X(i,j) <- 2 X(i,j) - sum_k X(i,k) Y(k,j)
 #pragma unroll
         for (int j = 0; j <= 7 - W; ++j) {
+            if (!mine(j)) continue;
             v4f xy[2] = {zero4(), zero4()};
             Ops::template products<W>(Xl, Y, j, xy);
 #pragma unroll
@@ -2099,22 +2121,34 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
         __syncthreads();  // nobody reads Y any more; two sets: X complete
         if (ONE_SET && it + 1 < n_iter) {
 #pragma unroll
-            for (int s = 0; s < 9; ++s) Ops::publish(X, tix(n128_row<W>(s), n128_col<W>(s)), Xn[s]);
+            for (int s = 0; s < 9; ++s)
+                if (mine(n128_col<W>(s))) Ops::publish(X, tix(n128_row<W>(s), n128_col<W>(s)), Xn[s]);
             __syncthreads();  // X complete
         }
     }
-    // X and Y in LDS are dead: their memory becomes the four store patches
-    n128_store<W, false>(Tm, Xn, reinterpret_cast<float*>(lds) + w * STORE_LDS_FLOATS, ln);
+    // X and Y in LDS are dead: their memory becomes the four store patches, or the strips of the whole result
+    if constexpr (PART < 0) {
+        n128_store<W, false>(Tm, Xn, reinterpret_cast<float*>(lds) + w * STORE_LDS_FLOATS, ln);
+    } else {
+        float* const strips = reinterpret_cast<float*>(lds);
+#pragma unroll
+        for (int s = 0; s < 9; ++s) {
+            const int i = n128_row<W>(s), j = n128_col<W>(s);
+            if (mine(j)) strip_tile<NS128_STRIP_LD>(strips + i * 16 * NS128_STRIP_LD, i, j, Xn[s], false, ln);
+        }
+        __syncthreads();
+        flush_strip<N128_NB, false, NS128_STRIP_LD>(Tm, w, strips + w * 16 * NS128_STRIP_LD, ln);
+    }
 }
 
 // The fused kernel's tiles of A: the four waves load the chunk's keys once between them (wave w its tile rows w and
 // 7 - w), pass them through LDS in mailbox form (slot [tile row][k-step][lane], one 16-byte
 // key vector each) and every wave forms only its own nine tiles.
-template <int KD, int DKS> struct SharedKeys128 {
+template <int KD, int DKS, int ROWS = 2> struct SharedKeys128 {
     typedef typename KeyVec<KD>::type kvec;
     static constexpr int KSTEP = (KD == OP_F32) ? 16 : 32;
     static constexpr int BYTES = 8 * DKS * 64 * 16;
-    kvec own[2][DKS];
+    kvec own[ROWS][DKS];  // ROWS = 2: tile rows w and 7 - w, 1: w
 
     // Kc: first key element of (chunk row 0, this head); row_stride in elements; rows beyond valid read the last real token and become zero.
     __device__ __forceinline__ void load(const void* Kc, int64_t row_stride, int valid, int w, Lane ln)
@@ -2122,7 +2156,7 @@ template <int KD, int DKS> struct SharedKeys128 {
         constexpr int per_lane = (KD == OP_F32) ? 4 : 8;
         const kvec zero = __builtin_bit_cast(kvec, v4u{0u, 0u, 0u, 0u});
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < ROWS; ++h)
 #pragma unroll
             for (int s = 0; s < DKS; ++s) {
                 const int row = 16 * (h == 0 ? w : 7 - w) + ln.n;
@@ -2138,7 +2172,7 @@ template <int KD, int DKS> struct SharedKeys128 {
     __device__ __forceinline__ void publish(char* lds, int w, Lane ln) const
     {
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < ROWS; ++h)
 #pragma unroll
             for (int s = 0; s < DKS; ++s)
                 *reinterpret_cast<kvec*>(lds + (((h == 0 ? w : 7 - w) * DKS + s) * 64 + 16 * ln.q + ln.n) * 16) = own[h][s];
@@ -2162,8 +2196,8 @@ template <int KD, int DKS> struct SharedKeys128 {
 };
 
 // SharedKeys128 behind the tile-source interface, for the tiles of wave W only.
-template <int KD, int DKS, int W> struct SharedA128 {
-    const SharedKeys128<KD, DKS>& keys;
+template <int KD, int DKS, int W, int ROWS = 2> struct SharedA128 {
+    const SharedKeys128<KD, DKS, ROWS>& keys;
     const GateVec<N128_NB>& gate;
     const char* lds;
     Lane ln;
@@ -2364,31 +2398,36 @@ __global__ __launch_bounds__(256) void k_gdn_tri_inv_refine128(const void* __res
     TRIINV_PER_WAVE(w, (refine128_run<OP, W>(src, T + m * C * C, Y, ln, w)))
 }
 
-template <int IN, int OP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_tri_inv_ns128(const void* A, float* T, int64_t n_mat, int n_iter, int out_dt)  // may run in place
+// WAVES: 4 or 8.
+template <int IN, int OP, int WAVES = 4>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 8 || OP == OP_F32 ? 2 : 3))) void k_tri_inv_ns128(const void* A, float* T, int64_t n_mat, int n_iter, int out_dt)  // may run in place
 {
-    __shared__ __attribute__((aligned(16))) char lds[ns128_lds_bytes<OP>()];
+    __shared__ __attribute__((aligned(16))) char lds[ns128_lds_bytes<OP, WAVES>()];
     const int64_t m = blockIdx.x;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const Lane ln = lane_id();
     const GlobalA<N128_NB, IN> src{static_cast<const char*>(A) + m * 128 * 128 * (IN == OP_F32 ? 4 : 2), ln};
     (void)n_mat;
     Opnd<OP> At[9];
-    TRIINV_PER_WAVE(w, (ns128_tiles_of<OP, W>(src, At)))
     // in place: every wave has read its rows of A before any wave stores (the iteration's barriers lie between)
-    TRIINV_PER_WAVE(w, (ns128_run<OP, W>(At, out_matrix(T, m, 128, out_dt), lds, ln, n_iter, w)))
+    if constexpr (WAVES == 8) {
+        TRIINV_PER_HALF_WAVE(w, (ns128_tiles_of<OP, W>(src, At), ns128_run<OP, W, PART>(At, out_matrix(T, m, 128, out_dt), lds, ln, n_iter, w)))
+    } else {
+        TRIINV_PER_WAVE(w, (ns128_tiles_of<OP, W>(src, At)))
+        TRIINV_PER_WAVE(w, (ns128_run<OP, W>(At, out_matrix(T, m, 128, out_dt), lds, ln, n_iter, w)))
+    }
 }
 
-template <int KD, int OP, int DKS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F32 ? 2 : 3))) void k_gdn_tri_inv_ns128(const void* __restrict__ K, const float* __restrict__ beta,
+template <int KD, int OP, int DKS, int WAVES = 4>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVES == 8 || OP == OP_F32 ? 2 : 3))) void k_gdn_tri_inv_ns128(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T,
                                                            uint32_t n_chunk, InvMap map, int H, int d_k, uint8_t n_iter, uint8_t out_dt)
 {
     arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 128;
-    typedef SharedKeys128<KD, DKS> Keys;
-    constexpr int GATE_BYTES = 4 * 2 * C * 4;  // beta and g of the chunk, staged by every wave for itself
-    constexpr int LDS_BYTES = ns128_lds_bytes<OP>() > Keys::BYTES + GATE_BYTES ? ns128_lds_bytes<OP>() : Keys::BYTES + GATE_BYTES;
+    typedef SharedKeys128<KD, DKS, 8 / WAVES> Keys;
+    constexpr int GATE_BYTES = WAVES * 2 * C * 4;  // beta and g of the chunk, staged by every wave for itself
+    constexpr int LDS_BYTES = ns128_lds_bytes<OP, WAVES>() > Keys::BYTES + GATE_BYTES ? ns128_lds_bytes<OP, WAVES>() : Keys::BYTES + GATE_BYTES;
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
     const int64_t m = head_group_swizzle(blockIdx.x, n_chunk, H);
     const uint32_t bc = (uint32_t)m / (uint32_t)H;
@@ -2406,9 +2445,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F3
     keys.publish(lds, w, ln);
     __syncthreads();
     Opnd<OP> At[9];
-    TRIINV_PER_WAVE(w, (ns128_tiles_of<OP, W>(SharedA128<KD, DKS, W>{keys, gate, lds, ln}, At)))
-    __syncthreads();  // the keys in LDS are dead: X and Y take their place
-    TRIINV_PER_WAVE(w, (ns128_run<OP, W>(At, out_matrix(T, m, C, out_dt), lds, ln, n_iter, w)))
+    if constexpr (WAVES == 8) {
+        TRIINV_PER_HALF_WAVE(w, (ns128_tiles_of<OP, W>(SharedA128<KD, DKS, W, 1>{keys, gate, lds, ln}, At), __syncthreads(),
+                                 ns128_run<OP, W, PART>(At, out_matrix(T, m, C, out_dt), lds, ln, n_iter, w)))
+    } else {
+        TRIINV_PER_WAVE(w, (ns128_tiles_of<OP, W>(SharedA128<KD, DKS, W>{keys, gate, lds, ln}, At)))
+        __syncthreads();  // the keys in LDS are dead: X and Y take their place
+        TRIINV_PER_WAVE(w, (ns128_run<OP, W>(At, out_matrix(T, m, C, out_dt), lds, ln, n_iter, w)))
+    }
 }
 
 template <int IN, int OP>
