@@ -336,6 +336,9 @@ static int kda_method(const GdnArgs& a)
 #else
     // C = 128: one matrix per workgroup of four wavefronts that build A together (kda128.hpp)
     case M_NEWTON_SCHULZ:
+        if (newton_by_eight(a.n_mat))
+            return launch_kernel(a.dry, k_kda_tri_inv_ns128<OP, 8>, dim3((unsigned)a.n_mat), dim3(512), 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk, a.map, a.H,
+                                 a.d_k, a.k_dt, a.iters, a.out_dt);
         return launch_kernel(a.dry, k_kda_tri_inv_ns128<OP>, dim3((unsigned)a.n_mat), dim3(256), 0, a.stream, a.K, a.beta, a.g, a.T, a.n_chunk,
                              a.map, a.H, a.d_k, a.k_dt, a.iters, a.out_dt);
     case M_NEUMANN:

@@ -177,23 +177,27 @@ template <int OP> constexpr int kda128_lds_bytes(int rest)
     return rest > 2 * KdaStep128<OP>::BYTES ? rest : 2 * KdaStep128<OP>::BYTES;
 }
 
-// Newton-Schulz, per-channel gate, C = 128, any d_k (multiple of 32).
-template <int OP>
-__global__ __launch_bounds__(256) void k_kda_tri_inv_ns128(const void* __restrict__ K, const float* __restrict__ beta,
+// Newton-Schulz, per-channel gate, C = 128, any d_k (multiple of 32).  WAVES: 4 or 8 (both of a pair of tile rows form its tiles).
+template <int OP, int WAVES = 4>
+__global__ __launch_bounds__(64 * WAVES) void k_kda_tri_inv_ns128(const void* __restrict__ K, const float* __restrict__ beta,
                                                            const float* __restrict__ g, float* __restrict__ T, uint32_t n_chunk,
                                                            InvMap map, int H, int d_k, uint8_t k_dt, uint8_t n_iter, uint8_t out_dt)
 {
     arguments_together(n_chunk, K, beta, g, T, map);
-    __shared__ __attribute__((aligned(16))) char lds[kda128_lds_bytes<OP>(ns128_lds_bytes<OP>())];
+    __shared__ __attribute__((aligned(16))) char lds[kda128_lds_bytes<OP>(ns128_lds_bytes<OP, WAVES>())];
     const KdaHead128 hd = kda_head128(K, beta, g, n_chunk, map, H, d_k, k_dt);
     const Lane ln = lane_id();
     v4f an[9], at[9];
     Opnd<OP> At[9];
-    TRIINV_PER_WAVE(hd.w, (kda128_rows_any<OP, W, false, true>(lds, an, at, hd, k_dt, H, d_k, ln)))
+    TRIINV_PER_WAVE(WAVES == 8 ? n128_pair(hd.w) : hd.w, (kda128_rows_any<OP, W, false, true>(lds, an, at, hd, k_dt, H, d_k, ln)))
 #pragma unroll
     for (int s = 0; s < 9; ++s) At[s] = pack<OP>(at[s]);
     __syncthreads();  // the gated keys in LDS are dead: X and Y take their place
-    TRIINV_PER_WAVE(hd.w, (ns128_run<OP, W>(At, out_matrix(T, hd.m, 128, out_dt), lds, ln, n_iter, hd.w)))
+    if constexpr (WAVES == 8) {
+        TRIINV_PER_HALF_WAVE(hd.w, (ns128_run<OP, W, PART>(At, out_matrix(T, hd.m, 128, out_dt), lds, ln, n_iter, hd.w)))
+    } else {
+        TRIINV_PER_WAVE(hd.w, (ns128_run<OP, W>(At, out_matrix(T, hd.m, 128, out_dt), lds, ln, n_iter, hd.w)))
+    }
 }
 
 // Neumann product, per-channel gate, C = 128.

@@ -1894,6 +1894,8 @@ __device__ __forceinline__ void n128_store(Out Tm, const v4f (&Xt)[9], float* pa
     case 6: { constexpr int W = 2, PART = 1; CALL; } break; \
     default: { constexpr int W = 2, PART = 0; CALL; } break; \
     }
+// Its W.
+__device__ __forceinline__ int n128_pair(int w) { return w < 4 ? w >> 1 : 5 - (w >> 1); }
 
 // ---------------------------------------------------------------------------------------------
 // Newton-Schulz at C = 128 (paper Alg. 3, Eq. 8, for I + A): the same four-wavefront workgroup.

@@ -304,17 +304,19 @@ def test_teams_of_large_chunks_give_the_bits_of_a_larger_call(method, op, k_dtyp
 # Newton-Schulz at C = 128, up to 256 matrices: eight wavefronts of one tile row each, above four of two: the same bits, from keys and from given matrices.
 @pytest.mark.parametrize("k_dtype, d_k", [(torch.bfloat16, 64), (torch.float16, 128), (torch.float32, 64)], ids=str)
 @pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
-def test_newton_schulz_by_eight_wavefronts_gives_the_bits_of_a_larger_call(op, k_dtype, d_k):
+@pytest.mark.parametrize("gate", GATES)
+def test_newton_schulz_by_eight_wavefronts_gives_the_bits_of_a_larger_call(gate, op, k_dtype, d_k):
     C, H, most = 128, 2, 128
     T = (most + 1) * C - 9
-    K, beta, g = make_inputs(T, H, d_k, tri.GATE_SCALAR, k_dtype)
-    run = lambda t, o: tri.gdn_chunk_tri_inv_ex(*(x[:, :t].contiguous() for x in (K, beta, g)), C, method=tri.NEWTON_SCHULZ, op_dtype=op, out_dtype=o)
+    K, beta, g = make_inputs(T, H, d_k, gate, k_dtype)
+    part = lambda x, t: None if x is None else x[:, :t].contiguous()
+    run = lambda t, o: tri.gdn_chunk_tri_inv_ex(part(K, t), part(beta, t), part(g, t), C, gate_kind=gate, method=tri.NEWTON_SCHULZ, op_dtype=op, out_dtype=o)
     for o in (torch.float32, torch.bfloat16):
         many = run(T, o)
         for t in (C, 3 * C, most * C):
             assert torch.equal(run(t, o), many[:t // C * H]), t
-        few = run(17, o)
-        assert torch.equal(few[:, :17, :17], many[:H, :17, :17]) and not few[:, 17:, :17].any()
+        last = [None if x is None else x[:, most * C:].contiguous() for x in (K, beta, g)]  # the short chunk by itself
+        assert torch.equal(tri.gdn_chunk_tri_inv_ex(*last, C, gate_kind=gate, method=tri.NEWTON_SCHULZ, op_dtype=op, out_dtype=o), many[most * H:])
     A = torch.tril(torch.randn(257, C, C, device=DEV) * 0.03, -1).to(k_dtype)
     many = tri.tri_inv_ex(A, method=tri.NEWTON_SCHULZ, op_dtype=op)
     for n in (1, 5, 256):
