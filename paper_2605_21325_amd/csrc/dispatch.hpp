@@ -60,7 +60,7 @@ inline int head_spread(int H) { return H >= 8 ? 0 : (H >= 4 ? 1 : 4 / H); }
 // them) a workgroup holds one: four wavefronts would load their keys and store their results through one compute unit while
 // others have nothing to do.  Kernel time at C = 64, four / one to a workgroup: 256 matrices 6.4 / 5.4 us (bf16), 16.1 / 11.6
 // (per-channel gate), 13.9 / 11.7 (fp32 keys and operands), applied to two right-hand sides 11.2 / 9.3; 512 6.5 / 6.0 and 17.1 / 13.3; 1024
-// 7.6 / 7.5 and 18.2 / 18.8; 1536 9.3 / 12.2.
+// 7.6 / 7.5 and 18.2 / 18.8; 1536 9.3 / 12.2.  (Recursions at C = 64 with few matrices go to the teams below first.)
 constexpr int ONE_WAVE_PER_GROUP = -1;  // in place of the spread
 constexpr int64_t FEW_MATRICES = 512;
 // The channel loops (per-channel gate, head dimensions without a kernel of their own) share a matrix of such a call between four

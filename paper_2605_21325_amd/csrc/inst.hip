@@ -115,7 +115,7 @@ int CAT(launch_tri_inv_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP, SUFFIX)(const Tr
     case M_NEWTON_SCHULZ:
 #if TRIINV_INST_NB <= 4
         return go_tri<M_NEWTON_SCHULZ>(a);
-#else   // A, X and X as a left factor do not fit one wave's registers at C = 128: four waves, X and Y in LDS
+#else   // A, X and X as a left factor do not fit one wave's registers at C = 128: four waves (few matrices: eight), X and Y in LDS
         if (newton_by_eight(a.n_mat)) {
             TRIINV_FOR_INPUT(a.in_dt, return launch_kernel(a.dry, (k_tri_inv_ns128<IN, OP, 8>), dim3((unsigned)a.n_mat), dim3(512), 0, a.stream, a.A, a.T,
                                                            a.n_mat, a.iters, a.out_dt))

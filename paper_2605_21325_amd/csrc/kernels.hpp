@@ -6,7 +6,8 @@
 //   k_gdn_any_dk_tri_inv  head dimensions without a specialised build (channel loop)
 //   k_tri_inv_fwd_shuffle64  row-by-row forward substitution with wavefront shuffles (baseline variant)
 // and, at C = 128, four wavefronts per matrix with tiles in LDS for the methods whose state does not fit
-// one wavefront: k_*_neumann128 (Neumann product), k_*_ns128 (Newton-Schulz).
+// one wavefront: k_*_neumann128 (Neumann product), k_*_ns128 (Newton-Schulz; eight with few matrices).
+// With few matrices the recursions have kernels that spread one over four or eight wavefronts: team64.hpp, team128.hpp.
 // Methods: forward substitution (fp32, 16 rows at a time), blocked recursion, mixed
 // recursion, blocked recursion from directly solved blocks, Neumann product, Newton-Schulz, refinement
 // (inv_core.hpp).  csrc/chunk_map.hpp says where a chunk's tokens are.
@@ -759,7 +760,8 @@ __device__ __forceinline__ void accumulate_gated_gram(PreA<NB>& out, const void*
 // instructions, beside which nothing else runs), each wavefront some of the tiles, over all channels.  Between the two the operands go
 // through LDS.  Every tile's products are added in one chain in the order of the channels, with the same operands as in the
 // loops of one wavefront: a matrix's bits do not depend on how many others its call has.
-// Bound by the one wavefront's recursion that follows, and by these products where they are fp32.  256 matrices of C = 64, d_k = 128, one
+// Bound by what follows on one wavefront, but for the recursions at C = 64, which the four carry on together (team64.hpp), and by these products where they
+// are fp32.  With a recursion on one wavefront, 256 matrices of C = 64, d_k = 128, one
 // wavefront / four: per-channel gate 10.8 / 8.2 us, with fp32 operands 19.2 / 12.7, applied to two right-hand sides 14.6 / 12.0, forward
 // substitution 17.9 / 12.1; d_k = 256 without a gate, fp32 keys and operands 22.4 / 11.8, bf16 8.1 / 6.8.  512 matrices: 12.1 / 10.2, 20.3 / 16.4,
 // 17.5 / 15.4, 19.4 / 15.2, 24.6 / 15.7, 9.2 / 7.7.  (Each wavefront all the products of its own channels and the first adding the sums, another
@@ -1898,14 +1900,14 @@ __device__ __forceinline__ void n128_store(Out Tm, const v4f (&Xt)[9], float* pa
 __device__ __forceinline__ int n128_pair(int w) { return w < 4 ? w >> 1 : 5 - (w >> 1); }
 
 // ---------------------------------------------------------------------------------------------
-// Newton-Schulz at C = 128 (paper Alg. 3, Eq. 8, for I + A): the same four-wavefront workgroup.
+// Newton-Schulz at C = 128 (paper Alg. 3, Eq. 8, for I + A): the same four-wavefront workgroup (few matrices: eight, see TRIINV_PER_HALF_WAVE).
 //   X <- I / C;  n_iter times:  Y <- X + A X;  X <- 2 X - X Y.
 // Wave w owns tile rows w and 7 - w: it keeps its rows of A (T orientation, packed operands) and of X (N
 // orientation, fp32) in registers and reads the right factor of every product (a tile of X, then of Y, in N
 // orientation) from LDS.  A right factor in N orientation is exactly the register image its producer holds,
 // so a tile crosses between waves as a mailbox: 64 consecutive slots of one packed operand each, lane l of the
 // reader taking what lane l of the writer left.  No transposition, no bank conflicts, and the rounding to the
-// operand type happens once, at the writer.  X and Y take 2 x 36 tiles: 36 KB for 16-bit operands, 72 KB for fp32.
+// operand type happens once, at the writer.  X and Y take 2 x 36 tiles, 36 KB, with 16-bit operands; fp32 ones, split in three, take turns on 54 KB.
 // ---------------------------------------------------------------------------------------------
 template <int OP> struct MailTiles {
     static constexpr int TILE_BYTES = 64 * (int)sizeof(Opnd<OP>);
