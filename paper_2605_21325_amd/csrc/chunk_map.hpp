@@ -73,6 +73,8 @@ template <int WORDS> struct KernelMap {
         const int bits = 64 - __builtin_clzll((unsigned long long)any);
         return bits * n <= 32 * WORDS ? bits : 0;
     }
+    // Whether a kernel with this argument can be told where the tokens of m are (launch_kernel asks every one).
+    static bool takes(const ChunkMap& m) { return !m.lens || bits_of(m.lens, (int)m.n_seq) > 0; }
     TRIINV_HOST_DEVICE bool packed() const { return cps & PACKED; }
     TRIINV_HOST_DEVICE uint32_t length(uint32_t s) const
     {
@@ -87,6 +89,7 @@ struct OffsetMap {
     int64_t Tlen;
     uint32_t cps, n_seq;
     const int64_t *cu_seqlens, *cu_chunks;
+    static bool takes(const ChunkMap& m) { return !m.lens; }
     OffsetMap() = default;
     explicit OffsetMap(const ChunkMap& m) : Tlen(m.Tlen), cps(m.cps), n_seq(m.n_seq), cu_seqlens(m.cu_seqlens), cu_chunks(m.cu_chunks) {}
 };

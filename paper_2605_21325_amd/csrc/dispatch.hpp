@@ -4,7 +4,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <tuple>
+#include <type_traits>
 #include <utility>
+#include "../../include/triinv.h"
 #include "chunk_map.hpp"
 
 namespace triinv {
@@ -117,14 +119,23 @@ inline FusedGrid fused_grid(int64_t n_mat, int H, int waves)
 
 // Lengths of packed sequences go with the arguments of the storing kernels but for the Neumann product, b0 = 32 and the refinement step, some of which lose
 // a wavefront per SIMD by the registers of the search (refined Neumann product, C = 64, d_k = 64, 4096 matrices: 20.9 -> 23.3 us).
-constexpr bool lengths_in_arguments(int method, bool refine) { return !refine && method != 2 /* Neumann */ && method != 6 /* b0 = 32 */; }
+constexpr bool lengths_in_arguments(int method, bool refine) { return !refine && method != TRIINV_NEUMANN && method != TRIINV_MIXED_B32; }
 
 // Launcher return codes.
 enum : int { LAUNCHED = 0, NOT_BUILT = 1, LAUNCH_FAILED = 2 };
 
+// Whether a kernel's parameter holds all of this argument.
+template <class Param, class Arg> inline bool holds(const Arg& a)
+{
+    if constexpr (std::is_same_v<Arg, ChunkMap>)
+        return Param::takes(a);
+    else
+        return (void)a, true;
+}
+
 // One kernel launch whose own status is returned (the runtime's sticky per-thread error state, which may hold an
 // unrelated earlier error of the caller, is neither read nor cleared).  The arguments are converted to the kernel's
-// exact parameter types first.  dry: report LAUNCHED without launching.
+// exact parameter types first.  dry: report LAUNCHED without launching.  Lengths of packed sequences for a kernel that cannot be given them: NOT_BUILT.
 template <class... KArgs, class... Args, size_t... I>
 inline int launch_kernel_impl(void (*kernel)(KArgs...), dim3 grid, dim3 block, unsigned lds_bytes, hipStream_t stream,
                               std::index_sequence<I...>, Args&&... args)
@@ -137,6 +148,7 @@ template <class... KArgs, class... Args>
 inline int launch_kernel(bool dry, void (*kernel)(KArgs...), dim3 grid, dim3 block, unsigned lds_bytes, hipStream_t stream, Args&&... args)
 {
     static_assert(sizeof...(KArgs) == sizeof...(Args), "one argument per kernel parameter");
+    if (!(holds<KArgs>(args) && ...)) return NOT_BUILT;
     if (dry) return LAUNCHED;
     return launch_kernel_impl(kernel, grid, block, lds_bytes, stream, std::index_sequence_for<KArgs...>{}, std::forward<Args>(args)...);
 }

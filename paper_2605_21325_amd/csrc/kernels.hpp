@@ -20,6 +20,9 @@ namespace triinv {
 
 enum : int { M_FWD = 0, M_BLOCK = 1, M_NEUMANN = 2, M_MIXED = 3, M_BLOCK_DIRECT = 4, M_NEWTON_SCHULZ = 5, M_MIXED32 = 6,
              M_BUILD_A = 100 /* no inversion: the chunk matrix A itself is written (not a triinv_method) */ };
+static_assert(M_FWD == TRIINV_FWD_SUBST && M_BLOCK == TRIINV_BLOCK_RECURSIVE && M_NEUMANN == TRIINV_NEUMANN && M_MIXED == TRIINV_MIXED &&
+                  M_BLOCK_DIRECT == TRIINV_BLOCK_DIRECT && M_NEWTON_SCHULZ == TRIINV_NEWTON_SCHULZ && M_MIXED32 == TRIINV_MIXED_B32,
+              "the numbers of triinv_method");
 enum : int { G_SCALAR = 0, G_CHANNEL = 1, G_NONE = 2 };
 
 __device__ __forceinline__ void wave_lds_sync()

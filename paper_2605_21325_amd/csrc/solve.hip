@@ -90,7 +90,6 @@ template <int KD, int METHOD, int DKS> static int go_gdn(const SolveArgs& a)
 #endif
     const FusedGrid shape = fused_grid(f.n_mat, f.H, WPB);
     const dim3 grid(shape.groups), block(shape.threads);
-    if (f.map.lens && !solve_packed<OP, NB>()) return 1;
     if (a.n_rhs == 1) {
         return launch_kernel(f.dry, k_gdn_tri_solve<KD, OP, NB, METHOD, DKS, WPB, XPOS, 1>, grid, block, 0, f.stream, f.K, f.beta, f.g,
                            rhs_of(a), f.n_chunk, f.map, f.H, f.d_k, f.iters, shape.spread);
@@ -201,7 +200,6 @@ int CAT(launch_solve_nb, TRIINV_INST_NB, _op, TRIINV_INST_OP)(const SolveArgs& a
     const GdnArgs& f = a.f;
     if (f.refine) return 1;
     if (a.n_rhs < 1 || a.n_rhs > MAX_RHS) return 1;
-    if (a.n_rhs > 1 && f.map.lens) return 1;
     if (NB <= 4 && !rows_fit_32_bits(a)) return 1;  // (H * d_x beyond 8 million elements)
     if (f.gate == G_CHANNEL) {
         if (f.method == M_BLOCK) return go_kda<M_BLOCK>(a);
