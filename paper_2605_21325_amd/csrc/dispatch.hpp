@@ -101,9 +101,9 @@ inline bool solve_by_team128(int64_t n_mat) { return n_mat <= 256; }
 // 14.5, applied 20.0 / 15.5 (two sides 27.2 / 19.6), fp32 operands 34.8 / 21.8, applied 49.5 / 28.2, fp16 mixed of 64 channels 11.7 / 10.7; 128 of 256 channels
 // 23.4 / 17.6, of 32 8.3 / 7.7.
 inline bool channels_by_team128(int64_t n_mat) { return n_mat <= 256; }
-// Newton-Schulz at C = 128: eight wavefronts in place of four, as long as a compute unit has one matrix.  Four / eight, 16 matrices with fp32 operands 70 /
-// 48 us, 64 with bf16 24.0 / 18.3; 256: fp32 71 / 52, bf16 25.7 / 20.7, standalone 24.1 / 18.7, fp32 69 / 49.  Per-channel gate (the two of a pair of tile
-// rows form the same tiles), 64 bf16 of 256 channels 33.3 / 31.7; kernel of larger calls before X was turned by LDS reads / eight: 16 fp32 80 / 62, 256 bf16
+// Newton-Schulz at C = 128: eight wavefronts in place of four, as long as a compute unit has one matrix.  Four / eight, 16 matrices with fp32 operands 71 /
+// 50 us, 64 with bf16 24.0 / 18.3; 256: fp32 72 / 53, bf16 25.7 / 20.7, standalone 24.1 / 18.7, fp32 70 / 51.  Per-channel gate (the two of a pair of tile
+// rows form the same tiles), 64 bf16 of 256 channels 33.3 / 31.7; kernel of larger calls before X was turned by LDS reads / eight: 16 fp32 80 / 63, 256 bf16
 // 31.1 / 26.4, of 64 channels 28.6 / 22.6.  (One tile row a wave gave nothing, 69 of 70 us: the wave of the last row has as much to do as one of four.)
 inline bool newton_by_eight(int64_t n_mat) { return n_mat <= 256; }
 struct FusedGrid {

@@ -1958,6 +1958,7 @@ template <int W> __host__ __device__ constexpr int n128_slot(int i, int k) { ret
 // The wave's two tile rows as left operands, and one tile column as right operand.  16-bit operands: pairs of tiles for the
 // 32-deep instructions; fp32: tile by tile, each split into three bf16 parts (see Split3).
 template <int OP> struct Ns128Operands {
+    static constexpr float SCALE = 1.f;  // of X and Y
     typedef PairOp<OP> Row[4];
     static __device__ __forceinline__ void put(Row& row, int k, Opnd<OP> x) { row[k / 2].set(k & 1, x); }
     template <bool TR> static __device__ __forceinline__ void get(Row& row, int k, const TurnTiles<OP>& tiles, int tile)
@@ -1989,6 +1990,8 @@ template <int OP> struct Ns128Operands {
     }
 };
 template <> struct Ns128Operands<OP_F32> {
+    // Halved: the leading part of a split tile is up to 2^-8 larger than the tile and infinite from 3.396e38 on, where the iterate is finite.
+    static constexpr float SCALE = 0.5f;
     typedef Split3 Row[8];
     static __device__ __forceinline__ void put(Row& row, int k, Opnd<OP_F32> x) { row[k] = split3_any(x.x); }
     template <bool TR> static __device__ __forceinline__ void get(Row& row, int k, const TurnTiles<OP_F32>& tiles, int tile)
@@ -2048,7 +2051,9 @@ template <int OP> __device__ __forceinline__ v4f turned(Opnd<OP> x, Opnd<OP_BF16
 // right factor is read from LDS once for both of the wave's rows; 16-bit operands contract two tiles per instruction, fp32 ones are split
 // into three bf16 parts; the first iteration from I / C is a scaling.
 // Bound by latency: LDS reads a column at a time and two (fp32: four) barriers an iteration.  1024 fused matrices with fp32 operands, by fp32
-// instructions / split 245.6 / 183.8 us, standalone 240.9 / 180.2, 16 of them 73 / 70 (by eight wavefronts 48), error against 64 bits 1.34e-7 / 1.32e-7 (standalone 8.6e-8 / 5.8e-8);
+// instructions / split 245.1 / 182.3 us, standalone 239.4 / 179.1, 16 of them 73 / 71 (by eight wavefronts 50; a fiftieth of each for the halving), error
+// against 64 bits at most that of fp32 instructions for every gate, head dimension and key type: 1.33e-7 / 1.31e-7 (standalone 8.6e-8 / 5.8e-8, correlated
+// keys 3.75e-7 / 3.70e-7, per-channel gate 2.34e-7 / 2.33e-7).  Iterates below 2^-109 lose low bits that fp32 instructions keep.
 // X turned by products with the identity / by LDS reads: 4096 bf16 188 / 173, 2048 standalone 96 / 86.
 // PART: 0, 1: of eight wavefronts, this one's columns are the even / odd ones (TRIINV_PER_HALF_WAVE); -1: all.
 template <int OP, int W, int PART = -1>
@@ -2073,7 +2078,7 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
             if (!mine(j)) continue;
             v4f a = turned<OP>(At[s], id_bf16, id);
             if (i == j) a += unit;
-            Xn[s] = (i == j ? 2.f * X0 : 0.f) * unit - X0 * X0 * a;
+            Xn[s] = Ops::SCALE * ((i == j ? 2.f * X0 : 0.f) * unit - X0 * X0 * a);
             Ops::publish(X, tix(i, j), Xn[s]);
         }
     }
@@ -2120,7 +2125,13 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
             for (int h = 0; h < 2; ++h) {
                 if (j > ROW[h]) continue;
                 const int s = n128_slot<W>(ROW[h], j);
-                Xn[s] = 2.f * Xn[s] - xy[h];
+                if constexpr (Ops::SCALE == 1.f) {
+                    Xn[s] = 2.f * Xn[s] - xy[h];
+                } else {  // 2 X and X Y may overflow where their difference does not; the same rounding
+                    static_assert(Ops::SCALE == 0.5f, "X and Y in halves");
+                    const v4f d = Xn[s] - xy[h];
+                    Xn[s] = d + d;
+                }
                 if (!ONE_SET) Ops::publish(X, tix(ROW[h], j), Xn[s]);
             }
             if (ONE_SET) __builtin_amdgcn_sched_barrier(0);
@@ -2133,6 +2144,9 @@ __device__ __forceinline__ void ns128_run(const Opnd<OP> (&At)[9], Out Tm, char*
             __syncthreads();  // X complete
         }
     }
+#pragma unroll
+    for (int s = 0; s < 9; ++s)
+        if (mine(n128_col<W>(s))) Xn[s] *= 1.f / Ops::SCALE;
     // X and Y in LDS are dead: their memory becomes the four store patches, or the strips of the whole result
     if constexpr (PART < 0) {
         n128_store<W, false>(Tm, Xn, reinterpret_cast<float*>(lds) + w * STORE_LDS_FLOATS, ln);

@@ -3,6 +3,8 @@ inputs, through the C-ABI.  Tolerances (relative Frobenius error per matrix, max
 batch): 1e-5 for the fp32 path (forward substitution, fp32 matrix-core operands), 2e-2 for
 fp16 / bf16 operands.  The Neumann product is held to them on the benign workloads only; on the
 stress workload the paper predicts it breaks, and its error is reported, not asserted."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -925,6 +927,24 @@ def test_newton_schulz_takes_entries_beyond_the_largest_bf16(C):
             assert abs(T[m, i, j] / want - 1) < 1e-6, (C, iters, i, j, T[m, i, j], want)
             T[m, i, j] = 0
         assert np.array_equal(T, np.broadcast_to(np.eye(C), T.shape))
+
+
+@pytest.mark.parametrize("n_mat", [1, 257])  # by eight wavefronts, by four
+def test_newton_schulz_takes_iterates_beyond_the_largest_bf16(n_mat):
+    """C = 128, fp32 operands: Y of the second iteration has one entry between the largest bf16 and the largest fp32 number,
+    (A X1)_ij = -A_ik A_kj / C^2, and the iterate made of it is finite (about 4 / C of it)."""
+    from oracle import methods
+    C, pos = 128, [(2, 1, 0), (20, 17, 16), (100, 40, 39), (127, 126, 125), (127, 64, 3)]
+    A = torch.zeros(max(n_mat, len(pos)), C, C)
+    for m, (i, k, j) in enumerate(pos):
+        A[m, i, k] = A[m, k, j] = math.sqrt(3.396e38) * C
+    for first in range(0, len(pos), n_mat):
+        part = A[first:first + n_mat]
+        T = tri.tri_inv_ex(part.to(DEV), method=tri.NEWTON_SCHULZ, op_dtype=tri.F32, flags=tri.flag_iters(2)).cpu().double().numpy()
+        assert np.isfinite(T).all()
+        for m, (i, k, j) in enumerate(pos[first:first + n_mat]):
+            want = methods.newton_schulz_closed_form(part[m].double().numpy(), 2)[i, j]
+            assert abs(T[m, i, j] / want - 1) < 1e-6, (i, k, j, T[m, i, j], want)
 
 
 # ------------------------------------------------------------------ packed sequences: the offsets' way to the device
