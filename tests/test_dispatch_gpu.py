@@ -282,6 +282,43 @@ def test_packed_lengths_as_arguments_and_in_memory(monkeypatch, C, gate, d_k, op
         assert torch.equal(a, b)
 
 
+# The same over the methods whose storing kernels take lengths, on both sides of the lines between few and many matrices.
+@pytest.mark.parametrize("C, d_k", [(16, 64), (32, 96), (64, 64), (64, 96), (64, 128), (128, 64), (128, 96), (128, 128)])  # (96: channel loops; at C = 128 "mixed" and Newton-Schulz build A first)
+@pytest.mark.parametrize("gate", [tri.GATE_SCALAR, tri.GATE_PER_CHANNEL])
+@pytest.mark.parametrize("method, op", [(tri.FWD_SUBST, tri.F32), (tri.MIXED, tri.F32), (tri.MIXED, tri.F16), (tri.BLOCK_DIRECT, tri.BF16),
+                                        (tri.NEWTON_SCHULZ, tri.F32), (tri.NEWTON_SCHULZ, tri.BF16)])
+def test_packed_lengths_for_every_method(monkeypatch, method, op, gate, C, d_k):
+    H = 5
+    lines = {16: [512], 32: [512], 64: [256, 512, 768], 128: [256]}[C]
+    for chunks in [3] + [m // H for m in lines] + [m // H + 1 for m in lines]:
+        lens = [C + 1, 1, 0, C]                                  # four chunks, the second of one token
+        lens += [(chunks - 4) * C - C // 2] if chunks > 4 else []
+        K, beta, g = (x[0] for x in make_inputs(sum(lens), H, d_k, gate))
+        call = lambda: tri.gdn_chunk_tri_inv_varlen(K, beta, g, lens, C, gate_kind=gate, method=method, op_dtype=op)
+        with monkeypatch.context() as python_route:
+            python_route.setattr(tri.binding, "_fast_lib", None)
+            python = call()
+        native = call()
+        assert native._triinv_keepalive == () and native.shape[0] == max(chunks, 4) * H
+        assert len(python._triinv_keepalive) == 1 and torch.equal(native, python), chunks
+
+
+# Rows of 2^31 bytes and more per chunk: at C = 128 with 16-bit operands a kernel that is not given lengths.
+@pytest.mark.parametrize("d_x, native", [(504, True), (512, False)])
+def test_packed_lengths_beside_wide_rows(monkeypatch, d_x, native):
+    H, lens = 1 << 14, [2, 1]
+    K, beta, g = (x[0] for x in make_inputs(3, H, 128, tri.GATE_SCALAR))
+    X = torch.randn(3, H, d_x, device=DEV, dtype=torch.bfloat16)
+    call = lambda: tri.gdn_chunk_tri_solve_varlen(K, beta, g, X, lens, 128, row_scale=beta)
+    W = call()
+    assert (W._triinv_keepalive == ()) == native
+    want = (beta[..., None] * X.float())
+    want[1] -= (beta[1] * (K[1].float() * K[0].float()).sum(-1) * torch.exp(g[1] - g[0]))[:, None] * want[0]
+    assert (W.float() - want).norm() <= 1e-2 * want.norm()
+    monkeypatch.setattr(tri.binding, "_fast_lib", None)
+    assert torch.equal(call(), W)
+
+
 # C = 128, head dimensions without a kernel of their own: up to 256 matrices four wavefronts form one (and its diagonal tiles once), above one wavefront:
 # the same bits.  fp32 keys of 128 channels with fp32 operands go this way too; "mixed" builds A first.
 @pytest.mark.parametrize("k_dtype, d_k", [(torch.float32, 128), (torch.float32, 256), (torch.bfloat16, 96), (torch.float16, 160)])
