@@ -80,9 +80,9 @@ int pick_tri_inv(const TriInvArgs& a, int C, int op_dtype)
 // Shared tail of the fused entry points: everything but the token layout has been validated.
 // A matrix-product method that has no fused kernel for this gate kind / head dimension / chunk size runs as two
 // launches instead: the chunk matrices are written into T as fp32 (the build kernel every combination has), then the
-// standalone kernel of the method inverts them in place.  In place is safe for those kernels: a wavefront stores rows of
-// T only after it has fetched every tile of A in those rows (each stored row depends on all of them), and in the
-// four-wavefront C = 128 kernels a wavefront fetches, before the first barrier, exactly the tile rows it later stores.
+// standalone kernel of the method inverts them in place.  In place is safe for those kernels: where one wavefront has a matrix, it
+// stores rows of T only after it has fetched every tile of A in those rows (each stored row depends on all of them); where several
+// share one (C = 128), all of them have fetched all their tiles of A before a barrier that precedes every store.
 // The values of A are the fp32 tiles a fused kernel would hold in registers, so the result is the same.  Forward
 // substitution (always fused), the refinement flag (needs A and T side by side) and a 16-bit result (T must hold an
 // fp32 A) are not composed.

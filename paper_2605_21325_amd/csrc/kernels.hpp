@@ -1907,11 +1907,12 @@ __device__ __forceinline__ int n128_pair(int w) { return w < 4 ? w >> 1 : 5 - (w
 //   X <- I / C;  n_iter times:  Y <- X + A X;  X <- 2 X - X Y.
 // Wave w owns tile rows w and 7 - w: it keeps its rows of A (T orientation, packed operands) and of X (N
 // orientation, fp32) in registers and reads the right factor of every product (a tile of X, then of Y, in N
-// orientation) from LDS.  A right factor in N orientation is exactly the register image its producer holds,
-// so a tile crosses between waves as a mailbox: 64 consecutive slots of one packed operand each, lane l of the
-// reader taking what lane l of the writer left.  No transposition, no bank conflicts, and the rounding to the
+// orientation) from LDS, and X's left form, turned, from its own tiles there (TurnTiles).  The rounding to the
 // operand type happens once, at the writer.  X and Y take 2 x 36 tiles, 36 KB, with 16-bit operands; fp32 ones, split in three, take turns on 54 KB.
 // ---------------------------------------------------------------------------------------------
+// The tiles of the Neumann product below.  A right factor in N orientation is exactly the register image its producer holds,
+// so a tile crosses between waves as a mailbox: 64 consecutive slots of one packed operand each, lane l of the
+// reader taking what lane l of the writer left.  No transposition, no bank conflicts.
 template <int OP> struct MailTiles {
     static constexpr int TILE_BYTES = 64 * (int)sizeof(Opnd<OP>);
     static constexpr int BYTES = N128_NT * TILE_BYTES;
@@ -2236,7 +2237,7 @@ template <int OP, int W, class ASrc> __device__ __forceinline__ void ns128_tiles
 
 // ---------------------------------------------------------------------------------------------
 // Neumann product at C = 128, (I + A)^-1 = (I - A) (I + A^2) (I + A^4) ... (I + A^64): the four-wavefront workgroup
-// and the mailbox tiles of the Newton-Schulz kernel above.  Wave w owns tile rows w and 7 - w.  It keeps X^T (fp32)
+// and mailbox tiles (MailTiles).  Wave w owns tile rows w and 7 - w.  It keeps X^T (fp32)
 // and its rows of the running power Y = A^(2^k) in T orientation (packed) in registers; every product takes its
 // other factor, a tile of Y in N orientation, from the mailbox.  Squaring forms both orientations of the new tile
 // (two matrix-core instructions per product instead of one transposing read through LDS); the N image goes to the
@@ -2430,7 +2431,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(WAVE
     const GlobalA<N128_NB, IN> src{static_cast<const char*>(A) + m * 128 * 128 * (IN == OP_F32 ? 4 : 2), ln};
     (void)n_mat;
     Opnd<OP> At[9];
-    // in place: every wave has read its rows of A before any wave stores (the iteration's barriers lie between)
+    // in place: every wave has read its tiles of A before any wave stores (a barrier lies between)
     if constexpr (WAVES == 8) {
         TRIINV_PER_HALF_WAVE(w, (ns128_tiles_of<OP, W>(src, At), ns128_run<OP, W, PART>(At, out_matrix(T, m, 128, out_dt), lds, ln, n_iter, w)))
     } else {
@@ -2490,7 +2491,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OP == OP_F3
     char* const nxt = lds + MailTiles<OP>::BYTES;
     float* const patch = reinterpret_cast<float*>(lds) + w * STORE_LDS_FLOATS;
     TRIINV_PER_WAVE(w, (neumann128_prepare<OP, W>(src, Xt, yt, lds, ln)))
-    // in place: every wave has read its rows of A before any wave stores (the iteration's barriers lie between)
+    // in place: every wave has read its tiles of A before any wave stores (a barrier lies between)
     TRIINV_PER_WAVE(w, (neumann128_run<OP, W>(Xt, yt, out_matrix(T, m, 128, out_dt), lds, nxt, patch, ln)))
 }
 

@@ -9,8 +9,9 @@
 //   store    wave w the strip of tile row w.
 // Where a wavefront's part depends on w, that is a matter of LDS addresses: all eight run the same code.  Every sum is the one that the kernels of larger
 // calls form (c128_invert with 16-bit operands, block_recursive with fp32 ones), in the same order: a matrix's bits do not depend on how many others its
-// call has.  Bound by latency: the loads, a leaf's chain, seven barriers.
-// With the per-channel gate (team128_kda_tiles) wave w gates tile row w, 32 channels at a time, and the same tiles are formed from what the eight leave in LDS.
+// call has.  Bound by latency: the loads, a leaf's chain, six barriers.
+// With the per-channel gate (team128_kda_tiles) wave w gates tile row w, 32 channels at a time, and the same tiles are formed from what the eight leave in LDS
+// (a barrier for each 32 channels, and six more).
 #pragma once
 #include "team64.hpp"
 

@@ -338,7 +338,8 @@ def test_teams_of_large_chunks_give_the_bits_of_a_larger_call(method, op, k_dtyp
             assert torch.equal(few[whole:, :v, :v], many[whole:whole + H, :v, :v]), tokens
 
 
-# Newton-Schulz at C = 128, up to 256 matrices: eight wavefronts of one tile row each, above four of two: the same bits, from keys and from given matrices.
+# Newton-Schulz at C = 128: up to 256 matrices eight wavefronts, of which two share a pair of tile rows by even and odd tile columns, above four with a
+# pair each: the same bits, from keys and from given matrices.
 @pytest.mark.parametrize("k_dtype, d_k", [(torch.bfloat16, 64), (torch.float16, 128), (torch.float32, 64)], ids=str)
 @pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
 @pytest.mark.parametrize("gate", GATES)
@@ -358,6 +359,19 @@ def test_newton_schulz_by_eight_wavefronts_gives_the_bits_of_a_larger_call(gate,
     many = tri.tri_inv_ex(A, method=tri.NEWTON_SCHULZ, op_dtype=op)
     for n in (1, 5, 256):
         assert torch.equal(tri.tri_inv_ex(A[:n].contiguous(), method=tri.NEWTON_SCHULZ, op_dtype=op), many[:n]), n
+
+
+# Methods without a kernel of their own for a head dimension at C = 128: A is written into T and inverted there, also where wavefronts store tile rows that
+# others have fetched.  The bits of the same A inverted elsewhere.
+@pytest.mark.parametrize("H", [1, 64, 257])
+@pytest.mark.parametrize("op", [tri.F32, tri.F16, tri.BF16], ids=lambda o: tri.DTYPE_NAMES[o])
+@pytest.mark.parametrize("method, flags", [(tri.NEWTON_SCHULZ, 0), (tri.NEWTON_SCHULZ, tri.flag_iters(1)), (tri.NEUMANN, 0), (tri.MIXED, 0)])
+@pytest.mark.parametrize("tokens", [1, 4 * 128])
+def test_matrices_inverted_in_place(tokens, method, flags, op, H):
+    K, beta, g = make_inputs(tokens, H, 96, tri.GATE_SCALAR, torch.float32)
+    T = tri.gdn_chunk_tri_inv_ex(K, beta, g, 128, method=method, op_dtype=op, flags=flags)
+    A = tri.gdn_chunk_build_A(K, beta, g, 128, op_dtype=op)
+    assert torch.equal(T, tri.tri_inv_ex(A, method=method, op_dtype=op, flags=flags))
 
 
 # C = 64, up to 768 matrices (direct leaves 256, applied 512): four wavefronts carry one matrix through the recursion and the store too; C = 128, up to 256:
