@@ -1248,15 +1248,17 @@ template <int NB, bool ZEROED, int LD = store_ld<NB>()> __device__ __forceinline
     wave_lds_sync();
 }
 
-// Tile (i, j) of strip i into the patch, in T orientation or not; a diagonal tile gets `diag` on its diagonal and zeros above.
-template <int LD> __device__ __forceinline__ void strip_tile(float* lds, int i, int j, v4f v, bool is_t, Lane ln, float diag = 1.f)
+// Tile (i, j) of strip i into the patch, in T orientation or not; a diagonal tile gets ones on its diagonal and zeros above.  For the kernels that
+// spread a matrix over wavefronts.  store_strip does the same in its own words: by way of this function the standalone Neumann product with
+// 16-bit operands takes 131 registers in place of 128 and loses a wavefront per SIMD (C = 64, 8192 fp32 matrices 33.3 -> 35.2 us).
+template <int LD> __device__ __forceinline__ void strip_tile(float* lds, int i, int j, v4f v, bool is_t, Lane ln)
 {
     if (is_t) {  // v[r] = T[16i + n][16j + 4q + r]
         if (i == j) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int rr = ln.n, cc = 4 * ln.q + r;
-                v[r] = (rr == cc) ? diag : ((rr > cc) ? v[r] : 0.f);
+                v[r] = (rr == cc) ? 1.f : ((rr > cc) ? v[r] : 0.f);
             }
         }
         *reinterpret_cast<v4f*>(&lds[ln.n * LD + 16 * j + 4 * ln.q]) = v;
@@ -1265,7 +1267,7 @@ template <int LD> __device__ __forceinline__ void strip_tile(float* lds, int i, 
         for (int r = 0; r < 4; ++r) {
             const int rr = 4 * ln.q + r, cc = ln.n;
             float x = v[r];
-            if (i == j) x = (rr == cc) ? diag : ((rr > cc) ? x : 0.f);
+            if (i == j) x = (rr == cc) ? 1.f : ((rr > cc) ? x : 0.f);
             lds[rr * LD + 16 * j + cc] = x;
         }
     }
@@ -1277,10 +1279,29 @@ template <int NB, bool ZEROED = false, class RowIsT>
 __device__ __forceinline__ void store_strip(Out Tm, int i, const v4f (&row)[NB], RowIsT row_is_t, float* lds, Lane ln,
                                             float diag = 1.f)
 {
+    constexpr int LD = store_ld<NB>();
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
         if (j > i) break;
-        strip_tile<store_ld<NB>()>(lds, i, j, row[j], row_is_t(j), ln, diag);
+        v4f v = row[j];
+        if (row_is_t(j)) {  // v[r] = T[16i + n][16j + 4q + r]
+            if (i == j) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int rr = ln.n, cc = 4 * ln.q + r;
+                    v[r] = (rr == cc) ? diag : ((rr > cc) ? v[r] : 0.f);
+                }
+            }
+            *reinterpret_cast<v4f*>(&lds[ln.n * LD + 16 * j + 4 * ln.q]) = v;
+        } else {            // v[r] = T[16i + 4q + r][16j + n]
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int rr = 4 * ln.q + r, cc = ln.n;
+                float x = v[r];
+                if (i == j) x = (rr == cc) ? diag : ((rr > cc) ? x : 0.f);
+                lds[rr * LD + 16 * j + cc] = x;
+            }
+        }
     }
     flush_strip<NB, ZEROED>(Tm, i, lds, ln);
 }
