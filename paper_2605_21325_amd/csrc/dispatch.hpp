@@ -120,6 +120,10 @@ inline FusedGrid fused_grid(int64_t n_mat, int H, int waves)
 // Lengths of packed sequences go with the arguments of the storing kernels but for the Neumann product, b0 = 32 and the refinement step, some of which lose
 // a wavefront per SIMD by the registers of the search (refined Neumann product, C = 64, d_k = 64, 4096 matrices: 20.9 -> 23.3 us).
 constexpr bool lengths_in_arguments(int method, bool refine) { return !refine && method != TRIINV_NEUMANN && method != TRIINV_MIXED_B32; }
+// Single kernels that are slower by it than a packed call gains, with all calls that are not packed.
+// Per-channel gate, forward substitution at C = 128 (all of the register file; offsets / lengths, and the arguments loaded at once): 1024 matrices of bf16 keys,
+// d_k = 128, 61.9 / 66.1 us, 4096 241 / 259 (fp32 keys 277 / 294).
+constexpr bool kda_lengths(int C, int method, bool refine) { return lengths_in_arguments(method, refine) && !(method == TRIINV_FWD_SUBST && C == 128); }
 
 // Launcher return codes.
 enum : int { LAUNCHED = 0, NOT_BUILT = 1, LAUNCH_FAILED = 2 };

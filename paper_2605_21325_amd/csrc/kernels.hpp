@@ -1839,9 +1839,9 @@ __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64) __attribute__((amdgpu_
 template <int OP, int NB, int METHOD, int WPB = 1, bool REFINE = false, bool TEAM = false>
 __global__ __launch_bounds__(TEAM ? 64 * TEAM_WAVES : 64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE, true>()))) void k_kda_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
-                                                          uint32_t n_chunk, InvMap map, int H, int d_k, uint8_t k_dt, uint8_t aux, uint8_t out_dt, int8_t spread)
+                                                          uint32_t n_chunk, InvMapIf<kda_lengths(16 * NB, METHOD, REFINE)> map, int H, int d_k, uint8_t k_dt, uint8_t aux, uint8_t out_dt, int8_t spread)
 {
-    arguments_together(n_chunk, K, beta, g, T, map);
+    if constexpr (kda_lengths(16 * NB, METHOD, REFINE)) arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 16 * NB;
     constexpr int CORE = core_lds_floats<NB, METHOD>();
     constexpr int PER_WAVE = CORE > C ? CORE : C;

@@ -271,6 +271,26 @@ def test_negative_sequence_lengths_are_refused():
             tri.gdn_chunk_tri_solve_varlen(torch.zeros(4, 1, 64), torch.zeros(4, 1), None, torch.zeros(4, 1, 8), lens, 64, gate_kind=tri.GATE_NONE)
 
 
+# Single kernels that lengths in their arguments slow down by more than a packed call gains: refused before any launch, and the call goes with offsets.
+@pytest.mark.parametrize("entry, k_dtype, d_k, C, gate, method, op", [
+    *[("inv", k, d_k, 128, 1, 0, 0) for k, d_k in ((0, 64), (2, 128), (1, 256))],  # per-channel gate, forward substitution, C = 128
+])
+def test_packed_helpers_refuse_kernels_without_lengths(L, entry, k_dtype, d_k, C, gate, method, op):
+    vp, i32, i64 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
+    inv, solve = L.triinv_detail_inv_packed, L.triinv_detail_solve_packed
+    inv.argtypes = [vp, vp, vp, vp, vp, i32, i64, i32, i32, i32, i32, i32, i32, i32, vp, ctypes.c_uint32]
+    solve.argtypes = [vp, vp, vp, vp, vp, vp, vp, i32, i64, i32, i32, i32, i32, i32, i32, i32, i32, vp, ctypes.c_uint32]
+    for n in (2, 2000):                                             # (few matrices, many)
+        lens, head = (i64 * n)(*[1] * n) if n <= 64 else (i64 * 2)(n * C, 1), 1
+        n_seq, total = (n, n) if n <= 64 else (2, n * C + 1)
+        base = 1 << 44                                              # addresses far apart: nothing overlaps
+        Kp, bp, gp, Tp, Xp = (vp(base * (i + 1)) for i in range(5))
+        if entry == "inv":
+            assert inv(Kp, bp, gp, Tp, lens, n_seq, total, head, d_k, C, k_dtype, gate, method, op, None, 0) == -9
+        elif n > 768:                                               # (fewer: the kernels that spread a matrix over wavefronts)
+            assert solve(Kp, bp, gp, Xp, None, Tp, lens, n_seq, total, head, d_k, 64, C, k_dtype, gate, method, op, None, 0) == -9
+
+
 @pytest.mark.parametrize("kernel, waves", [("9k_tri_invILi0ELi1ELi4ELi2ELb0EE", 4), ("9k_tri_invILi0ELi2ELi4ELi2ELb0EE", 4),
                                            ("9k_tri_invILi1ELi1ELi4ELi2ELb0EE", 4)])
 def test_wavefronts_per_simd_that_were_measured(kernel, waves):
