@@ -124,6 +124,16 @@ constexpr bool lengths_in_arguments(int method, bool refine) { return !refine &&
 // Per-channel gate, forward substitution at C = 128 (all of the register file; offsets / lengths, and the arguments loaded at once): 1024 matrices of bf16 keys,
 // d_k = 128, 61.9 / 66.1 us, 4096 241 / 259 (fp32 keys 277 / 294).
 constexpr bool kda_lengths(int C, int method, bool refine) { return lengths_in_arguments(method, refine) && !(method == TRIINV_FWD_SUBST && C == 128); }
+// Channels of a kernel with this many k-steps.  (A function: written out with the operand codes, whose enumeration has no name, the type of a kernel's
+// parameter has another name on the host than on the device, and the launch aborts.)
+constexpr int key_channels(int k_dtype, int k_steps) { return k_steps * (k_dtype == TRIINV_F32 ? 16 : 32); }
+// The inverse applied to one right-hand side.  fp16 keys of 64 channels at C = 64, blocked recursion (offsets / lengths): 3000 matrices 19.9 / 21.7 us, 3500
+// 23.1 / 24.3, 8192 49.6 / 50.4; bf16 keys 21.7 / 21.9, 128 channels 22.5 / 22.8, mixed recursion 21.1 / 21.1.  C = 128 with 16-bit operands: this kernel stands in
+// for rows too long for the one on two wavefronts and fills the register file.
+constexpr bool solve_lengths(int C, int k_dtype, int d_k, int op, int method)
+{
+    return C == 128 ? op == TRIINV_F32 : !(C == 64 && k_dtype == TRIINV_F16 && d_k == 64 && op == TRIINV_F16 && method == TRIINV_BLOCK_RECURSIVE);
+}
 
 // Launcher return codes.
 enum : int { LAUNCHED = 0, NOT_BUILT = 1, LAUNCH_FAILED = 2 };

@@ -289,12 +289,10 @@ __device__ __forceinline__ void invert_and_apply(const ASrc& src, RhsX<OP, NB>& 
 // (C = 64: at most two wavefronts per SIMD -- like the storing kernels, these run slower with more resident: 146 against
 // 138 us at three on the batched workload, 122 against 120 us with d_k = 64, whose build would otherwise fit three)
 //
-// Lengths of packed sequences in the arguments: with one right-hand side; at C = 128 with 16-bit operands, where this kernel stands in for rows
-// too long for the one on two wavefronts and fills the register file, offsets in memory.
-template <int OP, int NB> constexpr bool solve_packed() { return NB < 8 || OP == OP_F32; }
+// Lengths of packed sequences in the arguments: with one right-hand side, see solve_lengths.
 template <int KD, int OP, int NB, int METHOD, int DKS, int WPB, int XPOS, int NRHS>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(1, NB == 4 ? 2 : 8))) void k_gdn_tri_solve(const void* __restrict__ K, const float* __restrict__ beta,
-                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<solve_packed<OP, NB>() && NRHS == 1> map,
+                                                            const float* __restrict__ g, RhsList rhs, int64_t n_chunk, SolveMap<NRHS == 1 && solve_lengths(16 * NB, KD, key_channels(KD, DKS), OP, METHOD)> map,
                                                             int H, int d_k, int aux, int spread)
 {
     arguments_together(n_chunk, K, beta, g, rhs.r[0].X, map);

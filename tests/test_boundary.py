@@ -228,6 +228,16 @@ def test_no_kernel_uses_scratch_memory_or_spills():
     assert not bad, bad
 
 
+def test_no_kernel_is_named_by_an_unnamed_type():
+    """The host numbers unnamed enumerations otherwise than the device: a kernel whose parameter's type names one is not found, and its launch aborts."""
+    import json
+
+    path = os.path.join(os.path.dirname(tri.binding.LIB_PATH), "kernel_resources.json")
+    if not os.path.exists(path):
+        pytest.skip("no compiler resource report beside the library")
+    assert not [k for k in json.load(open(path)) if "$_" in k]
+
+
 def test_chunk_offsets_helper_refuses_before_any_launch(L):
     f = L.triinv_detail_chunk_offsets
     out = ctypes.c_int64(-1)
@@ -274,6 +284,7 @@ def test_negative_sequence_lengths_are_refused():
 # Single kernels that lengths in their arguments slow down by more than a packed call gains: refused before any launch, and the call goes with offsets.
 @pytest.mark.parametrize("entry, k_dtype, d_k, C, gate, method, op", [
     *[("inv", k, d_k, 128, 1, 0, 0) for k, d_k in ((0, 64), (2, 128), (1, 256))],  # per-channel gate, forward substitution, C = 128
+    *[("solve", 1, 64, 64, gate, 1, 1) for gate in (0, 2)],                        # fp16 keys of 64 channels at C = 64, blocked recursion applied
 ])
 def test_packed_helpers_refuse_kernels_without_lengths(L, entry, k_dtype, d_k, C, gate, method, op):
     vp, i32, i64 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64

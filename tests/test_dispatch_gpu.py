@@ -409,3 +409,17 @@ def test_teams_through_the_recursion_give_the_bits_of_a_larger_call(op, k_dtype,
                 assert torch.equal(a[whole:, v:, v:], torch.eye(C - v, device=DEV).to(a.dtype).expand(H, -1, -1)) and not a[whole:, v:, :v].any(), t
         for a, b in zip(Ws, applied):
             assert torch.equal(a, b[:, :t]), t
+
+
+# Applied to one side, fp16 keys of 64 channels at C = 64: the kernel of the larger calls has offsets in memory, the others lengths.
+@pytest.mark.parametrize("method, k_dtype, chunks, offsets", [(tri.BLOCK_RECURSIVE, torch.float16, 128, False), (tri.BLOCK_RECURSIVE, torch.float16, 130, True),
+                                                              (tri.MIXED, torch.float16, 130, False), (tri.BLOCK_RECURSIVE, torch.bfloat16, 130, False)])
+def test_packed_applied_calls_of_fp16_keys(monkeypatch, method, k_dtype, chunks, offsets):
+    H, lens = 4, [1, 65, (chunks - 4) * 64, 7]
+    K, beta, g = (x[0] for x in make_inputs(sum(lens), H, 64, tri.GATE_SCALAR, k_dtype))
+    X = torch.randn(sum(lens), H, 72, device=DEV).to(k_dtype)
+    call = lambda: tri.gdn_chunk_tri_solve_varlen(K, beta, g, X, lens, 64, row_scale=beta, method=method)
+    W = call()
+    assert (W._triinv_keepalive == ()) == (not offsets)
+    monkeypatch.setattr(tri.binding, "_fast_lib", None)
+    assert torch.equal(W, call())
