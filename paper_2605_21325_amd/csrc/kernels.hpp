@@ -1780,7 +1780,7 @@ template <int KD, int OP, int NB, int METHOD, int DKS> constexpr int gdn_lds_flo
 template <int KD, int OP, int NB, int METHOD, int DKS, bool REFINE = false, int WPB = 1>
 __global__ __launch_bounds__(64 * WPB) __attribute__((amdgpu_waves_per_eu(min_waves_per_simd<OP, NB, METHOD, REFINE>()))) void k_gdn_tri_inv(const void* __restrict__ K, const float* __restrict__ beta,
                                                           const float* __restrict__ g, float* __restrict__ T,
-                                                          uint32_t n_chunk, InvMapIf<lengths_in_arguments(METHOD, REFINE)> map, int H, int d_k, uint8_t aux, uint8_t out_dt, int8_t spread)
+                                                          uint32_t n_chunk, InvMapIf<gdn_lengths(16 * NB, KD, key_channels(KD, DKS), METHOD, REFINE)> map, int H, int d_k, uint8_t aux, uint8_t out_dt, int8_t spread)
 {
     arguments_together(n_chunk, K, beta, g, T, map);
     constexpr int C = 16 * NB;

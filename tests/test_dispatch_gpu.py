@@ -423,3 +423,16 @@ def test_packed_applied_calls_of_fp16_keys(monkeypatch, method, k_dtype, chunks,
     assert (W._triinv_keepalive == ()) == (not offsets)
     monkeypatch.setattr(tri.binding, "_fast_lib", None)
     assert torch.equal(W, call())
+
+
+# Forward substitution at C = 64: fp32 keys of 64 channels have offsets in memory, of 128 and 16-bit ones lengths.
+@pytest.mark.parametrize("k_dtype, d_k, offsets", [(torch.float32, 64, True), (torch.float32, 128, False), (torch.float16, 64, False)])
+@pytest.mark.parametrize("chunks", [5, 150])
+def test_packed_calls_of_forward_substitution(monkeypatch, chunks, k_dtype, d_k, offsets):
+    H, lens = 4, [1, 65, (chunks - 4) * 64, 7]
+    K, beta, g = (x[0] for x in make_inputs(sum(lens), H, d_k, tri.GATE_SCALAR, k_dtype))
+    call = lambda: tri.gdn_chunk_tri_inv_varlen(K, beta, g, lens, 64, method=tri.FWD_SUBST, op_dtype=tri.F32)
+    T = call()
+    assert (T._triinv_keepalive == ()) == (not offsets)
+    monkeypatch.setattr(tri.binding, "_fast_lib", None)
+    assert torch.equal(T, call())
