@@ -81,7 +81,9 @@ inline bool by_team128(int64_t n_mat, int d_k) { return n_mat <= FEW_MATRICES / 
 constexpr int FP32_KEYS_TEAM_DK = 128;
 inline bool fp32_keys_by_team(int64_t n_mat, int d_k, int C) { return C == 64 && d_k == FP32_KEYS_TEAM_DK && n_mat <= FEW_MATRICES / 2; }
 // C = 64, d_k = 64 or 128, blocked, mixed and direct-leaf recursion: four wavefronts to a matrix from the keys to the store (team64.hpp), up to three
-// teams per compute unit; the direct leaves, whose one chain of vector instructions nothing shortens, up to one.  One wavefront to a matrix / a team: 8
+// teams per compute unit (fp32 keys of 128 channels: two fit, and more than 512 matrices take two rounds; still level or ahead: one wavefront / a team, 520
+// matrices 14.2 / 13.5 us, with 16-bit operands 12.4 / 12.3, 640 14.1 / 13.8 and 12.4 / 12.4, 768 14.2 / 13.7 and 12.5 / 12.5, of one head 640 14.3 / 13.0 and
+// 12.4 / 11.8); the direct leaves, whose one chain of vector instructions nothing shortens, up to one.  One wavefront to a matrix / a team: 8
 // matrices bf16 4.9 / 4.0 us, fp32 keys and operands 8.9 / 5.2; 256: 5.1 / 4.4, fp32 operands 7.4 / 5.2, fp32 keys and operands of 128 channels (whose
 // tiles a team formed before too) 9.5 / 6.7, direct leaves 5.0 / 4.9; 512: 5.6 / 5.3, 8.0 / 6.6, 12.4 / 9.3, 5.8 / 5.9; 768: 6.8 / 6.3, 9.2 / 8.1; 1024:
 // 7.6 / 8.3, 10.0 / 10.2, 15.6 / 17.3.
