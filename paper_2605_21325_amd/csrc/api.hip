@@ -89,6 +89,12 @@ int pick_tri_inv(const TriInvArgs& a, int C, int op_dtype)
 int launch_fused(const GdnArgs& a, int C, int op_dtype)
 {
     int nb = pick_fused(a, C, op_dtype);
+    if (nb == NOT_BUILT && a.map.lens) {  // a fused kernel that is not given lengths: refused, and the caller has offsets for it
+        GdnArgs o = a;
+        o.map.lens = nullptr;
+        o.dry = true;
+        if (pick_fused(o, C, op_dtype) == LAUNCHED) return finish(nb);
+    }
     if (nb == NOT_BUILT && !a.refine && a.out_dt == TRIINV_F32 && a.method != TRIINV_FWD_SUBST && a.method != 100 /* M_BUILD_A */) {
         GdnArgs b = a;
         b.method = 100;

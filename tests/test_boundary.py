@@ -285,6 +285,7 @@ def test_negative_sequence_lengths_are_refused():
 @pytest.mark.parametrize("entry, k_dtype, d_k, C, gate, method, op", [
     *[("inv", k, d_k, 128, 1, 0, 0) for k, d_k in ((0, 64), (2, 128), (1, 256))],  # per-channel gate, forward substitution, C = 128
     ("inv", 0, 64, 64, 0, 0, 0), ("inv", 0, 64, 64, 2, 0, 0),                      # fp32 keys of 64 channels, forward substitution, C = 64
+    *[("inv", 2, d_k, C, 0, 5, op) for d_k in (64, 128) for C in (16, 32, 64) for op in (0, 2)],  # Newton-Schulz at C <= 64
     *[("solve", 1, 64, 64, gate, 1, 1) for gate in (0, 2)],                        # fp16 keys of 64 channels at C = 64, blocked recursion applied
 ])
 def test_packed_helpers_refuse_kernels_without_lengths(L, entry, k_dtype, d_k, C, gate, method, op):
