@@ -130,11 +130,13 @@ constexpr bool kda_lengths(int C, int method, bool refine) { return lengths_in_a
 // parameter has another name on the host than on the device, and the launch aborts.)
 constexpr int key_channels(int k_dtype, int k_steps) { return k_steps * (k_dtype == TRIINV_F32 ? 16 : 32); }
 // Forward substitution of fp32 keys of 64 channels at C = 64 (offsets / lengths): 3000 matrices 21.9 / 23.7 us, 8192 53.5 / 54.5.  Newton-Schulz at C <= 64,
-// 16-bit keys and operands: 600 matrices of C = 32 4.9 / 5.3 us, 3000 7.5 / 7.7, 600 of C = 16 3.8 / 4.0, of C = 64 10.8 / 11.3, 3000 20.9 / 21.9.
+// 16-bit keys and operands: 600 matrices of C = 32 4.9 / 5.3 us, 3000 7.5 / 7.7, 600 of C = 16 3.8 / 4.0, of C = 64 10.8 / 11.3, 3000 20.9 / 21.9.  The
+// mixed recursion at C <= 64, every type: 64 matrices of C = 32, bf16, 3.7 / 4.1 us, fp32 keys and operands 5.1 / 5.5, 3000 7.4 / 7.6 and 11.2 / 11.4, 900 of C =
+// 16 3.6 / 3.75, 800 of C = 64 6.8 / 7.0 and 11.0 / 11.5 (up to 768 it is a team's; blocked recursion, direct leaves and forward substitution otherwise level).
 constexpr bool gdn_lengths(int C, int k_dtype, int d_k, int method, bool refine)
 {
     return lengths_in_arguments(method, refine) && !(method == TRIINV_FWD_SUBST && C == 64 && k_dtype == TRIINV_F32 && d_k == 64) &&
-           !(method == TRIINV_NEWTON_SCHULZ && C <= 64);
+           !(method == TRIINV_NEWTON_SCHULZ && C <= 64) && !(method == TRIINV_MIXED && C <= 64);
 }
 // The inverse applied to one right-hand side.  fp16 keys of 64 channels at C = 64, blocked recursion (offsets / lengths): 3000 matrices 19.9 / 21.7 us, 3500
 // 23.1 / 24.3, 8192 49.6 / 50.4; bf16 keys 21.7 / 21.9, 128 channels 22.5 / 22.8, mixed recursion 21.1 / 21.1.  C = 128 with 16-bit operands: this kernel stands in

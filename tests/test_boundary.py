@@ -286,6 +286,8 @@ def test_negative_sequence_lengths_are_refused():
     *[("inv", k, d_k, 128, 1, 0, 0) for k, d_k in ((0, 64), (2, 128), (1, 256))],  # per-channel gate, forward substitution, C = 128
     ("inv", 0, 64, 64, 0, 0, 0), ("inv", 0, 64, 64, 2, 0, 0),                      # fp32 keys of 64 channels, forward substitution, C = 64
     *[("inv", 2, d_k, C, 0, 5, op) for d_k in (64, 128) for C in (16, 32, 64) for op in (0, 2)],  # Newton-Schulz at C <= 64
+    *[("inv", 0, 64, C, 0, 3, op) for C in (16, 32) for op in (0, 1)],             # mixed recursion at C <= 32, and at C = 64 beyond the teams
+    *[("inv", 0, 64, 64, 0, 3, op) for op in (0, 1)],
     *[("solve", 1, 64, 64, gate, 1, 1) for gate in (0, 2)],                        # fp16 keys of 64 channels at C = 64, blocked recursion applied
 ])
 def test_packed_helpers_refuse_kernels_without_lengths(L, entry, k_dtype, d_k, C, gate, method, op):
@@ -298,9 +300,9 @@ def test_packed_helpers_refuse_kernels_without_lengths(L, entry, k_dtype, d_k, C
         n_seq, total = (n, n) if n <= 64 else (2, n * C + 1)
         base = 1 << 44                                              # addresses far apart: nothing overlaps
         Kp, bp, gp, Tp, Xp = (vp(base * (i + 1)) for i in range(5))
-        if entry == "inv":
+        if entry == "inv" and not (n <= 768 and C == 64 and method == 3):
             assert inv(Kp, bp, gp, Tp, lens, n_seq, total, head, d_k, C, k_dtype, gate, method, op, None, 0) == -9
-        elif n > 768:                                               # (fewer: the kernels that spread a matrix over wavefronts)
+        elif entry == "solve" and n > 768:                          # (fewer: the kernels that spread a matrix over wavefronts)
             assert solve(Kp, bp, gp, Xp, None, Tp, lens, n_seq, total, head, d_k, 64, C, k_dtype, gate, method, op, None, 0) == -9
 
 
