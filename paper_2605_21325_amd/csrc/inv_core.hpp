@@ -580,21 +580,24 @@ __device__ __forceinline__ void neumann(const ASrc& A, v4f (&Xt)[NB * (NB + 1) /
 // X lives in N orientation (fp32).  Column j of tiles of Y = X + A X needs column j of X only, and column j of X Y the
 // columns j and up of X as a left factor, so the iteration runs over the columns from the last to the first and turns each
 // into its left form (T orientation) just before changing it: the packed tiles go through LDS and come back by transposing reads
-// (Turn16), which take none of the issue slots that bound the kernel.  Two products per iteration instead of the three that
+// (Turn16), which take none of the vector unit's time.  Two products per iteration instead of the three that
 // updating X in both orientations takes, and half of the state.
 // The first iteration from X0 = I / C is a scaling, X1 = 2/C I - (I + A) / C^2, and is written down directly.
 // Result: Xn, every tile in N orientation.
 //
 // What bounds it is the vector instructions and the matrix cores (16 cycles a 16-bit instruction, whether it contracts 16 or
-// 32 deep, beside which two vector instructions fit), whose sum two wavefronts per SIMD fill:
+// 32 deep, beside which two vector instructions fit): with fp32 operands 38 700 of the 47 300 cycles of a matrix.  The rest is the chain of a
+// column, split, LDS, turned read, product, split, product, which two wavefronts per SIMD do not cover all of:
 //   16-bit operands: a 32-deep instruction contracts two adjacent tiles, a 16-deep one a tile without a partner in its sum: 28
 //     instructions per iteration at C = 64.  8 192 fused matrices of C = 64, bf16 / fp16: 56.7 / 56.4 us, standalone 46.1 us
 //     (turned by ten products with the identity and 20 conversions more: 58.8 / 59.7 and 50.2; both orientations kept: 73 and 60).
 //   fp32 operands: three 32-deep bf16 instructions per tile product on values split into three bf16 parts (Split3) instead of four
 //     16x16x4 fp32 instructions of 32 cycles: 120 matrix and 560 vector instructions an iteration (turned by products: 150 and 680, 60 of
-//     them copies that keep a tile's parts in a row).  The same matrices: 174 us, standalone 169, with the refinement step 256 and 195
-//     (206, 195, 258 and 267 turned by products; 344 and 348 with fp32 instructions); 32768 of C = 32 149 (173); error against 64
-//     bits 9.9e-8 and 4.4e-8 (below the diagonal; fp32 instructions 1.01e-7 and 4.1e-8 ... 4.5e-8).
+//     them copies that keep a tile's parts in a row).  The same matrices: 177 us a call (191 turned by products, 344 with fp32 instructions),
+//     standalone 169 (195, 348), with the refinement step 256 and 195 (258 and 267 turned by products).  C = 32: 32768 matrices 147 (160 turned by products);
+//     of 64 channels, whose kernel has four wavefronts per SIMD for its 100 registers where it had five, 136 (147), 8192 of them 34.6 (38.7); of
+//     96 channels of fp32 keys, the same, 8192 51.7 (57.1).  Error against 64 bits 9.9e-8 and 4.4e-8 (below the diagonal; fp32 instructions 1.01e-7
+//     and 4.1e-8 ... 4.5e-8).
 // ---------------------------------------------------------------------------------------------
 
 // 16-bit operands: tile rows / columns 2 p and 2 p + 1 side by side.
